@@ -67,7 +67,7 @@ typedef struct {
  * NULL): the "first 10 % of the timesteps dense" policy of Sec. 4.1 without touching the class
  * buffer.  Ignored by the ARM. */
 #define RF_FLAG_FORCE_DENSE 4
-/* rf_sparse_attention visits each query block's key tiles in an order fixed by the layout alone, which
+/* rf_sparse_attention visits each query block's key tiles in an order fixed by the call's sizes alone, which
  * makes O bitwise identical from call to call.  Without the flag a query block starts its (cyclic) walk
  * over its tiles wherever the workgroups already running on the same part of the GPU are, so that they
  * share K/V tiles through the L2 cache: every tile is still visited exactly once, but the fp32 sums are
@@ -158,10 +158,11 @@ int rf_arm_classify_plus(const void *Q, const void *K, int B, int nH, int D, con
 /*
  * Sparse attention forward, Eq. 1-2 with the mask of each head's pattern (Eq. 3-5):
  *   O[b,h,i,:] = sum_j softmax_j(q_i . k_j / sqrt(D) over kept j) * v_j.
- * The mask is token-level; `block` (64, 128, 256 or 384) is the number of query rows per block (= per
- * workgroup: larger blocks share each K/V tile among more queries and run faster on long sequences), and
- * (query block, 64-key tile) pairs with no kept token pair are skipped, so O does not
- * depend on it.  Scores and sums are accumulated in fp32, O is rounded to bf16.
+ * The mask is token-level; `block` (64, 128, 256 or 384) is the number of query rows per block of the lists
+ * that rf_plan_host shows, and O does not depend on it.  How many rows a workgroup takes at a time (and
+ * whether it splits their keys) the library chooses from the layout, B * nH, D and the workspace; (query
+ * block, 64-key tile) pairs with no kept token pair are skipped at that size.  Only under
+ * RF_FLAG_WIDE_ROWS is it `block`.  Scores and sums are accumulated in fp32, O is rounded to bf16.
  * Q, K, V     : device, bf16 [B, nH, N, D].
  * head_class  : device, int32 [B*nH], values of rf_head_class; read on the device, so the
  *               output of rf_arm_classify can be passed on without a host round trip.
@@ -169,11 +170,13 @@ int rf_arm_classify_plus(const void *Q, const void *K, int B, int nH, int D, con
  * O           : device, bf16 [B, nH, N, D], written.
  * workspace   : device scratch, 256-byte aligned, REQUIRED: at least RF_ATTENTION_MIN_WORKSPACE bytes
  *               (the kernel's work-queue counters, zeroed by the call itself).  If it has
- *               rf_attention_workspace_bytes() bytes or more, K and V of the heads that profit are
- *               first copied into the rest of it in a friendlier order: the kept keys of Textural heads
- *               made contiguous (K_C, V_C of Eq. 5), the tokens of Temporal heads in position-major order
- *               (same in-frame position of all frames adjacent), where the Temporal band is one
- *               contiguous run of keys per query block.  The result is the same either way.  Contents
+ *               rf_attention_workspace_bytes() bytes or more, the kernels that take the most rows may be
+ *               chosen, and K and V of the heads that profit are then first copied into the rest of it in
+ *               the order the heads walk them: the kept keys of Textural heads made contiguous (K_C, V_C of
+ *               Eq. 5), the tokens of Temporal heads in position-major order (same in-frame position of
+ *               all frames adjacent), where the Temporal band is one contiguous run of keys per query
+ *               block; the other kernels gather their rows in those orders instead.  The result is the
+ *               same either way.  Contents
  *               undefined afterwards; calls that overlap in time need separate workspaces.
  */
 #define RF_ATTENTION_MIN_WORKSPACE 512
@@ -198,17 +201,17 @@ int rf_sparse_attention_plus(const void *Q, const void *K, const void *V, const 
 size_t rf_attention_workspace_bytes(int B, int nH, int D, const rf_layout *layout, const rf_params *params);
 
 /*
- * Host-side view of the list rf_sparse_attention walks (Fig. 2a "applying the sparse
+ * Host-side view of the lists rf_sparse_attention walks (Fig. 2a "applying the sparse
  * pattern"): for pattern `cls`, which key tiles each query block visits.  Query blocks are
- * `block` rows; key tiles are always RF_KEY_TILE = 64 keys, so a list is never coarser than
+ * `block` rows (the library walks the lists of one of the four block sizes, see there); key tiles are always RF_KEY_TILE = 64 keys, so a list is never coarser than
  * a block x block tiling would be.  Pure host code, no GPU needed.
  *   row_ptr : host, int32 [nQB + 1] (nQB = ceil(N / block)), written; may be NULL to only size.
  *   cols    : host, int32 [cap]; entry = key-tile index, plus RF_PLAN_PARTIAL if the pair
  *             contains a dropped token pair or runs past the last token (the kernel applies the
  *             token predicate there).  For RF_TEXTURAL, query blocks made only of video tokens
  *             index tiles of the COMPACTED key sequence (kept keys in token order, then text).
- *             cls = RF_LIST_TEMPORAL_POSITION_MAJOR gives the list a Temporal head walks when a
- *             workspace is given: query blocks and key tiles are then runs of the position-major
+ *             cls = RF_LIST_TEMPORAL_POSITION_MAJOR gives the list a Temporal head walks (in token order
+ *             only under RF_FLAG_WIDE_ROWS without room for copies): query blocks and key tiles are then runs of the position-major
  *             order (see rf_plan_position_major).
  *   needed  : host, receives the number of entries.
  * Under RF_FLAG_TEXT_FIRST rows are counted in the order the kernel walks: video tokens first

@@ -116,6 +116,8 @@ int get_attention_plan(const Geometry& geometry, int block, DevicePlan* out) {
         d.radius[RF_TEMPORAL] = g.r_temporal;
         d.radius[RF_TEXTURAL] = 0;
         d.radius[kListTemporalPM] = g.r_temporal;
+        d.group_rows[RF_SPATIAL] = g.HW;
+        d.group_rows[kListTemporalPM] = g.T;
         d.video_shift = g.video_shift();
         d.text_shift = g.text_shift();
         d.N = g.N; d.Nv = g.Nv; d.Nc = hp.Nc;
@@ -318,6 +320,8 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     const bool room_to_pack = workspace_bytes >= rf_attention_workspace_bytes(B, nH, D, layout, params);
 
     AttnArgs a{};
+    a.wide_rows = (params && (params->flags & RF_FLAG_WIDE_ROWS)) ? 1 : 0;
+    const int rows = a.wide_rows ? block : choose_rows(g, B * nH, D, force_dense, room_to_pack);
     a.n_plans = bandwidths ? n_bw : 1;
     for (int k = 0; k < a.n_plans; ++k) {
         Geometry gk = g;
@@ -325,7 +329,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
             st = geometry_with_bandwidth(layout, params, bandwidths[k], &gk);
             if (st != RF_OK) return st;
         }
-        st = get_attention_plan(gk, block, &a.plan[k]);
+        st = get_attention_plan(gk, rows, &a.plan[k]);
         if (st != RF_OK) return st;
     }
     a.Q = static_cast<const uint16_t*>(Q);
@@ -334,12 +338,14 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.O = static_cast<uint16_t*>(O);
     a.queue = static_cast<int*>(workspace);
     a.join_sweep = (params && (params->flags & RF_FLAG_FIXED_ORDER)) ? 0 : 1;
-    a.wide_rows = (params && (params->flags & RF_FLAG_WIDE_ROWS)) ? 1 : 0;
+    // Whole heads to an XCD (every L2 then fetches a head's K and V once) as long as the eight heads in work fit the
+    // memory-side cache with room to spare: 1-20 % up to 17776 tokens; beyond, all XCDs on one head at a time.
+    a.by_head = 8 * 2 * static_cast<size_t>(g.N) * D * sizeof(uint16_t) <= (size_t{128} << 20) ? 1 : 0;
     a.head_class = force_dense ? nullptr : head_class;
     a.head_bw = bandwidths ? head_bw : nullptr;
     a.BH = B * nH;
     a.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
-    if (room_to_pack && !force_dense) {
+    if (room_to_pack && !force_dense && (a.wide_rows || wants_copies(rows, D))) {
         a.packed_k = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) + RF_ATTENTION_MIN_WORKSPACE);
         a.packed_v = a.packed_k + static_cast<size_t>(B) * nH * g.N * D;
         if (launch_pack_textural(a, D, stream) != 0) return RF_ERR_HIP;

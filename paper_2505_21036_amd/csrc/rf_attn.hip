@@ -19,8 +19,14 @@ namespace rf {
 enum : int {
     MODE_ALL = 0,      // every key tile of the sequence in order (dense heads)
     MODE_COMPACT = 1,  // every tile of the compacted key sequence; rows go through the index table (Eq. 5)
-    MODE_LISTED = 2    // the CSR list of the head's pattern; partial tiles re-apply the predicate
+    MODE_LISTED = 2,   // the CSR list of the head's pattern; partial tiles re-apply the predicate on a table of key attributes
+    MODE_BAND = 3,     // the same for a band over groups of consecutive rows (Spatial; Temporal in position-major
+                       // order), where a query keeps one run of key indices (then the text keys): no table
+    MODE_BAND_GATHER = 4  // MODE_BAND on rows that go through the index table (position-major order without a copy)
 };
+constexpr bool gathers(int mode) { return mode == MODE_COMPACT || mode == MODE_BAND_GATHER; }
+constexpr bool has_list(int mode) { return mode == MODE_LISTED || mode == MODE_BAND || mode == MODE_BAND_GATHER; }
+constexpr bool is_band(int mode) { return mode == MODE_BAND || mode == MODE_BAND_GATHER; }
 
 // K/V tiles kept in flight ahead of the one being consumed.  Two (with a third buffer) measured no
 // faster than one at any shape: the loads are not what the wavefronts wait for.
@@ -28,17 +34,26 @@ enum : int {
 #define RF_TILES_AHEAD 1
 #endif
 
-template <int D, int NW>
+// NW: wavefronts that share a tile.  KS > 1: the workgroup is KS groups of NW wavefronts on the same query
+// rows, each with its own tiles (see attend).
+template <int D, int NW, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD>
 struct AttnSmem {
     using ST = DirectTile<D, NW>;
     // K/V tiles resident at a time: the one being consumed plus AHEAD on their way
-    static constexpr int AHEAD = RF_TILES_AHEAD;
+    static constexpr int AHEAD = TILES_AHEAD;
     static constexpr int DEPTH = AHEAD + 1;
     static constexpr int SIDE_SLOTS = DEPTH + 1;  // side data runs one tile further ahead than K/V
     static constexpr int K_OFF = 0;
     static constexpr int V_OFF = DEPTH * ST::K_BYTES;
-    static constexpr int SIDE_OFF = V_OFF + DEPTH * ST::V_BYTES;  // ring of 64-int slots: key indices or key attributes
-    static constexpr int ITEM_OFF = SIDE_OFF + SIDE_SLOTS * kTileK * 4;  // two ints: the work item just taken
+    static constexpr int TILE_BYTES = V_OFF + DEPTH * ST::V_BYTES;  // of one group
+    // KS > 1: at the end every group leaves its rows' references and denominators where its side data was and
+    // its share of the output, fp32, where its tiles were (see attend)
+    static constexpr int PART_BYTES = NW * D * 32 * 4;
+    static constexpr int GROUP_BYTES = KS > 1 && PART_BYTES > TILE_BYTES ? PART_BYTES : TILE_BYTES;
+    static constexpr int SIDE_OFF = KS * GROUP_BYTES;  // per group a ring of 64-int slots: key indices or key attributes
+    static constexpr int STAT_BYTES = KS > 1 ? NW * 2 * 32 * 4 : 0;
+    static constexpr int SIDE_BYTES = SIDE_SLOTS * kTileK * 4 > STAT_BYTES ? SIDE_SLOTS * kTileK * 4 : STAT_BYTES;
+    static constexpr int ITEM_OFF = SIDE_OFF + KS * SIDE_BYTES;  // two ints: the work item just taken
     static constexpr int BYTES = ITEM_OFF + 16;
     static_assert(K_OFF % 256 == 0 && V_OFF % 256 == 0 && ST::K_BYTES % 256 == 0 && ST::V_BYTES % 256 == 0,
                   "tile buffers must start at multiples of 256 bytes (see DirectTile::k_address)");
@@ -85,23 +100,29 @@ constexpr float kRescaleSlack = 8.f;
 namespace rf {
 
 // QH: 32-query halves a wavefront owns (1, or 2: every K and V slab read from LDS then feeds two MFMAs).
-template <int D, int NW, int MODE, int QH = 1>
-__device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, const QueryBlock& qk, unsigned char* smem) {
+// KS: groups of NW wavefronts that split the walk (group g takes its tiles g, g + KS, ... into LDS of its own
+// and keeps a softmax of its own); the groups' results are added up at the end.
+template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD>
+__device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, const QueryBlock& qk, unsigned char* smem_all) {
     constexpr int BQ = 32 * NW * QH;
     using ST = DirectTile<D, NW>;
-    using SM = AttnSmem<D, NW>;
+    using SM = AttnSmem<D, NW, KS, TILES_AHEAD>;
     constexpr int DEPTH = SM::DEPTH;
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
+    unsigned char* smem = smem_all + group * SM::GROUP_BYTES;
     // how many slabs ahead of their MFMAs the LDS operand reads run: with two halves every slab feeds two
     // MFMAs and the registers are all in use, and two measured best (dense CogVideoX-shaped layer 4.25 ->
     // 3.99 ms against the depths of the one-half loop); twelve wavefronts at head_dim 128 have 168
     // registers each, which the loops fit without spills at depth two
     constexpr int AK = (QH == 2 || (NW == 12 && D == 128)) ? 2 : kAheadK, AV = (QH == 2 || (NW == 12 && D == 128)) ? 2 : kAheadV;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5, m = lane & 31;
-    const int N = pl.N, Nv = pl.Nv, keyN = qk.keyN, ntiles = qk.ntiles;
+    const int tid = threadIdx.x - group * (64 * NW), lane = tid & 63, wave = tid >> 6, hf = lane >> 5, m = lane & 31;
+    const int N = pl.N, Nv = pl.Nv, keyN = qk.keyN;
+    const int ntiles = KS == 1 ? qk.ntiles : (qk.ntiles - group + KS - 1) / KS;  // of this group
+    const int nsteps = (qk.ntiles + KS - 1) / KS;                                // of the longest group
     // per-key side data staged through LDS two tiles ahead: the token index of each key of the
     // compacted sequence, or the pattern attribute (frame / position / kept flag) of each key
-    const int32_t* side_src = MODE == MODE_COMPACT ? pl.cidx : (MODE == MODE_LISTED ? pl.attr[qk.list] : nullptr);
-    int* side = reinterpret_cast<int*>(smem + SM::SIDE_OFF);
+    const int32_t* side_src = MODE == MODE_COMPACT ? pl.cidx : (MODE == MODE_BAND_GATHER ? pl.pm_token : (MODE == MODE_LISTED ? pl.attr[qk.list] : nullptr));
+    int* side = reinterpret_cast<int*>(smem_all + SM::SIDE_OFF + group * SM::SIDE_BYTES);
 
     const unsigned char* Kh = qk.kbase;
     const unsigned char* Vh = qk.vbase;
@@ -115,18 +136,26 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     for (int h = 0; h < QH; ++h) {
         qrow[h] = qk.qb * BQ + wave * (32 * QH) + 32 * h + m;  // row of the walked order
         const int qrow_c = min(qrow[h], N - 1);
-        qtok[h] = (MODE == MODE_LISTED && qk.row_token) ? qk.row_token[qrow_c]
+        qtok[h] = (has_list(MODE) && qk.row_token) ? qk.row_token[qrow_c]
                                                         : qrow_c + (qrow_c < Nv ? pl.video_shift : pl.text_shift);
         load_q_frags<D>(Qh, qtok[h], hf, qf[h]);
-        int q_attr = 0, q_rad = 0x3fffffff;  // text queries keep everything
-        if (MODE == MODE_LISTED) {
-            // Spatial / Temporal compare the query's frame / position with the key's; the Textural
-            // table is 0 on kept keys and 1 on dropped ones, compared against 0 with radius 0
-            if (qk.cls != RF_TEXTURAL) q_attr = side_src[qrow_c];
-            if (qrow_c < Nv) q_rad = pl.radius[qk.list];
+        // a key of attribute x is kept iff x + q_lo <= q_span (unsigned); text queries keep everything
+        if (is_band(MODE)) {
+            // attribute = key index: the rows of the groups within the radius of the query's
+            const int group_rows = pl.group_rows[qk.list], r = pl.radius[qk.list];
+            q_lo[h] = qrow_c < Nv ? static_cast<uint32_t>((r - qrow_c / group_rows) * group_rows) : 0x3fffffffu;
+            q_span[h] = qrow_c < Nv ? static_cast<uint32_t>((2 * r + 1) * group_rows - 1) : 0x7ffffffeu;
+        } else {
+            int q_attr = 0, q_rad = 0x3fffffff;
+            if (MODE == MODE_LISTED) {
+                // Spatial / Temporal compare the query's frame / position with the key's; the Textural
+                // table is 0 on kept keys and 1 on dropped ones, compared against 0 with radius 0
+                if (qk.cls != RF_TEXTURAL) q_attr = side_src[qrow_c];
+                if (qrow_c < Nv) q_rad = pl.radius[qk.list];
+            }
+            q_lo[h] = static_cast<uint32_t>(q_rad - q_attr);
+            q_span[h] = 2u * static_cast<uint32_t>(q_rad);
         }
-        q_lo[h] = static_cast<uint32_t>(q_rad - q_attr);
-        q_span[h] = 2u * static_cast<uint32_t>(q_rad);
     }
 
     f32x16 oacc[QH][D / 32];
@@ -154,16 +183,16 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     // v_readlane: no scalar-load latency in the loop.  ent_cur covers [ent_base, ent_base + 64).
     int ent_cur = 0, ent_nxt = 0, ent_base = 0;
     auto load_entries = [&](int from) {
-        const int j = min(from + lane, ntiles - 1) + qk.first;  // the walk starts at entry qk.first and wraps
-        return qk.cols[j < ntiles ? j : j - ntiles];
+        const int j = min((from + lane) * KS + group, qk.ntiles - 1) + qk.first;  // the walk starts at entry qk.first and wraps
+        return qk.cols[j < qk.ntiles ? j : j - qk.ntiles];
     };
-    if (MODE == MODE_LISTED && ntiles > 0) {
+    if (has_list(MODE) && ntiles > 0) {
         ent_cur = load_entries(0);
         ent_nxt = load_entries(64);
     }
     // entries must be asked for in increasing t
     auto entry_of = [&](int t) -> int {
-        if (MODE == MODE_LISTED) {
+        if (has_list(MODE)) {
             if (t >= ent_base + 64) {
                 ent_base += 64;
                 ent_cur = ent_nxt;
@@ -171,12 +200,12 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
             }
             return __builtin_amdgcn_readlane(ent_cur, t - ent_base);
         }
-        int tile = t + qk.first;  // the walk starts at tile qk.first and wraps
-        if (tile >= ntiles) tile -= ntiles;
+        int tile = t * KS + group + qk.first;  // the walk starts at tile qk.first and wraps
+        if (tile >= qk.ntiles) tile -= qk.ntiles;
         return tile | ((tile + 1) * kTileK > keyN ? (RF_PLAN_PARTIAL | kTileBoundary) : 0);
     };
-    // side data is needed for every tile of the compacted sequence, and for partial listed tiles
-    auto wants_side = [&](int entry) { return MODE == MODE_COMPACT || (MODE == MODE_LISTED && (entry & RF_PLAN_PARTIAL)); };
+    // side data is needed for every gathered tile, and for partial tiles masked by the table
+    auto wants_side = [&](int entry) { return gathers(MODE) || (MODE == MODE_LISTED && (entry & RF_PLAN_PARTIAL)); };
     auto load_side = [&](int entry) {
         if (!wants_side(entry)) return;
         const int k0 = (entry & kTileIndexMask) * kTileK;
@@ -188,26 +217,28 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     };
     auto k_lds = [&](int t) { return smem + SM::K_OFF + (t % DEPTH) * ST::K_BYTES; };
     auto v_lds = [&](int t) { return smem + SM::V_OFF + (t % DEPTH) * ST::V_BYTES; };
-    auto fetch_tile = [&](int t, int entry) {
+    auto fetch_some = [&](auto with_v, auto with_k, int t, int entry) {
+        constexpr bool WV = decltype(with_v)::value, WK = decltype(with_k)::value;
         const int k0 = (entry & kTileIndexMask) * kTileK;
-        if (MODE == MODE_COMPACT) {
+        if (gathers(MODE)) {
             const int* idx = side + (t % SM::SIDE_SLOTS) * kTileK;
-            st.issue(Kh, Vh, k_lds(t), v_lds(t), [&](int row) { return idx[row]; });
+            st.template issue<WV, WK>(Kh, Vh, k_lds(t), v_lds(t), [&](int row) { return idx[row]; });
         } else if (k0 + kTileK <= keyN && !(qk.text_shift != 0 && k0 < Nv && k0 + kTileK > Nv)) {
             // full tile of consecutive tensor rows: everything but the tile origin is loop invariant
             const int r0 = k0 + (k0 < Nv ? qk.video_shift : qk.text_shift);
             const size_t origin = static_cast<size_t>(r0) * (2 * D);
-            st.issue_consecutive(Kh + origin, Vh + origin, k_lds(t), v_lds(t));
+            st.template issue_consecutive<WV, WK>(Kh + origin, Vh + origin, k_lds(t), v_lds(t));
         } else {
-            st.issue(Kh, Vh, k_lds(t), v_lds(t), [&](int row) {
+            st.template issue<WV, WK, true>(Kh, Vh, k_lds(t), v_lds(t), [&](int row) {
                 const int n = min(k0 + row, keyN - 1);
                 return n + (n < Nv ? qk.video_shift : qk.text_shift);
             });
         }
     };
+    auto fetch_tile = [&](int t, int entry) { fetch_some(std::true_type{}, std::true_type{}, t, entry); };
 
     // S^T of tile t (64 keys x this lane's query of each half), predicate applied where the tile is partial
-    auto scores = [&](int t, int entry, f32x16 (&s)[QH][2]) {
+    auto scores = [&](int t, int entry, bool need_mask, f32x16 (&s)[QH][2]) {
         if (QH == 1) {
             st.template scores<AK>(st.k_address(k_lds(t)), qf[0], s[0]);
         } else {
@@ -232,21 +263,43 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                 }
             }
         }
-        if (entry & RF_PLAN_PARTIAL) {
+        if (need_mask) {
             const int k0 = (entry & kTileIndexMask) * kTileK;
             const int* al = side + (t % SM::SIDE_SLOTS) * kTileK;
+            const bool band_only = has_list(MODE) && !(entry & kTileBoundary);  // all 64 keys are video tokens
+            // element (kb2, 8*u + i) of this lane is key  8*hf + c  of the tile,  c = 32*kb2 + 16*u + i
+            typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
 #pragma unroll
             for (int h = 0; h < QH; ++h) {
-                // this lane's keys come in runs of eight: keys 32*kb2 + 16*u + 8*hf .. +7 sit in registers 8*u .. 8*u+7
-                typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
-                const bool band_only = MODE == MODE_LISTED && !(entry & kTileBoundary);  // all 64 keys are video tokens
+                auto drop = [&](auto keeps) {
 #pragma unroll
-                for (int kb2 = 0; kb2 < 2; ++kb2)
+                    for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int base = 32 * kb2 + 16 * u + 8 * hf;
-                        uint32_t at[8] = {};
-                        if (MODE == MODE_LISTED) {
+                        for (int r = 0; r < 16; ++r) {
+                            s[h][kb2][r] = keeps(32 * kb2 + 16 * (r >> 3) + (r & 7)) ? s[h][kb2][r] : -INFINITY;
+                            if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // few comparisons' results at a time
+                        }
+                };
+                if (is_band(MODE)) {
+                    // keys lo .. hi of the tile (counted from this half's first) are kept.  Where only one end of the
+                    // run lies in the tile for every row of the wavefront, one comparison with a constant decides.
+                    const int lo = -static_cast<int>(q_lo[h]) - k0 - 8 * hf, hi = lo + static_cast<int>(q_span[h]);
+                    if (band_only && __builtin_amdgcn_ballot_w64(hi < kTileK - 1) == 0) drop([&](int c) { return c >= lo; });
+                    else if (band_only && __builtin_amdgcn_ballot_w64(lo > 0) == 0) drop([&](int c) { return c <= hi; });
+                    else {
+                        const int text = band_only ? kTileK : Nv - k0 - 8 * hf, end = keyN - k0 - 8 * hf;
+                        drop([&](int c) { return (((c >= lo) & (c <= hi)) | (c >= text)) & (c < end); });
+                    }
+                } else if (MODE != MODE_LISTED) {
+                    const int end = keyN - k0 - 8 * hf;
+                    drop([&](int c) { return c < end; });
+                } else {
+#pragma unroll
+                    for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const int base = 32 * kb2 + 16 * u + 8 * hf;
+                            uint32_t at[8];
                             const u32x4 a0 = *(lds_u32x4*)(uintptr_t)ST::lds_offset(reinterpret_cast<const unsigned char*>(al + base));
                             const u32x4 a1 = *(lds_u32x4*)(uintptr_t)ST::lds_offset(reinterpret_cast<const unsigned char*>(al + base + 4));
 #pragma unroll
@@ -254,17 +307,33 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                                 at[i] = a0[i];
                                 at[4 + i] = a1[i];
                             }
-                        }
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) {
-                            const int kidx = k0 + base + i;
-                            bool ok = band_only || kidx < keyN;
-                            if (MODE == MODE_LISTED) ok = ok & ((at[i] + q_lo[h] <= q_span[h]) | (!band_only && kidx >= Nv));
-                            s[h][kb2][8 * u + i] = ok ? s[h][kb2][8 * u + i] : -INFINITY;
+                            for (int i = 0; i < 8; ++i) {
+                                const int kidx = k0 + base + i;
+                                bool ok = band_only || kidx < keyN;
+                                ok = ok & ((at[i] + q_lo[h] <= q_span[h]) | (!band_only && kidx >= Nv));
+                                s[h][kb2][8 * u + i] = ok ? s[h][kb2][8 * u + i] : -INFINITY;
+                            }
                         }
-                    }
+                }
             }
         }
+    };
+    // A partial tile of the block may lie inside or outside the run of keys of this wavefront's rows altogether
+    // (the block has many times as many rows): 0 = no score needs the predicate, 1 = it has to be applied,
+    // 2 = nothing is kept.
+    auto tile_kind = [&](int entry) -> int {
+        if (!(entry & RF_PLAN_PARTIAL)) return 0;
+        if (!is_band(MODE) || (entry & kTileBoundary)) return 1;
+        const int k0 = (entry & kTileIndexMask) * kTileK;
+        bool all = true, none = true;
+#pragma unroll
+        for (int h = 0; h < QH; ++h) {
+            const int lo = -static_cast<int>(q_lo[h]) - k0, hi = lo + static_cast<int>(q_span[h]);
+            all = all & (lo <= 0) & (hi >= kTileK - 1);
+            none = none & ((hi < 0) | (lo >= kTileK));
+        }
+        return __builtin_amdgcn_ballot_w64(!all) == 0 ? 0 : (__builtin_amdgcn_ballot_w64(!none) == 0 ? 2 : 1);
     };
 
     // O^T += V^T P^T for tile t, P (bf16) in pf
@@ -290,16 +359,24 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     // Software pipeline.  While tile t is consumed, the loads of tiles t+1 .. t+AHEAD are in flight
     // or landed, and the side data of tile t+DEPTH is on its way to its ring slot (one tile further,
     // because the loads of a compacted tile take their row indices from it).  e[i] = entry of tile t+i.
+    // AHEAD = 0 (one buffer for K and one for V): K(t+1) is loaded while P V of tile t runs, V(t) while
+    // the scores and the softmax of tile t do; each has a barrier that says its buffer is free and the other's full.
     constexpr int AHEAD = SM::AHEAD;
     int e[DEPTH + 1] = {};
+    auto fetch_k = [&](int t, int entry) { fetch_some(std::false_type{}, std::true_type{}, t, entry); };
+    auto fetch_v = [&](int t, int entry) { fetch_some(std::true_type{}, std::false_type{}, t, entry); };
 #pragma unroll
     for (int i = 0; i < DEPTH; ++i)
         if (i < ntiles) {
             e[i] = entry_of(i);
             load_side(e[i]);
+            if (AHEAD == 0 && !gathers(MODE)) fetch_k(i, e[i]);
             stash_side(i, e[i]);
         }
-    __syncthreads();
+    if (AHEAD > 0 || gathers(MODE)) {
+        __syncthreads();
+        if (AHEAD == 0 && ntiles > 0) fetch_k(0, e[0]);
+    }
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i)
         if (i < ntiles) fetch_tile(i, e[i]);
@@ -312,11 +389,16 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
 #pragma unroll
         for (int cc = 0; cc < D / 16; ++cc) asm volatile("" ::"v"(__builtin_bit_cast(u32x4, qf[h][cc])));
 
-    for (int t = 0; t < ntiles; ++t) {
+    for (int t = 0; t < nsteps; ++t) {
         // the buffer of tile t+AHEAD held tile t+AHEAD-DEPTH, which every wavefront left before the last barrier
         if (t + DEPTH < ntiles) e[DEPTH] = entry_of(t + DEPTH);
-        if (t + AHEAD < ntiles) fetch_tile(t + AHEAD, e[AHEAD]);
-        if (t + DEPTH < ntiles) load_side(e[DEPTH]);
+        if constexpr (AHEAD > 0) {
+            if (t + AHEAD < ntiles) fetch_tile(t + AHEAD, e[AHEAD]);
+            if (t + DEPTH < ntiles) load_side(e[DEPTH]);
+        } else {
+            if (t + DEPTH < ntiles) load_side(e[DEPTH]);
+            if (t < ntiles) fetch_v(t, e[0]);
+        }
         const int e_cur = e[0];
         // every eighth tile, tell the workgroups that start an item on this XCD where this walk is
         if (qk.sweep && (t & 7) == 0 && tid == 0)
@@ -325,8 +407,12 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
         // Online softmax (Eq. 1) in base 2 with 1/sqrt(D) folded into c.  The reference subtracted in
         // the exponent is moved, and the accumulators rescaled, only when a row outgrows it by more
         // than 2^kRescaleSlack (or has none yet): the softmax does not depend on the reference.
+        // a group with fewer tiles only keeps step with the others, and so does a wavefront none of whose rows see the tile
+        const int kind = KS == 1 || t < ntiles ? tile_kind(e_cur) : 2;
+        const bool mine = (KS == 1 && !is_band(MODE)) || kind != 2;
         f32x16 s[QH][2];
-        scores(t, e_cur, s);
+        if (mine) {
+        scores(t, e_cur, is_band(MODE) ? kind == 1 : (e_cur & RF_PLAN_PARTIAL) != 0, s);
         // With eight wavefronts at head_dim 128 the softmax section (VALU only) runs at raised
         // priority and the two MFMA sections at the default: the wavefront that shares the SIMD is
         // then served in the gaps of this one's VALU work rather than the other way round (measured
@@ -379,15 +465,76 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                 }
         }
         if (kSoftmaxPriority) __builtin_amdgcn_s_setprio(0);
-        accumulate(t);
+        if constexpr (AHEAD > 0) accumulate(t);
+        }
+        if constexpr (AHEAD == 0) {
+            ST::template wait_landed<0>();
+            if (t + DEPTH < ntiles) stash_side(t + DEPTH, e[DEPTH]);
+            __syncthreads();
+            if (t + 1 < ntiles) fetch_k(t + 1, e[1]);
+            if (mine) accumulate(t);
+        }
 
         // tile t+1 must be in LDS at the barrier; the loads of the tiles after it may stay in flight
         if (AHEAD > 1 && t + AHEAD < ntiles) ST::template wait_landed<AHEAD - 1>();
         else ST::template wait_landed<0>();
-        if (t + DEPTH < ntiles) stash_side(t + DEPTH, e[DEPTH]);
+        if (AHEAD > 0 && t + DEPTH < ntiles) stash_side(t + DEPTH, e[DEPTH]);
 #pragma unroll
         for (int i = 0; i < DEPTH; ++i) e[i] = e[i + 1];
         __syncthreads();
+    }
+    if constexpr (KS > 1) {
+        // The groups hold the same rows' results over different keys.  Every group's reference and denominator
+        // give the common ones; each group scales its share of the output by them and leaves it in LDS as
+        // [chunk of four channels][query], and then adds up 1/KS of the chunks of all groups and stores them.
+        static_assert(QH == 1 && (D / 4) % (2 * KS) == 0, "two halves of a wavefront take chunks in turn");
+        typedef __attribute__((address_space(3))) float lds_float;
+        typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+        auto stat = [&](int g, int which) {
+            return (lds_float*)(uintptr_t)(ST::lds_offset(smem_all + SM::SIDE_OFF) + g * SM::SIDE_BYTES + ((wave * 2 + which) * 32 + m) * 4);
+        };
+        auto part = [&](int g, int chunk) {
+            return (lds_f32x4*)(uintptr_t)(ST::lds_offset(smem_all) + g * SM::GROUP_BYTES + wave * (D * 128) + (chunk * 32 + m) * 16);
+        };
+        const float l_own = l_run[0] + other_half(l_run[0]), m_own = has_ref[0] ? m_ref[0] : -INFINITY;
+        if (hf == 0) {
+            *stat(group, 0) = m_own;
+            *stat(group, 1) = l_own;
+        }
+        __syncthreads();
+        float m_all = m_own;
+#pragma unroll
+        for (int g = 0; g < KS; ++g) m_all = fmaxf(m_all, *stat(g, 0));
+        float l_all = 0.f;
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            const float m_g = *stat(g, 0);
+            if (m_g > -INFINITY) l_all += *stat(g, 1) * fast_exp2((m_g - m_all) * c);
+        }
+        const float scale = l_all > 0.f && has_ref[0] ? fast_exp2((m_own - m_all) * c) / l_all : 0.f;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                f32x4 w;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) w[r] = oacc[0][db][4 * rq + r] * scale;
+                *part(group, 8 * db + 2 * rq + hf) = w;
+            }
+        __syncthreads();
+        uint16_t* orow = a.O + static_cast<size_t>(qk.bh) * N * D + static_cast<size_t>(qtok[0]) * D;
+#pragma unroll
+        for (int i = 0; i < D / 4 / KS / 2; ++i) {
+            const int chunk = group * (D / 4 / KS) + 2 * i + hf;
+            f32x4 sum = *part(0, chunk);
+#pragma unroll
+            for (int g = 1; g < KS; ++g) sum += *part(g, chunk);
+            u32x2 w;
+            w.x = pack_bf16(sum[0], sum[1]);
+            w.y = pack_bf16(sum[2], sum[3]);
+            if (qrow[0] < N) *reinterpret_cast<u32x2*>(orow + 4 * chunk) = w;
+        }
+        return;
     }
     // Eq. 2: divide by the softmax denominator and store.  Lane (hf, m) owns query m and, per
     // 32-channel block, channels 8*(r/4) + 4*hf + r%4.
@@ -395,7 +542,10 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     for (int h = 0; h < QH; ++h) {
         const float l_tot = l_run[h] + other_half(l_run[h]);
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        if (qrow[h] < N) {
+        // formed again from the thread index, which would otherwise cost a register throughout the tile loop
+        int thread = tid;
+        asm volatile("" : "+v"(thread));
+        if (qk.qb * BQ + (thread >> 6) * (32 * QH) + 32 * h + (thread & 31) < N) {
             uint16_t* orow = a.O + static_cast<size_t>(qk.bh) * N * D + static_cast<size_t>(qtok[h]) * D;
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
@@ -414,9 +564,15 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
 enum : int {
     LOOP_32 = 0,           // wavefronts of 32 query rows (attend)
     LOOP_64_PIPELINED = 1, // wavefronts of 64 rows, one per SIMD, software-pipelined (attend_wide)
+    LOOP_SPLIT = 3,        // wavefronts of 32 rows in four groups that split the walk (attend with KS = 4)
     LOOP_64 = 2            // wavefronts of 64 rows on the plain loop (attend with two halves): head_dim 64 only, where two fit a SIMD
 };
-constexpr int rows_per_wave(int LOOP) { return LOOP == LOOP_32 ? 32 : 64; }
+constexpr int key_groups(int LOOP) { return LOOP == LOOP_SPLIT ? 4 : 1; }
+constexpr int rows_per_wave(int LOOP) { return LOOP == LOOP_64_PIPELINED || LOOP == LOOP_64 ? 64 : 32; }
+// Which instances walk banded lists by key index (MODE_BAND, MODE_BAND_GATHER) instead of by attribute table
+// (MODE_LISTED): two halves, and twelve wavefronts but at head_dim 64, have no registers left for the other masks.
+// (Those that do are the ones that need no copies of K and V: wants_copies in rf_plan.cpp.)
+constexpr bool walks_bands(int D, int NW, int LOOP) { return rows_per_wave(LOOP) == 32 && (NW != 12 || D == 64); }
 
 // Wavefronts per SIMD the register allocation is held to: three for head_dim 64 with 128-row
 // blocks of 32-row wavefronts (measured best; its accumulators are half the size) and for the
@@ -430,13 +586,38 @@ template <int D, int NW, int LOOP>
 using SmemOf = std::conditional_t<LOOP == LOOP_64_PIPELINED, WideSmem<D, NW>, AttnSmem<D, NW>>;
 
 // Items of one launch.  Queue x holds first its share of the long items (the nTB text-holding blocks
-// of every head: global index i = head * nTB + k goes to queue i mod 8), then, head after head, the
-// ordinals [x * per_xcd, (x+1) * per_xcd) of the order of the nVB other blocks.
+// of every head: global index i = head * nTB + k goes to queue i mod 8), then its part of the nVB other
+// blocks of every head: of every head, head after head, the ordinals [x * per_xcd, (x+1) * per_xcd) of the
+// block order, or (by_head) the items [x * per_xcd, (x+1) * per_xcd) of all heads' blocks in a row.
 struct Queues {
-    int BH, nVB, nTB, per_xcd;
-    __device__ __forceinline__ int long_items(int x) const { return (nTB * BH - x + 7) >> 3; }
-    __device__ __forceinline__ int share(int x) const { return max(0, min(per_xcd, nVB - x * per_xcd)); }
-    __device__ __forceinline__ int items(int x) const { return long_items(x) + share(x) * BH; }
+    int BH, nVB, nTB, per_xcd, by_head;
+    __host__ __device__ __forceinline__ Queues(const AttnArgs& a)
+        : BH(a.BH), nVB(a.plan[0].first_text_qb), nTB(a.plan[0].nQB - a.plan[0].first_text_qb),
+          per_xcd(((a.by_head ? nVB * BH : nVB) + 7) >> 3), by_head(a.by_head) {}
+    __host__ __device__ __forceinline__ int long_items(int x) const { return (nTB * BH - x + 7) >> 3; }
+    // ordinals of each head, or items of all heads
+    __host__ __device__ __forceinline__ int share(int x) const {
+        const int left = (by_head ? nVB * BH : nVB) - x * per_xcd;
+        return left < 0 ? 0 : (left < per_xcd ? left : per_xcd);
+    }
+    __host__ __device__ __forceinline__ int items(int x) const { return long_items(x) + (by_head ? share(x) : share(x) * BH); }
+    // head and position in its block order of the item-th item of queue x
+    __device__ __forceinline__ void locate(int item, int x, int* bh, int* ordinal) const {
+        const int longs = long_items(x), j = item - longs;
+        if (j < 0) {
+            const int i = item * 8 + x;
+            *bh = i / nTB;
+            *ordinal = i % nTB;
+        } else if (by_head) {
+            const int i = x * per_xcd + j;
+            *bh = i / nVB;
+            *ordinal = nTB + i % nVB;
+        } else {
+            const int n = share(x);
+            *bh = j / n;
+            *ordinal = nTB + x * per_xcd + j % n;
+        }
+    }
 };
 
 // The next item for a workgroup whose home queue is `home`, or -1 when every queue is empty.
@@ -468,12 +649,6 @@ __device__ __forceinline__ int take_item(int* ctr, int home, const Queues& qs, i
     }
 }
 
-// head of the item-th item of queue xcd (see Queues)
-__device__ __forceinline__ int item_head(int item, int xcd, const Queues& qs) {
-    const int longs = qs.long_items(xcd);
-    return item < longs ? (item * 8 + xcd) / qs.nTB : (item - longs) / qs.share(xcd);
-}
-
 template <int D, int NW, int LOOP>
 __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues& qs, unsigned char* smem);
 
@@ -494,11 +669,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
     // K/V of the head in flight (tens of MB) stays resident in the memory-side cache for whatever
     // misses L2.  XCDs differ in speed by several per cent and shares in work; an XCD whose queue is
     // empty takes items from the others.
-    Queues qs;
-    qs.BH = a.BH;
-    qs.nVB = a.plan[0].first_text_qb;
-    qs.nTB = a.plan[0].nQB - qs.nVB;
-    qs.per_xcd = (qs.nVB + 7) >> 3;
+    const Queues qs(a);
     for (;;) {
         if (threadIdx.x == 0) {
             int q = 0;
@@ -507,8 +678,10 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
             // the sweep word for the item's head on this workgroup's XCD (it serves its own L2, whichever queue
             // the item came from), read ONCE for the whole workgroup: it changes all the time
             const int it = item_box[0];
+            int bh = 0, ordinal = 0;
+            if (it >= 0) qs.locate(it, q, &bh, &ordinal);
             item_box[2] = (a.join_sweep && it >= 0)
-                              ? __hip_atomic_load(sweep_word(a.queue, blockIdx.x & 7, item_head(it, q, qs)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                              ? __hip_atomic_load(sweep_word(a.queue, blockIdx.x & 7, bh), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                               : -1;
         }
         __syncthreads();
@@ -521,6 +694,18 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
     }
 }
 
+// Problems with few query rows: KS groups of NW wavefronts per workgroup split the walk of 32 * NW rows, one
+// workgroup per item and no queue (workgroup ids go to the XCDs round-robin, so workgroup i is item i / 8 of
+// queue i mod 8).
+template <int D, int NW, int LOOP>
+__global__ void __launch_bounds__(64 * NW * key_groups(LOOP)) __attribute__((amdgpu_waves_per_eu(2, 2))) attn_split_kernel(AttnArgs a) {
+    extern __shared__ __attribute__((aligned(256))) unsigned char smem[];  // the kernel's only LDS: starts at address 0
+    const Queues qs(a);
+    const int xcd = blockIdx.x & 7, item = blockIdx.x >> 3;
+    if (item >= qs.items(xcd)) return;
+    process_item<D, NW, LOOP>(a, item, xcd, -1, qs, smem);
+}
+
 // One (head, query block) item: item-th of queue xcd.  seen: the sweep word of this workgroup's XCD
 // (it serves its own L2, whichever queue the item came from), or -1.
 template <int D, int NW, int LOOP>
@@ -528,20 +713,11 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
     auto run = [&](auto mode, const DevicePlan& plan, const QueryBlock& block) {
         constexpr int MODE = decltype(mode)::value;
         if constexpr (LOOP == LOOP_64_PIPELINED) attend_wide<D, NW, MODE>(a, plan, block, smem);
+        else if constexpr (key_groups(LOOP) > 1) attend<D, NW, MODE, 1, key_groups(LOOP), 0>(a, plan, block, smem);
         else attend<D, NW, MODE, rows_per_wave(LOOP) / 32>(a, plan, block, smem);
     };
-    // position in the block order, and the head
-    int ordinal, bh;
-    const int longs = qs.long_items(xcd);
-    if (item < longs) {
-        const int i = item * 8 + xcd;
-        bh = i / qs.nTB;
-        ordinal = i % qs.nTB;
-    } else {
-        const int share = qs.share(xcd), j = item - longs;
-        bh = j / share;
-        ordinal = qs.nTB + xcd * qs.per_xcd + j % share;
-    }
+    int ordinal, bh;  // position in the block order, and the head
+    qs.locate(item, xcd, &bh, &ordinal);
     QueryBlock qk;
     qk.bh = bh;
     // per-head bandwidth: the plans differ only in the Spatial / Temporal lists, radii and block order
@@ -551,14 +727,28 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
         if (static_cast<unsigned>(which) >= static_cast<unsigned>(a.n_plans)) which = 0;
     }
     const DevicePlan& pl = a.plan[which];
+    // One item per workgroup: what stands between its start and its first tile are these loads, one after the
+    // other, so the list bounds of every pattern are asked for along with the class, and the blocks keep their order.
+    constexpr bool kOneItem = key_groups(LOOP) > 1;
+    int lo[kLists] = {}, hi[kLists] = {};
+    if constexpr (kOneItem) {
+        qk.qb = ordinal < qs.nTB ? qs.nVB + ordinal : ordinal - qs.nTB;
+#pragma unroll
+        for (int l = 0; l < kLists; ++l) {
+            lo[l] = pl.row_ptr[l][qk.qb];
+            hi[l] = pl.row_ptr[l][qk.qb + 1];
+        }
+    }
     int cls = a.head_class ? a.head_class[qk.bh] : RF_DENSE;
     if (static_cast<unsigned>(cls) > 3u) cls = RF_DENSE;
     qk.cls = cls;
-    // a Temporal head walks the position-major copy of its K and V if the caller gave room for one
-    const bool temporal_pm = cls == RF_TEMPORAL && a.packed_k;
+    // a Temporal head walks its keys in position-major order: a copy of its K and V if the caller gave room for
+    // one, else row by row through the index table (or, where that loop does not exist, in token order)
+    constexpr bool kBands = walks_bands(D, NW, LOOP);
+    const bool temporal_pm = cls == RF_TEMPORAL && (a.packed_k || kBands);
     const int list = temporal_pm ? kListTemporalPM : cls;
     // dense heads: text-holding blocks first, then token order
-    qk.qb = cls == RF_DENSE ? (ordinal < qs.nTB ? qs.nVB + ordinal : ordinal - qs.nTB) : pl.qorder[list][ordinal];
+    if constexpr (!kOneItem) qk.qb = cls == RF_DENSE ? (ordinal < qs.nTB ? qs.nVB + ordinal : ordinal - qs.nTB) : pl.qorder[list][ordinal];
     qk.first = 0;
     qk.cols = nullptr;
     qk.sweep = a.join_sweep ? sweep_word(a.queue, blockIdx.x & 7, bh) : nullptr;
@@ -600,14 +790,17 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
         qk.list = list;
         if (temporal_pm) {
             qk.row_token = pl.pm_token;
-            qk.kbase = reinterpret_cast<const unsigned char*>(a.packed_k) + head_bytes;
-            qk.vbase = reinterpret_cast<const unsigned char*>(a.packed_v) + head_bytes;
+            if (a.packed_k) {
+                qk.kbase = reinterpret_cast<const unsigned char*>(a.packed_k) + head_bytes;
+                qk.vbase = reinterpret_cast<const unsigned char*>(a.packed_v) + head_bytes;
+            }
             qk.video_shift = qk.text_shift = 0;
         }
-        const int e0 = pl.row_ptr[list][qk.qb];
-        qk.ntiles = pl.row_ptr[list][qk.qb + 1] - e0;
+        auto of_list = [&](const int (&v)[kLists]) { return list == 0 ? v[0] : list == 1 ? v[1] : list == 2 ? v[2] : v[3]; };
+        const int e0 = kOneItem ? of_list(lo) : pl.row_ptr[list][qk.qb];
+        qk.ntiles = (kOneItem ? of_list(hi) : pl.row_ptr[list][qk.qb + 1]) - e0;
         qk.cols = pl.cols[list] + e0;
-        qk.first = pl.first_entry[list][qk.qb];
+        if constexpr (!kOneItem) qk.first = pl.first_entry[list][qk.qb];
         qk.keyN = pl.N;
         qk.sweep_tag = tag_of(temporal_pm ? 2 : 0);
         if (same_sequence() && qk.ntiles > 0) {
@@ -618,7 +811,10 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
             // entirely), the start of the run is where they will be next
             qk.first = (at >= 0 && at < qk.ntiles && (qk.cols[at] & kTileIndexMask) == tile) ? at : 0;
         }
-        run(std::integral_constant<int, MODE_LISTED>{}, pl, qk);
+        if constexpr (!kBands) run(std::integral_constant<int, MODE_LISTED>{}, pl, qk);
+        else if (cls == RF_TEXTURAL) run(std::integral_constant<int, MODE_LISTED>{}, pl, qk);
+        else if (temporal_pm && !a.packed_k) run(std::integral_constant<int, MODE_BAND_GATHER>{}, pl, qk);
+        else run(std::integral_constant<int, MODE_BAND>{}, pl, qk);
     }
 }
 
@@ -691,6 +887,34 @@ static int launch_one(const AttnArgs& a, hipStream_t st) {
     return static_cast<int>(hipGetLastError());
 }
 
+template <int D, int NW, int LOOP>
+static int launch_split(const AttnArgs& a, hipStream_t st) {
+    constexpr int KS = key_groups(LOOP), NT = 64 * NW * KS;
+    constexpr int smem = AttnSmem<D, NW, KS, 0>::BYTES;
+    constexpr int kMaxDevices = 64;
+    static std::mutex mu;
+    static bool ready_on[kMaxDevices] = {};  // the kernel's dynamic-LDS limit has been raised there
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return static_cast<int>(e);
+    if (dev < 0 || dev >= kMaxDevices) return static_cast<int>(hipErrorInvalidDevice);
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!ready_on[dev]) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_split_kernel<D, NW, LOOP>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+            if (e != hipSuccess) return static_cast<int>(e);
+            ready_on[dev] = true;
+        }
+    }
+    const Queues qs(a);
+    int most = 0;
+    for (int x = 0; x < 8; ++x) most = std::max(most, qs.items(x));
+    AttnArgs s = a;
+    s.join_sweep = 0;  // the items start together
+    hipLaunchKernelGGL((attn_split_kernel<D, NW, LOOP>), dim3(8 * most), dim3(NT), smem, st, s);
+    return static_cast<int>(hipGetLastError());
+}
+
 int launch_attention(const AttnArgs& a, int D, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int nw = a.plan[0].block / 32;
@@ -698,11 +922,12 @@ int launch_attention(const AttnArgs& a, int D, void* stream) {
         if (D == 128 && nw == 8) return launch_one<128, 4, LOOP_64_PIPELINED>(a, st);
         return static_cast<int>(hipErrorInvalidValue);
     }
-    if (D == 64 && nw == 2) return launch_one<64, 2>(a, st);
+    // 64 rows: two wavefronts' worth, worked by four groups that split the keys
+    if (D == 64 && nw == 2) return launch_split<64, 2, LOOP_SPLIT>(a, st);
+    if (D == 96 && nw == 2) return launch_split<96, 2, LOOP_SPLIT>(a, st);
+    if (D == 128 && nw == 2) return launch_split<128, 2, LOOP_SPLIT>(a, st);
     if (D == 64 && nw == 4) return launch_one<64, 4>(a, st);
-    if (D == 96 && nw == 2) return launch_one<96, 2>(a, st);
     if (D == 96 && nw == 4) return launch_one<96, 4>(a, st);
-    if (D == 128 && nw == 2) return launch_one<128, 2>(a, st);
     if (D == 128 && nw == 4) return launch_one<128, 4>(a, st);
     // 256-row blocks at head_dim 64: four wavefronts of 64 rows (two still fit a SIMD; measured 8-15 %
     // faster than eight of 32: half the LDS operand reads and half the per-tile bookkeeping per MFMA)

@@ -15,6 +15,7 @@ namespace rf {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -176,10 +177,13 @@ struct DirectTile {
 
     // tok(row): token whose K/V row goes to tile row `row`; kh/vh: byte pointers the tokens index.
     // WITH_V = false: K only (the ARM needs no V); WITH_K = false: V only (the attention loop for 64-row
-    // wavefronts loads the K and V of different tiles).
-    template <bool WITH_V = true, bool WITH_K = true, typename F>
+    // wavefronts loads the K and V of different tiles).  RARE: the lane's rows and chunks are worked out on the spot
+    // instead of being kept in registers across the caller's loop.
+    template <bool WITH_V = true, bool WITH_K = true, bool RARE = false, typename F>
     __device__ __forceinline__ void issue(const unsigned char* kh, const unsigned char* vh, unsigned char* kl,
                                           unsigned char* vl, F tok) {
+        int lane = this->lane;
+        if (RARE) asm volatile("" : "+v"(lane));
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int seg = j * NW + wave;

@@ -42,7 +42,7 @@ constexpr int kListTemporalPM = 3;
 // Host copy of everything the attention kernel needs besides the tensors.
 struct HostPlan {
     Geometry g;
-    int block;     // query rows per block (64 or 128) = rows one workgroup owns
+    int block;     // query rows per block = rows one workgroup owns
     int nQB;       // ceil(N / block)
     int nKT;       // ceil(N / kTileK): key tiles of the token sequence
     int Nc;        // compacted key count of the Textural pattern: kept video keys + text keys
@@ -68,6 +68,12 @@ int resolve_geometry(const rf_layout* layout, const rf_params* params, Geometry*
 // Builds the block lists. Pure host code.
 void build_plan(const Geometry& g, int block, HostPlan* plan);
 
+// Query rows a workgroup of the attention kernel takes at a time, 64, 128, 256 or 384, for the shortest launch at
+// this size.  dense: every head is known to be dense; room: there is a workspace for copies of K and V.
+int choose_rows(const Geometry& g, int BH, int D, bool dense, bool room);
+// Whether the kernel for that many rows profits from those copies.
+bool wants_copies(int rows, int D);
+
 // Block list of one class as the kernel walks it (see rf_plan_host in rainfusion.h).
 void flatten_class(const HostPlan& plan, int cls, std::vector<int32_t>* row_ptr, std::vector<int32_t>* cols);
 
@@ -81,6 +87,7 @@ struct DevicePlan {
     const int32_t* cidx;
     const int32_t* pm_token;
     int radius[kLists];
+    int group_rows[kLists];  // rows per frame (Spatial), per position (Temporal in position-major order)
     int video_shift, text_shift;  // tensor row = walked index + (index < Nv ? video_shift : text_shift)
     int N, Nv, Nc;
     int block, nQB, nKT, nCT, first_text_qb;
@@ -101,6 +108,7 @@ struct AttnArgs {
     uint16_t* packed_v;
     const int32_t* head_bw;  // optional per-head index into plan[]; null or out of range: plan[0]
     int* queue;              // 8 work-queue counters and 8 sweep words (one each per XCD) at the start of the caller's workspace, reset by the launcher
+    int by_head;             // 1: an XCD takes whole heads; 0: its eighth of every head (see Queues in rf_attn.hip)
     int wide_rows;           // 1: wavefronts of 64 query rows (256-row blocks only)
     int join_sweep;          // 1: a starting item joins the tile walk of the workgroups already running on its XCD; 0: fixed start
     int n_plans;

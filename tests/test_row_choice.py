@@ -1,0 +1,87 @@
+"""The rule that chooses how many query rows a workgroup of the attention kernel takes, and the kernels behind
+it.  The rule is host code, asked through a small driver; the GPU test runs every kernel it can choose at a
+ragged size (blocks that end in text rows, a ragged last block and key tile, several rounds or one), every class,
+with and without a workspace, against the oracle on some heads of each class."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+import paper_2505_21036_amd as rf
+import rf_inputs as inp
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+needs_gxx = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+def rows_chosen(tmp_path, cases):
+    """choose_rows for each (T, H, W, text, BH, D, dense, room)."""
+    exe, csrc = str(tmp_path / "rows_driver"), os.path.join(ROOT, "paper_2505_21036_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+                           os.path.join(ROOT, "tests", "rows_driver.cpp"), os.path.join(csrc, "rf_plan.cpp"), "-o", exe])
+    text = "\n".join(" ".join(str(int(x)) for x in c) for c in cases)
+    return [int(x) for x in subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split()]
+
+
+@needs_gxx
+def test_small_problems_split_the_keys_and_the_largest_take_the_most_rows(tmp_path):
+    for D in (64, 96, 128):
+        small = [(4, 8, 8, 0, 2, D, d, r) for d in (0, 1) for r in (0, 1)]
+        small += [(7, 10, 13, 50, 6, D, d, r) for d in (0, 1) for r in (0, 1)] + [(2, 1, 1, 1, 1, D, 0, 0)]
+        assert set(rows_chosen(tmp_path, small)) == {64}
+        assert rows_chosen(tmp_path, [(33, 45, 80, 256, 24, D, 1, 0), (1, 4096, 4096, 0, 1 << 20, D, 1, 0)]) == [384, 384]
+    # with nowhere to copy K and V to, none of the kernels that need copies
+    rooms = [(T, 20, 20, text, BH, D, 0, 0) for T in (2, 9, 33) for text in (0, 77) for BH in (1, 7, 48, 300) for D in (64, 96, 128)]
+    for case, rows in zip(rooms, rows_chosen(tmp_path, rooms)):
+        assert rows != (256 if case[5] == 64 else 384), (case, rows)
+
+
+# (D, B, nH, layout, dense, room) -> rows: sizes at which the rule picks each kernel
+RAGGED, SHORT = (7, 10, 13, 50), (4, 9, 12, 0)
+KERNELS = [
+    ((64, 2, 3, RAGGED, False, True), 64), ((96, 2, 3, RAGGED, False, False), 64), ((128, 2, 3, RAGGED, False, True), 64),
+    ((64, 2, 60, RAGGED, False, False), 128), ((96, 2, 48, RAGGED, False, True), 128), ((128, 2, 48, RAGGED, False, False), 128),
+    ((64, 2, 120, SHORT, False, True), 256), ((96, 1, 72, RAGGED, False, True), 256), ((128, 2, 60, RAGGED, True, True), 256),
+    ((64, 1, 72, RAGGED, True, True), 384), ((96, 1, 72, RAGGED, True, False), 384), ((128, 1, 72, RAGGED, True, False), 384),
+]
+
+
+@needs_gxx
+def test_the_sizes_of_the_gpu_test_pick_the_kernels_it_names(tmp_path):
+    asked = [lay + (B * nH, D, dense, room) for (D, B, nH, lay, dense, room), _ in KERNELS]
+    assert rows_chosen(tmp_path, asked) == [rows for _, rows in KERNELS]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case,rows", KERNELS)
+@pytest.mark.parametrize("text_first", [False, True])
+def test_every_kernel_of_the_rule_against_the_oracle(case, rows, text_first):
+    D, B, nH, (T, H, W, tl), dense, room = case
+    if text_first and tl == 0:
+        pytest.skip("no text tokens to move")
+    print("case rows", rows, case, text_first, flush=True)
+    w = inp.Workload("rows", B, nH, D, T, H, W, tl, 64, 9000 + D + rows)
+    rl, ol = rf.rf_layout(T, H, W, tl), orc.Layout(T, H, W, tl)
+    flags = (rf.RF_FLAG_TEXT_FIRST if text_first else 0) | (rf.RF_FLAG_FORCE_DENSE if dense else 0)
+    rp, op = rf.rf_params(0.25, 0.25, 2, 0, flags), orc.Params(text_first=text_first)
+    shift, scale = (tl if text_first else 0), 5.0
+    Q, K, V = (torch.roll(t, shift, dims=2).contiguous() for t in inp.full_qkv(w, "cuda:0", scale))
+    classes = [i % 4 for i in range(B * nH)]
+    hc = torch.as_tensor(classes, dtype=torch.int32).reshape(B, nH).cuda()
+    ws = torch.empty(rf.rf_attention_workspace_bytes(B, nH, D, rl, rp), dtype=torch.uint8, device="cuda") if room else None
+    O = rf.rf_sparse_attention(Q, K, V, hc, rl, rp, 128, workspace=ws)
+    fixed = rf.rf_params(0.25, 0.25, 2, 0, flags | rf.RF_FLAG_FIXED_ORDER)
+    again = [rf.rf_sparse_attention(Q, K, V, hc, rl, fixed, b, workspace=ws) for b in (64, 384)]
+    torch.cuda.synchronize()
+    assert torch.equal(*again)  # bitwise, and whatever the block
+    for i in list(range(min(4, B * nH))) + list(range(max(4, B * nH - 4), B * nH)):
+        q, k, v = (np.roll(t.float().numpy(), shift, axis=0) for t in inp.head_qkv(w, i // nH, i % nH, scale))
+        ref = orc.attention(q, k, v, orc.DENSE if dense else classes[i], ol, op)
+        for got in (O, again[0]):
+            err = got[i // nH, i % nH].double().cpu().numpy() - ref
+            rel = np.linalg.norm(err) / np.linalg.norm(ref)
+            assert np.abs(err).max() <= 2e-2 and np.abs(err).mean() <= 2e-3 and rel <= 5.2e-3, (i, rel)  # the suite's bounds
