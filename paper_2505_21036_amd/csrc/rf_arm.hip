@@ -11,41 +11,61 @@
 // entry is kept or every entry is dropped; the kernel tells from the attribute ranges of the two
 // sides and applies the mask entry by entry only where the band's edge crosses the pair.
 // A sample's attribute (in-frame position or frame) follows from its index by arithmetic; no table of
-// samples exists anywhere.  Per-row recalls go to scratch and are reduced in a fixed order by
+// samples exists anywhere.  The recalls' sums over 32 rows go to scratch and are reduced in a fixed order by
 // arm_finish_kernel, which also applies the decision rule.
+//
+// Bound by vector issue (about nine vector instructions per MFMA; each score costs a maximum, an exponent and a
+// sum, and three or four more per pass where a band's edge crosses its tile).  Measured, recall and finish, 24
+// heads of 3600 samples at head_dim 128: equal-interval 257 -> 162 us, first-frame 249 -> 218 us; 24 heads of 448
+// at head_dim 96: 39.9 -> 14.6 and 29.0 -> 16.6 us; 6 heads of 130 at head_dim 128: 21.6 -> 12.5 us.
 #include <mutex>
 
 #include "rf_device.h"
 
 namespace rf {
 
-// Wavefronts per workgroup, 32 sampled queries each.  A workgroup walks all sampled keys, so the
-// launch has (samples / 32 / waves) workgroups per head and pass: 8 waves when the passes run apart,
-// 4 when one workgroup serves both (half as many items, each twice as long: the finer grain keeps
-// the 256 CUs evenly loaded).
-constexpr int kArmWavesApart = 8, kArmWavesBoth = 4;
+// A workgroup is KS groups of R wavefronts, 32 sampled queries each; the groups hold the same queries and split
+// the sampled keys.  Large samples: one group of four (eight measured 1-17 % slower, two at once on a CU leave
+// coarser steps).  Small ones, which would leave most CUs with one workgroup or none: four groups of two.
+constexpr int kArmWaves = 4, kArmSplitWaves = 2, kArmSplit = 4;
+// Up to this many workgroups of the first kind (128 queries of one head, and of one pass unless both share the
+// sample) the second kind is taken: 96 workgroups with both passes 23.0 -> 14.6 us, 256: 41.2 -> 35.7, 528: 60 ->
+// 100; one pass each, 120: 19.5 -> 14.2, 192: 16.6 -> 20.2.
+constexpr int kArmSplitItemsBoth = 256, kArmSplitItemsApart = 128;
 // as in the attention kernel: the reference in the exponent moves only when a row outgrows it by this
 constexpr float kArmRescaleSlack = 8.f;
 
-template <int D, int NW>
+// Wavefronts per SIMD the register allocation is held to: what fits without spills (one pass at head_dim 128 does
+// fit four, with spills on a rare path, and measured 2-7 % slower so).
+constexpr int arm_waves_per_simd(int D, bool both, int KS) { return KS > 1 ? 2 : (both ? (D == 64 ? 4 : 3) : (D == 128 ? 3 : 4)); }
+
+template <int D, int R, int KS>
 struct ArmSmem {
-    using ST = DirectTile<D, NW>;
-    static constexpr int K_OFF = 0;                      // two K' tiles
-    static constexpr int ATTR_OFF = 2 * ST::K_BYTES;     // per tile and pass: the 64 samples' attributes, then bounds on them (lowest, highest)
-    static constexpr int ATTR_SLOT = kTileK + 2;
-    static constexpr int BYTES = ATTR_OFF + 2 * 2 * ATTR_SLOT * 4 + 16;
+    using ST = DirectTile<D, R>;
+    // per group: two K' tiles, then per tile and pass the 64 samples' attributes and bounds on them (lowest, highest)
+    static constexpr int ATTR_SLOT = kTileK + 4;  // 16-byte aligned
+    static constexpr int ATTR_OFF = 2 * ST::K_BYTES;
+    static constexpr int GROUP_BYTES = (ATTR_OFF + 2 * 2 * ATTR_SLOT * 4 + 255) / 256 * 256;
+    static constexpr int BYTES = KS * GROUP_BYTES;
+    // at the end the groups exchange, per query, reference, denominator and kept sums where the tiles were
+    static constexpr int PART = 2 + 2 * kMaxBw;
+    static_assert(R * PART * 32 * 4 <= 2 * ST::K_BYTES, "the exchange fits the tile buffers");
     static_assert(ST::K_BYTES % 256 == 0, "tile buffers must start at multiples of 256 bytes (see DirectTile::k_address)");
 };
 
 // BOTH: the two passes use the same sample (equal-interval sampling), so one workgroup forms each
 // score tile once and keeps the kept-key sums of both masks; the arithmetic per pass, and so every
 // recall, is the same as when the passes run apart.
-template <int D, bool BOTH>
-__global__ void __launch_bounds__(64 * (BOTH ? kArmWavesBoth : kArmWavesApart)) arm_recall_kernel(ArmArgs a, int nQB) {
-    constexpr int NW = BOTH ? kArmWavesBoth : kArmWavesApart, BQ = 32 * NW, NP = BOTH ? 2 : 1;
-    using SM = ArmSmem<D, NW>;
+template <int D, bool BOTH, int R, int KS>
+__global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_eu(arm_waves_per_simd(D, BOTH, KS), arm_waves_per_simd(D, BOTH, KS)))) arm_recall_kernel(ArmArgs a, int nQB) {
+    constexpr int BQ = 32 * R, NP = BOTH ? 2 : 1;
+    using SM = ArmSmem<D, R, KS>;
     using ST = typename SM::ST;
-    extern __shared__ __attribute__((aligned(256))) unsigned char smem[];  // the kernel's only LDS: starts at address 0
+    typedef __attribute__((address_space(3))) float lds_float;
+    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+    extern __shared__ __attribute__((aligned(256))) unsigned char smem_all[];  // the kernel's only LDS: starts at address 0
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * R));
+    unsigned char* smem = smem_all + group * SM::GROUP_BYTES;
     int* abuf = reinterpret_cast<int*>(smem + SM::ATTR_OFF);
 
     const int item = xcd_contiguous_item(blockIdx.x, nQB * (2 / NP) * a.BH);
@@ -56,7 +76,7 @@ __global__ void __launch_bounds__(64 * (BOTH ? kArmWavesBoth : kArmWavesApart)) 
     for (int i = 0; i < NP; ++i) ps[i] = a.pass[pass0 + i];
     const int n = ps[0].n, stride = ps[0].stride;  // BOTH: the same in the two passes (the host checks)
     if (qb * BQ >= n) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5, m = lane & 31;
+    const int tid = threadIdx.x - group * (64 * R), lane = tid & 63, wave = tid >> 6, hf = lane >> 5, m = lane & 31;
 
     // samples are video tokens; first_video_row is where those start in the tensors
     const size_t head_off = (static_cast<size_t>(bh) * a.N + a.first_video_row) * D;
@@ -71,20 +91,34 @@ __global__ void __launch_bounds__(64 * (BOTH ? kArmWavesBoth : kArmWavesApart)) 
         const int token = sample * stride;
         return ps[i].by_frame ? token / ps[i].HW : token % ps[i].HW;
     };
-    // attribute of this lane's query and its range over the wavefront's 32 queries (both halves hold
-    // the same queries)
-    int q_attr[NP], q_min[NP], q_max[NP];
+    // With one candidate bandwidth, a query's kept samples are one run of sample indices if the attribute rises with
+    // the index (frames; positions inside the first frame): then lo .. hi, and no table is needed.  Otherwise the
+    // attributes of a tile's samples are compared with the query's.
+    const int n_bw = a.n_bw;
+    bool is_run[NP];
+    int q_attr[NP], lo[NP], hi[NP];
+    // range of the attribute over the wavefront's 32 queries (both halves hold the same queries)
+    int q_min[NP], q_max[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
+        is_run[i] = n_bw == 1 && (ps[i].by_frame || (stride == 1 && n <= ps[i].HW));
         q_attr[i] = attr_of(i, qsc);
-        int lo = q_attr[i], hi = q_attr[i];
+        int low = q_attr[i], high = q_attr[i];
 #pragma unroll
         for (int w = 1; w < 32; w <<= 1) {
-            lo = min(lo, __shfl_xor(lo, w, 64));
-            hi = max(hi, __shfl_xor(hi, w, 64));
+            low = min(low, __shfl_xor(low, w, 64));
+            high = max(high, __shfl_xor(high, w, 64));
         }
-        q_min[i] = __builtin_amdgcn_readfirstlane(lo);
-        q_max[i] = __builtin_amdgcn_readfirstlane(hi);
+        q_min[i] = __builtin_amdgcn_readfirstlane(low);
+        q_max[i] = __builtin_amdgcn_readfirstlane(high);
+        const int r = ps[i].radius[0];
+        if (ps[i].by_frame) {  // samples whose token lies in frames q_attr - r .. q_attr + r
+            lo[i] = static_cast<int>((static_cast<long long>(max(q_attr[i] - r, 0)) * ps[i].HW + stride - 1) / stride);
+            hi[i] = static_cast<int>((static_cast<long long>(q_attr[i] + r + 1) * ps[i].HW - 1) / stride);
+        } else {
+            lo[i] = q_attr[i] - r;
+            hi[i] = q_attr[i] + r;
+        }
     }
 
     // m_ref: reference subtracted inside exp2 (raw score units); l_all / l_kept: this lane's share of
@@ -95,17 +129,18 @@ __global__ void __launch_bounds__(64 * (BOTH ? kArmWavesBoth : kArmWavesApart)) 
     for (int i = 0; i < NP; ++i)
 #pragma unroll
         for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] = 0.f;
-    const int n_bw = a.n_bw;
     const float c = a.scale_log2;
-    const int ntiles = (n + kTileK - 1) / kTileK;
+    const int all_tiles = (n + kTileK - 1) / kTileK;
+    const int ntiles = (all_tiles - group + KS - 1) / KS, nsteps = (all_tiles + KS - 1) / KS;  // this group's; the longest's
 
     ST st;
     st.init(tid);
-    auto k_lds = [&](int t) { return smem + SM::K_OFF + (t & 1) * ST::K_BYTES; };
+    auto first_of = [&](int t) { return (t * KS + group) * kTileK; };  // the group's t-th tile starts at this sample
+    auto k_lds = [&](int t) { return smem + (t & 1) * ST::K_BYTES; };
     auto attr_slot = [&](int t, int i) { return abuf + ((t & 1) * 2 + i) * SM::ATTR_SLOT; };
     int attr_reg[NP] = {};
     auto fetch_tile = [&](int t) {
-        const int k0 = t * kTileK;
+        const int k0 = first_of(t);
         if (stride == 1 && k0 + kTileK <= n)
             st.template issue_consecutive<false>(Kh + static_cast<size_t>(k0) * (2 * D), nullptr, k_lds(t), nullptr);
         else
@@ -113,7 +148,8 @@ __global__ void __launch_bounds__(64 * (BOTH ? kArmWavesBoth : kArmWavesApart)) 
         // the tile's attributes (first wavefront, one sample per lane)
         if (tid < kTileK) {
 #pragma unroll
-            for (int i = 0; i < NP; ++i) attr_reg[i] = attr_of(i, min(k0 + tid, n - 1));
+            for (int i = 0; i < NP; ++i)
+                if (!is_run[i]) attr_reg[i] = attr_of(i, min(k0 + tid, n - 1));
         }
     };
     // Also bounds on the tile's attributes: samples are in token order, so frames never decrease, and
@@ -121,186 +157,293 @@ __global__ void __launch_bounds__(64 * (BOTH ? kArmWavesBoth : kArmWavesApart)) 
     // another frame gets the widest bounds (the caller then masks it entry by entry, which is exact).
     auto stash_attr = [&](int t) {
         if (tid >= kTileK) return;
-        const int first = t * kTileK * stride, last = min(t * kTileK + kTileK - 1, n - 1) * stride;
+        const int first = first_of(t) * stride, last = min(first_of(t) + kTileK - 1, n - 1) * stride;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
+            if (is_run[i]) continue;
             int* slot = attr_slot(t, i);
             slot[tid] = attr_reg[i];
-            int lo = __builtin_amdgcn_readlane(attr_reg[i], 0), hi = __builtin_amdgcn_readlane(attr_reg[i], kTileK - 1);
+            int low = __builtin_amdgcn_readlane(attr_reg[i], 0), high = __builtin_amdgcn_readlane(attr_reg[i], kTileK - 1);
             if (!ps[i].by_frame && first / ps[i].HW != last / ps[i].HW) {
-                lo = 0;
-                hi = ps[i].HW - 1;
+                low = 0;
+                high = ps[i].HW - 1;
             }
             if (tid == 0) {
-                slot[kTileK] = lo;
-                slot[kTileK + 1] = hi;
+                slot[kTileK] = low;
+                slot[kTileK + 1] = high;
             }
         }
     };
-    fetch_tile(0);
-    stash_attr(0);
+    if (ntiles > 0) {
+        fetch_tile(0);
+        stash_attr(0);
+    }
     ST::template wait_landed<0>();
     __syncthreads();
     // the compiler cannot see the tile loads; make its own wait for the Q loads happen here, not in the loop
 #pragma unroll
     for (int cc = 0; cc < D / 16; ++cc) asm volatile("" ::"v"(__builtin_bit_cast(u32x4, qf[cc])));
 
-    for (int t = 0; t < ntiles; ++t) {
+    for (int t = 0; t < nsteps; ++t) {
         if (t + 1 < ntiles) fetch_tile(t + 1);
-        const int k0 = t * kTileK;
+        if (KS == 1 || t < ntiles) {
+            const int k0 = first_of(t);
 
-        f32x16 s[2];
-        st.template scores<kAheadK>(st.k_address(k_lds(t)), qf, s);
-        if (k0 + kTileK > n) {  // ragged last tile: samples past the end do not exist
+            f32x16 s[2];
+            st.template scores<kAheadK>(st.k_address(k_lds(t)), qf, s);
+            if (k0 + kTileK > n) {  // ragged last tile: samples past the end do not exist
+#pragma unroll
+                for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (k0 + 32 * kb2 + key_of_reg(r, hf) >= n) s[kb2][r] = -INFINITY;
+            }
+            float mt = s[0][0];
 #pragma unroll
             for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (k0 + 32 * kb2 + key_of_reg(r, hf) >= n) s[kb2][r] = -INFINITY;
-        }
-        float mt = s[0][0];
+                for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[kb2][r]);
+            // the two halves of the wavefront hold different keys of the same 32 queries: their maxima are
+            // exchanged, and the sums rescaled, only when some lane asks for the reference to move
+            const bool grow = has_ref ? (mt - m_ref) * c > kArmRescaleSlack : mt > -INFINITY;
+            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+                mt = fmaxf(mt, other_half(mt));
+                if (mt > -INFINITY) {
+                    const float m_new = has_ref ? fmaxf(m_ref, mt) : mt;
+                    const float alpha = has_ref ? fast_exp2((m_ref - m_new) * c) : 0.f;  // nothing accumulated before
+                    l_all *= alpha;
 #pragma unroll
-        for (int kb2 = 0; kb2 < 2; ++kb2)
+                    for (int i = 0; i < NP; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[kb2][r]);
-        // the two halves of the wavefront hold different keys of the same 32 queries: their maxima are
-        // exchanged, and the sums rescaled, only when some lane asks for the reference to move
-        const bool grow = has_ref ? (mt - m_ref) * c > kArmRescaleSlack : mt > -INFINITY;
-        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-            mt = fmaxf(mt, other_half(mt));
-            if (mt > -INFINITY) {
-                const float m_new = has_ref ? fmaxf(m_ref, mt) : mt;
-                const float alpha = has_ref ? fast_exp2((m_ref - m_new) * c) : 0.f;  // nothing accumulated before
-                l_all *= alpha;
-#pragma unroll
-                for (int i = 0; i < NP; ++i)
-#pragma unroll
-                    for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] *= alpha;
-                m_ref = m_new;
-                has_ref = true;
+                        for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] *= alpha;
+                    m_ref = m_new;
+                    has_ref = true;
+                }
             }
-        }
-        const float mc = m_ref * c;
-        // the tile's terms of the denominator, summed in register order whatever the masks need
-        float sum_all = 0.f;
+            const float mc = m_ref * c;
+            // the tile's terms of the denominator, summed in the same order whatever the masks need: four chains,
+            // so that an addition need not wait for the one before it
+            float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kb2 = 0; kb2 < 2; ++kb2)
+            for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                s[kb2][r] = fast_exp2(fmaf(s[kb2][r], c, -mc));
-                sum_all += s[kb2][r];
-            }
-        l_all += sum_all;
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            // Where does the band's edge fall for this (wavefront, tile) pair?  inside: bit b set if every
-            // pair is within radius b; mixed: some candidate has both kept and dropped pairs here.
-            const int* al = attr_slot(t, i);
-            const int k_min = __builtin_amdgcn_readfirstlane(al[kTileK]), k_max = __builtin_amdgcn_readfirstlane(al[kTileK + 1]);
-            const int reach = max(k_max - q_min[i], q_max[i] - k_min), gap = max(k_min - q_max[i], q_min[i] - k_max);
-            int inside = 0;
-            bool mixed = false;
-#pragma unroll
-            for (int b = 0; b < kMaxBw; ++b) {
-                if (b >= n_bw) break;
-                if (reach <= ps[i].radius[b]) inside |= 1 << b;
-                else if (gap <= ps[i].radius[b]) mixed = true;
-            }
-            if (!mixed) {
-#pragma unroll
-                for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] += ((inside >> b) & 1) ? sum_all : 0.f;
-            } else {
-                float sum_kept[kMaxBw];
-#pragma unroll
-                for (int b = 0; b < kMaxBw; ++b) sum_kept[b] = 0.f;
+                for (int r = 0; r < 16; ++r) {
+                    s[kb2][r] = fast_exp2(fmaf(s[kb2][r], c, -mc));
+                    part[r & 3] += s[kb2][r];
+                    if ((r & 7) == 7) __builtin_amdgcn_sched_barrier(0);  // keeps the temporaries few
+                }
+            const float sum_all = (part[0] + part[1]) + (part[2] + part[3]);
+            l_all += sum_all;
+            // sum of the terms that keep(entry) holds, entry = (half, register)
+            auto sum_of = [&](auto keep) {
+                float k4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const float p = s[kb2][r];
-                        const int d = q_attr[i] - al[32 * kb2 + key_of_reg(r, hf)];
-                        const int dist = d < 0 ? -d : d;
-                        sum_kept[0] += dist <= ps[i].radius[0] ? p : 0.f;
-                        if (n_bw > 1) {  // uniform: the per-head bandwidth variant measures every candidate at once
-#pragma unroll
-                            for (int b = 1; b < kMaxBw; ++b) sum_kept[b] += (b < n_bw && dist <= ps[i].radius[b]) ? p : 0.f;
-                        }
+                        k4[r & 3] += keep(kb2, r) ? s[kb2][r] : 0.f;
+                        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
                     }
+                return (k4[0] + k4[1]) + (k4[2] + k4[3]);
+            };
 #pragma unroll
-                for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] += sum_kept[b];
+            for (int i = 0; i < NP; ++i) {
+                if (is_run[i]) {
+                    // entry (kb2, r) of this lane is sample  k0 + 8*hf + 32*kb2 + 16*(r/8) + r%8
+                    const bool all = lo[i] <= k0 && hi[i] >= min(k0 + kTileK, n) - 1, none = hi[i] < k0 || lo[i] >= k0 + kTileK;
+                    if (__builtin_amdgcn_ballot_w64(!all) == 0) {
+                        l_kept[i][0] += sum_all;
+                    } else if (__builtin_amdgcn_ballot_w64(!none) != 0) {
+                        const int from = lo[i] - k0 - 8 * hf, to = hi[i] - k0 - 8 * hf;
+                        // usually one end of the run lies in the tile for the 32 queries: one comparison each
+                        if (__builtin_amdgcn_ballot_w64(hi[i] < k0 + kTileK - 1) == 0)
+                            l_kept[i][0] += sum_of([&](int kb2, int r) { return 32 * kb2 + key_of_reg(r, 0) >= from; });
+                        else if (__builtin_amdgcn_ballot_w64(lo[i] > k0) == 0)
+                            l_kept[i][0] += sum_of([&](int kb2, int r) { return 32 * kb2 + key_of_reg(r, 0) <= to; });
+                        else
+                            l_kept[i][0] += sum_of([&](int kb2, int r) {
+                                const int at = 32 * kb2 + key_of_reg(r, 0);
+                                return (at >= from) & (at <= to);
+                            });
+                    }
+                    continue;
+                }
+                // Where does the band's edge fall for this (wavefront, tile) pair?  inside: bit b set if every
+                // pair is within radius b; mixed: some candidate has both kept and dropped pairs here.
+                const int* al = attr_slot(t, i);
+                const int k_min = __builtin_amdgcn_readfirstlane(al[kTileK]), k_max = __builtin_amdgcn_readfirstlane(al[kTileK + 1]);
+                const int reach = max(k_max - q_min[i], q_max[i] - k_min), gap = max(k_min - q_max[i], q_min[i] - k_max);
+                int inside = 0;
+                bool mixed = false;
+#pragma unroll
+                for (int b = 0; b < kMaxBw; ++b) {
+                    if (b >= n_bw) break;
+                    if (reach <= ps[i].radius[b]) inside |= 1 << b;
+                    else if (gap <= ps[i].radius[b]) mixed = true;
+                }
+                if (!mixed) {
+#pragma unroll
+                    for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] += ((inside >> b) & 1) ? sum_all : 0.f;
+                    continue;
+                }
+                // the test |difference| <= radius as one unsigned comparison
+                auto sum_within = [&](int radius) {
+                    const int low = q_attr[i] - radius;
+                    const uint32_t span = 2u * static_cast<uint32_t>(radius);
+                    uint32_t table = ST::lds_offset(reinterpret_cast<const unsigned char*>(al)) + 32 * hf;
+                    asm volatile("" : "+v"(table));  // read anew for every candidate: not kept in 32 registers
+                    float k4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+                        for (int r = 0; r < 16; r += 4) {
+                            const u32x4 at = *(lds_u32x4*)(uintptr_t)(table + 4 * (32 * kb2 + key_of_reg(r, 0)));
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) k4[j] += at[j] - static_cast<uint32_t>(low) <= span ? s[kb2][r + j] : 0.f;
+                            asm volatile("" : "+v"(k4[0]), "+v"(k4[1]), "+v"(k4[2]), "+v"(k4[3]));  // four attributes in registers at a time
+                        }
+                    return (k4[0] + k4[1]) + (k4[2] + k4[3]);
+                };
+#pragma clang loop unroll(disable)  // unrolled, the candidates' differences would be kept: 40 more registers
+                for (int b = 0; b < n_bw; ++b) {
+                    const float kept = sum_within(a.pass[pass0 + i].radius[b]);
+#pragma unroll
+                    for (int k = 0; k < kMaxBw; ++k) l_kept[i][k] += k == b ? kept : 0.f;
+                }
             }
         }
-
         if (t + 1 < ntiles) stash_attr(t + 1);
         ST::template wait_landed<0>();
         __syncthreads();
     }
+    // one value per query, in both halves
     l_all += other_half(l_all);
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+        for (int b = 0; b < kMaxBw; ++b)
+            if (b < n_bw) l_kept[i][b] += other_half(l_kept[i][b]);
+    if constexpr (KS > 1) {
+        // the first group adds up what the groups found, at the largest of their references
+        auto slot = [&](int g, int which) {
+            return (lds_float*)(uintptr_t)(ST::lds_offset(smem_all) + g * SM::GROUP_BYTES + ((wave * SM::PART + which) * 32 + m) * 4);
+        };
+        if (hf == 0) {
+            *slot(group, 0) = has_ref ? m_ref : -INFINITY;
+            *slot(group, 1) = l_all;
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+#pragma unroll
+                for (int b = 0; b < kMaxBw; ++b)
+                    if (b < n_bw) *slot(group, 2 + i * kMaxBw + b) = l_kept[i][b];
+        }
+        __syncthreads();
+        if (group != 0) return;
+        float top = -INFINITY;
+#pragma unroll
+        for (int g = 0; g < KS; ++g) top = fmaxf(top, *slot(g, 0));
+        l_all = 0.f;
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+            for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] = 0.f;
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            const float m_g = *slot(g, 0), w = m_g > -INFINITY ? fast_exp2((m_g - top) * c) : 0.f;
+            l_all += w * *slot(g, 1);
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+#pragma unroll
+                for (int b = 0; b < kMaxBw; ++b)
+                    if (b < n_bw) l_kept[i][b] += w * *slot(g, 2 + i * kMaxBw + b);
+        }
+    }
+    // Eq. 6: one recall per query; the wavefront's 32 are summed in a fixed order and leave as one number
 #pragma unroll
     for (int i = 0; i < NP; ++i)
 #pragma unroll
         for (int b = 0; b < kMaxBw; ++b) {
             if (b >= n_bw) break;
-            const float kept = l_kept[i][b] + other_half(l_kept[i][b]);
-            if (hf == 0 && qs < n)
-                a.row_recall[((static_cast<size_t>(bh) * 2 + pass0 + i) * n_bw + b) * a.max_n + qs] = kept / l_all;  // Eq. 6, one row
+            float sum = qs < n ? l_kept[i][b] / l_all : 0.f;
+#pragma unroll
+            for (int w = 16; w > 0; w >>= 1) sum += __shfl_xor(sum, w, 64);
+            const int at = qb * R + wave;
+            if (lane == 0 && at * 32 < n)
+                a.row_recall[((static_cast<size_t>(bh) * 2 + pass0 + i) * n_bw + b) * a.max_n + at] = sum;
         }
 }
 
-// Mean of the per-row recalls in a fixed summation order, then Alg. 1's rule (with several
-// candidate bandwidths: the narrowest one that holds the threshold, Temporal before Spatial).
-__global__ void __launch_bounds__(256) arm_finish_kernel(ArmArgs a) {
-    __shared__ float red[256];
+// Mean of the recalls from the wavefronts' sums, in a fixed order, one wavefront per pass and candidate; then
+// Alg. 1's rule (with several candidate bandwidths: the narrowest one that holds the threshold, Temporal before
+// Spatial).
+__global__ void __launch_bounds__(64 * 2 * kMaxBw) arm_finish_kernel(ArmArgs a) {
     __shared__ float rec[2][kMaxBw];
-    const int bh = blockIdx.x, tid = threadIdx.x, n_bw = a.n_bw;
-    for (int pass = 0; pass < 2; ++pass)
-        for (int b = 0; b < n_bw; ++b) {
-            const int n = a.pass[pass].n;
-            const float* rr = a.row_recall + ((static_cast<size_t>(bh) * 2 + pass) * n_bw + b) * a.max_n;
-            float acc = 0.f;
-            for (int i = tid; i < n; i += 256) acc += rr[i];
-            red[tid] = acc;
-            __syncthreads();
-            for (int w = 128; w > 0; w >>= 1) {
-                if (tid < w) red[tid] += red[tid + w];
-                __syncthreads();
-            }
-            if (tid == 0) rec[pass][b] = red[0] / static_cast<float>(n);
-            __syncthreads();
+    const int bh = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_bw = a.n_bw;
+    const int pass = wave / kMaxBw, b = wave % kMaxBw;
+    if (b < n_bw) {
+        const int n = a.pass[pass].n, sums = (n + 31) / 32;
+        const float* rr = a.row_recall + ((static_cast<size_t>(bh) * 2 + pass) * n_bw + b) * a.max_n;
+        float acc = 0.f;
+        for (int i = lane; i < sums; i += 64) acc += rr[i];
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) acc += __shfl_xor(acc, w, 64);
+        if (lane == 0) {
+            const float mean = acc / static_cast<float>(n);
+            rec[pass][b] = mean;
+            if (a.recalls) a.recalls[(bh * 2 + pass) * n_bw + b] = mean;
         }
-    if (tid == 0) {
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
         int cls = a.fallback_class, chosen = -1;
-        for (int pass = 0; pass < 2 && chosen < 0; ++pass)  // Temporal (pass 0) has priority
+        for (int p = 0; p < 2 && chosen < 0; ++p)  // Temporal (pass 0) has priority
             for (int i = 0; i < n_bw && chosen < 0; ++i) {
-                const int b = a.by_width[i];
-                if (rec[pass][b] >= a.threshold) {
-                    chosen = b;
-                    cls = pass == 0 ? RF_TEMPORAL : RF_SPATIAL;
+                const int k = a.by_width[i];
+                if (rec[p][k] >= a.threshold) {
+                    chosen = k;
+                    cls = p == 0 ? RF_TEMPORAL : RF_SPATIAL;
                 }
             }
         a.head_class[bh] = cls;
         if (a.head_bw) a.head_bw[bh] = chosen;
-        if (a.recalls)
-            for (int pass = 0; pass < 2; ++pass)
-                for (int b = 0; b < n_bw; ++b) a.recalls[(bh * 2 + pass) * n_bw + b] = rec[pass][b];
     }
+}
+
+template <int D, bool BOTH, int R, int KS>
+static int launch_recall(const ArmArgs& a, hipStream_t st) {
+    const int nQB = (a.max_n + 32 * R - 1) / (32 * R), total = nQB * (BOTH ? 1 : 2) * a.BH;
+    constexpr int smem = ArmSmem<D, R, KS>::BYTES;
+    if (smem > 64 * 1024) {  // above what a kernel may have by itself: once per device
+        constexpr int kMaxDevices = 64;
+        static std::mutex mu;
+        static bool ready_on[kMaxDevices] = {};
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return static_cast<int>(e);
+        if (dev < 0 || dev >= kMaxDevices) return static_cast<int>(hipErrorInvalidDevice);
+        std::lock_guard<std::mutex> lock(mu);
+        if (!ready_on[dev]) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&arm_recall_kernel<D, BOTH, R, KS>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+            if (e != hipSuccess) return static_cast<int>(e);
+            ready_on[dev] = true;
+        }
+    }
+    hipLaunchKernelGGL((arm_recall_kernel<D, BOTH, R, KS>), dim3(8 * ((total + 7) / 8)), dim3(64 * R * KS), smem, st, a, nQB);
+    return static_cast<int>(hipGetLastError());
 }
 
 template <int D>
 static int launch_arm_d(const ArmArgs& a, hipStream_t st) {
     const bool both = a.pass[0].n == a.pass[1].n && a.pass[0].stride == a.pass[1].stride;  // one sample for the two passes
-    const int NW = both ? kArmWavesBoth : kArmWavesApart;
-    const int nQB = (a.max_n + 32 * NW - 1) / (32 * NW);
-    const int total = nQB * (both ? 1 : 2) * a.BH;
-    const dim3 grid(8 * ((total + 7) / 8)), block(64 * NW);
-    constexpr int lds_both = ArmSmem<D, kArmWavesBoth>::BYTES, lds_apart = ArmSmem<D, kArmWavesApart>::BYTES;
-    if (both)
-        hipLaunchKernelGGL((arm_recall_kernel<D, true>), grid, block, lds_both, st, a, nQB);
+    const long long items = static_cast<long long>((a.max_n + 32 * kArmWaves - 1) / (32 * kArmWaves)) * a.BH * (both ? 1 : 2);
+    const bool split = items <= (both ? kArmSplitItemsBoth : kArmSplitItemsApart);
+    int e;
+    if (split)
+        e = both ? launch_recall<D, true, kArmSplitWaves, kArmSplit>(a, st) : launch_recall<D, false, kArmSplitWaves, kArmSplit>(a, st);
     else
-        hipLaunchKernelGGL((arm_recall_kernel<D, false>), grid, block, lds_apart, st, a, nQB);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return static_cast<int>(e);
-    hipLaunchKernelGGL(arm_finish_kernel, dim3(a.BH), dim3(256), 0, st, a);
+        e = both ? launch_recall<D, true, kArmWaves, 1>(a, st) : launch_recall<D, false, kArmWaves, 1>(a, st);
+    if (e != 0) return e;
+    hipLaunchKernelGGL(arm_finish_kernel, dim3(a.BH), dim3(64 * 2 * kMaxBw), 0, st, a);
     return static_cast<int>(hipGetLastError());
 }
 

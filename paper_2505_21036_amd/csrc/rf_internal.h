@@ -134,7 +134,7 @@ struct ArmArgs {
     ArmPass pass[2];   // 0: Temporal mask (R_hat), 1: Spatial mask (R_tilde)
     int n_bw;          // candidate bandwidths (1 for plain Alg. 1)
     int by_width[kMaxBw];  // candidate indices from the narrowest bandwidth to the widest
-    float* row_recall; // device [BH][2][n_bw][max_n]
+    float* row_recall; // device [BH][2][n_bw][max_n]: the first ceil(n / 32) of each max_n hold the sums over 32 sampled rows
     int max_n;
     float threshold;
     int fallback_class;   // class of a head that matches neither mask
