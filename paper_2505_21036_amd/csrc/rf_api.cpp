@@ -321,7 +321,9 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
 
     AttnArgs a{};
     a.wide_rows = (params && (params->flags & RF_FLAG_WIDE_ROWS)) ? 1 : 0;
-    const int rows = a.wide_rows ? block : choose_rows(g, B * nH, D, force_dense, room_to_pack);
+    const AttnForm form = a.wide_rows ? AttnForm{block, 1, true, true} : choose_form(g, B * nH, D, force_dense, room_to_pack);
+    a.queued = form.queued ? 1 : 0;
+    a.key_groups = form.key_groups;
     a.n_plans = bandwidths ? n_bw : 1;
     for (int k = 0; k < a.n_plans; ++k) {
         Geometry gk = g;
@@ -329,7 +331,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
             st = geometry_with_bandwidth(layout, params, bandwidths[k], &gk);
             if (st != RF_OK) return st;
         }
-        st = get_attention_plan(gk, rows, &a.plan[k]);
+        st = get_attention_plan(gk, form.rows, &a.plan[k]);
         if (st != RF_OK) return st;
     }
     a.Q = static_cast<const uint16_t*>(Q);
@@ -345,7 +347,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.head_bw = bandwidths ? head_bw : nullptr;
     a.BH = B * nH;
     a.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
-    if (room_to_pack && !force_dense && (a.wide_rows || wants_copies(rows, D))) {
+    if (room_to_pack && !force_dense && form.copies) {
         a.packed_k = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) + RF_ATTENTION_MIN_WORKSPACE);
         a.packed_v = a.packed_k + static_cast<size_t>(B) * nH * g.N * D;
         if (launch_pack_textural(a, D, stream) != 0) return RF_ERR_HIP;

@@ -564,14 +564,13 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
 enum : int {
     LOOP_32 = 0,           // wavefronts of 32 query rows (attend)
     LOOP_64_PIPELINED = 1, // wavefronts of 64 rows, one per SIMD, software-pipelined (attend_wide)
-    LOOP_SPLIT = 3,        // wavefronts of 32 rows in four groups that split the walk (attend with KS = 4)
+    LOOP_ITEM = 3,         // LOOP_32 for one item per workgroup, without a queue; its wavefronts may form groups that split the walk
     LOOP_64 = 2            // wavefronts of 64 rows on the plain loop (attend with two halves): head_dim 64 only, where two fit a SIMD
 };
-constexpr int key_groups(int LOOP) { return LOOP == LOOP_SPLIT ? 4 : 1; }
 constexpr int rows_per_wave(int LOOP) { return LOOP == LOOP_64_PIPELINED || LOOP == LOOP_64 ? 64 : 32; }
 // Which instances walk banded lists by key index (MODE_BAND, MODE_BAND_GATHER) instead of by attribute table
 // (MODE_LISTED): two halves, and twelve wavefronts but at head_dim 64, have no registers left for the other masks.
-// (Those that do are the ones that need no copies of K and V: wants_copies in rf_plan.cpp.)
+// (Those that do are the ones that need no copies of K and V: AttnForm::copies.)
 constexpr bool walks_bands(int D, int NW, int LOOP) { return rows_per_wave(LOOP) == 32 && (NW != 12 || D == 64); }
 
 // Wavefronts per SIMD the register allocation is held to: three for head_dim 64 with 128-row
@@ -649,7 +648,7 @@ __device__ __forceinline__ int take_item(int* ctr, int home, const Queues& qs, i
     }
 }
 
-template <int D, int NW, int LOOP>
+template <int D, int NW, int LOOP, int KS = 1, int AHEAD = RF_TILES_AHEAD>
 __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues& qs, unsigned char* smem);
 
 // Eight queue counters, then the sweep words (-1: nothing published yet).
@@ -694,27 +693,30 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
     }
 }
 
-// Problems with few query rows: KS groups of NW wavefronts per workgroup split the walk of 32 * NW rows, one
-// workgroup per item and no queue (workgroup ids go to the XCDs round-robin, so workgroup i is item i / 8 of
-// queue i mod 8).
-template <int D, int NW, int LOOP>
-__global__ void __launch_bounds__(64 * NW * key_groups(LOOP)) __attribute__((amdgpu_waves_per_eu(2, 2))) attn_split_kernel(AttnArgs a) {
+// The kernel for launches of few rounds: one workgroup per item and no queue (workgroup ids go to the XCDs
+// round-robin, so workgroup i is item i / 8 of queue i mod 8).  Without the queue there is no kernel to reset it,
+// no atomic round trip and no second barrier before an item's first load, and workgroups of any size share a CU:
+// 48 heads of 2000 tokens at head_dim 128, 128 rows: 109 -> 75 us; 256 rows: 88 -> 81 us; from about 16000 tokens on
+// the queue's balance between XCDs and its joined walks win (256 rows, 48 heads of 17776: 3.71 against 3.77 ms).
+// KS groups of NW wavefronts split the walk of 32 * NW rows.  AHEAD = 0 keeps one buffer for K and one for V, so
+// that twice the workgroups fit a CU's LDS.
+template <int D, int NW, int KS, int AHEAD, int WAVES>
+__global__ void __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) attn_item_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];  // the kernel's only LDS: starts at address 0
     const Queues qs(a);
     const int xcd = blockIdx.x & 7, item = blockIdx.x >> 3;
     if (item >= qs.items(xcd)) return;
-    process_item<D, NW, LOOP>(a, item, xcd, -1, qs, smem);
+    process_item<D, NW, LOOP_ITEM, KS, AHEAD>(a, item, xcd, -1, qs, smem);
 }
 
 // One (head, query block) item: item-th of queue xcd.  seen: the sweep word of this workgroup's XCD
 // (it serves its own L2, whichever queue the item came from), or -1.
-template <int D, int NW, int LOOP>
+template <int D, int NW, int LOOP, int KS, int AHEAD>
 __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues& qs, unsigned char* smem) {
     auto run = [&](auto mode, const DevicePlan& plan, const QueryBlock& block) {
         constexpr int MODE = decltype(mode)::value;
         if constexpr (LOOP == LOOP_64_PIPELINED) attend_wide<D, NW, MODE>(a, plan, block, smem);
-        else if constexpr (key_groups(LOOP) > 1) attend<D, NW, MODE, 1, key_groups(LOOP), 0>(a, plan, block, smem);
-        else attend<D, NW, MODE, rows_per_wave(LOOP) / 32>(a, plan, block, smem);
+        else attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD>(a, plan, block, smem);
     };
     int ordinal, bh;  // position in the block order, and the head
     qs.locate(item, xcd, &bh, &ordinal);
@@ -729,7 +731,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
     const DevicePlan& pl = a.plan[which];
     // One item per workgroup: what stands between its start and its first tile are these loads, one after the
     // other, so the list bounds of every pattern are asked for along with the class, and the blocks keep their order.
-    constexpr bool kOneItem = key_groups(LOOP) > 1;
+    constexpr bool kOneItem = LOOP == LOOP_ITEM;
     int lo[kLists] = {}, hi[kLists] = {};
     if constexpr (kOneItem) {
         qk.qb = ordinal < qs.nTB ? qs.nVB + ordinal : ordinal - qs.nTB;
@@ -887,10 +889,9 @@ static int launch_one(const AttnArgs& a, hipStream_t st) {
     return static_cast<int>(hipGetLastError());
 }
 
-template <int D, int NW, int LOOP>
-static int launch_split(const AttnArgs& a, hipStream_t st) {
-    constexpr int KS = key_groups(LOOP), NT = 64 * NW * KS;
-    constexpr int smem = AttnSmem<D, NW, KS, 0>::BYTES;
+template <int D, int NW, int KS, int AHEAD, int WAVES>
+static int launch_items(const AttnArgs& a, hipStream_t st) {
+    constexpr int NT = 64 * NW * KS, smem = AttnSmem<D, NW, KS, AHEAD>::BYTES;
     constexpr int kMaxDevices = 64;
     static std::mutex mu;
     static bool ready_on[kMaxDevices] = {};  // the kernel's dynamic-LDS limit has been raised there
@@ -901,8 +902,8 @@ static int launch_split(const AttnArgs& a, hipStream_t st) {
     {
         std::lock_guard<std::mutex> lock(mu);
         if (!ready_on[dev]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_split_kernel<D, NW, LOOP>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-            if (e != hipSuccess) return static_cast<int>(e);
+            const void* fn = reinterpret_cast<const void*>(&attn_item_kernel<D, NW, KS, AHEAD, WAVES>);
+            if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, smem)) != hipSuccess) return static_cast<int>(e);
             ready_on[dev] = true;
         }
     }
@@ -910,9 +911,21 @@ static int launch_split(const AttnArgs& a, hipStream_t st) {
     int most = 0;
     for (int x = 0; x < 8; ++x) most = std::max(most, qs.items(x));
     AttnArgs s = a;
-    s.join_sweep = 0;  // the items start together
-    hipLaunchKernelGGL((attn_split_kernel<D, NW, LOOP>), dim3(8 * most), dim3(NT), smem, st, s);
+    s.join_sweep = 0;  // its words are not there: nothing resets them
+    hipLaunchKernelGGL((attn_item_kernel<D, NW, KS, AHEAD, WAVES>), dim3(8 * most), dim3(NT), smem, st, s);
     return static_cast<int>(hipGetLastError());
+}
+
+// The item kernels of one head_dim: 64 rows with the keys split four or two ways, 128 rows, 256 rows (not at
+// head_dim 64, where 128 rows measured 6 % faster).  Wavefronts per SIMD: three where the registers allow it.
+template <int D>
+static int launch_items_d(const AttnArgs& a, hipStream_t st) {
+    if (a.plan[0].block == 64 && a.key_groups == 4) return launch_items<D, 2, 4, 0, 2>(a, st);
+    if (a.plan[0].block == 64 && a.key_groups == 2) return launch_items<D, 2, 2, 0, D == 64 ? 3 : 2>(a, st);
+    if (a.plan[0].block == 128) return launch_items<D, 4, 1, 0, D == 128 ? 2 : 3>(a, st);
+    if constexpr (D != 64)
+        if (a.plan[0].block == 256) return launch_items<D, 8, 1, 1, 2>(a, st);
+    return static_cast<int>(hipErrorInvalidValue);
 }
 
 int launch_attention(const AttnArgs& a, int D, void* stream) {
@@ -922,13 +935,8 @@ int launch_attention(const AttnArgs& a, int D, void* stream) {
         if (D == 128 && nw == 8) return launch_one<128, 4, LOOP_64_PIPELINED>(a, st);
         return static_cast<int>(hipErrorInvalidValue);
     }
-    // 64 rows: two wavefronts' worth, worked by four groups that split the keys
-    if (D == 64 && nw == 2) return launch_split<64, 2, LOOP_SPLIT>(a, st);
-    if (D == 96 && nw == 2) return launch_split<96, 2, LOOP_SPLIT>(a, st);
-    if (D == 128 && nw == 2) return launch_split<128, 2, LOOP_SPLIT>(a, st);
-    if (D == 64 && nw == 4) return launch_one<64, 4>(a, st);
-    if (D == 96 && nw == 4) return launch_one<96, 4>(a, st);
-    if (D == 128 && nw == 4) return launch_one<128, 4>(a, st);
+    if (D != 64 && D != 96 && D != 128) return static_cast<int>(hipErrorInvalidValue);
+    if (!a.queued) return D == 64 ? launch_items_d<64>(a, st) : D == 96 ? launch_items_d<96>(a, st) : launch_items_d<128>(a, st);
     // 256-row blocks at head_dim 64: four wavefronts of 64 rows (two still fit a SIMD; measured 8-15 %
     // faster than eight of 32: half the LDS operand reads and half the per-tile bookkeeping per MFMA)
     if (D == 64 && nw == 8) return launch_one<64, 4, LOOP_64>(a, st);

@@ -68,11 +68,16 @@ int resolve_geometry(const rf_layout* layout, const rf_params* params, Geometry*
 // Builds the block lists. Pure host code.
 void build_plan(const Geometry& g, int block, HostPlan* plan);
 
-// Query rows a workgroup of the attention kernel takes at a time, 64, 128, 256 or 384, for the shortest launch at
-// this size.  dense: every head is known to be dense; room: there is a workspace for copies of K and V.
-int choose_rows(const Geometry& g, int BH, int D, bool dense, bool room);
-// Whether the kernel for that many rows profits from those copies.
-bool wants_copies(int rows, int D);
+// How an attention call runs: query rows a workgroup takes at a time (64, 128, 256 or 384), groups of its
+// wavefronts that split the keys (4, 2 or 1), whether a resident set of workgroups takes items from queues or every
+// item has a workgroup, and whether the kernel profits from copies of K and V.
+struct AttnForm {
+    int rows, key_groups;
+    bool queued, copies;
+};
+// The form with the shortest launch at this size.  dense: every head is known to be dense; room: there is a
+// workspace for the copies.
+AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room);
 
 // Block list of one class as the kernel walks it (see rf_plan_host in rainfusion.h).
 void flatten_class(const HostPlan& plan, int cls, std::vector<int32_t>* row_ptr, std::vector<int32_t>* cols);
@@ -109,6 +114,8 @@ struct AttnArgs {
     const int32_t* head_bw;  // optional per-head index into plan[]; null or out of range: plan[0]
     int* queue;              // 8 work-queue counters and 8 sweep words (one each per XCD) at the start of the caller's workspace, reset by the launcher
     int by_head;             // 1: an XCD takes whole heads; 0: its eighth of every head (see Queues in rf_attn.hip)
+    int queued;              // see AttnForm
+    int key_groups;          // see AttnForm
     int wide_rows;           // 1: wavefronts of 64 query rows (256-row blocks only)
     int join_sweep;          // 1: a starting item joins the tile walk of the workgroups already running on its XCD; 0: fixed start
     int n_plans;

@@ -206,56 +206,79 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
     order_query_blocks(plan);
 }
 
-// The kernels for the four row counts differ in how many workgroups a CU holds and in how long one of them takes
-// per 64-key tile and to start and finish (us, a full chip, fitted to 48 sizes with three kinds of heads, a
-// nearly uniform mix of classes, with and without text; the choice is then within 1 % of the best of the four on
-// average, 25 % at the worst).  The 64-row kernel has four times the workgroups of the others' rows and splits the
-// keys four ways, so it takes the small problems (at 2 x 3 heads of 960 tokens, head_dim 128, it takes 21 us
-// against 44 / 55 / 70 of the others); it does half as much per tile and clock as the 384-row one, which takes
-// the largest; between them what counts is how full the last round of workgroups is.
-int choose_rows(const Geometry& g, int BH, int D, bool dense, bool room) {
-    struct Kernel { int rows, per_cu; double tile_us, item_us; };
-    static const Kernel kKernels[3][4] = {
-        {{64, 1, 0.417, 5.5}, {128, 3, 1.881, 16.1}, {256, 2, 2.207, 19.6}, {384, 1, 1.568, 19.1}},   // head_dim 64
-        {{64, 1, 0.501, 6.2}, {128, 2, 1.540, 19.8}, {256, 1, 1.584, 10.8}, {384, 1, 1.889, 19.0}},   // head_dim 96
-        {{64, 1, 0.658, 3.0}, {128, 2, 1.971, 10.1}, {256, 1, 1.631, 12.3}, {384, 1, 2.292, 23.0}}};  // head_dim 128
+// What a launch takes in each form: how many workgroups a CU holds, and the time (us, a full chip) one of them
+// takes per 64-key tile and to start and finish.  The numbers are fitted to 60 sizes (256 to 48000 tokens, 1 to 48
+// heads), all dense and with a nearly uniform mix of classes; the choice is then within 1.1 % of the best form on
+// average and 13 % at the worst.  Few rows: keys split four ways, then two ways (2 x 3 heads of 960 tokens,
+// head_dim 128: 21 us, 26 and with 128 rows 38; 24 heads of 4109: 206, 167 and 176).  Many: the forms with the most
+// rows do the least per row and tile (48 heads of 17776: 5.0, 4.6 and 4.0 ms for these, 3.75 and 3.67 with 256 rows from
+// the grid and from queues; 4 heads of 48000, dense: 4.63, 4.12 and 4.19 with 128 and 256 rows, 3.95 with 384).  Between them what counts is how full the last round of workgroups is.
+//
+// copies: up to 256 rows, rows gathered through an index table cost nothing that can be measured, so no copies are
+// made (17776 tokens, 24 heads, head_dim 128, 128 rows: 1.92 ms either way); twelve wavefronts at head_dim 96 and 128
+// and the 64-row wavefronts at 64 have no registers for the loop that gathers Temporal heads (3.79 ms in token order
+// against 1.85 ms with copies at 384 rows).
+AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
+    struct Kernel {
+        AttnForm form;
+        int per_cu;
+        double tile_us, item_us;
+    };
+    static const Kernel kKernels[3][6] = {{{{64, 4, false, false}, 1, 0.425, 7.6},  // head_dim 64
+                                           {{64, 2, false, false}, 3, 0.900, 7.4},
+                                           {{128, 1, false, false}, 3, 1.413, 10.8},
+                                           {{256, 1, true, true}, 2, 2.172, 18.2},
+                                           {{384, 1, true, false}, 1, 1.314, 22.8},
+                                           {{0, 0, false, false}, 0, 0, 0}},
+                                          {{{64, 4, false, false}, 1, 0.506, 6.8},  // head_dim 96
+                                           {{64, 2, false, false}, 2, 0.900, 7.8},
+                                           {{128, 1, false, false}, 3, 2.164, 8.1},
+                                           {{256, 1, false, false}, 1, 1.347, 12.2},
+                                           {{256, 1, true, false}, 1, 1.270, 24.9},
+                                           {{384, 1, true, true}, 1, 1.670, 14.9}},
+                                          {{{64, 4, false, false}, 1, 0.624, 7.7},  // head_dim 128
+                                           {{64, 2, false, false}, 2, 1.091, 6.7},
+                                           {{128, 1, false, false}, 2, 1.911, 6.1},
+                                           {{256, 1, false, false}, 1, 1.611, 12.9},
+                                           {{256, 1, true, false}, 1, 1.810, 17.1},
+                                           {{384, 1, true, true}, 1, 2.129, 20.6}}};
     constexpr int kCUs = 256;
     const int tiles = (g.N + kTileK - 1) / kTileK;
-    int best = 0;
+    const Kernel* best = nullptr;
     double best_us = 0;
     for (const Kernel& k : kKernels[D == 64 ? 0 : D == 96 ? 1 : 2]) {
-        const bool copies = wants_copies(k.rows, D);
-        if (copies && !room && !dense) continue;  // it would walk Temporal heads in token order: up to twice the time
+        if (k.per_cu == 0) continue;
+        if (k.form.copies && !room && !dense) continue;  // it would walk Temporal heads in token order: up to twice the time
+        const int rows = k.form.rows;
         const double slots = static_cast<double>(kCUs) * k.per_cu;
-        // how much longer an item takes when a CU holds n workgroups instead of one, relative to a full one
-        auto shared = [&](double n) { return 0.3 + 0.7 * std::ceil(n / kCUs) / k.per_cu; };
+        // how long an item takes where n workgroups share the chip, relative to a full one
+        auto shared = [&](double n) { return 0.635 + 0.365 * std::ceil(n / kCUs) / k.per_cu; };
         auto launch_us = [&](double items, double item_tiles) {
             const double rounds = items / slots, full = std::floor(rounds), rest = items - full * slots;
             double last = rest > 0 ? shared(rest) : 0;
-            if (rounds >= 3 && rest > 0) last = std::min(last, 0.5 + 0.5 * rest / slots);  // workgroups out of step by then
+            if (rounds >= 3) last = std::min(last, rest / slots);  // workgroups are out of step by then
             return (full + last) * (item_tiles * k.tile_us + k.item_us);
         };
-        const int nQB = (g.N + k.rows - 1) / k.rows, nTB = g.text_len > 0 ? nQB - g.Nv / k.rows : 0;
+        const int nQB = (g.N + rows - 1) / rows, nTB = g.text_len > 0 ? nQB - g.Nv / rows : 0;
         const double items = static_cast<double>(nQB) * BH, longs = static_cast<double>(nTB) * BH;
+        // from about there on the queues' balance is worth what they cost (head_dim 128, the 256-row form from the grid
+        // and from queues: 24 heads of 4109, 1.6 rounds, 186 and 190 us; 30 of 5632, 2.6 rounds, 281 and 281; 4 of
+        // 48000, 2.9 rounds, 2.42 and 2.29 ms)
+        if (rows == 256 && !k.form.queued && items > 2.5 * slots) continue;
         double us = launch_us(items, tiles);
         if (!dense) {
-            // about half the tiles, but for the blocks that hold text rows: those walk every tile, most of them masked
-            us = launch_us(items + 1.4 * longs, 0.48 * tiles);
-            if (longs > 0) us = std::max(us, (copies ? 1.8 : 1.35) * tiles * k.tile_us * shared(std::min(items, slots)) + k.item_us);
+            // about half the tiles, but for the blocks that hold text rows: those walk every tile, most of them
+            // masked, and nothing ends before the longest item
+            us = launch_us(items + 1.1 * longs, 0.54 * tiles);
+            if (longs > 0) us = std::max(us, (k.form.copies ? 1.81 : 1.33) * tiles * k.tile_us * shared(std::min(items, slots)) + k.item_us);
         }
-        if (best == 0 || us < best_us) {
-            best = k.rows;
+        if (!best || us < best_us) {
+            best = &k;
             best_us = us;
         }
     }
-    return best;
+    return best->form;
 }
-
-// Rows that are gathered through an index table cost the kernels of up to 256 rows nothing that can be measured,
-// and so they save the copies (17776 tokens, 24 heads, head_dim 128, 128 rows: 1.92 ms either way); twelve
-// wavefronts at head_dim 96 and 128 and the 64-row wavefronts have no registers for the loop that gathers Temporal
-// heads (3.79 ms in token order against 1.85 ms with copies at 384 rows).
-bool wants_copies(int rows, int D) { return rows == (D == 64 ? 256 : 384); }
 
 // cls in the public numbering: a head class, or RF_LIST_TEMPORAL_POSITION_MAJOR
 void flatten_class(const HostPlan& P, int cls, std::vector<int32_t>* row_ptr, std::vector<int32_t>* cols) {

@@ -1,4 +1,4 @@
-// Prints choose_rows() for every line  T H W text BH D dense room  on standard input.
+// Prints choose_form() for every line  T H W text BH D dense room  on standard input.
 #include <cstdio>
 
 #include "rf_internal.h"
@@ -9,7 +9,8 @@ int main() {
         const rf_layout layout = {T, H, W, text};
         rf::Geometry g;
         if (rf::resolve_geometry(&layout, nullptr, &g) != RF_OK) return 1;
-        std::printf("%d\n", rf::choose_rows(g, BH, D, dense != 0, room != 0));
+        const rf::AttnForm f = rf::choose_form(g, BH, D, dense != 0, room != 0);
+        std::printf("%d %d %d %d\n", f.rows, f.key_groups, f.queued ? 1 : 0, f.copies ? 1 : 0);
     }
     return 0;
 }

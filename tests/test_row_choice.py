@@ -1,7 +1,8 @@
-"""The rule that chooses how many query rows a workgroup of the attention kernel takes, and the kernels behind
-it.  The rule is host code, asked through a small driver; the GPU test runs every kernel it can choose at a
-ragged size (blocks that end in text rows, a ragged last block and key tile, several rounds or one), every class,
-with and without a workspace, against the oracle on some heads of each class."""
+"""The rule that chooses how the attention kernel divides a problem (query rows a workgroup takes, wavefront
+groups that split its keys, workgroups from queues or one per block, copies of K and V), and the kernels behind it.
+The rule is host code, asked through a small driver; the GPU test runs every kernel it can choose at a ragged size
+(blocks that end in text rows, a ragged last block and key tile, several rounds or one), every class, with and
+without a workspace, against the oracle on some heads of each class."""
 import os
 import shutil
 import subprocess
@@ -18,13 +19,14 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 needs_gxx = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 
 
-def rows_chosen(tmp_path, cases):
-    """choose_rows for each (T, H, W, text, BH, D, dense, room)."""
+def forms_chosen(tmp_path, cases):
+    """(rows, key groups, queued, copies) of choose_form for each (T, H, W, text, BH, D, dense, room)."""
     exe, csrc = str(tmp_path / "rows_driver"), os.path.join(ROOT, "paper_2505_21036_amd", "csrc")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", csrc,
                            os.path.join(ROOT, "tests", "rows_driver.cpp"), os.path.join(csrc, "rf_plan.cpp"), "-o", exe])
     text = "\n".join(" ".join(str(int(x)) for x in c) for c in cases)
-    return [int(x) for x in subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split()]
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+    return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
 
 
 @needs_gxx
@@ -32,39 +34,48 @@ def test_small_problems_split_the_keys_and_the_largest_take_the_most_rows(tmp_pa
     for D in (64, 96, 128):
         small = [(4, 8, 8, 0, 2, D, d, r) for d in (0, 1) for r in (0, 1)]
         small += [(7, 10, 13, 50, 6, D, d, r) for d in (0, 1) for r in (0, 1)] + [(2, 1, 1, 1, 1, D, 0, 0)]
-        assert set(rows_chosen(tmp_path, small)) == {64}
-        assert rows_chosen(tmp_path, [(33, 45, 80, 256, 24, D, 1, 0), (1, 4096, 4096, 0, 1 << 20, D, 1, 0)]) == [384, 384]
-    # with nowhere to copy K and V to, none of the kernels that need copies
+        assert all(rows == 64 and groups > 1 and not queued for rows, groups, queued, _ in forms_chosen(tmp_path, small))
+        largest = [(33, 45, 80, 256, 24, D, 1, 0), (1, 4096, 4096, 0, 1 << 20, D, 1, 0)]
+        assert all(form[:3] == (384, 1, 1) for form in forms_chosen(tmp_path, largest))
+    # with nowhere to copy K and V to, none of the forms that need copies
     rooms = [(T, 20, 20, text, BH, D, 0, 0) for T in (2, 9, 33) for text in (0, 77) for BH in (1, 7, 48, 300) for D in (64, 96, 128)]
-    for case, rows in zip(rooms, rows_chosen(tmp_path, rooms)):
-        assert rows != (256 if case[5] == 64 else 384), (case, rows)
+    assert not any(copies for _, _, _, copies in forms_chosen(tmp_path, rooms))
 
 
-# (D, B, nH, layout, dense, room) -> rows: sizes at which the rule picks each kernel
-RAGGED, SHORT = (7, 10, 13, 50), (4, 9, 12, 0)
+# (D, B, nH, layout, dense, room) -> (rows, key groups, queued): sizes at which the rule picks each kernel
+RAGGED, SHORT, WIDE = (7, 10, 13, 50), (4, 9, 12, 0), (5, 32, 33, 37)
 KERNELS = [
-    ((64, 2, 3, RAGGED, False, True), 64), ((96, 2, 3, RAGGED, False, False), 64), ((128, 2, 3, RAGGED, False, True), 64),
-    ((64, 2, 60, RAGGED, False, False), 128), ((96, 2, 48, RAGGED, False, True), 128), ((128, 2, 48, RAGGED, False, False), 128),
-    ((64, 2, 120, SHORT, False, True), 256), ((96, 1, 72, RAGGED, False, True), 256), ((128, 2, 60, RAGGED, True, True), 256),
-    ((64, 1, 72, RAGGED, True, True), 384), ((96, 1, 72, RAGGED, True, False), 384), ((128, 1, 72, RAGGED, True, False), 384),
+    ((64, 2, 3, RAGGED, False, True), (64, 4, 0)), ((96, 2, 3, RAGGED, False, False), (64, 4, 0)), ((128, 2, 3, RAGGED, False, True), (64, 4, 0)),
+    ((64, 2, 24, RAGGED, False, False), (64, 2, 0)), ((96, 2, 24, RAGGED, False, True), (64, 2, 0)), ((128, 2, 20, RAGGED, False, False), (64, 2, 0)),
+    ((64, 2, 60, RAGGED, False, False), (128, 1, 0)), ((96, 2, 60, RAGGED, False, True), (128, 1, 0)), ((128, 2, 48, RAGGED, False, False), (128, 1, 0)),
+    ((64, 2, 60, RAGGED, True, True), (256, 1, 1)), ((64, 1, 240, SHORT, False, True), (256, 1, 1)),
+    ((96, 1, 28, WIDE, False, True), (256, 1, 0)), ((128, 1, 28, WIDE, False, False), (256, 1, 0)),
+    ((96, 1, 32, WIDE, False, False), (256, 1, 1)), ((128, 1, 8, (5, 64, 65, 37), False, False), (256, 1, 1)),
+    ((64, 1, 8, (6, 40, 41, 37), True, True), (384, 1, 1)), ((64, 1, 4, (5, 64, 65, 0), False, False), (384, 1, 1)),
+    ((96, 1, 60, WIDE, False, True), (384, 1, 1)), ((96, 1, 76, RAGGED, True, False), (384, 1, 1)),
+    ((128, 1, 60, WIDE, False, True), (384, 1, 1)), ((128, 1, 76, RAGGED, True, False), (384, 1, 1)),
 ]
 
 
 @needs_gxx
 def test_the_sizes_of_the_gpu_test_pick_the_kernels_it_names(tmp_path):
     asked = [lay + (B * nH, D, dense, room) for (D, B, nH, lay, dense, room), _ in KERNELS]
-    assert rows_chosen(tmp_path, asked) == [rows for _, rows in KERNELS]
+    assert [form[:3] for form in forms_chosen(tmp_path, asked)] == [form for _, form in KERNELS]
+    named = {(case[0],) + form for case, form in KERNELS}
+    grid = [(T, 20, 20, text, BH, D, dense, room) for T in (1, 3, 7, 20) for text in (0, 77) for BH in (1, 4, 16, 48, 72, 160, 400)
+            for D in (64, 96, 128) for dense in (0, 1) for room in (0, 1)]
+    assert {(case[5],) + form[:3] for case, form in zip(grid, forms_chosen(tmp_path, grid))} <= named
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("case,rows", KERNELS)
+@pytest.mark.parametrize("case,form", KERNELS)
 @pytest.mark.parametrize("text_first", [False, True])
-def test_every_kernel_of_the_rule_against_the_oracle(case, rows, text_first):
+def test_every_kernel_of_the_rule_against_the_oracle(case, form, text_first):
     D, B, nH, (T, H, W, tl), dense, room = case
     if text_first and tl == 0:
         pytest.skip("no text tokens to move")
-    print("case rows", rows, case, text_first, flush=True)
-    w = inp.Workload("rows", B, nH, D, T, H, W, tl, 64, 9000 + D + rows)
+    print("case form", form, case, text_first, flush=True)
+    w = inp.Workload("rows", B, nH, D, T, H, W, tl, 64, 9000 + D + form[0])
     rl, ol = rf.rf_layout(T, H, W, tl), orc.Layout(T, H, W, tl)
     flags = (rf.RF_FLAG_TEXT_FIRST if text_first else 0) | (rf.RF_FLAG_FORCE_DENSE if dense else 0)
     rp, op = rf.rf_params(0.25, 0.25, 2, 0, flags), orc.Params(text_first=text_first)
