@@ -1,7 +1,7 @@
 // Block-sparse attention forward for RainFusion's head patterns (Eq. 1-5; Fig. 2a), gfx950.
 //
-// Work item = one query block (64, 128, 256 or 384 rows) of one head; a resident set of workgroups
-// takes items from per-XCD queues.  For its item a workgroup reads the head's class on the device,
+// Work item = one query block (64, 128, 256 or 384 rows) of one head; one workgroup per item in launches of a few
+// rounds, otherwise a resident set of workgroups that takes items from per-XCD queues.  For its item a workgroup reads the head's class on the device,
 // walks that class's list of 64-key tiles (skipped tiles cost no traffic), loads K and V tiles
 // global -> LDS one tile ahead without staging registers, forms the transposed score tile with
 // bf16 MFMA, runs the online softmax in fp32 with exp2, and accumulates O^T = V^T P^T with bf16
@@ -573,12 +573,11 @@ constexpr int rows_per_wave(int LOOP) { return LOOP == LOOP_64_PIPELINED || LOOP
 // (Those that do are the ones that need no copies of K and V: AttnForm::copies.)
 constexpr bool walks_bands(int D, int NW, int LOOP) { return rows_per_wave(LOOP) == 32 && (NW != 12 || D == 64); }
 
-// Wavefronts per SIMD the register allocation is held to: three for head_dim 64 with 128-row
-// blocks of 32-row wavefronts (measured best; its accumulators are half the size) and for the
-// twelve-wavefront workgroups of 384-row blocks, two otherwise; one for the pipelined 64-row loop,
-// which needs the whole register file.
-constexpr int attn_waves_per_simd(int D, int NW, int LOOP) {
-    return LOOP == LOOP_64_PIPELINED ? 1 : (LOOP == LOOP_32 && ((D == 64 && NW == 4) || NW == 12)) ? 3 : 2;
+// Wavefronts per SIMD the register allocation of the queued kernels is held to: three for the twelve-wavefront
+// workgroups of 384-row blocks, two otherwise; one for the pipelined 64-row loop, which needs the whole
+// register file.
+constexpr int attn_waves_per_simd(int NW, int LOOP) {
+    return LOOP == LOOP_64_PIPELINED ? 1 : LOOP == LOOP_32 && NW == 12 ? 3 : 2;
 }
 
 template <int D, int NW, int LOOP>
@@ -658,7 +657,7 @@ __global__ void reset_queue_kernel(int* ctr) {
 
 // NW wavefronts of rows_per_wave(LOOP) query rows each.
 template <int D, int NW, int LOOP>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(attn_waves_per_simd(D, NW, LOOP), attn_waves_per_simd(D, NW, LOOP)))) attn_kernel(AttnArgs a) {
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(attn_waves_per_simd(NW, LOOP), attn_waves_per_simd(NW, LOOP)))) attn_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];  // the kernel's only LDS: starts at address 0
     int* item_box = reinterpret_cast<int*>(smem + SmemOf<D, NW, LOOP>::ITEM_OFF);
     // A resident set of workgroups (as many as fit on the chip) works through the (head, query

@@ -207,41 +207,43 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
 }
 
 // What a launch takes in each form: how many workgroups a CU holds, and the time (us, a full chip) one of them
-// takes per 64-key tile and to start and finish.  The numbers are fitted to 60 sizes (256 to 48000 tokens, 1 to 48
-// heads), all dense and with a nearly uniform mix of classes; the choice is then within 1.1 % of the best form on
-// average and 13 % at the worst.  Few rows: keys split four ways, then two ways (2 x 3 heads of 960 tokens,
-// head_dim 128: 21 us, 26 and with 128 rows 38; 24 heads of 4109: 206, 167 and 176).  Many: the forms with the most
-// rows do the least per row and tile (48 heads of 17776: 5.0, 4.6 and 4.0 ms for these, 3.75 and 3.67 with 256 rows from
-// the grid and from queues; 4 heads of 48000, dense: 4.63, 4.12 and 4.19 with 128 and 256 rows, 3.95 with 384).  Between them what counts is how full the last round of workgroups is.
+// takes per 64-key tile and to start and finish. The numbers are fitted to 60 sizes (256 to 48000 tokens, 1 to 48
+// heads), all dense and with a nearly uniform mix of classes; the choice is then within 1.0 % of the best form on
+// average and 13 % at the worst. Few rows: keys split four ways, then two ways (2 x 3 heads of 960 tokens,
+// head_dim 128: 21 us, 26 and with 128 rows 38; 24 heads of 4109: 206, 167 and 176). Many: the forms with the most
+// rows do the least per row and tile (48 heads of 17776: 5.0, 4.6 and 4.0 ms for these, 3.75 and 3.67 with 256
+// rows from the grid and from queues; 4 heads of 48000, dense: 4.63, 4.12 and 4.19 with 128 and 256 rows, 3.95
+// with 384). Between them what counts is how full the last round of workgroups is.
 //
 // copies: up to 256 rows, rows gathered through an index table cost nothing that can be measured, so no copies are
-// made (17776 tokens, 24 heads, head_dim 128, 128 rows: 1.92 ms either way); twelve wavefronts at head_dim 96 and 128
-// and the 64-row wavefronts at 64 have no registers for the loop that gathers Temporal heads (3.79 ms in token order
-// against 1.85 ms with copies at 384 rows).
+// made (17776 tokens, 24 heads, head_dim 128, 128 rows: 1.92 ms either way); twelve wavefronts at head_dim 96 and
+// 128 and the 64-row wavefronts at 64 have no registers for the loop that gathers Temporal heads (3.79 ms in token
+// order against 1.85 ms with copies at 384 rows).
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
     struct Kernel {
         AttnForm form;
         int per_cu;
         double tile_us, item_us;
+        double dense;  // times tile_us where no list is walked (32 dense heads of 16384, head_dim 64: 2.45, 2.26, 2.47 ms from 128 rows on)
     };
-    static const Kernel kKernels[3][6] = {{{{64, 4, false, false}, 1, 0.425, 7.6},  // head_dim 64
-                                           {{64, 2, false, false}, 3, 0.900, 7.4},
-                                           {{128, 1, false, false}, 3, 1.413, 10.8},
-                                           {{256, 1, true, true}, 2, 2.172, 18.2},
-                                           {{384, 1, true, false}, 1, 1.314, 22.8},
-                                           {{0, 0, false, false}, 0, 0, 0}},
-                                          {{{64, 4, false, false}, 1, 0.506, 6.8},  // head_dim 96
-                                           {{64, 2, false, false}, 2, 0.900, 7.8},
-                                           {{128, 1, false, false}, 3, 2.164, 8.1},
-                                           {{256, 1, false, false}, 1, 1.347, 12.2},
-                                           {{256, 1, true, false}, 1, 1.270, 24.9},
-                                           {{384, 1, true, true}, 1, 1.670, 14.9}},
-                                          {{{64, 4, false, false}, 1, 0.624, 7.7},  // head_dim 128
-                                           {{64, 2, false, false}, 2, 1.091, 6.7},
-                                           {{128, 1, false, false}, 2, 1.911, 6.1},
-                                           {{256, 1, false, false}, 1, 1.611, 12.9},
-                                           {{256, 1, true, false}, 1, 1.810, 17.1},
-                                           {{384, 1, true, true}, 1, 2.129, 20.6}}};
+    static const Kernel kKernels[3][6] = {{{{64, 4, false, false}, 1, 0.425, 7.6, 1},  // head_dim 64
+                                           {{64, 2, false, false}, 3, 0.900, 7.4, 1},
+                                           {{128, 1, false, false}, 3, 1.413, 10.8, 1.3},
+                                           {{256, 1, true, true}, 2, 2.172, 18.2, 1},
+                                           {{384, 1, true, false}, 1, 1.314, 22.8, 1.15},
+                                           {{0, 0, false, false}, 0, 0, 0, 1}},
+                                          {{{64, 4, false, false}, 1, 0.506, 6.8, 1},  // head_dim 96
+                                           {{64, 2, false, false}, 2, 0.900, 7.8, 1},
+                                           {{128, 1, false, false}, 3, 2.164, 8.1, 1},
+                                           {{256, 1, false, false}, 1, 1.347, 12.2, 1},
+                                           {{256, 1, true, false}, 1, 1.270, 24.9, 1},
+                                           {{384, 1, true, true}, 1, 1.670, 14.9, 1}},
+                                          {{{64, 4, false, false}, 1, 0.624, 7.7, 1},  // head_dim 128
+                                           {{64, 2, false, false}, 2, 1.091, 6.7, 1},
+                                           {{128, 1, false, false}, 2, 1.911, 6.1, 1},
+                                           {{256, 1, false, false}, 1, 1.611, 12.9, 1},
+                                           {{256, 1, true, false}, 1, 1.810, 17.1, 1},
+                                           {{384, 1, true, true}, 1, 2.129, 20.6, 1}}};
     constexpr int kCUs = 256;
     const int tiles = (g.N + kTileK - 1) / kTileK;
     const Kernel* best = nullptr;
@@ -256,8 +258,8 @@ AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
         auto launch_us = [&](double items, double item_tiles) {
             const double rounds = items / slots, full = std::floor(rounds), rest = items - full * slots;
             double last = rest > 0 ? shared(rest) : 0;
-            if (rounds >= 3) last = std::min(last, rest / slots);  // workgroups are out of step by then
-            return (full + last) * (item_tiles * k.tile_us + k.item_us);
+            if (rounds >= 3) last = std::min(last, dense && rest > 0 ? 0.5 + 0.5 * rest / slots : rest / slots);  // out of step by then
+            return (full + last) * (item_tiles * k.tile_us * (dense ? k.dense : 1) + k.item_us);
         };
         const int nQB = (g.N + rows - 1) / rows, nTB = g.text_len > 0 ? nQB - g.Nv / rows : 0;
         const double items = static_cast<double>(nQB) * BH, longs = static_cast<double>(nTB) * BH;
