@@ -258,7 +258,10 @@ AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
         auto launch_us = [&](double items, double item_tiles) {
             const double rounds = items / slots, full = std::floor(rounds), rest = items - full * slots;
             double last = rest > 0 ? shared(rest) : 0;
-            if (rounds >= 3) last = std::min(last, dense && rest > 0 ? 0.5 + 0.5 * rest / slots : rest / slots);  // out of step by then
+            // workgroups are out of step by then; dense walks at head_dim 64, all of one length, less so (at 128 it
+            // would pick 384 rows for 10 heads of 22626: 2.64 ms against 2.56)
+            const double part = dense && D == 64 && rest > 0 ? 0.5 + 0.5 * rest / slots : rest / slots;
+            if (rounds >= 3) last = std::min(last, part);
             return (full + last) * (item_tiles * k.tile_us * (dense ? k.dense : 1) + k.item_us);
         };
         const int nQB = (g.N + rows - 1) / rows, nTB = g.text_len > 0 ? nQB - g.Nv / rows : 0;
