@@ -650,7 +650,9 @@ __device__ __forceinline__ int take_item(int* ctr, int home, const Queues& qs, i
 template <int D, int NW, int LOOP, int KS = 1, int AHEAD = RF_TILES_AHEAD>
 __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues& qs, unsigned char* smem);
 
-// Eight queue counters, then the sweep words (-1: nothing published yet).
+// Eight queue counters, then the sweep words (-1: nothing published yet).  One workgroup, one thread per word.
+constexpr int kResetThreads = 128;
+static_assert(kResetThreads >= kQueueWords, "every counter and sweep word is reset");
 __global__ void reset_queue_kernel(int* ctr) {
     if (threadIdx.x < kQueueWords) ctr[threadIdx.x] = threadIdx.x < 8 ? 0 : -1;
 }
@@ -881,7 +883,7 @@ static int launch_one(const AttnArgs& a, hipStream_t st) {
     }
     const long long items = static_cast<long long>(a.plan[0].nQB) * a.BH;
     const int grid = static_cast<int>(std::min<long long>(resident, items));
-    hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, st, a.queue);
+    hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(kResetThreads), 0, st, a.queue);
     e = hipGetLastError();
     if (e != hipSuccess) return static_cast<int>(e);
     hipLaunchKernelGGL((attn_kernel<D, NW, LOOP>), dim3(grid), dim3(NT), smem, st, a);
