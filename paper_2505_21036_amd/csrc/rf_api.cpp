@@ -301,7 +301,7 @@ size_t rf_attention_workspace_bytes(int B, int nH, int D, const rf_layout* layou
 static int sparse_attention_impl(const void* Q, const void* K, const void* V, const int32_t* head_class,
                                  const int32_t* head_bw, const float* bandwidths, int n_bw, int B, int nH, int D,
                                  const rf_layout* layout, const rf_params* params, int block, void* O, void* workspace,
-                                 size_t workspace_bytes, void* stream) {
+                                 size_t workspace_bytes, void* stream, const AttnForm* named = nullptr) {
     if (!Q || !K || !V || !O || !layout) return RF_ERR_NULL;
     const bool force_dense = params && (params->flags & RF_FLAG_FORCE_DENSE);
     if (!head_class && !force_dense) return RF_ERR_NULL;
@@ -321,7 +321,8 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
 
     AttnArgs a{};
     a.wide_rows = (params && (params->flags & RF_FLAG_WIDE_ROWS)) ? 1 : 0;
-    const AttnForm form = a.wide_rows ? AttnForm{block, 1, true, true} : choose_form(g, B * nH, D, force_dense, room_to_pack);
+    const AttnForm form = named ? *named : a.wide_rows ? AttnForm{block, 1, true, true} : choose_form(g, B * nH, D, force_dense, room_to_pack);
+    if (named && named->copies && !room_to_pack && !force_dense) return RF_ERR_WORKSPACE;
     a.queued = form.queued ? 1 : 0;
     a.key_groups = form.key_groups;
     a.n_plans = bandwidths ? n_bw : 1;
@@ -371,6 +372,22 @@ int rf_sparse_attention_plus(const void* Q, const void* K, const void* V, const 
     if (st != RF_OK) return st;
     return sparse_attention_impl(Q, K, V, head_class, head_bw, bandwidths, n_bw, B, nH, D, layout, params, block, O,
                                  workspace, workspace_bytes, stream);
+}
+
+int rf_internal_attention_as(int rows, int key_groups, int queued, const void* Q, const void* K, const void* V,
+                             const int32_t* head_class, const int32_t* head_bw, const float* bandwidths, int n_bw, int B,
+                             int nH, int D, const rf_layout* layout, const rf_params* params, void* O, void* workspace,
+                             size_t workspace_bytes, void* stream) {
+    AttnForm form;
+    if ((D != 64 && D != 96 && D != 128) || !find_form(D, rows, key_groups, queued != 0, &form)) return RF_ERR_PARAM;
+    if (params && (params->flags & RF_FLAG_WIDE_ROWS)) return RF_ERR_PARAM;
+    if (bandwidths) {
+        if (!head_bw) return RF_ERR_NULL;
+        const int st = check_bandwidths(bandwidths, n_bw);
+        if (st != RF_OK) return st;
+    }
+    return sparse_attention_impl(Q, K, V, head_class, head_bw, bandwidths, n_bw, B, nH, D, layout, params, rows, O, workspace,
+                                 workspace_bytes, stream, &form);
 }
 
 int rf_plan_host(const rf_layout* layout, const rf_params* params, int block, int cls, int32_t* row_ptr,

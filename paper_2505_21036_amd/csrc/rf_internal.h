@@ -78,6 +78,8 @@ struct AttnForm {
 // The form with the shortest launch at this size.  dense: every head is known to be dense; room: there is a
 // workspace for the copies.
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room);
+// The form with these numbers, if head_dim D has one.
+bool find_form(int D, int rows, int key_groups, bool queued, AttnForm* form);
 
 // Block list of one class as the kernel walks it (see rf_plan_host in rainfusion.h).
 void flatten_class(const HostPlan& plan, int cls, std::vector<int32_t>* row_ptr, std::vector<int32_t>* cols);
@@ -159,3 +161,12 @@ int arm_static_scratch(void** ptr, size_t* bytes);
 constexpr size_t kArmStaticScratchBytes = RF_ARM_STATIC_SCRATCH_BYTES;
 
 }  // namespace rf
+
+// rf_sparse_attention_plus (or, with bandwidths and head_bw null, rf_sparse_attention) in the form named instead of
+// the one choose_form picks: for tests and measurements, which have to reach every kernel at small sizes.
+// RF_ERR_PARAM if the head_dim has no such form, RF_ERR_WORKSPACE if the form walks copies of K and V and the
+// workspace has no room for them (and the call is not RF_FLAG_FORCE_DENSE).
+extern "C" int rf_internal_attention_as(int rows, int key_groups, int queued, const void* Q, const void* K, const void* V,
+                                        const int32_t* head_class, const int32_t* head_bw, const float* bandwidths, int n_bw,
+                                        int B, int nH, int D, const rf_layout* layout, const rf_params* params, void* O,
+                                        void* workspace, size_t workspace_bytes, void* stream);

@@ -206,6 +206,8 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
     order_query_blocks(plan);
 }
 
+namespace {
+
 // What a launch takes in each form: how many workgroups a CU holds, and the time (us, a full chip) one of them
 // takes per 64-key tile and to start and finish. The numbers are fitted to 60 sizes (256 to 48000 tokens, 1 to 48
 // heads), all dense and with a nearly uniform mix of classes; the choice is then within 1.0 % of the best form on
@@ -219,36 +221,55 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
 // made (17776 tokens, 24 heads, head_dim 128, 128 rows: 1.92 ms either way); twelve wavefronts at head_dim 96 and
 // 128 and the 64-row wavefronts at 64 have no registers for the loop that gathers Temporal heads (3.79 ms in token
 // order against 1.85 ms with copies at 384 rows).
+struct Kernel {
+    AttnForm form;
+    int per_cu;
+    double tile_us, item_us;
+    double dense;  // times tile_us where no list is walked (32 dense heads of 16384, head_dim 64: 2.45, 2.26, 2.47 ms from 128 rows on)
+};
+constexpr int kForms = 6;  // of one head_dim, at most
+const Kernel kKernels[3][kForms] = {{{{64, 4, false, false}, 1, 0.425, 7.6, 1},  // head_dim 64
+                                       {{64, 2, false, false}, 3, 0.900, 7.4, 1},
+                                       {{128, 1, false, false}, 3, 1.413, 10.8, 1.3},
+                                       {{256, 1, true, true}, 2, 2.172, 18.2, 1},
+                                       {{384, 1, true, false}, 1, 1.314, 22.8, 1.15},
+                                       {{0, 0, false, false}, 0, 0, 0, 1}},
+                                      {{{64, 4, false, false}, 1, 0.506, 6.8, 1},  // head_dim 96
+                                       {{64, 2, false, false}, 2, 0.900, 7.8, 1},
+                                       {{128, 1, false, false}, 3, 2.164, 8.1, 1},
+                                       {{256, 1, false, false}, 1, 1.347, 12.2, 1},
+                                       {{256, 1, true, false}, 1, 1.270, 24.9, 1},
+                                       {{384, 1, true, true}, 1, 1.670, 14.9, 1}},
+                                      {{{64, 4, false, false}, 1, 0.624, 7.7, 1},  // head_dim 128
+                                       {{64, 2, false, false}, 2, 1.091, 6.7, 1},
+                                       {{128, 1, false, false}, 2, 1.911, 6.1, 1},
+                                       {{256, 1, false, false}, 1, 1.611, 12.9, 1},
+                                       {{256, 1, true, false}, 1, 1.810, 17.1, 1},
+                                       {{384, 1, true, true}, 1, 2.129, 20.6, 1}}};
+const Kernel* kernels_of(int D) { return kKernels[D == 64 ? 0 : D == 96 ? 1 : 2]; }
+
+}  // namespace
+
+bool find_form(int D, int rows, int key_groups, bool queued, AttnForm* form) {
+    const Kernel* of_d = kernels_of(D);
+    for (int i = 0; i < kForms; ++i) {
+        const AttnForm& f = of_d[i].form;
+        if (of_d[i].per_cu > 0 && f.rows == rows && f.key_groups == key_groups && f.queued == queued) {
+            *form = f;
+            return true;
+        }
+    }
+    return false;
+}
+
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
-    struct Kernel {
-        AttnForm form;
-        int per_cu;
-        double tile_us, item_us;
-        double dense;  // times tile_us where no list is walked (32 dense heads of 16384, head_dim 64: 2.45, 2.26, 2.47 ms from 128 rows on)
-    };
-    static const Kernel kKernels[3][6] = {{{{64, 4, false, false}, 1, 0.425, 7.6, 1},  // head_dim 64
-                                           {{64, 2, false, false}, 3, 0.900, 7.4, 1},
-                                           {{128, 1, false, false}, 3, 1.413, 10.8, 1.3},
-                                           {{256, 1, true, true}, 2, 2.172, 18.2, 1},
-                                           {{384, 1, true, false}, 1, 1.314, 22.8, 1.15},
-                                           {{0, 0, false, false}, 0, 0, 0, 1}},
-                                          {{{64, 4, false, false}, 1, 0.506, 6.8, 1},  // head_dim 96
-                                           {{64, 2, false, false}, 2, 0.900, 7.8, 1},
-                                           {{128, 1, false, false}, 3, 2.164, 8.1, 1},
-                                           {{256, 1, false, false}, 1, 1.347, 12.2, 1},
-                                           {{256, 1, true, false}, 1, 1.270, 24.9, 1},
-                                           {{384, 1, true, true}, 1, 1.670, 14.9, 1}},
-                                          {{{64, 4, false, false}, 1, 0.624, 7.7, 1},  // head_dim 128
-                                           {{64, 2, false, false}, 2, 1.091, 6.7, 1},
-                                           {{128, 1, false, false}, 2, 1.911, 6.1, 1},
-                                           {{256, 1, false, false}, 1, 1.611, 12.9, 1},
-                                           {{256, 1, true, false}, 1, 1.810, 17.1, 1},
-                                           {{384, 1, true, true}, 1, 2.129, 20.6, 1}}};
     constexpr int kCUs = 256;
     const int tiles = (g.N + kTileK - 1) / kTileK;
     const Kernel* best = nullptr;
     double best_us = 0;
-    for (const Kernel& k : kKernels[D == 64 ? 0 : D == 96 ? 1 : 2]) {
+    const Kernel* of_d = kernels_of(D);
+    for (int i = 0; i < kForms; ++i) {
+        const Kernel& k = of_d[i];
         if (k.per_cu == 0) continue;
         if (k.form.copies && !room && !dense) continue;  // it would walk Temporal heads in token order: up to twice the time
         const int rows = k.form.rows;

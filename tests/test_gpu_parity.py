@@ -18,6 +18,7 @@ import torch
 import oracle as orc
 import paper_2505_21036_amd as rf
 import rf_inputs as inp
+from attn_forms import attention_as, forms
 
 pytestmark = pytest.mark.gpu
 
@@ -49,15 +50,24 @@ def check(O_gpu_rows, O_ref, what):
     assert rel <= REL_L2, what
 
 
-def run_attention(w, Q, K, V, classes, block, params=None, packed=False):
+def run_attention(w, Q, K, V, classes, block, params=None, packed=False, form=None):
+    """form: None (the library chooses), or one of attn_forms.forms()."""
     rl, _ = lay(w)
     hc = torch.as_tensor(classes, dtype=torch.int32).reshape(w.B, w.nH).to(DEV)
     ws = None
     if packed:  # Textural heads pack K_C, V_C, Temporal heads a position-major copy, into this workspace first
         ws = torch.empty(rf.rf_attention_workspace_bytes(w.B, w.nH, w.D, rl, params), dtype=torch.uint8, device=DEV)
-    O = rf.rf_sparse_attention(Q, K, V, hc, rl, params, block, workspace=ws)
+    if form:
+        O = attention_as(form, Q, K, V, hc, rl, params, workspace=ws)
+    else:
+        O = rf.rf_sparse_attention(Q, K, V, hc, rl, params, block, workspace=ws)
     torch.cuda.synchronize()
     return O
+
+
+def forms_and_rooms(D):
+    """Every form, with and without room for copies of K and V."""
+    return [(f, packed) for packed in (False, True) for f in forms(D, room=packed)]
 
 
 SMALL = ["tiny", "ragged64", "ragged96", "ragged128"]
@@ -111,6 +121,27 @@ def test_parameter_corners(bs, bt, tau):
                 check(O[b, h], ref, "corner bs%g bt%g tau%d blk%d packed%d head(%d,%d)" % (bs, bt, tau, block, packed, b, h))
 
 
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("bs,bt,tau", [(0.0, 0.0, 1), (1.0, 1.0, 3), (0.13, 0.18, 4), (0.5, 0.02, 5)])
+def test_parameter_corners_in_every_form(D, bs, bt, tau):
+    """Radius 0, full bandwidth, bands with both ends inside a tile, other strides, in every kernel: five heads, every
+    class, text in front or behind, every row."""
+    T, H, W, tl, scale = 6, 11, 13, 45, 6.0
+    w = inp.Workload("corner", 1, 5, D, T, H, W, tl, 64, 2500 + D + tau)
+    for text_first in (False, True):
+        shift = tl if text_first else 0
+        rp = rf.rf_params(bs, bt, tau, 0, rf.RF_FLAG_TEXT_FIRST if text_first else 0)
+        ol, op = lay(w)[1], orc.Params(bs, bt, tau, 0, False, text_first)
+        Q, K, V = (torch.roll(t, shift, dims=2).contiguous() for t in inp.full_qkv(w, DEV, scale))
+        classes = [0, 1, 2, 3, 1 if text_first else 0]
+        refs = [orc.attention(*(np.roll(f32(t), shift, axis=0) for t in inp.head_qkv(w, 0, h, scale)), classes[h], ol, op) for h in range(5)]
+        for form, packed in forms_and_rooms(D):
+            print("case corners", (D, bs, bt, tau), "text first", text_first, form, packed, flush=True)
+            O = run_attention(w, Q, K, V, classes, 64, rp, packed, form)
+            for h in range(5):
+                check(O[0, h], refs[h], "corner %s packed%d head %d cls%d" % (form, packed, h, classes[h]))
+
+
 @pytest.mark.parametrize("shape", [(1, 5, 5, 0), (1, 3, 3, 40), (2, 2, 2, 1), (3, 7, 9, 0)])
 def test_degenerate_layouts(shape):
     """Fewer tokens than one block, mostly-text sequences, single frame."""
@@ -120,11 +151,12 @@ def test_degenerate_layouts(shape):
     _, ol = lay(w)
     Q, K, V = inp.full_qkv(w, DEV, 4.0)
     classes = [0, 1, 2, 3]
-    for block in (64, 128):
-        O = run_attention(w, Q, K, V, classes, block)
+    for form, packed in [(None, False)] + forms_and_rooms(64):
+        print("form", form, packed, flush=True)
+        O = run_attention(w, Q, K, V, classes, 64, packed=packed, form=form)
         for h in range(4):
             q, k, v = (f32(t) for t in inp.head_qkv(w, 0, h, 4.0))
-            check(O[0, h], orc.attention(q, k, v, classes[h], ol), "deg %s blk%d cls%d" % (shape, block, h))
+            check(O[0, h], orc.attention(q, k, v, classes[h], ol), "deg %s form %s packed%d cls%d" % (shape, form, packed, h))
 
 
 def test_out_of_range_class_runs_dense_and_constant_values_give_ones():
@@ -345,6 +377,18 @@ def test_plus_attention_with_a_workspace_and_two_bandwidths_per_pattern(text_fir
                     ref = orc.attention(q, k, v, classes[i], ol, orc.Params(bw, bw, 2, 0, False, text_first))
                     check(O[b, h], ref, "plus ws%d text-first%d blk%d head(%d,%d) cls%d bw%g" % (
                         workspace is not None, text_first, block, b, h, classes[i], bw))
+    # the same through every form; those that walk copies walk every head's list of ITS bandwidth over them
+    refs = []
+    for i, cls in enumerate(classes):
+        q, k, v = (np.roll(f32(t), shift, axis=0) for t in inp.head_qkv(w, i // w.nH, i % w.nH, scale))
+        bw = bws[chosen[i]] if chosen[i] >= 0 else 0.25
+        refs.append(orc.attention(q, k, v, cls, ol, orc.Params(bw, bw, 2, 0, False, text_first)))
+    for form, room in forms_and_rooms(w.D):
+        print("form", form, room, flush=True)
+        O = attention_as(form, Q, K, V, hc, rl, rp, workspace=ws if room else None, head_bw=hbw, bandwidths=bws)
+        torch.cuda.synchronize()
+        for i, ref in enumerate(refs):
+            check(O[i // w.nH, i % w.nH], ref, "plus %s room%d text-first%d head %d cls%d" % (form, room, text_first, i, classes[i]))
 
 
 # ----------------------------------------------------------------------------- paper-sized layers
@@ -524,10 +568,12 @@ def test_step_replays_from_a_hip_graph():
                 check(O_graph[b, h], orc.attention(q, k, v, int(hc_graph[b, h]), ol), "graph replay %d head(%d,%d)" % (trial, b, h))
 
 
-def test_many_calls_on_three_streams_and_a_replayed_graph():
+@pytest.mark.parametrize("queued", [False, True])
+def test_many_calls_on_three_streams_and_a_replayed_graph(queued):
     """The work-queue counters live in each call's own workspace, so any number of calls may be in
     flight: 72 launches over three streams (each stream with its own workspace and output) while a
-    captured graph with a fourth workspace is replayed in between; every output against the oracle."""
+    captured graph with a fourth workspace is replayed in between; every output against the oracle.
+    queued: in forms that run from queues, two of them with copies of K and V; else as the library chooses."""
     w = inp.WORKLOADS["ragged96"]
     print("case many streams", flush=True)
     rl, ol = lay(w)
@@ -539,13 +585,21 @@ def test_many_calls_on_three_streams_and_a_replayed_graph():
     wss = [torch.empty(n, dtype=torch.uint8, device=DEV) for n in (full, rf.RF_ATTENTION_MIN_WORKSPACE, full, full)]
     outs = [torch.empty_like(Q) for _ in range(4)]
     blocks = (64, 384, 256, 128)
+    queued_forms = ((384, 1, 1), (256, 1, 1), (256, 1, 1), (384, 1, 1))
+
+    def call(i):
+        if queued:
+            attention_as(queued_forms[i], Q, K, V, classes[i], rl, out=outs[i], workspace=wss[i])
+        else:
+            rf.rf_sparse_attention(Q, K, V, classes[i], rl, None, blocks[i], out=outs[i], workspace=wss[i])
+
     for i in range(4):  # lists built, kernel attributes set
-        rf.rf_sparse_attention(Q, K, V, classes[i], rl, None, blocks[i], out=outs[i], workspace=wss[i])
+        call(i)
     torch.cuda.synchronize()
     side = torch.cuda.Stream()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=side):
-        rf.rf_sparse_attention(Q, K, V, classes[3], rl, None, blocks[3], out=outs[3], workspace=wss[3])
+        call(3)
     torch.cuda.synchronize()
     for o in outs:
         o.zero_()
@@ -553,7 +607,7 @@ def test_many_calls_on_three_streams_and_a_replayed_graph():
     for rep in range(24):
         for i, s in enumerate(streams):
             with torch.cuda.stream(s):
-                rf.rf_sparse_attention(Q, K, V, classes[i], rl, None, blocks[i], out=outs[i], workspace=wss[i])
+                call(i)
         if rep % 4 == 0:
             graph.replay()
     torch.cuda.synchronize()
@@ -566,19 +620,20 @@ def test_many_calls_on_three_streams_and_a_replayed_graph():
 @pytest.mark.parametrize("shape", [(3, 5, 64, 3, 7, 9, 33), (1, 7, 96, 9, 8, 8, 0), (2, 9, 128, 2, 16, 17, 300), (5, 1, 64, 11, 5, 5, 7)])
 def test_odd_batch_and_head_counts_through_the_queues(shape):
     """Head counts that are not multiples of 8, fewer query blocks than XCDs, more text than video:
-    every (head, block) item must be processed exactly once whatever the queue shapes are."""
+    every (head, block) item must be processed exactly once whatever the queue shapes are, and however the
+    blocks of a launch without queues are dealt out."""
     B, nH, D, T, H, W, tl = shape
     print("case queues", shape, flush=True)
     w = inp.Workload("odd", B, nH, D, T, H, W, tl, 64, 3000 + B * 17 + nH)
     _, ol = lay(w)
     Q, K, V = inp.full_qkv(w, DEV, 5.0)
     classes = [(b * nH + h) % 4 for b in range(B) for h in range(nH)]
-    for block, packed in ((64, False), (128, True), (256, True)):
-        O = run_attention(w, Q, K, V, classes, block, packed=packed)
-        for b in range(B):
-            for h in range(nH):
-                q, k, v = (f32(t) for t in inp.head_qkv(w, b, h, 5.0))
-                check(O[b, h], orc.attention(q, k, v, classes[b * nH + h], ol), "odd %s blk%d head(%d,%d)" % (shape, block, b, h))
+    refs = [orc.attention(*(f32(t) for t in inp.head_qkv(w, i // nH, i % nH, 5.0)), classes[i], ol) for i in range(B * nH)]
+    for form, packed in [(None, False), (None, True)] + forms_and_rooms(D):
+        print("form", form, packed, flush=True)
+        O = run_attention(w, Q, K, V, classes, 128, packed=packed, form=form)
+        for i in range(B * nH):
+            check(O[i // nH, i % nH], refs[i], "odd %s form %s packed%d head %d" % (shape, form, packed, i))
 
 
 def test_random_small_configurations():
@@ -603,12 +658,13 @@ def test_random_small_configurations():
         shift = tl if text_first else 0
         Q, K, V = (torch.roll(t, shift, dims=2).contiguous() for t in inp.full_qkv(w, DEV, scale))
         classes = [int(c) for c in rng.integers(0, 4, size=B * nH)]
-        O = run_attention(w, Q, K, V, classes, block, rp, packed)
-        for b in range(B):
-            for h in range(nH):
-                q, k, v = (np.roll(f32(t), shift, axis=0) for t in inp.head_qkv(w, b, h, scale))
-                check(O[b, h], orc.attention(q, k, v, classes[b * nH + h], ol, op),
-                      "random %d head(%d,%d) cls%d" % (case, b, h, classes[b * nH + h]))
+        refs = [orc.attention(*(np.roll(f32(t), shift, axis=0) for t in inp.head_qkv(w, i // nH, i % nH, scale)), classes[i], ol, op)
+                for i in range(B * nH)]
+        for form in [None] + forms(D, room=packed):
+            print("form", form, flush=True)
+            O = run_attention(w, Q, K, V, classes, block, rp, packed, form)
+            for i in range(B * nH):
+                check(O[i // nH, i % nH], refs[i], "random %d form %s head %d cls%d" % (case, form, i, classes[i]))
 
 
 def test_random_small_arm_configurations():
