@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "rf_internal.h"
+#include "rf_queues.h"
 
 namespace rf {
 namespace {
@@ -342,8 +343,10 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.queue = static_cast<int*>(workspace);
     a.join_sweep = (params && (params->flags & RF_FLAG_FIXED_ORDER)) ? 0 : 1;
     // Whole heads to an XCD (every L2 then fetches a head's K and V once) as long as the eight heads in work fit the
-    // memory-side cache with room to spare: 1-20 % up to 17776 tokens; beyond, all XCDs on one head at a time.
-    a.by_head = 8 * 2 * static_cast<size_t>(g.N) * D * sizeof(uint16_t) <= (size_t{128} << 20) ? 1 : 0;
+    // memory-side cache with room to spare: 1-20 % up to 17776 tokens; beyond, all XCDs on one head at a time.  In a
+    // row where every head is dense or XCDs with nothing left help the others (queues), else dealt out.
+    const bool whole_heads = 8 * 2 * static_cast<size_t>(g.N) * D * sizeof(uint16_t) <= (size_t{128} << 20);
+    a.item_order = !whole_heads ? ORDER_EIGHTHS : form.queued || force_dense ? ORDER_HEADS : ORDER_DEALT;
     a.head_class = force_dense ? nullptr : head_class;
     a.head_bw = bandwidths ? head_bw : nullptr;
     a.BH = B * nH;

@@ -12,6 +12,7 @@
 #include <type_traits>
 
 #include "rf_device.h"
+#include "rf_queues.h"
 
 namespace rf {
 
@@ -583,40 +584,10 @@ constexpr int attn_waves_per_simd(int NW, int LOOP) {
 template <int D, int NW, int LOOP>
 using SmemOf = std::conditional_t<LOOP == LOOP_64_PIPELINED, WideSmem<D, NW>, AttnSmem<D, NW>>;
 
-// Items of one launch.  Queue x holds first its share of the long items (the nTB text-holding blocks
-// of every head: global index i = head * nTB + k goes to queue i mod 8), then its part of the nVB other
-// blocks of every head: of every head, head after head, the ordinals [x * per_xcd, (x+1) * per_xcd) of the
-// block order, or (by_head) the items [x * per_xcd, (x+1) * per_xcd) of all heads' blocks in a row.
-struct Queues {
-    int BH, nVB, nTB, per_xcd, by_head;
-    __host__ __device__ __forceinline__ Queues(const AttnArgs& a)
-        : BH(a.BH), nVB(a.plan[0].first_text_qb), nTB(a.plan[0].nQB - a.plan[0].first_text_qb),
-          per_xcd(((a.by_head ? nVB * BH : nVB) + 7) >> 3), by_head(a.by_head) {}
-    __host__ __device__ __forceinline__ int long_items(int x) const { return (nTB * BH - x + 7) >> 3; }
-    // ordinals of each head, or items of all heads
-    __host__ __device__ __forceinline__ int share(int x) const {
-        const int left = (by_head ? nVB * BH : nVB) - x * per_xcd;
-        return left < 0 ? 0 : (left < per_xcd ? left : per_xcd);
-    }
-    __host__ __device__ __forceinline__ int items(int x) const { return long_items(x) + (by_head ? share(x) : share(x) * BH); }
-    // head and position in its block order of the item-th item of queue x
-    __device__ __forceinline__ void locate(int item, int x, int* bh, int* ordinal) const {
-        const int longs = long_items(x), j = item - longs;
-        if (j < 0) {
-            const int i = item * 8 + x;
-            *bh = i / nTB;
-            *ordinal = i % nTB;
-        } else if (by_head) {
-            const int i = x * per_xcd + j;
-            *bh = i / nVB;
-            *ordinal = nTB + i % nVB;
-        } else {
-            const int n = share(x);
-            *bh = j / n;
-            *ordinal = nTB + x * per_xcd + j % n;
-        }
-    }
-};
+__host__ __device__ __forceinline__ Queues queues_of(const AttnArgs& a) {
+    const DevicePlan& p = a.plan[0];
+    return Queues(a.BH, p.first_text_qb, p.nQB - p.first_text_qb, a.item_order);
+}
 
 // The next item for a workgroup whose home queue is `home`, or -1 when every queue is empty.
 // ctr[x] counts how many items of queue x have been handed out.  A workgroup drains its home queue
@@ -669,7 +640,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
     // K/V of the head in flight (tens of MB) stays resident in the memory-side cache for whatever
     // misses L2.  XCDs differ in speed by several per cent and shares in work; an XCD whose queue is
     // empty takes items from the others.
-    const Queues qs(a);
+    const Queues qs = queues_of(a);
     for (;;) {
         if (threadIdx.x == 0) {
             int q = 0;
@@ -704,7 +675,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
 template <int D, int NW, int KS, int AHEAD, int WAVES>
 __global__ void __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) attn_item_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];  // the kernel's only LDS: starts at address 0
-    const Queues qs(a);
+    const Queues qs = queues_of(a);
     const int xcd = blockIdx.x & 7, item = blockIdx.x >> 3;
     if (item >= qs.items(xcd)) return;
     process_item<D, NW, LOOP_ITEM, KS, AHEAD>(a, item, xcd, -1, qs, smem);
@@ -908,7 +879,7 @@ static int launch_items(const AttnArgs& a, hipStream_t st) {
             ready_on[dev] = true;
         }
     }
-    const Queues qs(a);
+    const Queues qs = queues_of(a);
     int most = 0;
     for (int x = 0; x < 8; ++x) most = std::max(most, qs.items(x));
     AttnArgs s = a;

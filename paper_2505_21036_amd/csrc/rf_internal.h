@@ -115,7 +115,7 @@ struct AttnArgs {
     uint16_t* packed_v;
     const int32_t* head_bw;  // optional per-head index into plan[]; null or out of range: plan[0]
     int* queue;              // 8 work-queue counters (one per XCD) and 64 sweep words (8 per XCD) at the start of the caller's workspace, reset by the launcher
-    int by_head;             // 1: an XCD takes whole heads; 0: its eighth of every head (see Queues in rf_attn.hip)
+    int item_order;          // ORDER_*: which items an XCD takes, and when (rf_queues.h)
     int queued;              // see AttnForm
     int key_groups;          // see AttnForm
     int wide_rows;           // 1: wavefronts of 64 query rows (256-row blocks only)
