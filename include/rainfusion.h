@@ -14,13 +14,16 @@
  *     them under RF_FLAG_TEXT_FIRST.  N = T*H*W + text_len.
  *   - Calls are asynchronous on `stream` (a hipStream_t passed as void*, NULL = the
  *     default stream) and never synchronise it, except that the first call for a new
- *     (layout, params, block) builds and uploads its block lists synchronously.  After
- *     such a warm-up call a sequence of calls only launches kernels (no memsets, no
- *     allocations) and can be captured into a HIP graph; the ARM's results are bitwise the
- *     same from call to call, the attention's under RF_FLAG_FIXED_ORDER.  All per-call device state lives in the caller's workspaces, so
+ *     (layout, params) builds and uploads its block lists synchronously: those of every
+ *     block size, so that neither B, nH, D, `block`, the workspace nor RF_FLAG_FORCE_DENSE
+ *     of a later call asks for others (only RF_FLAG_WIDE_ROWS has lists of its own; several
+ *     bandwidths have one set each).  After such a warm-up call a sequence of calls only
+ *     launches kernels (no memsets, no allocations) and can be captured into a HIP graph;
+ *     the ARM's results are bitwise the same from call to call, the attention's under
+ *     RF_FLAG_FIXED_ORDER.  All per-call device state lives in the caller's workspaces, so
  *     any number of calls may be in flight as long as each has its own workspace.  The
- *     library keeps at most 16 block lists per process (least recently used first out;
- *     making room synchronises the device).
+ *     library keeps the block lists of at most 16 (layout, params) per process (least
+ *     recently used first out; making room synchronises the device).
  *   - Return value: RF_OK or a negative rf_status.  Arguments are validated before
  *     any GPU work, so a bad argument never launches a kernel.
  *   - `params == NULL` selects the paper's defaults (Sec. 4.1: both bandwidths 1/4,

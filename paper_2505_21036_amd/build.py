@@ -8,7 +8,6 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librainfusion.so")
 SOURCES = ["rf_api.cpp", "rf_plan.cpp", "rf_attn.hip", "rf_arm.hip"]
-HEADERS = ["rf_internal.h", "rf_device.h"]
 
 
 def hipcc():

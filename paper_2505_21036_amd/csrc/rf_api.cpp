@@ -16,13 +16,18 @@
 namespace rf {
 namespace {
 
+// The lists of one (layout, params): of every block size, so that whichever form a later call takes (it depends on the
+// number of heads, the head_dim, the workspace and the dense flag) finds its lists there.  A call captured into a graph
+// may not build any.
+constexpr int kBlocks[] = {64, 128, 256, 384};
+constexpr int kBlockSizes = 4;
 struct CachedPlan {
-    Geometry g;  // with the fields the lists do not depend on zeroed (see list_key)
-    int block;
+    Geometry g;       // with the fields the lists do not depend on zeroed (see list_key)
+    bool wide;        // for RF_FLAG_WIDE_ROWS: 256-row blocks only, and the Temporal list in token order
     int device;
     unsigned long long last_use = 0;
     void* blob = nullptr;
-    DevicePlan dev{};
+    DevicePlan dev[kBlockSizes] = {};
 };
 
 std::mutex g_mu;
@@ -40,25 +45,30 @@ Geometry list_key(Geometry g) {
 
 bool same_geometry(const Geometry& a, const Geometry& b) { return std::memcmp(&a, &b, sizeof(Geometry)) == 0; }
 
-CachedPlan* find_plan(const Geometry& g, int block, int device) {
+CachedPlan* find_plan(const Geometry& g, bool wide, int device) {
     for (auto& p : g_plans)
-        if (p->block == block && p->device == device && same_geometry(p->g, g)) return p.get();
+        if (p->wide == wide && p->device == device && same_geometry(p->g, g)) return p.get();
     return nullptr;
 }
 
-// Uploads `words` and returns the device address; segments are 256-byte aligned inside one blob.
+// Lays vectors out in one device allocation, each at a multiple of 256 bytes.
 struct BlobBuilder {
-    std::vector<int32_t> words;
-    size_t add(const std::vector<int32_t>& v) {
-        while (words.size() % 64) words.push_back(0);
-        const size_t off = words.size();
-        words.insert(words.end(), v.begin(), v.end());
-        if (v.empty()) words.push_back(0);
-        return off;
+    struct Part { const std::vector<int32_t>* v; size_t at; };
+    std::vector<Part> parts;
+    size_t words = 0;
+    size_t add(const std::vector<int32_t>& v) {  // v must stay as it is until upload()
+        const size_t at = words;
+        parts.push_back({&v, at});
+        words += std::max<size_t>(v.size(), 1);
+        words = (words + 63) / 64 * 64;
+        return at;
     }
-    int upload(void** blob) {
-        if (hipMalloc(blob, words.size() * sizeof(int32_t)) != hipSuccess) return RF_ERR_HIP;
-        if (hipMemcpy(*blob, words.data(), words.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) {
+    int upload(void** blob) const {
+        std::unique_ptr<int32_t[]> staged(new int32_t[words]);
+        for (const Part& p : parts)
+            if (!p.v->empty()) std::memcpy(staged.get() + p.at, p.v->data(), p.v->size() * sizeof(int32_t));
+        if (hipMalloc(blob, words * sizeof(int32_t)) != hipSuccess) return RF_ERR_HIP;
+        if (hipMemcpy(*blob, staged.get(), words * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(*blob);
             *blob = nullptr;
             return RF_ERR_HIP;
@@ -67,51 +77,41 @@ struct BlobBuilder {
     }
 };
 
-// out receives a COPY of the plan: the cache entry may be evicted by a later call (its device memory
-// is only freed after the device has drained, so kernels already launched keep reading valid lists).
-int get_attention_plan(const Geometry& geometry, int block, DevicePlan* out) {
-    int device = 0;
-    if (hipGetDevice(&device) != hipSuccess) return RF_ERR_HIP;
-    const Geometry g = list_key(geometry);
-    std::lock_guard<std::mutex> lock(g_mu);
-    CachedPlan* cp = find_plan(g, block, device);
-    if (!cp) {
-        if (g_plans.size() >= kMaxCachedPlans) {
-            size_t oldest = 0;
-            for (size_t i = 1; i < g_plans.size(); ++i)
-                if (g_plans[i]->last_use < g_plans[oldest]->last_use) oldest = i;
-            if (hipDeviceSynchronize() != hipSuccess) return RF_ERR_HIP;
-            if (g_plans[oldest]->blob && hipFree(g_plans[oldest]->blob) != hipSuccess) return RF_ERR_HIP;
-            g_plans.erase(g_plans.begin() + static_cast<std::ptrdiff_t>(oldest));
-        }
-        HostPlan hp;
-        build_plan(g, block, &hp);
-        BlobBuilder bb;
-        size_t off_rp[kLists], off_co[kLists], off_at[kLists], off_qo[kLists], off_fe[kLists];
+int build_and_upload(const Geometry& g, bool wide, CachedPlan* p) {
+    TokenTables tables;
+    build_tables(g, &tables);
+    HostPlan plans[kBlockSizes];
+    BlobBuilder bb;
+    struct Offsets { size_t row_ptr[kLists], cols[kLists], qorder[kLists], first_entry[kLists]; } off[kBlockSizes];
+    size_t off_attr[kLists];
+    for (int c = 0; c < kLists; ++c) off_attr[c] = bb.add(tables.attr[c]);
+    const size_t off_cidx = bb.add(tables.cidx), off_pm = bb.add(tables.pm_token);
+    auto wanted = [&](int i) { return wide ? kBlocks[i] == 256 : kBlocks[i] >= 256 || g.N <= kSmallBlockTokens; };
+    for (int i = 0; i < kBlockSizes; ++i) {
+        if (!wanted(i)) continue;
+        build_plan(g, tables, kBlocks[i], wide, &plans[i]);
         for (int c = 0; c < kLists; ++c) {
-            off_rp[c] = bb.add(hp.row_ptr[c]);
-            off_co[c] = bb.add(hp.cols[c]);
-            off_at[c] = bb.add(hp.attr[c]);
-            off_qo[c] = bb.add(hp.qorder[c]);
-            off_fe[c] = bb.add(hp.first_entry[c]);
+            off[i].row_ptr[c] = bb.add(plans[i].row_ptr[c]);
+            off[i].cols[c] = bb.add(plans[i].cols[c]);
+            off[i].qorder[c] = bb.add(plans[i].qorder[c]);
+            off[i].first_entry[c] = bb.add(plans[i].first_entry[c]);
         }
-        const size_t off_ci = bb.add(hp.cidx), off_pm = bb.add(hp.pm_token);
-        auto p = std::make_unique<CachedPlan>();
-        p->g = g;
-        p->block = block;
-        p->device = device;
-        const int st = bb.upload(&p->blob);
-        if (st != RF_OK) return st;
-        const int32_t* base = static_cast<const int32_t*>(p->blob);
-        DevicePlan& d = p->dev;
+    }
+    const int st = bb.upload(&p->blob);
+    if (st != RF_OK) return st;
+    const int32_t* base = static_cast<const int32_t*>(p->blob);
+    for (int i = 0; i < kBlockSizes; ++i) {
+        if (!wanted(i)) continue;
+        const HostPlan& hp = plans[i];
+        DevicePlan& d = p->dev[i];
         for (int c = 0; c < kLists; ++c) {
-            d.row_ptr[c] = base + off_rp[c];
-            d.cols[c] = base + off_co[c];
-            d.attr[c] = base + off_at[c];
-            d.qorder[c] = base + off_qo[c];
-            d.first_entry[c] = base + off_fe[c];
+            d.row_ptr[c] = base + off[i].row_ptr[c];
+            d.cols[c] = base + off[i].cols[c];
+            d.attr[c] = base + off_attr[c];
+            d.qorder[c] = base + off[i].qorder[c];
+            d.first_entry[c] = base + off[i].first_entry[c];
         }
-        d.cidx = base + off_ci;
+        d.cidx = base + off_cidx;
         d.pm_token = base + off_pm;
         d.radius[RF_SPATIAL] = g.r_spatial;
         d.radius[RF_TEMPORAL] = g.r_temporal;
@@ -122,19 +122,46 @@ int get_attention_plan(const Geometry& geometry, int block, DevicePlan* out) {
         d.video_shift = g.video_shift();
         d.text_shift = g.text_shift();
         d.N = g.N; d.Nv = g.Nv; d.Nc = hp.Nc;
-        d.block = block; d.nQB = hp.nQB; d.nKT = hp.nKT; d.nCT = hp.nCT;
+        d.block = hp.block; d.nQB = hp.nQB; d.nKT = hp.nKT; d.nCT = hp.nCT;
         d.first_text_qb = hp.first_text_qb;
+    }
+    return RF_OK;
+}
+
+// out receives a COPY of the plan: the cache entry may be evicted by a later call (its device memory
+// is only freed after the device has drained, so kernels already launched keep reading valid lists).
+int get_attention_plan(const Geometry& geometry, int block, bool wide, DevicePlan* out) {
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return RF_ERR_HIP;
+    const Geometry g = list_key(geometry);
+    std::lock_guard<std::mutex> lock(g_mu);
+    CachedPlan* cp = find_plan(g, wide, device);
+    if (!cp) {
+        if (g_plans.size() >= kMaxCachedPlans) {
+            size_t oldest = 0;
+            for (size_t i = 1; i < g_plans.size(); ++i)
+                if (g_plans[i]->last_use < g_plans[oldest]->last_use) oldest = i;
+            if (hipDeviceSynchronize() != hipSuccess) return RF_ERR_HIP;
+            if (g_plans[oldest]->blob && hipFree(g_plans[oldest]->blob) != hipSuccess) return RF_ERR_HIP;
+            g_plans.erase(g_plans.begin() + static_cast<std::ptrdiff_t>(oldest));
+        }
+        auto p = std::make_unique<CachedPlan>();
+        p->g = g;
+        p->wide = wide;
+        p->device = device;
+        const int st = build_and_upload(g, wide, p.get());
+        if (st != RF_OK) return st;
         cp = p.get();
         g_plans.push_back(std::move(p));
     }
     cp->last_use = ++g_use_counter;
-    *out = cp->dev;
+    *out = cp->dev[std::find(kBlocks, kBlocks + kBlockSizes, block) - kBlocks];
     return RF_OK;
 }
 
 int global_sample_count(const Geometry& g) { return (g.Nv + g.omega - 1) / g.omega; }
 
-bool valid_block(int block) { return block == 64 || block == 128 || block == 256 || block == 384; }  // query rows per block
+bool valid_block(int block) { return std::find(kBlocks, kBlocks + kBlockSizes, block) != kBlocks + kBlockSizes; }  // query rows per block
 
 // (token counts that overflow int32 indices were already refused by resolve_geometry)
 int check_shape(int B, int nH, int D) {
@@ -324,6 +351,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.wide_rows = (params && (params->flags & RF_FLAG_WIDE_ROWS)) ? 1 : 0;
     const AttnForm form = named ? *named : a.wide_rows ? AttnForm{block, 1, true, true} : choose_form(g, B * nH, D, force_dense, room_to_pack);
     if (named && named->copies && !room_to_pack && !force_dense) return RF_ERR_WORKSPACE;
+    if (named && named->rows < 256 && g.N > kSmallBlockTokens) return RF_ERR_PARAM;  // no such lists
     a.queued = form.queued ? 1 : 0;
     a.key_groups = form.key_groups;
     a.n_plans = bandwidths ? n_bw : 1;
@@ -333,7 +361,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
             st = geometry_with_bandwidth(layout, params, bandwidths[k], &gk);
             if (st != RF_OK) return st;
         }
-        st = get_attention_plan(gk, form.rows, &a.plan[k]);
+        st = get_attention_plan(gk, form.rows, a.wide_rows != 0, &a.plan[k]);
         if (st != RF_OK) return st;
     }
     a.Q = static_cast<const uint16_t*>(Q);

@@ -39,7 +39,15 @@ struct Geometry {
 constexpr int kLists = 4;
 constexpr int kListTemporalPM = 3;
 
-// Host copy of everything the attention kernel needs besides the tensors.
+// What the attention kernel needs of a layout whatever the block size: one entry per token.
+struct TokenTables {
+    // per row of the list's order: frame index / in-frame index / 0 if kept by Eq. 4 else 1 / in-frame index
+    std::vector<int32_t> attr[kLists];
+    std::vector<int32_t> cidx;      // compacted position -> tensor row (Textural): kept video keys, then text keys
+    std::vector<int32_t> pm_token;  // position-major row -> tensor row
+};
+
+// Host copy of the block lists of one block size.
 struct HostPlan {
     Geometry g;
     int block;     // query rows per block = rows one workgroup owns
@@ -56,17 +64,16 @@ struct HostPlan {
     // its (cyclic) walk at.
     std::vector<int32_t> qorder[kLists];
     std::vector<int32_t> first_entry[kLists];
-    // per row of the list's order: frame index / in-frame index / 0 if kept by Eq. 4 else 1 / in-frame index
-    std::vector<int32_t> attr[kLists];
-    std::vector<int32_t> cidx;      // compacted position -> tensor row (Textural)
-    std::vector<int32_t> pm_token;  // position-major row -> tensor row
 };
 
 // Fills g from layout/params (params may be null -> paper defaults). Returns an rf_status.
 int resolve_geometry(const rf_layout* layout, const rf_params* params, Geometry* g);
 
-// Builds the block lists. Pure host code.
-void build_plan(const Geometry& g, int block, HostPlan* plan);
+// Builds the token tables and the block lists. Pure host code.  token_order_temporal: also the Temporal list in token
+// order, the longest to build, which only RF_FLAG_WIDE_ROWS walks; without it that list is empty.
+void build_tables(const Geometry& g, TokenTables* tables);
+void build_plan(const Geometry& g, const TokenTables& tables, int block, bool token_order_temporal, HostPlan* plan);
+void build_plan(const Geometry& g, int block, HostPlan* plan);  // tables of its own, every list
 
 // How an attention call runs: query rows a workgroup takes at a time (64, 128, 256 or 384), groups of its
 // wavefronts that split the keys (4, 2 or 1), whether a resident set of workgroups takes items from queues or every
@@ -75,6 +82,9 @@ struct AttnForm {
     int rows, key_groups;
     bool queued, copies;
 };
+// Forms of fewer than 256 rows are taken up to here (beyond, one head fills the chip with larger blocks), so that the
+// lists of 64- and 128-row blocks, which grow with the square of the length, need not exist for longer sequences.
+constexpr int kSmallBlockTokens = 1 << 17;
 // The form with the shortest launch at this size.  dense: every head is known to be dense; room: there is a
 // workspace for the copies.
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room);

@@ -118,7 +118,37 @@ static void order_query_blocks(HostPlan* plan) {
     }
 }
 
+void build_tables(const Geometry& g, TokenTables* tables) {
+    TokenTables& T = *tables;
+    const int N = g.N, Nv = g.Nv, HW = g.HW;
+    for (auto& a : T.attr) a.assign(N, 0);
+    T.pm_token.resize(N);
+    for (int p = 0; p < HW; ++p)  // position-major row p*T + f
+        for (int f = 0; f < g.T; ++f) {
+            T.pm_token[p * g.T + f] = g.row_of(f * HW + p);
+            T.attr[kListTemporalPM][p * g.T + f] = p;
+        }
+    for (int n = Nv; n < N; ++n) T.pm_token[n] = g.row_of(n);
+    T.cidx.clear();
+    for (int f = 0, n = 0; f < g.T; ++f)
+        for (int y = 0, p = 0; y < g.H; ++y)
+            for (int x = 0; x < g.W; ++x, ++p, ++n) {
+                T.attr[RF_SPATIAL][n] = f;
+                T.attr[RF_TEMPORAL][n] = p;
+                const bool kept = ((y - x) % g.tau) == 0;
+                T.attr[RF_TEXTURAL][n] = kept ? 0 : 1;
+                if (kept) T.cidx.push_back(g.row_of(n));
+            }
+    for (int n = Nv; n < N; ++n) T.cidx.push_back(g.row_of(n));
+}
+
 void build_plan(const Geometry& g, int block, HostPlan* plan) {
+    TokenTables tables;
+    build_tables(g, &tables);
+    build_plan(g, tables, block, true, plan);
+}
+
+void build_plan(const Geometry& g, const TokenTables& tables, int block, bool token_order_temporal, HostPlan* plan) {
     HostPlan& P = *plan;
     P.g = g;
     P.block = block;
@@ -126,30 +156,12 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
     P.nQB = (N + block - 1) / block;
     P.nKT = (N + kTileK - 1) / kTileK;
     P.first_text_qb = g.text_len > 0 ? Nv / block : P.nQB;
-
-    // per-token attributes
-    for (auto& a : P.attr) a.assign(N, 0);
-    P.cidx.clear();
-    P.pm_token.resize(N);
-    for (int n = 0; n < Nv; ++n) {  // position-major row n = p*T + f
-        const int p = n / g.T, f = n % g.T;
-        P.pm_token[n] = g.row_of(f * HW + p);
-        P.attr[kListTemporalPM][n] = p;
-    }
-    for (int n = Nv; n < N; ++n) P.pm_token[n] = g.row_of(n);
-    for (int n = 0; n < Nv; ++n) {
-        const int f = n / HW, p = n % HW, y = p / g.W, x = p % g.W;
-        P.attr[RF_SPATIAL][n] = f;
-        P.attr[RF_TEMPORAL][n] = p;
-        const bool kept = ((y - x) % g.tau) == 0;
-        P.attr[RF_TEXTURAL][n] = kept ? 0 : 1;
-        if (kept) P.cidx.push_back(g.row_of(n));
-    }
-    for (int n = Nv; n < N; ++n) P.cidx.push_back(g.row_of(n));
-    P.Nc = static_cast<int>(P.cidx.size());
+    P.Nc = static_cast<int>(tables.cidx.size());
     P.nCT = (P.Nc + kTileK - 1) / kTileK;
+    const int first_text_tile = g.text_len > 0 ? Nv / kTileK : P.nKT;
 
-    std::vector<Span> qs, ks;
+    std::vector<Span> qs, ks, tile(P.nKT);
+    std::vector<char> every_kept(P.nKT), some_kept(P.nKT);
     for (int cls = 0; cls < kLists; ++cls) {
         // a band over groups of consecutive rows: frames of HW tokens (Spatial), positions of T tokens
         // (Temporal in position-major order)
@@ -159,22 +171,56 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
         auto& co = P.cols[cls];
         rp.assign(P.nQB + 1, 0);
         co.clear();
+        if (cls == RF_TEMPORAL && !token_order_temporal) continue;
+        // of the video keys of every tile: the groups they lie in, or which of them the Textural pattern keeps
+        for (int kb = 0; kb < P.nKT; ++kb) {
+            const int k0 = kb * kTileK, kv1 = std::min(k0 + kTileK, Nv);
+            if (k0 >= Nv) break;
+            if (banded) tile[kb] = Span{k0 / group, (kv1 - 1) / group};
+            if (cls == RF_TEXTURAL && P.first_text_qb < P.nQB) {
+                int kept = 0;
+                for (int j = k0; j < kv1; ++j) kept += tables.attr[RF_TEXTURAL][j] == 0;
+                every_kept[kb] = kept == kv1 - k0;
+                some_kept[kb] = kept > 0;
+            }
+        }
         for (int qb = 0; qb < P.nQB; ++qb) {
             const int q0 = qb * block, q1 = std::min(N, q0 + block);
             const int qv1 = std::min(q1, Nv);  // video part [q0, qv1)
             const bool q_text = q1 > Nv, q_video = q0 < Nv;
             if (cls == RF_TEXTURAL && !q_text) { rp[qb + 1] = static_cast<int32_t>(co.size()); continue; }
             if (cls == RF_TEMPORAL && q_video) position_spans(q0, qv1, HW, &qs);
+            auto add = [&](int kb, bool all) {
+                const bool tail = (kb + 1) * kTileK > N, k_text = (kb + 1) * kTileK > Nv, k_video = kb * kTileK < Nv;
+                // a tile of text keys only is never partial; one that mixes text and video keys, or
+                // runs past N, needs the position checks as well as the pattern's band check
+                const bool boundary = tail || (k_text && k_video && !all);
+                co.push_back(kb | ((!all || tail) ? RF_PLAN_PARTIAL : 0) | (boundary ? kTileBoundary : 0));
+            };
+            if (banded && q_video && !q_text) {
+                // the tiles with a key of a group within reach (their video keys are the tokens below Nv), then those with text keys
+                const int lo = q0 / group, hi = (qv1 - 1) / group;
+                const int run0 = std::max(lo - group_radius, 0) * group / kTileK;
+                const int run1 = static_cast<int>((std::min<int64_t>(Nv, static_cast<int64_t>(hi + group_radius + 1) * group) + kTileK - 1) / kTileK);
+                // full tiles of video keys, nearly all there are, without the other cases' tests
+                const int whole = std::min(run1, Nv / kTileK);
+                const size_t at = co.size();
+                co.resize(at + std::max(whole - run0, 0));
+                for (int kb = run0; kb < whole; ++kb)
+                    co[at + kb - run0] = kb | (span_reach(Span{lo, hi}, tile[kb]) <= group_radius ? 0 : RF_PLAN_PARTIAL);
+                for (int kb = std::max(run0, whole); kb < run1; ++kb) add(kb, span_reach(Span{lo, hi}, tile[kb]) <= group_radius);
+                for (int kb = std::max(run1, first_text_tile); kb < P.nKT; ++kb)
+                    add(kb, kb * kTileK >= Nv || span_reach(Span{lo, hi}, tile[kb]) <= group_radius);
+                rp[qb + 1] = static_cast<int32_t>(co.size());
+                continue;
+            }
             for (int kb = 0; kb < P.nKT; ++kb) {
                 const int k0 = kb * kTileK, k1 = std::min(N, k0 + kTileK);
                 const int kv1 = std::min(k1, Nv);
-                const bool k_text = k1 > Nv, k_video = k0 < Nv;
-                bool any = q_text || k_text, all = true;
-                if (q_video && k_video) {
+                bool any = q_text || k1 > Nv, all = true;
+                if (q_video && k0 < Nv) {
                     if (banded) {
-                        Span a{q0 / group, (qv1 - 1) / group}, b{k0 / group, (kv1 - 1) / group};
-                        any = any || span_gap(a, b) <= group_radius;
-                        all = span_reach(a, b) <= group_radius;
+                        all = span_reach(Span{q0 / group, (qv1 - 1) / group}, tile[kb]) <= group_radius;
                     } else if (cls == RF_TEMPORAL) {
                         position_spans(k0, kv1, HW, &ks);
                         for (Span a : qs)
@@ -183,22 +229,11 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
                                 all = all && span_reach(a, b) <= g.r_temporal;
                             }
                     } else {  // Textural rows of a block that also holds text rows
-                        bool every_kept = true, some_kept = false;
-                        for (int j = k0; j < kv1; ++j) {
-                            const bool kept = P.attr[RF_TEXTURAL][j] == 0;
-                            every_kept = every_kept && kept;
-                            some_kept = some_kept || kept;
-                        }
-                        any = any || some_kept;
-                        all = every_kept;
+                        any = any || some_kept[kb];
+                        all = every_kept[kb];
                     }
                 }
-                if (!any) continue;
-                const bool tail = k0 + kTileK > N;
-                // a tile of text keys only is never partial; one that mixes text and video keys, or
-                // runs past N, needs the position checks as well as the pattern's band check
-                const bool boundary = tail || (k_text && k_video && !all);
-                co.push_back(kb | ((!all || tail) ? RF_PLAN_PARTIAL : 0) | (boundary ? kTileBoundary : 0));
+                if (any) add(kb, all);
             }
             rp[qb + 1] = static_cast<int32_t>(co.size());
         }
@@ -273,6 +308,7 @@ AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
         if (k.per_cu == 0) continue;
         if (k.form.copies && !room && !dense) continue;  // it would walk Temporal heads in token order: up to twice the time
         const int rows = k.form.rows;
+        if (rows < 256 && g.N > kSmallBlockTokens) continue;
         const double slots = static_cast<double>(kCUs) * k.per_cu;
         // how long an item takes where n workgroups share the chip, relative to a full one
         auto shared = [&](double n) { return 0.635 + 0.365 * std::ceil(n / kCUs) / k.per_cu; };
