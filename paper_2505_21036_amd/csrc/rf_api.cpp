@@ -349,7 +349,11 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
 
     AttnArgs a{};
     a.wide_rows = (params && (params->flags & RF_FLAG_WIDE_ROWS)) ? 1 : 0;
-    const AttnForm form = named ? *named : a.wide_rows ? AttnForm{block, 1, true, true} : choose_form(g, B * nH, D, force_dense, room_to_pack);
+    const bool fixed_order = params && (params->flags & RF_FLAG_FIXED_ORDER);
+    const AttnForm form = named         ? *named
+                          : a.wide_rows ? AttnForm{block, 1, true, true}
+                          : fixed_order ? choose_fixed_form(g, D)
+                                        : choose_form(g, B * nH, D, force_dense, room_to_pack);
     if (named && named->copies && !room_to_pack && !force_dense) return RF_ERR_WORKSPACE;
     if (named && named->rows < 256 && g.N > kSmallBlockTokens) return RF_ERR_PARAM;  // no such lists
     a.queued = form.queued ? 1 : 0;
@@ -369,7 +373,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.V = static_cast<const uint16_t*>(V);
     a.O = static_cast<uint16_t*>(O);
     a.queue = static_cast<int*>(workspace);
-    a.join_sweep = (params && (params->flags & RF_FLAG_FIXED_ORDER)) ? 0 : 1;
+    a.join_sweep = fixed_order ? 0 : 1;
     // Whole heads to an XCD (every L2 then fetches a head's K and V once) as long as the eight heads in work fit the
     // memory-side cache with room to spare: 1-20 % up to 17776 tokens; beyond, all XCDs on one head at a time.  In a
     // row where every head is dense or XCDs with nothing left help the others (queues), else dealt out.

@@ -297,49 +297,72 @@ bool find_form(int D, int rows, int key_groups, bool queued, AttnForm* form) {
     return false;
 }
 
-AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
+namespace {
+
+// Time of a launch in form k, us; HUGE_VAL if the form is not to be taken at this size.
+double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense) {
     constexpr int kCUs = 256;
-    const int tiles = (g.N + kTileK - 1) / kTileK;
-    const Kernel* best = nullptr;
-    double best_us = 0;
+    const int tiles = (g.N + kTileK - 1) / kTileK, rows = k.form.rows;
+    if (rows < 256 && g.N > kSmallBlockTokens) return HUGE_VAL;
+    const double slots = static_cast<double>(kCUs) * k.per_cu;
+    // how long an item takes where n workgroups share the chip, relative to a full one
+    auto shared = [&](double n) { return 0.635 + 0.365 * std::ceil(n / kCUs) / k.per_cu; };
+    auto rounds_us = [&](double items, double item_tiles) {
+        const double rounds = items / slots, full = std::floor(rounds), rest = items - full * slots;
+        double last = rest > 0 ? shared(rest) : 0;
+        // workgroups are out of step by then; dense walks at head_dim 64, all of one length, less so (at 128 it
+        // would pick 384 rows for 10 heads of 22626: 2.64 ms against 2.56)
+        const double part = dense && D == 64 && rest > 0 ? 0.5 + 0.5 * rest / slots : rest / slots;
+        if (rounds >= 3) last = std::min(last, part);
+        return (full + last) * (item_tiles * k.tile_us * (dense ? k.dense : 1) + k.item_us);
+    };
+    const int nQB = (g.N + rows - 1) / rows, nTB = g.text_len > 0 ? nQB - g.Nv / rows : 0;
+    const double items = static_cast<double>(nQB) * BH, longs = static_cast<double>(nTB) * BH;
+    // from about there on the queues' balance is worth what they cost (head_dim 128, the 256-row form from the grid
+    // and from queues: 24 heads of 4109, 1.6 rounds, 186 and 190 us; 30 of 5632, 2.6 rounds, 281 and 281; 4 of
+    // 48000, 2.9 rounds, 2.42 and 2.29 ms)
+    if (rows == 256 && !k.form.queued && items > 2.5 * slots) return HUGE_VAL;
+    double us = rounds_us(items, tiles);
+    if (!dense) {
+        // about half the tiles, but for the blocks that hold text rows: those walk every tile, most of them
+        // masked, and nothing ends before the longest item
+        us = rounds_us(items + 1.1 * longs, 0.54 * tiles);
+        if (longs > 0) us = std::max(us, (k.form.copies ? 1.81 : 1.33) * tiles * k.tile_us * shared(std::min(items, slots)) + k.item_us);
+    }
+    return us;
+}
+
+// The form of least cost(form) among those of head_dim D, copies: with those that walk copies of K and V.
+template <typename F>
+AttnForm cheapest(int D, bool copies, F cost) {
     const Kernel* of_d = kernels_of(D);
+    const Kernel* best = nullptr;
+    double least = 0;
     for (int i = 0; i < kForms; ++i) {
         const Kernel& k = of_d[i];
-        if (k.per_cu == 0) continue;
-        if (k.form.copies && !room && !dense) continue;  // it would walk Temporal heads in token order: up to twice the time
-        const int rows = k.form.rows;
-        if (rows < 256 && g.N > kSmallBlockTokens) continue;
-        const double slots = static_cast<double>(kCUs) * k.per_cu;
-        // how long an item takes where n workgroups share the chip, relative to a full one
-        auto shared = [&](double n) { return 0.635 + 0.365 * std::ceil(n / kCUs) / k.per_cu; };
-        auto launch_us = [&](double items, double item_tiles) {
-            const double rounds = items / slots, full = std::floor(rounds), rest = items - full * slots;
-            double last = rest > 0 ? shared(rest) : 0;
-            // workgroups are out of step by then; dense walks at head_dim 64, all of one length, less so (at 128 it
-            // would pick 384 rows for 10 heads of 22626: 2.64 ms against 2.56)
-            const double part = dense && D == 64 && rest > 0 ? 0.5 + 0.5 * rest / slots : rest / slots;
-            if (rounds >= 3) last = std::min(last, part);
-            return (full + last) * (item_tiles * k.tile_us * (dense ? k.dense : 1) + k.item_us);
-        };
-        const int nQB = (g.N + rows - 1) / rows, nTB = g.text_len > 0 ? nQB - g.Nv / rows : 0;
-        const double items = static_cast<double>(nQB) * BH, longs = static_cast<double>(nTB) * BH;
-        // from about there on the queues' balance is worth what they cost (head_dim 128, the 256-row form from the grid
-        // and from queues: 24 heads of 4109, 1.6 rounds, 186 and 190 us; 30 of 5632, 2.6 rounds, 281 and 281; 4 of
-        // 48000, 2.9 rounds, 2.42 and 2.29 ms)
-        if (rows == 256 && !k.form.queued && items > 2.5 * slots) continue;
-        double us = launch_us(items, tiles);
-        if (!dense) {
-            // about half the tiles, but for the blocks that hold text rows: those walk every tile, most of them
-            // masked, and nothing ends before the longest item
-            us = launch_us(items + 1.1 * longs, 0.54 * tiles);
-            if (longs > 0) us = std::max(us, (k.form.copies ? 1.81 : 1.33) * tiles * k.tile_us * shared(std::min(items, slots)) + k.item_us);
-        }
-        if (!best || us < best_us) {
+        if (k.per_cu == 0 || (k.form.copies && !copies)) continue;
+        const double c = cost(k);
+        if (!best || c < least) {
             best = &k;
-            best_us = us;
+            least = c;
         }
     }
     return best->form;
+}
+
+}  // namespace
+
+AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
+    // without room a form with copies would walk Temporal heads in token order: up to twice the time
+    return cheapest(D, room || dense, [&](const Kernel& k) { return launch_us(k, g, BH, D, dense); });
+}
+
+AttnForm choose_fixed_form(const Geometry& g, int D) {
+    return cheapest(D, false, [&](const Kernel& k) {
+        double log_us = 0;
+        for (int heads : {6, 12, 24, 48}) log_us += std::log(launch_us(k, g, heads, D, false));
+        return log_us;
+    });
 }
 
 // cls in the public numbering: a head class, or RF_LIST_TEMPORAL_POSITION_MAJOR

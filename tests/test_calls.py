@@ -1,6 +1,7 @@
 """What a call of rf_sparse_attention asks of the runtime and which kernel it launches with what, seen on the host side
 alone (calls_driver.cpp counts the allocations and records the launches).  Contracts of include/rainfusion.h: after one
-warm-up call for a (layout, params) no call allocates, whatever its heads, head_dim, block, workspace and dense flag."""
+warm-up call for a (layout, params) no call allocates, whatever its heads, head_dim, block, workspace and dense flag;
+RF_FLAG_FIXED_ORDER gives a head the same bits in any call of the layout."""
 import os
 import shutil
 import subprocess
@@ -45,6 +46,41 @@ def test_one_warm_up_call_covers_every_later_call_of_the_layout(driver, layout):
     out = driver([warm] + calls)
     assert all(r[0] == 0 and r[1] == 1 for r in out), sorted({r[:2] for r in out})
     assert len({r[2] for r in out}) > 1 or layout == LAYOUTS[-1]  # the calls do differ in their row counts
+
+
+@needs_gxx
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_fixed_order_takes_one_form_per_layout_and_head_dim(driver, layout):
+    calls = every_call(layout, rf.RF_FLAG_FIXED_ORDER)
+    out = driver(calls)
+    for D in (64, 96, 128):
+        assert len({(r[2], r[3], r[4], r[6], r[7]) for r, c in zip(out, calls) if c[7] == D}) == 1, D
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("T,H,W,tl", [(4, 8, 8, 0), (7, 10, 13, 50), (5, 32, 33, 37), (6, 64, 65, 11)])
+def test_fixed_order_bits_do_not_depend_on_the_other_heads(D, T, H, W, tl):
+    """Bitwise: a head alone, in a batch, with and without a workspace; all heads dense by class and by flag."""
+    print("case fixed order", D, (T, H, W, tl), flush=True)
+    layout, N, nH = rf.rf_layout(T, H, W, tl), T * H * W + tl, 30
+    params = rf.rf_params(0.25, 0.25, 2, 0, rf.RF_FLAG_FIXED_ORDER)
+    flagged = rf.rf_params(0.25, 0.25, 2, 0, rf.RF_FLAG_FIXED_ORDER | rf.RF_FLAG_FORCE_DENSE)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(D + N)
+    Q, K, V = (torch.randn(2, nH // 2, N, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    hc = (torch.arange(nH, dtype=torch.int32) % 4).reshape(2, nH // 2).cuda()
+    ws = torch.empty(rf.rf_attention_workspace_bytes(2, nH // 2, D, layout), dtype=torch.uint8, device="cuda")
+    want = rf.rf_sparse_attention(Q, K, V, hc, layout, params, 128)
+    assert torch.equal(want, rf.rf_sparse_attention(Q, K, V, hc, layout, params, 256, workspace=ws))
+    for b, h0, n in ((0, 0, 1), (0, 1, 1), (1, 2, 1), (1, 3, 4), (0, 0, nH // 2)):
+        part = [t[b:b + 1, h0:h0 + n].contiguous() for t in (Q, K, V, hc)]
+        for workspace in (None, ws):
+            got = rf.rf_sparse_attention(*part, layout, params, 64, workspace=workspace)
+            assert torch.equal(got[0], want[b, h0:h0 + n]), (b, h0, n)
+    dense = rf.rf_sparse_attention(Q, K, V, torch.full_like(hc, rf.RF_DENSE), layout, params, workspace=ws)
+    assert torch.equal(dense, rf.rf_sparse_attention(Q, K, V, None, layout, flagged))
+    assert torch.equal(dense[0, 3], want[0, 3])
 
 
 @pytest.mark.gpu
