@@ -374,11 +374,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.O = static_cast<uint16_t*>(O);
     a.queue = static_cast<int*>(workspace);
     a.join_sweep = fixed_order ? 0 : 1;
-    // Whole heads to an XCD (every L2 then fetches a head's K and V once) as long as the eight heads in work fit the
-    // memory-side cache with room to spare: 1-20 % up to 17776 tokens; beyond, all XCDs on one head at a time.  In a
-    // row where every head is dense or XCDs with nothing left help the others (queues), else dealt out.
-    const bool whole_heads = 8 * 2 * static_cast<size_t>(g.N) * D * sizeof(uint16_t) <= (size_t{128} << 20);
-    a.item_order = !whole_heads ? ORDER_EIGHTHS : form.queued || force_dense ? ORDER_HEADS : ORDER_DEALT;
+    a.item_order = item_order(!whole_heads_fit(g, D), form.queued, force_dense);
     a.head_class = force_dense ? nullptr : head_class;
     a.head_bw = bandwidths ? head_bw : nullptr;
     a.BH = B * nH;

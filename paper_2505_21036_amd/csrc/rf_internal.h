@@ -82,6 +82,10 @@ struct AttnForm {
     int rows, key_groups;
     bool queued, copies;
 };
+// Whole heads to an XCD (every L2 then fetches a head's K and V once) as long as the eight heads in work fit the
+// memory-side cache with room to spare: 1-20 % up to 17776 tokens; beyond, all XCDs on one head at a time.
+inline bool whole_heads_fit(const Geometry& g, int D) { return 8 * 2 * static_cast<size_t>(g.N) * D * sizeof(uint16_t) <= (size_t{128} << 20); }
+
 // Forms of fewer than 256 rows are taken up to here (beyond, one head fills the chip with larger blocks), so that the
 // lists of 64- and 128-row blocks, which grow with the square of the length, need not exist for longer sequences.
 constexpr int kSmallBlockTokens = 1 << 17;

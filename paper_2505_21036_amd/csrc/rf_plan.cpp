@@ -7,9 +7,11 @@
 // arithmetic on frame indices and in-frame positions.
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 #include <utility>
 
 #include "rf_internal.h"
+#include "rf_queues.h"
 
 namespace rf {
 
@@ -243,14 +245,16 @@ void build_plan(const Geometry& g, const TokenTables& tables, int block, bool to
 
 namespace {
 
-// What a launch takes in each form: how many workgroups a CU holds, and the time (us, a full chip) one of them
-// takes per 64-key tile and to start and finish. The numbers are fitted to 60 sizes (256 to 48000 tokens, 1 to 48
-// heads), all dense and with a nearly uniform mix of classes; the choice is then within 1.0 % of the best form on
-// average and 13 % at the worst. Few rows: keys split four ways, then two ways (2 x 3 heads of 960 tokens,
-// head_dim 128: 21 us, 26 and with 128 rows 38; 24 heads of 4109: 206, 167 and 176). Many: the forms with the most
-// rows do the least per row and tile (48 heads of 17776: 5.0, 4.6 and 4.0 ms for these, 3.75 and 3.67 with 256
-// rows from the grid and from queues; 4 heads of 48000, dense: 4.63, 4.12 and 4.19 with 128 and 256 rows, 3.95
-// with 384). Between them what counts is how full the last round of workgroups is.
+// What a launch takes in each form, us: the model by which the form is chosen.  The numbers are fitted to the times of
+// every form at 107 sizes (256 to 119056 tokens, 1 to 160 heads), dense and with the three patterns in turn at
+// bandwidth 1/4 and stride 2, and at 58 of them at bandwidths 1/8 to 1/2 and strides 1 to 4 (profiles/forms_sweep.tsv).
+// The form it picks is then, on the geometric mean, 0.3 % from the best where all heads are dense (1.3 % at head_dim
+// 64) and 1.1 to 2.1 % with the patterns; the worst are 20 to 35 %, mostly a few heads of short layouts with text.  Few
+// rows: keys split four ways, then two ways (16 heads of 960 tokens, head_dim 128: 24 us, 28 and with 128 rows 40; 24
+// heads of 4109: 191, 158 and 167).  Many: the forms with the most rows do the least per row and tile (48 heads of
+// 17776: 5.1, 4.5 and 3.8 ms for these, 3.72 and 3.65 with 256 rows from the grid and from queues; 24 of 48000, dense:
+// 26.6 ms with 128 rows, 24.4 with 256, 23.7 with 384).  Between them what counts is how full the last round of
+// workgroups is, on the fullest XCD where the XCDs cannot help each other.
 //
 // copies: up to 256 rows, rows gathered through an index table cost nothing that can be measured, so no copies are
 // made (17776 tokens, 24 heads, head_dim 128, 128 rows: 1.92 ms either way); twelve wavefronts at head_dim 96 and
@@ -258,30 +262,48 @@ namespace {
 // order against 1.85 ms with copies at 384 rows).
 struct Kernel {
     AttnForm form;
-    int per_cu;
-    double tile_us, item_us;
-    double dense;  // times tile_us where no list is walked (32 dense heads of 16384, head_dim 64: 2.45, 2.26, 2.47 ms from 128 rows on)
+    int per_cu;           // workgroups a CU holds
+    double tile_us;       // per 64-key tile of a listed walk, where every CU holds that many
+    double item_us;       // to start and finish a workgroup
+    double spread;        // share of its time that a workgroup saves as its CU's only one of very many
+    double dense;         // times tile_us where no list is walked
+    double text;          // times tile_us in a block that holds text rows, which walks every tile, most of them masked
+    double text_tile_us;  // per tile of such a block where nothing else is left to run: no launch ends before it
+};
+struct Chip {
+    double start_us;             // of a launch
+    double smooth, smoother;     // how far the last, partial round is spread over the chip: after one round, more with every further one
+    double smooth_dense;         // likewise for dense walks, which are all of one length
+    double queue_us;             // the reset and the atomics of a launch from queues
+    double copy_us;              // per MB read and written for copies of K and V
+    double far, far_dense;       // times tile_us where eight heads' K and V do not fit the memory-side cache (workgroups from the grid: nothing keeps them in step)
+    double alone;                // share of text_tile_us on a nearly empty chip
+    double many, many_dense;     // gain, resp. loss if negative, of a launch of very many rounds
 };
 constexpr int kForms = 6;  // of one head_dim, at most
-const Kernel kKernels[3][kForms] = {{{{64, 4, false, false}, 1, 0.425, 7.6, 1},  // head_dim 64
-                                       {{64, 2, false, false}, 3, 0.900, 7.4, 1},
-                                       {{128, 1, false, false}, 3, 1.413, 10.8, 1.3},
-                                       {{256, 1, true, true}, 2, 2.172, 18.2, 1},
-                                       {{384, 1, true, false}, 1, 1.314, 22.8, 1.15},
-                                       {{0, 0, false, false}, 0, 0, 0, 1}},
-                                      {{{64, 4, false, false}, 1, 0.506, 6.8, 1},  // head_dim 96
-                                       {{64, 2, false, false}, 2, 0.900, 7.8, 1},
-                                       {{128, 1, false, false}, 3, 2.164, 8.1, 1},
-                                       {{256, 1, false, false}, 1, 1.347, 12.2, 1},
-                                       {{256, 1, true, false}, 1, 1.270, 24.9, 1},
-                                       {{384, 1, true, true}, 1, 1.670, 14.9, 1}},
-                                      {{{64, 4, false, false}, 1, 0.624, 7.7, 1},  // head_dim 128
-                                       {{64, 2, false, false}, 2, 1.091, 6.7, 1},
-                                       {{128, 1, false, false}, 2, 1.911, 6.1, 1},
-                                       {{256, 1, false, false}, 1, 1.611, 12.9, 1},
-                                       {{256, 1, true, false}, 1, 1.810, 17.1, 1},
-                                       {{384, 1, true, true}, 1, 2.129, 20.6, 1}}};
-const Kernel* kernels_of(int D) { return kKernels[D == 64 ? 0 : D == 96 ? 1 : 2]; }
+const Kernel kKernels[3][kForms] = {{{{64, 4, false, false}, 1, 0.478, 5.0, 0, 0.750, 2.00, 0.59},  // head_dim 64
+                                     {{64, 2, false, false}, 3, 1.175, 6.1, 0.72, 0.754, 1.58, 1.09},
+                                     {{128, 1, false, false}, 3, 2.130, 4.7, 0.72, 0.765, 1.02, 2.15},
+                                     {{256, 1, true, true}, 2, 2.675, 3.9, 0.74, 0.779, 0.50, 3.46},
+                                     {{384, 1, true, false}, 1, 2.022, 1.7, 0, 0.774, 1.10, 3.00},
+                                     {{0, 0, false, false}, 0, 0, 0, 0, 0, 0, 0}},
+                                    {{{64, 4, false, false}, 1, 0.630, 6.0, 0, 0.704, 2.00, 0.72},  // head_dim 96
+                                     {{64, 2, false, false}, 2, 1.156, 7.2, 0.66, 0.696, 1.49, 1.13},
+                                     {{128, 1, false, false}, 3, 2.844, 7.4, 0.77, 0.725, 1.14, 2.38},
+                                     {{256, 1, false, false}, 1, 1.923, 4.7, 0, 0.692, 1.40, 2.53},
+                                     {{256, 1, true, false}, 1, 1.901, 6.2, 0, 0.735, 1.19, 2.65},
+                                     {{384, 1, true, true}, 1, 2.505, 3.2, 0, 0.768, 1.22, 3.29}},
+                                    {{{64, 4, false, false}, 1, 0.753, 7.6, 0, 0.714, 2.00, 0.87},  // head_dim 128
+                                     {{64, 2, false, false}, 2, 1.409, 8.5, 0.69, 0.715, 1.30, 1.33},
+                                     {{128, 1, false, false}, 2, 2.430, 7.5, 0.73, 0.728, 1.20, 2.44},
+                                     {{256, 1, false, false}, 1, 2.250, 7.1, 0, 0.707, 1.23, 2.70},
+                                     {{256, 1, true, false}, 1, 2.196, 6.8, 0, 0.762, 1.07, 2.85},
+                                     {{384, 1, true, true}, 1, 3.043, 6.3, 0, 0.775, 1.22, 3.70}}};
+const Chip kChips[3] = {{4.4, 0.51, 0.05, 0.15, 6.1, 0.46, 1.11, 1.02, 0.40, 0.112, -0.048},
+                        {3.2, 0.50, 0.13, 0.08, 4.9, 0.30, 1.08, 1.03, 0.52, 0.103, -0.090},
+                        {2.6, 0.53, 0.10, 0.08, 6.6, 0.24, 1.07, 1.03, 0.51, 0.087, -0.112}};
+int index_of(int D) { return D == 64 ? 0 : D == 96 ? 1 : 2; }
+const Kernel* kernels_of(int D) { return kKernels[index_of(D)]; }
 
 }  // namespace
 
@@ -299,36 +321,61 @@ bool find_form(int D, int rows, int key_groups, bool queued, AttnForm* form) {
 
 namespace {
 
+// Tiles of 64 keys that a block of `rows` rows visits on the average over the three patterns.
+double mean_tiles(const Geometry& g, int rows) {
+    const double tiles = (g.N + kTileK - 1) / kTileK;
+    // a band of radius r over n groups of `group` rows: its share of the pairs, and what blocks and tiles that are not
+    // aligned with the groups take in beside it
+    auto band = [&](int n, int r, int group) {
+        if (r >= n - 1) return tiles;
+        const double share = (static_cast<double>(n) * (2 * r + 1) - static_cast<double>(r) * (r + 1)) / (static_cast<double>(n) * n);
+        const double beside = rows - std::gcd(rows, group) + kTileK - std::gcd(kTileK, group);
+        return std::min(tiles, (share * g.Nv + beside + g.text_len) / kTileK);
+    };
+    // rows y and columns x with (y - x) mod tau == 0, by residue
+    const int64_t tau = g.tau;
+    int64_t kept = 0;
+    for (int64_t c = 0; c < std::min<int64_t>(tau, std::min(g.W, g.H)); ++c)
+        kept += (g.W - c + tau - 1) / tau * ((g.H - c + tau - 1) / tau);
+    const double textural = (static_cast<double>(kept) * g.T + g.text_len) / kTileK;
+    return (band(g.T, g.r_spatial, g.HW) + band(g.HW, g.r_temporal, g.T) + textural) / 3;
+}
+
 // Time of a launch in form k, us; HUGE_VAL if the form is not to be taken at this size.
 double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense) {
-    constexpr int kCUs = 256;
-    const int tiles = (g.N + kTileK - 1) / kTileK, rows = k.form.rows;
+    constexpr int kCUs = 256;  // MI355X
+    const Chip& chip = kChips[index_of(D)];
+    const int rows = k.form.rows;
     if (rows < 256 && g.N > kSmallBlockTokens) return HUGE_VAL;
-    const double slots = static_cast<double>(kCUs) * k.per_cu;
-    // how long an item takes where n workgroups share the chip, relative to a full one
-    auto shared = [&](double n) { return 0.635 + 0.365 * std::ceil(n / kCUs) / k.per_cu; };
-    auto rounds_us = [&](double items, double item_tiles) {
-        const double rounds = items / slots, full = std::floor(rounds), rest = items - full * slots;
-        double last = rest > 0 ? shared(rest) : 0;
-        // workgroups are out of step by then; dense walks at head_dim 64, all of one length, less so (at 128 it
-        // would pick 384 rows for 10 heads of 22626: 2.64 ms against 2.56)
-        const double part = dense && D == 64 && rest > 0 ? 0.5 + 0.5 * rest / slots : rest / slots;
-        if (rounds >= 3) last = std::min(last, part);
-        return (full + last) * (item_tiles * k.tile_us * (dense ? k.dense : 1) + k.item_us);
-    };
-    const int nQB = (g.N + rows - 1) / rows, nTB = g.text_len > 0 ? nQB - g.Nv / rows : 0;
-    const double items = static_cast<double>(nQB) * BH, longs = static_cast<double>(nTB) * BH;
-    // from about there on the queues' balance is worth what they cost (head_dim 128, the 256-row form from the grid
-    // and from queues: 24 heads of 4109, 1.6 rounds, 186 and 190 us; 30 of 5632, 2.6 rounds, 281 and 281; 4 of
-    // 48000, 2.9 rounds, 2.42 and 2.29 ms)
-    if (rows == 256 && !k.form.queued && items > 2.5 * slots) return HUGE_VAL;
-    double us = rounds_us(items, tiles);
-    if (!dense) {
-        // about half the tiles, but for the blocks that hold text rows: those walk every tile, most of them
-        // masked, and nothing ends before the longest item
-        us = rounds_us(items + 1.1 * longs, 0.54 * tiles);
-        if (longs > 0) us = std::max(us, (k.form.copies ? 1.81 : 1.33) * tiles * k.tile_us * shared(std::min(items, slots)) + k.item_us);
+    if (rows >= 2 * std::max(g.N, kTileK)) return HUGE_VAL;  // half of the block would have no rows
+    const int nQB = (g.N + rows - 1) / rows, nTB = g.text_len > 0 ? nQB - g.Nv / rows : 0, nVB = nQB - nTB;
+    const bool far = !whole_heads_fit(g, D);
+    const double tiles = (g.N + kTileK - 1) / kTileK, slots = static_cast<double>(kCUs) * k.per_cu;
+    const double items = static_cast<double>(nQB) * BH, longs = dense ? 0 : static_cast<double>(nTB) * BH;
+    const double tile_us = k.tile_us * (dense ? k.dense : 1) * (!far || k.form.queued ? 1 : dense ? chip.far_dense : chip.far);
+    const double item = (dense ? tiles : mean_tiles(g, rows)) * tile_us + k.item_us;
+    const double text_item = tiles * tile_us * k.text + k.item_us;
+    double rounds = items / slots;
+    if (!k.form.queued) {  // what the fullest XCD has to do; beyond some thousand heads all are equally full
+        const int heads = std::min(BH, 4096);
+        const Queues qs(heads, nVB, nTB, item_order(far, false, dense));
+        int most = 0;
+        for (int x = 0; x < 8; ++x) most = std::max(most, qs.items(x));
+        rounds = 8.0 * most * (static_cast<double>(BH) / heads) / slots;
     }
+    rounds *= 1 + longs / items * (text_item / item - 1);
+    // how long an item takes where n workgroups share the chip, relative to a full one
+    auto shared = [&](double n) { return 1 - k.spread * (1 - std::min<double>(k.per_cu, std::ceil(n / kCUs)) / k.per_cu); };
+    const double full = std::floor(rounds), rest = rounds - full;
+    double length = full > 0 ? full : shared(rest * slots);
+    if (full > 0 && rest > 0) {
+        const double even = dense ? chip.smooth_dense : std::min(1.0, chip.smooth + chip.smoother * (full - 1));
+        length += shared(rest * slots) * (1 - even) + rest * even;
+    }
+    double us = item * length * (1 - (dense ? chip.many_dense : chip.many) * (1 - 1 / std::max(1.0, rounds)));
+    if (longs > 0) us = std::max(us, k.text_tile_us * tiles * (chip.alone + (1 - chip.alone) * std::min(1.0, items / slots)) + k.item_us);
+    us += chip.start_us + (k.form.queued ? chip.queue_us : 0);
+    if (k.form.copies && !dense) us += 3 + chip.copy_us * (2. / 3) * 8e-6 * BH * g.N * D;  // two patterns in three walk copies
     return us;
 }
 
@@ -352,15 +399,24 @@ AttnForm cheapest(int D, bool copies, F cost) {
 
 }  // namespace
 
+// A call whose heads have classes on the device may be all dense (a program that runs the first tenth of its steps dense
+// may say so through the classes), so a tenth of the weight goes to the dense walk.  It decides between forms that are
+// nearly even for the patterns; head_dim 64 has the widest gap, 48 heads of 17776 tokens: 128 rows 2221 us with the
+// patterns in turn and 4252 dense, 256 from queues 2316 and 3994, 384 2318 and 4085.
+static double mixed_log_us(const Kernel& k, const Geometry& g, int BH, int D) {
+    constexpr double kDenseShare = 0.1;
+    return (1 - kDenseShare) * std::log(launch_us(k, g, BH, D, false)) + kDenseShare * std::log(launch_us(k, g, BH, D, true));
+}
+
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
     // without room a form with copies would walk Temporal heads in token order: up to twice the time
-    return cheapest(D, room || dense, [&](const Kernel& k) { return launch_us(k, g, BH, D, dense); });
+    return cheapest(D, room || dense, [&](const Kernel& k) { return dense ? launch_us(k, g, BH, D, true) : mixed_log_us(k, g, BH, D); });
 }
 
 AttnForm choose_fixed_form(const Geometry& g, int D) {
     return cheapest(D, false, [&](const Kernel& k) {
         double log_us = 0;
-        for (int heads : {6, 12, 24, 48}) log_us += std::log(launch_us(k, g, heads, D, false));
+        for (int heads : {6, 12, 24, 48}) log_us += mixed_log_us(k, g, heads, D);
         return log_us;
     });
 }

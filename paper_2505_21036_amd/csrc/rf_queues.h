@@ -25,6 +25,9 @@ enum : int {
     ORDER_DEALT = 2
 };
 
+// far: the heads in work do not fit the memory-side cache; queued: XCDs with nothing left help the others.
+inline int item_order(bool far, bool queued, bool dense) { return far ? ORDER_EIGHTHS : queued || dense ? ORDER_HEADS : ORDER_DEALT; }
+
 struct Queues {
     int BH, nVB, nTB, order, per_xcd, whole, shift;
     RF_BOTH Queues(int heads, int video_blocks, int text_blocks, int item_order)

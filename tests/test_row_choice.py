@@ -20,11 +20,11 @@ needs_gxx = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 
 
 def forms_chosen(tmp_path, cases):
-    """(rows, key groups, queued, copies) of choose_form for each (T, H, W, text, BH, D, dense, room)."""
+    """(rows, key groups, queued, copies) of choose_form for each (T, H, W, text, BH, D, dense, room[, bandwidth, stride])."""
     exe, csrc = str(tmp_path / "rows_driver"), os.path.join(ROOT, "paper_2505_21036_amd", "csrc")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", csrc,
                            os.path.join(ROOT, "tests", "rows_driver.cpp"), os.path.join(csrc, "rf_plan.cpp"), "-o", exe])
-    text = "\n".join(" ".join(str(int(x)) for x in c) for c in cases)
+    text = "\n".join(" ".join(str(x) for x in tuple(int(x) for x in c[:8]) + (tuple(c[8:]) or (0.25, 2))) for c in cases)
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
     return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
 
@@ -35,25 +35,25 @@ def test_small_problems_split_the_keys_and_the_largest_take_the_most_rows(tmp_pa
         small = [(4, 8, 8, 0, 2, D, d, r) for d in (0, 1) for r in (0, 1)]
         small += [(7, 10, 13, 50, 6, D, d, r) for d in (0, 1) for r in (0, 1)] + [(2, 1, 1, 1, 1, D, 0, 0)]
         assert all(rows == 64 and groups > 1 and not queued for rows, groups, queued, _ in forms_chosen(tmp_path, small))
-        largest = [(33, 45, 80, 256, 24, D, 1, 0), (1, 4096, 4096, 0, 1 << 20, D, 1, 0)]
-        assert all(form[:3] == (384, 1, 1) for form in forms_chosen(tmp_path, largest))
+        largest = [(33, 45, 80, 256, 24, D, 1, 0), (1, 4096, 4096, 0, 1 << 20, D, 1, 0)]  # 256: wavefronts of 64 rows
+        assert all(form[:3] == (256 if D == 64 else 384, 1, 1) for form in forms_chosen(tmp_path, largest))
     # with nowhere to copy K and V to, none of the forms that need copies
     rooms = [(T, 20, 20, text, BH, D, 0, 0) for T in (2, 9, 33) for text in (0, 77) for BH in (1, 7, 48, 300) for D in (64, 96, 128)]
     assert not any(copies for _, _, _, copies in forms_chosen(tmp_path, rooms))
 
 
 # (D, B, nH, layout, dense, room) -> (rows, key groups, queued): sizes at which the rule picks each kernel
-RAGGED, SHORT, WIDE = (7, 10, 13, 50), (4, 9, 12, 0), (5, 32, 33, 37)
+RAGGED, SHORT, WIDE, MID, SQUARE, LONG = (7, 10, 13, 50), (4, 9, 12, 0), (5, 32, 33, 37), (8, 17, 24, 45), (6, 40, 41, 37), (5, 64, 65, 0)
 KERNELS = [
     ((64, 2, 3, RAGGED, False, True), (64, 4, 0)), ((96, 2, 3, RAGGED, False, False), (64, 4, 0)), ((128, 2, 3, RAGGED, False, True), (64, 4, 0)),
     ((64, 2, 24, RAGGED, False, False), (64, 2, 0)), ((96, 2, 24, RAGGED, False, True), (64, 2, 0)), ((128, 2, 20, RAGGED, False, False), (64, 2, 0)),
     ((64, 2, 60, RAGGED, False, False), (128, 1, 0)), ((96, 2, 60, RAGGED, False, True), (128, 1, 0)), ((128, 2, 48, RAGGED, False, False), (128, 1, 0)),
-    ((64, 2, 60, RAGGED, True, True), (256, 1, 1)), ((64, 1, 240, SHORT, False, True), (256, 1, 1)),
-    ((96, 1, 28, WIDE, False, True), (256, 1, 0)), ((128, 1, 28, WIDE, False, False), (256, 1, 0)),
-    ((96, 1, 32, WIDE, False, False), (256, 1, 1)), ((128, 1, 8, (5, 64, 65, 37), False, False), (256, 1, 1)),
-    ((64, 1, 8, (6, 40, 41, 37), True, True), (384, 1, 1)), ((64, 1, 4, (5, 64, 65, 0), False, False), (384, 1, 1)),
-    ((96, 1, 60, WIDE, False, True), (384, 1, 1)), ((96, 1, 76, RAGGED, True, False), (384, 1, 1)),
-    ((128, 1, 60, WIDE, False, True), (384, 1, 1)), ((128, 1, 76, RAGGED, True, False), (384, 1, 1)),
+    ((64, 1, 30, MID, True, True), (256, 1, 1)), ((64, 1, 6, LONG, False, True), (256, 1, 1)),
+    ((96, 1, 10, MID, True, True), (256, 1, 0)), ((96, 1, 96, SHORT, False, False), (256, 1, 0)), ((128, 1, 10, MID, True, False), (256, 1, 0)), ((128, 1, 96, SHORT, False, False), (256, 1, 0)),
+    ((96, 1, 19, SQUARE, False, False), (256, 1, 1)), ((128, 1, 8, (5, 64, 65, 37), False, False), (256, 1, 1)),
+    ((64, 1, 13, WIDE, True, True), (384, 1, 1)), ((64, 1, 4, LONG, False, False), (384, 1, 1)),
+    ((96, 1, 12, (5, 64, 65, 37), False, True), (384, 1, 1)), ((96, 1, 20, MID, True, False), (384, 1, 1)),
+    ((128, 1, 13, (5, 64, 65, 37), False, True), (384, 1, 1)), ((128, 1, 20, MID, True, False), (384, 1, 1)),
 ]
 
 
@@ -65,6 +65,29 @@ def test_the_sizes_of_the_gpu_test_pick_the_kernels_it_names(tmp_path):
     grid = [(T, 20, 20, text, BH, D, dense, room) for T in (1, 3, 7, 20) for text in (0, 77) for BH in (1, 4, 16, 48, 72, 160, 400)
             for D in (64, 96, 128) for dense in (0, 1) for room in (0, 1)]
     assert {(case[5],) + form[:3] for case, form in zip(grid, forms_chosen(tmp_path, grid))} <= named
+
+
+@needs_gxx
+def test_the_rule_is_near_the_best_form_over_the_measured_sizes(tmp_path):
+    """Replays the times of every form (profiles/forms_sweep.tsv) through the rule: what its choice costs over the best
+    form there is, with room for copies and without.  The bounds are what the fit reached, rounded up."""
+    with open(os.path.join(ROOT, "profiles", "forms_sweep.tsv")) as f:
+        lines = [l.rstrip("\n").split("\t") for l in f if not l.startswith("#")]
+    names, rows = lines[0][9:], lines[1:]
+    lost = {}
+    for room in (True, False):
+        asked = [tuple(int(x) for x in r[1:6]) + (int(r[0]), r[6] == "dense", room, float(r[7]), int(r[8])) for r in rows]
+        for r, c, (n_rows, groups, queued, _) in zip(rows, asked, forms_chosen(tmp_path, asked)):
+            D, dense = c[5], c[6]
+            us = {n: float(t) for n, t in zip(names, r[9:]) if t != "-"}
+            copies = "256/1q" if D == 64 else "384/1q"
+            best = min(t for n, t in us.items() if room or dense or n != copies)
+            default = (c[8], c[9]) == (0.25, 2)
+            lost.setdefault((D, dense, default), []).append((us["%d/%d%s" % (n_rows, groups, "q" if queued else "")] / best, c))
+    for key, ratios in lost.items():
+        mean, worst = np.exp(np.mean([np.log(x) for x, _ in ratios])), max(ratios)
+        print(key, "mean %.3f worst %.2f at %s" % ((mean,) + worst))
+        assert mean <= 1.03 and worst[0] <= 1.35, (key, mean, worst)
 
 
 @pytest.mark.gpu
