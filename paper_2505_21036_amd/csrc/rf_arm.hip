@@ -35,8 +35,9 @@ constexpr int kArmSplitItemsBoth = 256, kArmSplitItemsApart = 128;
 // as in the attention kernel: the reference in the exponent moves only when a row outgrows it by this
 constexpr float kArmRescaleSlack = 8.f;
 
-// Wavefronts per SIMD the register allocation is held to: what fits without spills (one pass at head_dim 128 does
-// fit four, with spills on a rare path, and measured 2-7 % slower so).
+// Wavefronts per SIMD the register allocation is held to: what the tile loop fits without spills (head_dim 96, one pass:
+// four with eight bytes spilled outside the loop; one pass at head_dim 128 does fit four, with spills on a rare path of
+// the loop, and measured 2-7 % slower so).
 constexpr int arm_waves_per_simd(int D, bool both, int KS) { return KS > 1 ? 2 : (both ? (D == 64 ? 4 : 3) : (D == 128 ? 3 : 4)); }
 
 template <int D, int R, int KS>

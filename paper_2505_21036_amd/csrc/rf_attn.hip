@@ -218,6 +218,8 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     };
     auto k_lds = [&](int t) { return smem + SM::K_OFF + (t % DEPTH) * ST::K_BYTES; };
     auto v_lds = [&](int t) { return smem + SM::V_OFF + (t % DEPTH) * ST::V_BYTES; };
+    // three workgroups of four wavefronts per CU at head_dim 96 have 168 registers each, and the banded loop one pair too few
+    constexpr bool kNarrow = D == 96 && NW == 4 && KS == 1 && MODE == MODE_BAND;
     auto fetch_some = [&](auto with_v, auto with_k, int t, int entry) {
         constexpr bool WV = decltype(with_v)::value, WK = decltype(with_k)::value;
         const int k0 = (entry & kTileIndexMask) * kTileK;
@@ -228,7 +230,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
             // full tile of consecutive tensor rows: everything but the tile origin is loop invariant
             const int r0 = k0 + (k0 < Nv ? qk.video_shift : qk.text_shift);
             const size_t origin = static_cast<size_t>(r0) * (2 * D);
-            st.template issue_consecutive<WV, WK>(Kh + origin, Vh + origin, k_lds(t), v_lds(t));
+            st.template issue_consecutive<WV, WK, kNarrow>(Kh + origin, Vh + origin, k_lds(t), v_lds(t));
         } else {
             st.template issue<WV, WK, true>(Kh, Vh, k_lds(t), v_lds(t), [&](int row) {
                 const int n = min(k0 + row, keyN - 1);

@@ -194,16 +194,21 @@ struct DirectTile {
             if (WITH_V) dma16(vh, row_off + 16u * v_slot(row, pos), lds_offset(vl) + seg * 1024);
         }
     }
-    // same for a tile of 64 consecutive tokens starting at kh / vh
-    template <bool WITH_V = true, bool WITH_K = true>
+    // same for a tile of 64 consecutive tokens starting at kh / vh.  NARROW: the lane offsets stay 32 bits wide between
+    // calls; left to itself the compiler keeps each beside a register that holds its upper half, zero
+    template <bool WITH_V = true, bool WITH_K = true, bool NARROW = false>
     __device__ __forceinline__ void issue_consecutive(const unsigned char* kh, const unsigned char* vh, unsigned char* kl,
                                                       unsigned char* vl) {
+        auto off = [](uint32_t o) {
+            if (NARROW) asm volatile("" : "+v"(o));
+            return o;
+        };
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int seg = j * NW + wave;
             if (!EVEN && seg >= SEGS) break;
-            if (WITH_K) dma16(kh + j * STEP, k_lane_off[j % K_VARIANTS], lds_offset(kl) + seg * 1024);
-            if (WITH_V) dma16(vh + j * STEP, v_lane_off[j % V_VARIANTS], lds_offset(vl) + seg * 1024);
+            if (WITH_K) dma16(kh + j * STEP, off(k_lane_off[j % K_VARIANTS]), lds_offset(kl) + seg * 1024);
+            if (WITH_V) dma16(vh + j * STEP, off(v_lane_off[j % V_VARIANTS]), lds_offset(vl) + seg * 1024);
         }
     }
     // load instructions per tensor and tile this wavefront issues (the first SEGS % NW wavefronts take the odd round)

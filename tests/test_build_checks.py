@@ -1,10 +1,12 @@
 """Checks on the generated gfx950 code that no GPU is needed for."""
+import functools
 import re
 
-from paper_2505_21036_amd.build import device_assembly
-
-
 import pytest
+
+from paper_2505_21036_amd import build
+
+device_assembly = functools.lru_cache(maxsize=None)(build.device_assembly)
 
 
 @pytest.mark.parametrize("source", ["rf_attn.hip", "rf_arm.hip"])
@@ -30,11 +32,11 @@ def test_m0_is_used_only_by_the_tile_loads(source):
     assert sum("s_waitcnt vmcnt(0)" in l for l in code) >= (4 if source == "rf_attn.hip" else 2)
 
 
-def _tile_loops(asm, kernel):
-    """Instruction lists of the innermost loops of `kernel` that hold one tile's 32 MFMAs."""
+def _tile_loops(asm, kernel, mfmas=32):
+    """Instruction lists of the innermost loops of `kernel` that hold one tile's MFMAs."""
     lines = asm.splitlines()
     start = next(i for i, l in enumerate(lines) if l.startswith(kernel + ":"))
-    end = next(i for i in range(start, len(lines)) if "s_endpgm" in lines[i])
+    end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
     lines = lines[start:end]
     label_at = {m.group(1): i for i, l in enumerate(lines) for m in [re.match(r"^(\.LBB\d+_\d+):", l)] if m}
     loops = []
@@ -43,7 +45,7 @@ def _tile_loops(asm, kernel):
         if m and label_at.get(m.group(1), len(lines)) < i:
             body = [x.strip() for x in lines[label_at[m.group(1)]:i + 1]]
             body = [x for x in body if x and not x.startswith((";", "."))]
-            if sum(x.startswith("v_mfma") for x in body) == 32:
+            if sum(x.startswith("v_mfma") for x in body) == mfmas:
                 loops.append(body)
     return loops
 
@@ -77,3 +79,25 @@ def test_twelve_wavefront_kernel_fits_its_registers():
     m = re.search(r"\.amdhsa_kernel _ZN2rf11attn_kernelILi128ELi12ELi0EEEvNS_8AttnArgsE.*?\.amdhsa_next_free_vgpr\s+(\d+)", asm, re.S)
     assert m and int(m.group(1)) <= 168
 
+
+def test_no_tile_loop_reloads_from_scratch():
+    """The same for every kernel instance of both files: the tile loops of the attention (D / 4 MFMAs per tile and 32
+    query rows) and of the ARM (D / 8) hold no access to scratch.  The pipelined loop for 64-row wavefronts, which runs
+    only under its flag, is left out."""
+    for source, kinds in (("rf_attn.hip", ("attn_item_kernel", "attn_kernel")), ("rf_arm.hip", ("arm_recall_kernel",))):
+        asm = device_assembly(source)
+        seen = 0
+        for name in re.findall(r"\.amdhsa_kernel (\S+)", asm):
+            m = re.search(r"(%s)ILi(\d+)E((?:L[ib]\d+E)+)" % "|".join(kinds), name)
+            if not m:
+                continue
+            D, args = int(m.group(2)), [int(x) for x in re.findall(r"L[ib](\d+)E", m.group(3))]
+            if m.group(1) == "attn_kernel" and args[1] == 1:  # RF_FLAG_WIDE_ROWS
+                continue
+            halves = 2 if m.group(1) == "attn_kernel" and args[1] == 2 else 1
+            loops = _tile_loops(asm, name, D // 8 if source == "rf_arm.hip" else D // 4 * halves)
+            assert loops, name
+            for body in loops:
+                assert not any(x.startswith("scratch_") for x in body), name
+            seen += 1
+        assert seen >= 9, (source, seen)
