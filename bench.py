@@ -24,8 +24,8 @@ PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA
 # HBM-side bytes of one attention launch of the timed step (ARM-chosen classes).  NOT observed by
 # this script: copied from the rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised in
 # profiles/attn_kernel_hunyuan720p.md (counter values in KiB, FETCH_SIZE scaled x2.0 and WRITE_SIZE
-# x1.0, what the same counters read for a 1 GiB device copy).  Only known for the workload / block
-# it was profiled on; the bench line says where the figure comes from.
+# x1.0, what the same counters read for a 1 GiB device copy).  Only known for the workload and the rows per
+# workgroup it was profiled on; the bench line says where the figure comes from.
 PROFILED_TRAFFIC_BYTES = {("hunyuan720p", 384): (2.0 * 7.9694e6 + 1.0 * 8.3882e5) * 1024,
                           ("hunyuan720p", 256): (2.0 * 9.5379e6 + 1.0 * 7.5577e5) * 1024}
 
@@ -56,7 +56,8 @@ def main():
     ap.add_argument("--steps", type=int, default=5)
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--workload", default="hunyuan720p")
-    ap.add_argument("--block", type=int, default=0, help="query rows per block (64|128|256|384); 0 = the workload's")
+    ap.add_argument("--block", type=int, default=0, help="the calls' block argument (64|128|256|384); 0 = the workload's. The library "
+                                                         "chooses the rows a workgroup takes by itself (but under --wide-rows)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--wide-rows", action="store_true",
                     help="run the attention with RF_FLAG_WIDE_ROWS (64 query rows per wavefront; head_dim 128, block 256)")
@@ -71,8 +72,8 @@ def main():
     ap.add_argument("--configs", action="store_true",
                     help="instead of the step: the other named configurations, each against the same kernel run dense: "
                          "the CogVideoX-shaped layer with round-robin classes and with ARM-chosen classes (equal-interval "
-                         "sampling), the Open-Sora-Plan-shaped layer at blocks 128 and 256, the planted layer at blocks "
-                         "64 and 128 with ARM-chosen classes; prints one JSON line")
+                         "sampling), the Open-Sora-Plan-shaped layer, the planted layer with ARM-chosen classes; prints one "
+                         "JSON line")
     ap.add_argument("--only", default="", help="profiling aid: run just 'step', 'arm', 'thirds', 'dense', every head 'spatial' / 'temporal' / 'textural', or 'copy' (a 1 GiB device copy)")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -97,7 +98,6 @@ def main():
     ws = torch.empty(max(rf.rf_arm_workspace_bytes(w.B, w.nH, rl), 4), dtype=torch.uint8, device=dev)
     ws_attn = torch.empty(rf.rf_attention_workspace_bytes(w.B, w.nH, w.D, rl), dtype=torch.uint8, device=dev)
     thirds = inp.thirds_classes(w).to(dev)
-    dense = torch.full((w.B, w.nH), rf.RF_DENSE, dtype=torch.int32, device=dev)
 
     def arm():
         rf.rf_arm_classify(Q, K, rl, None, rf.RF_SAMPLE_FIRST_FRAME, 0.9, hc, rec, ws)
@@ -105,8 +105,14 @@ def main():
     attn_flags = (rf.RF_FLAG_FIXED_ORDER if args.fixed_order else 0) | (rf.RF_FLAG_WIDE_ROWS if args.wide_rows else 0)
     attn_params = rf.rf_params(0.25, 0.25, 2, 0, attn_flags) if attn_flags else None
 
+    dense_params = rf.rf_params(0.25, 0.25, 2, 0, attn_flags | rf.RF_FLAG_FORCE_DENSE)
+    rows, groups, queued, _ = rf.attention_form(w.B, w.nH, w.D, rl, attn_params, block, ws_attn.numel())
+
     def attn(classes):
         rf.rf_sparse_attention(Q, K, V, classes, rl, attn_params, block, O, ws_attn)
+
+    def attn_dense():
+        rf.rf_sparse_attention(Q, K, V, None, rl, dense_params, block, O, ws_attn)
 
     def step():
         arm()
@@ -125,15 +131,15 @@ def main():
         return sum(a.elapsed_time(b) for a, b in pairs) / reps
 
     if args.sweep:
-        attn(dense)
-        ms_dense = event_ms(lambda: attn(dense), 2)
-        rows = []
+        attn_dense()
+        ms_dense = event_ms(attn_dense, 2)
+        table = []
         for bw, tau, paper in ((0.25, 2, 1.85), (0.18, 3, 2.50), (0.13, 4, 3.00)):
             prm = rf.rf_params(bw, bw, tau, 0, 0)
             ws_s = torch.empty(rf.rf_attention_workspace_bytes(w.B, w.nH, w.D, rl, prm), dtype=torch.uint8, device=dev)
             row = {"bandwidth": bw, "tex_stride": tau, "paper_speedup_with_10pct_dense_steps": paper}
-            for name, classes in (("spatial", torch.zeros_like(dense)), ("temporal", torch.ones_like(dense)),
-                                  ("textural", torch.full_like(dense, 2)), ("thirds", thirds)):
+            for name, classes in (("spatial", torch.zeros_like(thirds)), ("temporal", torch.ones_like(thirds)),
+                                  ("textural", torch.full_like(thirds, 2)), ("thirds", thirds)):
                 fn = lambda: rf.rf_sparse_attention(Q, K, V, classes, rl, prm, block, O, ws_s)
                 fn()
                 ms = event_ms(fn, 2)
@@ -141,8 +147,8 @@ def main():
                 row[name] = {"ms": round(ms, 3), "speedup_vs_dense": round(ms_dense / ms, 3),
                              "kept_fraction": round(kept, 4), "flop_count_speedup": round(1 / kept, 3),
                              "speedup_if_10pct_steps_dense": round(1 / (0.1 + 0.9 * ms / ms_dense), 3)}
-            rows.append(row)
-        print(json.dumps({"sweep": rows, "dense_ms": round(ms_dense, 3), "workload": w.name, "block": block}))
+            table.append(row)
+        print(json.dumps({"sweep": table, "dense_ms": round(ms_dense, 3), "workload": w.name, "block": block}))
         return
 
     if args.plus:
@@ -152,13 +158,13 @@ def main():
         bws = [0.5, 0.25, 0.125]
         hc_p, hbw_p, _ = rf.rf_arm_classify_plus(Qp, Kp, rlp, None, rf.RF_SAMPLE_FIRST_FRAME, 0.9, bws)
         hc_b, _ = rf.rf_arm_classify(Qp, Kp, rlp, None, rf.RF_SAMPLE_FIRST_FRAME, 0.9)
-        dense_p = torch.full_like(hc_p, rf.RF_DENSE)
+        dense_p = rf.rf_params(0.25, 0.25, 2, 0, rf.RF_FLAG_FORCE_DENSE)
         Op = torch.empty_like(Qp)
         runs = {"arm_plus": lambda: rf.rf_arm_classify_plus(Qp, Kp, rlp, None, rf.RF_SAMPLE_FIRST_FRAME, 0.9, bws),
                 "arm_base": lambda: rf.rf_arm_classify(Qp, Kp, rlp, None, rf.RF_SAMPLE_FIRST_FRAME, 0.9),
                 "attention_plus": lambda: rf.rf_sparse_attention_plus(Qp, Kp, Vp, hc_p, hbw_p, bws, rlp, None, wp.block, Op),
                 "attention_base": lambda: rf.rf_sparse_attention(Qp, Kp, Vp, hc_b, rlp, None, wp.block, Op),
-                "attention_dense": lambda: rf.rf_sparse_attention(Qp, Kp, Vp, dense_p, rlp, None, wp.block, Op)}
+                "attention_dense": lambda: rf.rf_sparse_attention(Qp, Kp, Vp, None, rlp, dense_p, wp.block, Op)}
         res = {}
         for name, fn in runs.items():
             fn()
@@ -176,9 +182,9 @@ def main():
     if args.configs:
         del Q, K, V, O, ws_attn
         torch.cuda.empty_cache()
-        rows = []
+        table = []
 
-        def time_config(name, blocks, arm_mode=None, forced=None):
+        def time_config(name, arm_mode=None, forced=None):
             wc = inp.WORKLOADS[name]
             rlc = rf.rf_layout(wc.T, wc.H, wc.W, wc.text_len)
             Qc, Kc, Vc = inp.full_qkv(wc, dev)
@@ -200,27 +206,35 @@ def main():
             row["class_histogram"] = {"spatial": ch.count(0), "temporal": ch.count(1), "textural": ch.count(2), "dense": ch.count(3)}
             kept = sum(kept_pairs(c, wc) for c in ch) / float(wc.B * wc.nH * wc.N * wc.N)
             row["kept_fraction"] = round(kept, 4)
-            for blk in blocks:
-                sparse = lambda: rf.rf_sparse_attention(Qc, Kc, Vc, hcc, rlc, None, blk, Oc, wsc)
-                densef = lambda: rf.rf_sparse_attention(Qc, Kc, Vc, densec, rlc, None, blk, Oc, wsc)
-                sparse()
-                ms = event_ms(sparse, 5)
-                densef()
-                msd = event_ms(densef, 3)
-                row["block_%d" % blk] = {"sparse_ms": round(ms, 4), "dense_ms": round(msd, 4), "speedup_vs_dense": round(msd / ms, 3),
-                                         "flop_count_speedup": round(1 / kept, 3),
-                                         "tflops_useful": round(kept * wc.dense_flops() / ms / 1e9, 1),
-                                         "tflops_dense": round(wc.dense_flops() / msd / 1e9, 1),
-                                         "mfma_frac_dense": round(wc.dense_flops() / msd / 1e9 / PEAK_BF16_TFLOPS, 4)}
-                if "arm_ms" in row:
-                    row["block_%d" % blk]["arm_pct_of_sparse_attention"] = round(100 * row["arm_ms"] / ms, 3)
-            rows.append(row)
+            flagged = rf.rf_params(0.25, 0.25, 2, 0, rf.RF_FLAG_FORCE_DENSE)
+            runs = {"sparse": lambda: rf.rf_sparse_attention(Qc, Kc, Vc, hcc, rlc, None, wc.block, Oc, wsc),
+                    "sparse_without_room": lambda: rf.rf_sparse_attention(Qc, Kc, Vc, hcc, rlc, None, wc.block, Oc),
+                    "dense": lambda: rf.rf_sparse_attention(Qc, Kc, Vc, None, rlc, flagged, wc.block, Oc, wsc),
+                    "dense_by_class": lambda: rf.rf_sparse_attention(Qc, Kc, Vc, densec, rlc, None, wc.block, Oc, wsc)}
+            ms = {}
+            for _ in range(10):  # the clock has dropped while the inputs were made
+                for fn in runs.values():
+                    fn()
+            for n, fn in runs.items():
+                ms[n] = event_ms(fn, 5)
+                row[n + "_ms"] = round(ms[n], 4)
+            shape = (wc.B, wc.nH, wc.D, rlc)
+            row["rows_per_workgroup"] = {"sparse": rf.attention_form(*shape, None, wc.block, wsc.numel())[0],
+                                         "sparse_without_room": rf.attention_form(*shape, None, wc.block)[0],
+                                         "dense": rf.attention_form(*shape, flagged, wc.block, wsc.numel())[0]}
+            row.update({"speedup_vs_dense": round(ms["dense"] / ms["sparse"], 3), "flop_count_speedup": round(1 / kept, 3),
+                        "tflops_useful": round(kept * wc.dense_flops() / ms["sparse"] / 1e9, 1),
+                        "tflops_dense": round(wc.dense_flops() / ms["dense"] / 1e9, 1),
+                        "mfma_frac_dense": round(wc.dense_flops() / ms["dense"] / 1e9 / PEAK_BF16_TFLOPS, 4)})
+            if "arm_ms" in row:
+                row["arm_pct_of_sparse_attention"] = round(100 * row["arm_ms"] / ms["sparse"], 3)
+            table.append(row)
 
-        time_config("cogvideox", (128, 256), forced=inp.round_robin_classes)
-        time_config("cogvideox", (128, 256), arm_mode=rf.RF_SAMPLE_EQUAL_INTERVAL)
-        time_config("osp720p", (128, 256, 384), forced=inp.thirds_classes)
-        time_config("planted", (64, 128), arm_mode=rf.RF_SAMPLE_FIRST_FRAME)
-        print(json.dumps({"configs": rows}))
+        time_config("cogvideox", forced=inp.round_robin_classes)
+        time_config("cogvideox", arm_mode=rf.RF_SAMPLE_EQUAL_INTERVAL)
+        time_config("osp720p", forced=inp.thirds_classes)
+        time_config("planted", arm_mode=rf.RF_SAMPLE_FIRST_FRAME)
+        print(json.dumps({"configs": table}))
         return
 
     if args.only:
@@ -228,7 +242,7 @@ def main():
                for n, c in (("spatial", rf.RF_SPATIAL), ("temporal", rf.RF_TEMPORAL), ("textural", rf.RF_TEXTURAL))}
         src = torch.empty(1 << 30, dtype=torch.uint8, device=dev) if args.only == "copy" else None
         dst = torch.empty_like(src) if src is not None else None
-        fn = {"step": step, "arm": arm, "thirds": lambda: attn(thirds), "dense": lambda: attn(dense),
+        fn = {"step": step, "arm": arm, "thirds": lambda: attn(thirds), "dense": attn_dense,
               "copy": lambda: dst.copy_(src),  # 1 GiB read + 1 GiB written: calibrates FETCH_SIZE / WRITE_SIZE
               "spatial": lambda: attn(one["spatial"]), "temporal": lambda: attn(one["temporal"]),
               "textural": lambda: attn(one["textural"])}[args.only]
@@ -266,8 +280,8 @@ def main():
     ms_arm = event_ms(arm, reps)
     attn(thirds)
     ms_thirds = event_ms(lambda: attn(thirds), reps)
-    attn(dense)
-    ms_dense = event_ms(lambda: attn(dense), max(2, reps // 2))
+    attn_dense()
+    ms_dense = event_ms(attn_dense, max(2, reps // 2))
 
     # ---- the same step on planted heads of the same shape, where the ARM picks all three patterns
     planted = None
@@ -315,10 +329,10 @@ def main():
     def executed(classes):
         tot = 0
         for c in set(classes):
-            # Temporal heads walk the position-major copy (the workspace is always given here)
-            vis, _, _ = rf.plan_block_counts(rl, None, block, rf.RF_LIST_TEMPORAL_POSITION_MAJOR if c == 1 else c)
+            # Temporal heads walk the position-major order (the workspace is always given here)
+            vis, _, _ = rf.plan_block_counts(rl, None, rows, rf.RF_LIST_TEMPORAL_POSITION_MAJOR if c == 1 else c)
             tot += vis * classes.count(c)
-        return per_pair * block * rf.RF_KEY_TILE * tot
+        return per_pair * rows * rf.RF_KEY_TILE * tot
 
     exec_arm, exec_thirds = executed(classes_host), executed(thirds_host)
     dense_flops = w.dense_flops()
@@ -342,23 +356,25 @@ def main():
                         "step = ARM (first-frame sampling, threshold 0.9) + block-sparse attention with the classes "
                         "the ARM chose" % (w.name, w.B, w.nH, w.D, w.T, w.H, w.W, w.text_len, w.N),
             "block": block,
+            "rows_per_workgroup": rows,
             "bandwidth": 0.25,
             "tex_stride": 2,
             "arm_classes": {"spatial": classes_host.count(0), "temporal": classes_host.count(1),
                             "textural": classes_host.count(2)},
         },
         "roofline": {
-            "kernel": "attn_kernel<%d,%d> (ARM-chosen classes)" % (w.D, block // 32),
+            "kernel": "%s, head_dim %d, %d query rows per workgroup%s (ARM-chosen classes)" % (
+                "attn_kernel" if queued else "attn_item_kernel", w.D, rows, "" if groups == 1 else ", %d key groups" % groups),
             "bound": "mfma",
             "achieved": round(useful_arm / ms_attn_arm_classes / 1e9, 2),
             "peak": PEAK_BF16_TFLOPS,
             "unit": "TFLOP/s",
             "frac": round(useful_arm / ms_attn_arm_classes / 1e9 / PEAK_BF16_TFLOPS, 4),
-            "traffic": PROFILED_TRAFFIC_BYTES.get((w.name, block)),
+            "traffic": PROFILED_TRAFFIC_BYTES.get((w.name, rows)),
             "traffic_source": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE run recorded in profiles/attn_kernel_hunyuan720p.md; "
                               "not observed by this run",
-            "traffic_gbps_at_this_runs_time": (round(PROFILED_TRAFFIC_BYTES[(w.name, block)] / ms_attn_arm_classes / 1e6, 1)
-                                               if (w.name, block) in PROFILED_TRAFFIC_BYTES else None),
+            "traffic_gbps_at_this_runs_time": (round(PROFILED_TRAFFIC_BYTES[(w.name, rows)] / ms_attn_arm_classes / 1e6, 1)
+                                               if (w.name, rows) in PROFILED_TRAFFIC_BYTES else None),
             "algorithmic_bytes": 8.0 * w.N * w.D * w.nH * w.B,
             "algorithmic_gbps": round(8.0 * w.N * w.D * w.nH * w.B / ms_attn_arm_classes / 1e6, 1),
         },
@@ -394,23 +410,23 @@ def main():
         ol = orc.Layout(w.T, w.H, w.W, w.text_len)
         q, k, v = (t.float().numpy() for t in inp.head_qkv(w, 0, 0))
         nthreads = orc.num_threads()
-        rows = np.array(inp.sample_rows(w, 1536 * nthreads))  # ~10-30 s of oracle time
+        sample = np.array(inp.sample_rows(w, 1536 * nthreads))  # ~10-30 s of oracle time
         cls0 = classes_host[0]
-        orc.attention_rows(q, k, v, cls0, ol, orc.Params(), rows[:nthreads])  # warm the library / threads
+        orc.attention_rows(q, k, v, cls0, ol, orc.Params(), sample[:nthreads])  # warm the library / threads
         t0 = time.perf_counter()
-        orc.attention_rows(q, k, v, cls0, ol, orc.Params(), rows)
+        orc.attention_rows(q, k, v, cls0, ol, orc.Params(), sample)
         t_rows = time.perf_counter() - t0
         t0 = time.perf_counter()
         orc.arm_classify(q, k, ol, orc.Params(), orc.SAMPLE_FIRST_FRAME, 0.9)
         t_arm = time.perf_counter() - t0
-        layer_ms = (t_rows / len(rows) * w.N + t_arm) * w.nH * w.B * 1e3
+        layer_ms = (t_rows / len(sample) * w.N + t_arm) * w.nH * w.B * 1e3
         out["cpu_baseline"] = {
             "value": round(layer_ms, 1),
             "unit": "ms",
             "cores": nthreads,
             "kind": "oracle",
             "sample": "fp64 oracle on head (0,0): %d complete query rows of class %d in %.2f s plus the full ARM of "
-                      "that head in %.2f s, scaled by N*nH*B/rows to one layer" % (len(rows), cls0, t_rows, t_arm),
+                      "that head in %.2f s, scaled by N*nH*B/rows to one layer" % (len(sample), cls0, t_rows, t_arm),
         }
     print(json.dumps(out))
 

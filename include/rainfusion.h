@@ -166,10 +166,13 @@ int rf_arm_classify_plus(const void *Q, const void *K, int B, int nH, int D, con
  * Sparse attention forward, Eq. 1-2 with the mask of each head's pattern (Eq. 3-5):
  *   O[b,h,i,:] = sum_j softmax_j(q_i . k_j / sqrt(D) over kept j) * v_j.
  * The mask is token-level; `block` (64, 128, 256 or 384) is the number of query rows per block of the lists
- * that rf_plan_host shows, and O does not depend on it.  How many rows a workgroup takes at a time (and
- * whether it splits their keys) the library chooses from the layout, B * nH, D and the workspace; (query
- * block, 64-key tile) pairs with no kept token pair are skipped at that size.  Only under
- * RF_FLAG_WIDE_ROWS is it `block`.  Scores and sums are accumulated in fp32, O is rounded to bf16.
+ * that rf_plan_host shows, and O does not depend on it.  How many rows a workgroup takes at a time, whether its
+ * wavefronts split their keys and whether workgroups take their blocks from queues the library chooses from the
+ * layout, `params`, B * nH, D and whether the workspace is full (under RF_FLAG_FIXED_ORDER from the layout, the band
+ * widths and D alone; under RF_FLAG_WIDE_ROWS the rows are `block`); (query block, 64-key tile) pairs with no kept
+ * token pair are skipped at that size.  The classes are on the device and do not enter the choice: where every head
+ * is dense, RF_FLAG_FORCE_DENSE lets the library take the kernel that is fastest for that (4-5 % at head_dim 64).
+ * Scores and sums are accumulated in fp32, O is rounded to bf16.
  * Q, K, V     : device, bf16 [B, nH, N, D].
  * head_class  : device, int32 [B*nH], values of rf_head_class; read on the device, so the
  *               output of rf_arm_classify can be passed on without a host round trip.
@@ -183,8 +186,8 @@ int rf_arm_classify_plus(const void *Q, const void *K, int B, int nH, int D, con
  *               Eq. 5), the tokens of Temporal heads in position-major order (same in-frame position of
  *               all frames adjacent), where the Temporal band is one contiguous run of keys per query
  *               block; the other kernels gather their rows in those orders instead.  The result is the
- *               same either way.  Contents
- *               undefined afterwards; calls that overlap in time need separate workspaces.
+ *               same either way.  Contents undefined afterwards; calls that overlap in time need separate
+ *               workspaces.
  */
 #define RF_ATTENTION_MIN_WORKSPACE 512
 int rf_sparse_attention(const void *Q, const void *K, const void *V, const int32_t *head_class, int B,
@@ -232,17 +235,22 @@ int rf_plan_host(const rf_layout *layout, const rf_params *params, int block, in
                  int32_t *row_ptr, int32_t *cols, size_t cap, size_t *needed);
 
 /*
- * Host-side view of how rf_sparse_attention schedules a head's query blocks under pattern `cls`
- * (scheduling only: it affects cache behaviour and load balance, never the result).
+ * Host-side view of the order in which a head's query blocks are handed out by the kernels that run from queues
+ * (256 rows and more, long sequences), under pattern `cls` (scheduling only: it affects cache behaviour and load
+ * balance, never the result).
  *   order       : host, int32 [nQB], receives a permutation of 0..nQB-1.  First the blocks that hold
  *                 text rows (the long ones: text queries see every key): they are handed out, for all
  *                 heads, before anything else.  Then the other nV blocks in a locality order (token
- *                 order for RF_DENSE), of which XCD x of the GPU owns entries
- *                 [x * ceil(nV/8), (x+1) * ceil(nV/8)), head after head.
+ *                 order for RF_DENSE).  Of these XCD x of the GPU owns entries
+ *                 [x * ceil(nV/8), (x+1) * ceil(nV/8)) of every head, head after head; where eight heads' K and V
+ *                 fit the memory-side cache (128 MB) it owns instead one of eight equal runs of all heads' entries
+ *                 laid end to end.  The other kernels, one workgroup per block, take the blocks that hold text rows
+ *                 first and then the rest in token order, and deal them out over the XCDs.
  *   first_entry : host, int32 [nQB] or NULL: per query block, the entry of its rf_plan_host list at
- *                 which its walk starts (it wraps around), chosen so that blocks in flight together
- *                 on an XCD sweep the same key tiles at the same time; 0 where the list is not one
- *                 sliding range of tiles.
+ *                 which its walk starts under RF_FLAG_FIXED_ORDER or where no walk is there to be joined (it wraps
+ *                 around), chosen so that blocks in flight together on an XCD, as many as fit it out of its eighth
+ *                 of one head, sweep the same key tiles at the same time; 0 where the list is not one
+ *                 sliding range of tiles.  Kernels with one workgroup per block start at 0.
  */
 int rf_plan_order(const rf_layout *layout, const rf_params *params, int block, int cls, int32_t *order,
                   int32_t *first_entry);

@@ -226,8 +226,9 @@ def rf_attention_workspace_bytes(B, nH, D, layout, params=None):
 def rf_sparse_attention(Q, K, V, head_class, layout, params=None, block=128, out=None, workspace=None):
     """Sparse attention forward (Eq. 1-5). head_class: int32 device tensor [B, nH] (may be None under
     RF_FLAG_FORCE_DENSE). Returns O.
-    workspace: uint8 device tensor; with rf_attention_workspace_bytes() bytes the call packs K_C, V_C and
-    position-major copies into it; None allocates the RF_ATTENTION_MIN_WORKSPACE bytes every call needs."""
+    workspace: uint8 device tensor; with rf_attention_workspace_bytes() bytes the call may take a kernel that walks
+    copies of K and V (K_C, V_C of Textural heads, position-major ones of Temporal heads) and makes them there; None
+    allocates the RF_ATTENTION_MIN_WORKSPACE bytes every call needs."""
     import torch
     _check_bf16(Q, "Q")
     _check_bf16(K, "K", Q.shape)
@@ -254,6 +255,18 @@ def rf_sparse_attention(Q, K, V, head_class, layout, params=None, block=128, out
     return out
 
 
+def attention_form(B, nH, D, layout, params=None, block=128, workspace_bytes=RF_ATTENTION_MIN_WORKSPACE):
+    """How rf_sparse_attention with these arguments runs: (query rows per workgroup, groups that split their keys, from
+    queues?, copies of K and V?).  Bookkeeping for measurements."""
+    form = (C.c_int32 * 4)()
+    f = load_library().rf_internal_attention_form
+    f.restype, f.argtypes = C.c_int, [C.c_int] * 3 + [C.POINTER(rf_layout), C.POINTER(rf_params), C.c_int, C.c_size_t, C.POINTER(C.c_int32)]
+    st = f(B, nH, D, C.byref(layout), _pp(params), block, workspace_bytes, form)
+    if st != 0:
+        raise RfError(st, "rf_internal_attention_form")
+    return form[0], form[1], bool(form[2]), bool(form[3])
+
+
 def rf_plan_host(layout, params, block, cls):
     """Host copy of one class's block list: (row_ptr int32 [nQB+1], cols int32 [nnz])."""
     lib = load_library()
@@ -273,8 +286,8 @@ def rf_plan_host(layout, params, block, cls):
 
 
 def rf_plan_order(layout, params, block, cls, full=False):
-    """Order in which a head's query blocks are handed to workgroups: int32 permutation of 0..nQB-1.
-    full=True: (order, first_entry int32 [nQB])."""
+    """Order in which a head's query blocks are handed to workgroups that take them from queues: int32 permutation of
+    0..nQB-1.  full=True: (order, first_entry int32 [nQB])."""
     N = layout.T * layout.H * layout.W + layout.text_len
     nqb = (N + block - 1) // block
     order = np.full(nqb, -1, dtype=np.int32)

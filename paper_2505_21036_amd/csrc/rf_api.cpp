@@ -326,6 +326,13 @@ size_t rf_attention_workspace_bytes(int B, int nH, int D, const rf_layout* layou
     return RF_ATTENTION_MIN_WORKSPACE + 2 * static_cast<size_t>(B) * nH * g.N * D * sizeof(uint16_t);
 }
 
+static AttnForm form_of_call(const Geometry& g, int BH, int D, const rf_params* params, int block, bool room) {
+    const int flags = params ? params->flags : 0;
+    if (flags & RF_FLAG_WIDE_ROWS) return AttnForm{block, 1, true, true};
+    if (flags & RF_FLAG_FIXED_ORDER) return choose_fixed_form(g, D);
+    return choose_form(g, BH, D, (flags & RF_FLAG_FORCE_DENSE) != 0, room);
+}
+
 static int sparse_attention_impl(const void* Q, const void* K, const void* V, const int32_t* head_class,
                                  const int32_t* head_bw, const float* bandwidths, int n_bw, int B, int nH, int D,
                                  const rf_layout* layout, const rf_params* params, int block, void* O, void* workspace,
@@ -349,11 +356,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
 
     AttnArgs a{};
     a.wide_rows = (params && (params->flags & RF_FLAG_WIDE_ROWS)) ? 1 : 0;
-    const bool fixed_order = params && (params->flags & RF_FLAG_FIXED_ORDER);
-    const AttnForm form = named         ? *named
-                          : a.wide_rows ? AttnForm{block, 1, true, true}
-                          : fixed_order ? choose_fixed_form(g, D)
-                                        : choose_form(g, B * nH, D, force_dense, room_to_pack);
+    const AttnForm form = named ? *named : form_of_call(g, B * nH, D, params, block, room_to_pack);
     if (named && named->copies && !room_to_pack && !force_dense) return RF_ERR_WORKSPACE;
     if (named && named->rows < 256 && g.N > kSmallBlockTokens) return RF_ERR_PARAM;  // no such lists
     a.queued = form.queued ? 1 : 0;
@@ -373,7 +376,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.V = static_cast<const uint16_t*>(V);
     a.O = static_cast<uint16_t*>(O);
     a.queue = static_cast<int*>(workspace);
-    a.join_sweep = fixed_order ? 0 : 1;
+    a.join_sweep = (params && (params->flags & RF_FLAG_FIXED_ORDER)) ? 0 : 1;
     a.item_order = item_order(!whole_heads_fit(g, D), form.queued, force_dense);
     a.head_class = force_dense ? nullptr : head_class;
     a.head_bw = bandwidths ? head_bw : nullptr;
@@ -419,6 +422,20 @@ int rf_internal_attention_as(int rows, int key_groups, int queued, const void* Q
     }
     return sparse_attention_impl(Q, K, V, head_class, head_bw, bandwidths, n_bw, B, nH, D, layout, params, rows, O, workspace,
                                  workspace_bytes, stream, &form);
+}
+
+int rf_internal_attention_form(int B, int nH, int D, const rf_layout* layout, const rf_params* params, int block,
+                               size_t workspace_bytes, int32_t* form) {
+    Geometry g;
+    int st = resolve_geometry(layout, params, &g);
+    if (st != RF_OK || (st = check_shape(B, nH, D)) != RF_OK) return st;
+    const bool room = workspace_bytes >= rf_attention_workspace_bytes(B, nH, D, layout, params);
+    const AttnForm f = form_of_call(g, B * nH, D, params, block, room);
+    form[0] = f.rows;
+    form[1] = f.key_groups;
+    form[2] = f.queued;
+    form[3] = f.copies && room && !(params && (params->flags & RF_FLAG_FORCE_DENSE));
+    return RF_OK;
 }
 
 int rf_plan_host(const rf_layout* layout, const rf_params* params, int block, int cls, int32_t* row_ptr,

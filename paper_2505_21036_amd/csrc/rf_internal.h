@@ -188,3 +188,8 @@ extern "C" int rf_internal_attention_as(int rows, int key_groups, int queued, co
                                         const int32_t* head_class, const int32_t* head_bw, const float* bandwidths, int n_bw,
                                         int B, int nH, int D, const rf_layout* layout, const rf_params* params, void* O,
                                         void* workspace, size_t workspace_bytes, void* stream);
+
+// The form a call of rf_sparse_attention with these arguments takes: form[0..3] = query rows per workgroup, groups that
+// split the keys, whether from queues, whether K and V are copied.  For tests and measurements.
+extern "C" int rf_internal_attention_form(int B, int nH, int D, const rf_layout* layout, const rf_params* params, int block,
+                                          size_t workspace_bytes, int32_t* form);

@@ -247,7 +247,7 @@ namespace {
 
 // What a launch takes in each form, us: the model by which the form is chosen.  The numbers are fitted to the times of
 // every form at 107 sizes (256 to 119056 tokens, 1 to 160 heads), dense and with the three patterns in turn at
-// bandwidth 1/4 and stride 2, and at 58 of them at bandwidths 1/8 to 1/2 and strides 1 to 4 (profiles/forms_sweep.tsv).
+// bandwidth 1/4 and stride 2, and at 58 of them at bandwidths 1/8 to 1/2 and strides 1 to 4 (profiles/forms_sweep.txt).
 // The form it picks is then, on the geometric mean, 0.3 % from the best where all heads are dense (1.3 % at head_dim
 // 64) and 1.1 to 2.1 % with the patterns; the worst are 20 to 35 %, mostly a few heads of short layouts with text.  Few
 // rows: keys split four ways, then two ways (16 heads of 960 tokens, head_dim 128: 24 us, 28 and with 128 rows 40; 24

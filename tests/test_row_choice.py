@@ -69,9 +69,9 @@ def test_the_sizes_of_the_gpu_test_pick_the_kernels_it_names(tmp_path):
 
 @needs_gxx
 def test_the_rule_is_near_the_best_form_over_the_measured_sizes(tmp_path):
-    """Replays the times of every form (profiles/forms_sweep.tsv) through the rule: what its choice costs over the best
+    """Replays the times of every form (profiles/forms_sweep.txt) through the rule: what its choice costs over the best
     form there is, with room for copies and without.  The bounds are what the fit reached, rounded up."""
-    with open(os.path.join(ROOT, "profiles", "forms_sweep.tsv")) as f:
+    with open(os.path.join(ROOT, "profiles", "forms_sweep.txt")) as f:
         lines = [l.rstrip("\n").split("\t") for l in f if not l.startswith("#")]
     names, rows = lines[0][9:], lines[1:]
     lost = {}
