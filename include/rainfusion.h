@@ -242,10 +242,11 @@ int rf_plan_host(const rf_layout *layout, const rf_params *params, int block, in
  *                 text rows (the long ones: text queries see every key): they are handed out, for all
  *                 heads, before anything else.  Then the other nV blocks in a locality order (token
  *                 order for RF_DENSE).  Of these XCD x of the GPU owns entries
- *                 [x * ceil(nV/8), (x+1) * ceil(nV/8)) of every head, head after head; where eight heads' K and V
- *                 fit the memory-side cache (128 MB) it owns instead one of eight equal runs of all heads' entries
- *                 laid end to end.  The other kernels, one workgroup per block, take the blocks that hold text rows
- *                 first and then the rest in token order, and deal them out over the XCDs.
+ *                 [x * ceil(nV/8), (x+1) * ceil(nV/8)) of every head, head after head; with 16 heads or more whose K and
+ *                 V, of eight heads, fit the memory-side cache (128 MB), or all dense ones, it owns instead one of eight
+ *                 equal runs of all heads' entries laid end to end.  The other kernels, one workgroup per block,
+ *                 take the blocks that hold text rows first and then the rest in token order, and deal them out
+ *                 over the XCDs.
  *   first_entry : host, int32 [nQB] or NULL: per query block, the entry of its rf_plan_host list at
  *                 which its walk starts under RF_FLAG_FIXED_ORDER or where no walk is there to be joined (it wraps
  *                 around), chosen so that blocks in flight together on an XCD, as many as fit it out of its eighth

@@ -377,10 +377,10 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     a.O = static_cast<uint16_t*>(O);
     a.queue = static_cast<int*>(workspace);
     a.join_sweep = (params && (params->flags & RF_FLAG_FIXED_ORDER)) ? 0 : 1;
-    a.item_order = item_order(!whole_heads_fit(g, D), form.queued, force_dense);
+    a.BH = B * nH;
+    a.item_order = item_order(!whole_heads_fit(g, D), form.queued, force_dense, a.BH, static_cast<long long>(a.plan[0].nQB) * a.BH);
     a.head_class = force_dense ? nullptr : head_class;
     a.head_bw = bandwidths ? head_bw : nullptr;
-    a.BH = B * nH;
     a.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
     if (room_to_pack && !force_dense && form.copies) {
         a.packed_k = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) + RF_ATTENTION_MIN_WORKSPACE);

@@ -586,9 +586,10 @@ constexpr int attn_waves_per_simd(int NW, int LOOP) {
 template <int D, int NW, int LOOP>
 using SmemOf = std::conditional_t<LOOP == LOOP_64_PIPELINED, WideSmem<D, NW>, AttnSmem<D, NW>>;
 
-__host__ __device__ __forceinline__ Queues queues_of(const AttnArgs& a) {
+template <bool MAY_DEAL>
+__host__ __device__ __forceinline__ Queues<MAY_DEAL> queues_of(const AttnArgs& a) {
     const DevicePlan& p = a.plan[0];
-    return Queues(a.BH, p.first_text_qb, p.nQB - p.first_text_qb, a.item_order);
+    return Queues<MAY_DEAL>(a.BH, p.first_text_qb, p.nQB - p.first_text_qb, a.item_order);
 }
 
 // The next item for a workgroup whose home queue is `home`, or -1 when every queue is empty.
@@ -596,7 +597,7 @@ __host__ __device__ __forceinline__ Queues queues_of(const AttnArgs& a) {
 // first (its neighbours on the XCD are on the same part of the same head, which is what the L2
 // wants) and then helps whichever queue has the most left.  Every path ends: counters only grow, a
 // failed take means another workgroup took that item, and once all are taken -1 is returned.
-__device__ __forceinline__ int take_item(int* ctr, int home, const Queues& qs, int* queue) {
+__device__ __forceinline__ int take_item(int* ctr, int home, const Queues<false>& qs, int* queue) {
     auto taken = [&](int x) { return __hip_atomic_load(ctr + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     int q = home;
     for (;;) {
@@ -621,7 +622,7 @@ __device__ __forceinline__ int take_item(int* ctr, int home, const Queues& qs, i
 }
 
 template <int D, int NW, int LOOP, int KS = 1, int AHEAD = RF_TILES_AHEAD>
-__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues& qs, unsigned char* smem);
+__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem);
 
 // Eight queue counters, then the sweep words (-1: nothing published yet).  One workgroup, one thread per word.
 constexpr int kResetThreads = 128;
@@ -642,7 +643,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
     // K/V of the head in flight (tens of MB) stays resident in the memory-side cache for whatever
     // misses L2.  XCDs differ in speed by several per cent and shares in work; an XCD whose queue is
     // empty takes items from the others.
-    const Queues qs = queues_of(a);
+    const Queues<false> qs = queues_of<false>(a);
     for (;;) {
         if (threadIdx.x == 0) {
             int q = 0;
@@ -677,7 +678,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
 template <int D, int NW, int KS, int AHEAD, int WAVES>
 __global__ void __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) attn_item_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];  // the kernel's only LDS: starts at address 0
-    const Queues qs = queues_of(a);
+    const Queues<true> qs = queues_of<true>(a);
     const int xcd = blockIdx.x & 7, item = blockIdx.x >> 3;
     if (item >= qs.items(xcd)) return;
     process_item<D, NW, LOOP_ITEM, KS, AHEAD>(a, item, xcd, -1, qs, smem);
@@ -686,7 +687,7 @@ __global__ void __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_
 // One (head, query block) item: item-th of queue xcd.  seen: the sweep word of this workgroup's XCD
 // (it serves its own L2, whichever queue the item came from), or -1.
 template <int D, int NW, int LOOP, int KS, int AHEAD>
-__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues& qs, unsigned char* smem) {
+__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem) {
     auto run = [&](auto mode, const DevicePlan& plan, const QueryBlock& block) {
         constexpr int MODE = decltype(mode)::value;
         if constexpr (LOOP == LOOP_64_PIPELINED) attend_wide<D, NW, MODE>(a, plan, block, smem);
@@ -881,9 +882,7 @@ static int launch_items(const AttnArgs& a, hipStream_t st) {
             ready_on[dev] = true;
         }
     }
-    const Queues qs = queues_of(a);
-    int most = 0;
-    for (int x = 0; x < 8; ++x) most = std::max(most, qs.items(x));
+    const int most = queues_of<true>(a).items(0);
     AttnArgs s = a;
     s.join_sweep = 0;  // its words are not there: nothing resets them
     hipLaunchKernelGGL((attn_item_kernel<D, NW, KS, AHEAD, WAVES>), dim3(8 * most), dim3(NT), smem, st, s);

@@ -321,8 +321,18 @@ bool find_form(int D, int rows, int key_groups, bool queued, AttnForm* form) {
 
 namespace {
 
+// Tiles of 64 keys of the compacted sequence that Textural heads walk.
+double textural_tiles(const Geometry& g) {
+    // rows y and columns x with (y - x) mod tau == 0, by residue
+    const int64_t tau = g.tau;
+    int64_t kept = 0;
+    for (int64_t c = 0; c < std::min<int64_t>(tau, std::min(g.W, g.H)); ++c)
+        kept += (g.W - c + tau - 1) / tau * ((g.H - c + tau - 1) / tau);
+    return (static_cast<double>(kept) * g.T + g.text_len) / kTileK;
+}
+
 // Tiles of 64 keys that a block of `rows` rows visits on the average over the three patterns.
-double mean_tiles(const Geometry& g, int rows) {
+double mean_tiles(const Geometry& g, int rows, double textural) {
     const double tiles = (g.N + kTileK - 1) / kTileK;
     // a band of radius r over n groups of `group` rows: its share of the pairs, and what blocks and tiles that are not
     // aligned with the groups take in beside it
@@ -332,17 +342,11 @@ double mean_tiles(const Geometry& g, int rows) {
         const double beside = rows - std::gcd(rows, group) + kTileK - std::gcd(kTileK, group);
         return std::min(tiles, (share * g.Nv + beside + g.text_len) / kTileK);
     };
-    // rows y and columns x with (y - x) mod tau == 0, by residue
-    const int64_t tau = g.tau;
-    int64_t kept = 0;
-    for (int64_t c = 0; c < std::min<int64_t>(tau, std::min(g.W, g.H)); ++c)
-        kept += (g.W - c + tau - 1) / tau * ((g.H - c + tau - 1) / tau);
-    const double textural = (static_cast<double>(kept) * g.T + g.text_len) / kTileK;
     return (band(g.T, g.r_spatial, g.HW) + band(g.HW, g.r_temporal, g.T) + textural) / 3;
 }
 
-// Time of a launch in form k, us; HUGE_VAL if the form is not to be taken at this size.
-double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense) {
+// Time of a launch in form k, us; HUGE_VAL if the form is not to be taken at this size.  textural: textural_tiles(g).
+double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense, double textural) {
     constexpr int kCUs = 256;  // MI355X
     const Chip& chip = kChips[index_of(D)];
     const int rows = k.form.rows;
@@ -353,14 +357,12 @@ double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense) 
     const double tiles = (g.N + kTileK - 1) / kTileK, slots = static_cast<double>(kCUs) * k.per_cu;
     const double items = static_cast<double>(nQB) * BH, longs = dense ? 0 : static_cast<double>(nTB) * BH;
     const double tile_us = k.tile_us * (dense ? k.dense : 1) * (!far || k.form.queued ? 1 : dense ? chip.far_dense : chip.far);
-    const double item = (dense ? tiles : mean_tiles(g, rows)) * tile_us + k.item_us;
+    const double item = (dense ? tiles : mean_tiles(g, rows, textural)) * tile_us + k.item_us;
     const double text_item = tiles * tile_us * k.text + k.item_us;
     double rounds = items / slots;
     if (!k.form.queued) {  // what the fullest XCD has to do; beyond some thousand heads all are equally full
         const int heads = std::min(BH, 4096);
-        const Queues qs(heads, nVB, nTB, item_order(far, false, dense));
-        int most = 0;
-        for (int x = 0; x < 8; ++x) most = std::max(most, qs.items(x));
+        const int most = Queues<true>(heads, nVB, nTB, item_order(far, false, dense, BH, static_cast<long long>(nQB) * BH)).items(0);
         rounds = 8.0 * most * (static_cast<double>(BH) / heads) / slots;
     }
     rounds *= 1 + longs / items * (text_item / item - 1);
@@ -403,21 +405,23 @@ AttnForm cheapest(int D, bool copies, F cost) {
 // may say so through the classes), so a tenth of the weight goes to the dense walk.  It decides between forms that are
 // nearly even for the patterns; head_dim 64 has the widest gap, 48 heads of 17776 tokens: 128 rows 2221 us with the
 // patterns in turn and 4252 dense, 256 from queues 2316 and 3994, 384 2318 and 4085.
-static double mixed_log_us(const Kernel& k, const Geometry& g, int BH, int D) {
-    constexpr double kDenseShare = 0.1;
-    return (1 - kDenseShare) * std::log(launch_us(k, g, BH, D, false)) + kDenseShare * std::log(launch_us(k, g, BH, D, true));
+static double mixed_cost(const Kernel& k, const Geometry& g, int BH, int D, double textural) {
+    const double sparse = launch_us(k, g, BH, D, false, textural), cube = sparse * sparse * sparse;
+    return cube * cube * cube * launch_us(k, g, BH, D, true, textural);  // tenth power of the weighted geometric mean
 }
 
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
+    const double textural = textural_tiles(g);
     // without room a form with copies would walk Temporal heads in token order: up to twice the time
-    return cheapest(D, room || dense, [&](const Kernel& k) { return dense ? launch_us(k, g, BH, D, true) : mixed_log_us(k, g, BH, D); });
+    return cheapest(D, room || dense, [&](const Kernel& k) { return dense ? launch_us(k, g, BH, D, true, textural) : mixed_cost(k, g, BH, D, textural); });
 }
 
 AttnForm choose_fixed_form(const Geometry& g, int D) {
+    const double textural = textural_tiles(g);
     return cheapest(D, false, [&](const Kernel& k) {
-        double log_us = 0;
-        for (int heads : {6, 12, 24, 48}) log_us += mixed_log_us(k, g, heads, D);
-        return log_us;
+        double product = 1;  // of numbers below 1e10 ^ 10 each at any size that runs
+        for (int heads : {6, 12, 24, 48}) product *= std::pow(mixed_cost(k, g, heads, D, textural), 0.1);
+        return product;
     });
 }
 

@@ -7,7 +7,7 @@
 int main() {
     int heads, video, text, order;
     while (std::scanf("%d %d %d %d", &heads, &video, &text, &order) == 4) {
-        const rf::Queues qs(heads, video, text, order);
+        const rf::Queues<true> qs(heads, video, text, order);
         for (int x = 0; x < 8; ++x) {
             for (int i = 0; i < qs.items(x); ++i) {
                 int bh = -1, ordinal = -1;

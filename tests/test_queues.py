@@ -31,8 +31,9 @@ def test_every_item_once_and_text_blocks_first(tmp_path):
         for q in qs:  # ordinals below `text` are the blocks that hold text rows
             longs = [o < text for _, o in q]
             assert longs == sorted(longs, reverse=True)
+        counts = [len(q) for q in qs]
+        assert max(counts) == counts[0]  # what the launcher sizes the grid by
         if order == DEALT:
-            counts = [len(q) for q in qs]
             assert max(counts) - min(counts) <= 4 + 1, (bh, video, text, counts)  # a run of blocks, a text block
 
 
@@ -51,3 +52,5 @@ def test_no_xcd_waits_long_for_another_whatever_the_classes(tmp_path):
             mean = sum(load) / 8
             # whole heads: at most one heavier head than the mean, of three or more (four eighths in a row: 24 heads)
             assert max(load) <= (1.34 if bh >= 24 else 1.15) * mean, (bh, video, name, load)
+            if bh in (24, 48) and name == "classes in turn":
+                assert max(load) == min(load), (bh, video, load)
