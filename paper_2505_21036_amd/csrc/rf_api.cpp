@@ -8,6 +8,7 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "rf_internal.h"
@@ -149,7 +150,11 @@ int get_attention_plan(const Geometry& geometry, int block, bool wide, DevicePla
         p->g = g;
         p->wide = wide;
         p->device = device;
-        const int st = build_and_upload(g, wide, p.get());
+        int st = RF_ERR_HIP;
+        try {
+            st = build_and_upload(g, wide, p.get());
+        } catch (const std::bad_alloc&) {  // host memory for the lists, before any device memory is taken
+        }
         if (st != RF_OK) return st;
         cp = p.get();
         g_plans.push_back(std::move(p));

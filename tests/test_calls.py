@@ -3,6 +3,7 @@ alone (calls_driver.cpp counts the allocations and records the launches).  Contr
 warm-up call for a (layout, params) no call allocates, whatever its heads, head_dim, block, workspace and dense flag;
 RF_FLAG_FIXED_ORDER gives a head the same bits in any call of the layout."""
 import os
+import resource
 import shutil
 import subprocess
 
@@ -22,10 +23,11 @@ def driver(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-Wno-unused-result", "-I", HIP, "-I", os.path.join(ROOT, "include"), "-I", csrc,
                            os.path.join(ROOT, "tests", "calls_driver.cpp"), os.path.join(csrc, "rf_api.cpp"), os.path.join(csrc, "rf_plan.cpp"), "-o", exe])
 
-    def run(calls):
-        """calls: (layout 4-tuple, bandwidth, stride, flags, block, B, nH, D, full workspace) -> rows of the driver's output"""
+    def run(calls, memory=None):
+        """memory: limit on the process's address space, bytes; calls: (layout 4-tuple, bandwidth, stride, flags, block, B, nH, D, full workspace) -> rows of the driver's output"""
         text = "\n".join(" ".join(str(v) for v in c[0] + tuple(int(x) if isinstance(x, bool) else x for x in c[1:])) for c in calls)
-        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+        limit = (lambda: resource.setrlimit(resource.RLIMIT_AS, (memory, memory))) if memory else None
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, preexec_fn=limit).stdout.splitlines()
         return [tuple(v if i == 7 else int(v) for i, v in enumerate(l.split())) for l in out]
     return run
 
@@ -46,6 +48,13 @@ def test_one_warm_up_call_covers_every_later_call_of_the_layout(driver, layout):
     out = driver([warm] + calls)
     assert all(r[0] == 0 and r[1] == 1 for r in out), sorted({r[:2] for r in out})
     assert len({r[2] for r in out}) > 1 or layout == LAYOUTS[-1]  # the calls do differ in their row counts
+
+
+@needs_gxx
+def test_lists_that_do_not_fit_in_host_memory_are_an_error_and_leave_the_library_usable(driver):
+    long, short = (33, 200, 300, 0), LAYOUTS[1]
+    out = driver([(long, 0.25, 2, 0, 128, 1, 1, 64, False), (short, 0.25, 2, 0, 128, 1, 1, 64, False)], memory=256 << 20)
+    assert out[0][:2] == (-7, 0) and out[1][:2] == (0, 1), out  # RF_ERR_HIP, then as ever
 
 
 @needs_gxx
