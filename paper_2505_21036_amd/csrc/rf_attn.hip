@@ -1,10 +1,10 @@
 // Block-sparse attention forward for RainFusion's head patterns (Eq. 1-5; Fig. 2a), gfx950.
 //
 // Work item = one query block (64, 128, 256 or 384 rows) of one head; one workgroup per item in launches of a few
-// rounds, otherwise a resident set of workgroups that takes items from per-XCD queues.  For its item a workgroup reads the head's class on the device,
-// walks that class's list of 64-key tiles (skipped tiles cost no traffic), loads K and V tiles
-// global -> LDS one tile ahead without staging registers, forms the transposed score tile with
-// bf16 MFMA, runs the online softmax in fp32 with exp2, and accumulates O^T = V^T P^T with bf16
+// rounds, otherwise a resident set of workgroups that takes items from per-XCD queues (rf_queues.h says which XCD takes
+// which).  For its item a workgroup reads the head's class on the device, walks that class's list of 64-key tiles
+// (skipped tiles cost no traffic), loads K and V tiles global -> LDS one tile ahead without staging registers, forms
+// the transposed score tile with bf16 MFMA, runs the online softmax in fp32 with exp2, and accumulates O^T = V^T P^T with bf16
 // MFMA.  In tiles flagged partial the token-level predicate of the pattern is re-applied to each
 // score.
 #include <algorithm>
