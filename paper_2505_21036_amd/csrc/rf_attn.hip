@@ -671,8 +671,10 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
 // The kernel for launches of few rounds: one workgroup per item and no queue (workgroup ids go to the XCDs
 // round-robin, so workgroup i is item i / 8 of queue i mod 8).  Without the queue there is no kernel to reset it,
 // no atomic round trip and no second barrier before an item's first load, and workgroups of any size share a CU:
-// 48 heads of 2000 tokens at head_dim 128, 128 rows: 109 -> 75 us; 256 rows: 88 -> 81 us; from about 16000 tokens on
-// the queue's balance between XCDs and its joined walks win (256 rows, 48 heads of 17776: 3.71 against 3.77 ms).
+// 48 heads of 2000 tokens at head_dim 128, 128 rows: 109 -> 75 us; 256 rows: 88 -> 81 us.  With the patterns the
+// queue's balance between XCDs and its joined walks win from about 17000 tokens on (256 rows, 48 heads of 17776: 3.65
+// against 3.72 ms; 24 of 48000: 12.7 against 14.3); dense walks stay even or better from the grid (32 of 16384: 3.73
+// against 3.84 ms; 24 of 119056: 147 against 149).
 // KS groups of NW wavefronts split the walk of 32 * NW rows.  AHEAD = 0 keeps one buffer for K and one for V, so
 // that twice the workgroups fit a CU's LDS.
 template <int D, int NW, int KS, int AHEAD, int WAVES>

@@ -48,6 +48,7 @@ KERNELS = [
     ((64, 2, 3, RAGGED, False, True), (64, 4, 0)), ((96, 2, 3, RAGGED, False, False), (64, 4, 0)), ((128, 2, 3, RAGGED, False, True), (64, 4, 0)),
     ((64, 2, 24, RAGGED, False, False), (64, 2, 0)), ((96, 2, 24, RAGGED, False, True), (64, 2, 0)), ((128, 2, 20, RAGGED, False, False), (64, 2, 0)),
     ((64, 2, 60, RAGGED, False, False), (128, 1, 0)), ((96, 2, 60, RAGGED, False, True), (128, 1, 0)), ((128, 2, 48, RAGGED, False, False), (128, 1, 0)),
+    ((64, 3, 9, (9, 16, 28, 77), False, True), (64, 2, 0)), ((96, 1, 25, (10, 25, 44, 256), False, True), (128, 1, 0)),  # heads dealt, some left over
     ((64, 1, 30, MID, True, True), (256, 1, 1)), ((64, 1, 6, LONG, False, True), (256, 1, 1)),
     ((96, 1, 10, MID, True, True), (256, 1, 0)), ((96, 1, 96, SHORT, False, False), (256, 1, 0)), ((128, 1, 10, MID, True, False), (256, 1, 0)), ((128, 1, 96, SHORT, False, False), (256, 1, 0)),
     ((96, 1, 19, SQUARE, False, False), (256, 1, 1)), ((128, 1, 8, (5, 64, 65, 37), False, False), (256, 1, 1)),
@@ -110,7 +111,10 @@ def test_every_kernel_of_the_rule_against_the_oracle(case, form, text_first):
     O = rf.rf_sparse_attention(Q, K, V, hc, rl, rp, 128, workspace=ws)
     fixed = rf.rf_params(0.25, 0.25, 2, 0, flags | rf.RF_FLAG_FIXED_ORDER)
     again = [rf.rf_sparse_attention(Q, K, V, hc, rl, fixed, b, workspace=ws) for b in (64, 384)]
+    # every row of every head is written: values of one come back as one
+    ones = rf.rf_sparse_attention(Q, K, torch.ones_like(V), hc, rl, rp, 128, out=torch.full_like(Q, float("nan")), workspace=ws)
     torch.cuda.synchronize()
+    assert (ones.float() - 1).abs().max().item() <= 1e-2  # bf16
     assert torch.equal(*again)  # bitwise, and whatever the block
     for i in list(range(min(4, B * nH))) + list(range(max(4, B * nH - 4), B * nH)):
         q, k, v = (np.roll(t.float().numpy(), shift, axis=0) for t in inp.head_qkv(w, i // nH, i % nH, scale))
