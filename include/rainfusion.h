@@ -73,9 +73,10 @@ typedef struct {
 /* rf_sparse_attention visits each query block's key tiles in an order fixed by the layout, the band widths and D
  * alone, which makes a head's O bitwise identical from call to call, whatever B, nH, `block`, the workspace and
  * RF_FLAG_FORCE_DENSE (against head_class = RF_DENSE) are.  (Under RF_FLAG_WIDE_ROWS a Temporal head's also depends on
- * whether the workspace has room for copies.)  The kernel is then one that suits the layout with 6 to 48 heads and
- * needs no workspace: mostly within 10 % of the one the call would otherwise get, 20 % at 24 short heads, twice the
- * time for a single head of a long layout.  Without the flag a query block starts its (cyclic) walk
+ * whether the workspace has room for copies.)  The kernel is then one that suits the layout with 12 to 48 heads and
+ * needs no workspace: the one the call would get anyway or close to it from 12 heads on, 7 % slower for the longest
+ * layouts (against copies in a full workspace), 20-30 % for a few heads of a short layout, twice the time for a single
+ * head of a long one.  Without the flag a query block starts its (cyclic) walk
  * over its tiles wherever the workgroups already running on the same part of the GPU are, so that they
  * share K/V tiles through the L2 cache: every tile is still visited exactly once, but the fp32 sums are
  * formed in an order that depends on timing, so the last bit of O can differ between calls (faster,

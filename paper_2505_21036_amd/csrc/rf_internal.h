@@ -94,7 +94,7 @@ constexpr int kSmallBlockTokens = 1 << 17;
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room);
 // The same from the layout and head_dim alone, for RF_FLAG_FIXED_ORDER: a form decides the order in which a row's tiles
 // are summed up, so a head's bits are the same in any batch, on any share of the heads and with any workspace only if
-// none of these decides the form.  Without copies, and best on the (geometric) mean of 6, 12, 24 and 48 heads.
+// none of these decides the form.  Without copies, and best on the (geometric) mean of 12, 24 and 48 heads.
 AttnForm choose_fixed_form(const Geometry& g, int D);
 // The form with these numbers, if head_dim D has one.
 bool find_form(int D, int rows, int key_groups, bool queued, AttnForm* form);

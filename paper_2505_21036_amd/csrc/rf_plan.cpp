@@ -420,7 +420,7 @@ AttnForm choose_fixed_form(const Geometry& g, int D) {
     const double textural = textural_tiles(g);
     return cheapest(D, false, [&](const Kernel& k) {
         double product = 1;  // of numbers below 1e10 ^ 10 each at any size that runs
-        for (int heads : {6, 12, 24, 48}) product *= std::pow(mixed_cost(k, g, heads, D, textural), 0.1);
+        for (int heads : {12, 24, 48}) product *= std::pow(mixed_cost(k, g, heads, D, textural), 0.1);
         return product;
     });
 }
