@@ -70,7 +70,7 @@ typedef struct {
  * NULL): the "first 10 % of the timesteps dense" policy of Sec. 4.1 without touching the class
  * buffer.  Ignored by the ARM. */
 #define RF_FLAG_FORCE_DENSE 4
-/* rf_sparse_attention visits each query block's key tiles in an order fixed by the layout, the band widths and D
+/* rf_sparse_attention visits each query block's key tiles in an order fixed by the layout, the masks (`params`) and D
  * alone, which makes a head's O bitwise identical from call to call, whatever B, nH, `block`, the workspace and
  * RF_FLAG_FORCE_DENSE (against head_class = RF_DENSE) are.  (Under RF_FLAG_WIDE_ROWS a Temporal head's also depends on
  * whether the workspace has room for copies.)  The kernel is then one that suits the layout with 12 to 48 heads and
@@ -169,8 +169,8 @@ int rf_arm_classify_plus(const void *Q, const void *K, int B, int nH, int D, con
  * The mask is token-level; `block` (64, 128, 256 or 384) is the number of query rows per block of the lists
  * that rf_plan_host shows, and O does not depend on it.  How many rows a workgroup takes at a time, whether its
  * wavefronts split their keys and whether workgroups take their blocks from queues the library chooses from the
- * layout, `params`, B * nH, D and whether the workspace is full (under RF_FLAG_FIXED_ORDER from the layout, the band
- * widths and D alone; under RF_FLAG_WIDE_ROWS the rows are `block`); (query block, 64-key tile) pairs with no kept
+ * layout, `params`, B * nH, D and whether the workspace is full (under RF_FLAG_FIXED_ORDER from the layout, the
+ * masks and D alone; under RF_FLAG_WIDE_ROWS the rows are `block`); (query block, 64-key tile) pairs with no kept
  * token pair are skipped at that size.  The classes are on the device and do not enter the choice: where every head
  * is dense, RF_FLAG_FORCE_DENSE lets the library take the kernel that is fastest for that (4-5 % at head_dim 64).
  * Scores and sums are accumulated in fp32, O is rounded to bf16.
