@@ -8,6 +8,7 @@
 // MFMA.  In tiles flagged partial the token-level predicate of the pattern is re-applied to each
 // score.
 #include <algorithm>
+#include <cfloat>
 #include <mutex>
 #include <type_traits>
 
@@ -15,6 +16,23 @@
 #include "rf_queues.h"
 
 namespace rf {
+
+// Which part of its tile a wavefront works at raised priority.  The wavefronts of a SIMD leave the barrier together; at
+// one priority they form their scores together and then want the vector unit together, while the matrix pipe idles.
+// One that forms scores going before one in its softmax (and one in P V too) staggers them.
+enum : int { RAISE_NONE = 0, RAISE_SCORES = 1, RAISE_PRODUCTS = 2, RAISE_SOFTMAX = 3 };
+// Measured, mixed classes, us, none / scores / both products: head_dim 64 from queues, 256 rows, 48 heads of 17776
+// 2232 / 2224 / 2135, 384 rows 2258 / 2272 / 2293; keys split two ways, 32 heads of 16384 at head_dim 128 2543 / 2481 /
+// 2468, four ways, 6 heads of 960 21.4 / 20.8 / 20.9; 384 rows, the former 1989 / 1957 / 1963, 24 heads of 17776 at
+// head_dim 96 1525 / 1493 / 1496; 256 rows from the grid, 24 of 4109 at 96 168 / 163 / -, from queues 32 of 16384 at 128
+// 2000 / 2010 / 2015; 128 rows at head_dim 96, 24 of 4109 160 / 163 / 162, at 128 2149 / 2113 / 2127 (32 of 16384).
+constexpr int raise_of(int D, int NW, int KS, bool queued) {
+    if (KS > 1) return RAISE_PRODUCTS;
+    if (D == 64) return NW == 12 ? RAISE_NONE : RAISE_PRODUCTS;
+    if (NW == 4) return D == 96 ? RAISE_NONE : RAISE_SCORES;
+    if (NW == 8 && queued) return D == 128 ? RAISE_SOFTMAX : RAISE_NONE;
+    return RAISE_SCORES;
+}
 
 // How a query block finds its key tiles.
 enum : int {
@@ -103,7 +121,7 @@ namespace rf {
 // QH: 32-query halves a wavefront owns (1, or 2: every K and V slab read from LDS then feeds two MFMAs).
 // KS: groups of NW wavefronts that split the walk (group g takes its tiles g, g + KS, ... into LDS of its own
 // and keeps a softmax of its own); the groups' results are added up at the end.
-template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD>
+template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD, int RAISE = RAISE_NONE>
 __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, const QueryBlock& qk, unsigned char* smem_all) {
     constexpr int BQ = 32 * NW * QH;
     using ST = DirectTile<D, NW>;
@@ -117,7 +135,11 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     // registers each, which the loops fit without spills at depth two
     constexpr int AK = (QH == 2 || (NW == 12 && D == 128)) ? 2 : kAheadK, AV = (QH == 2 || (NW == 12 && D == 128)) ? 2 : kAheadV;
     const int tid = threadIdx.x - group * (64 * NW), lane = tid & 63, wave = tid >> 6, hf = lane >> 5, m = lane & 31;
-    const int N = pl.N, Nv = pl.Nv, keyN = qk.keyN;
+    const int N = pl.N, keyN = qk.keyN;
+    // opaque, or the loop may load it anew from the arguments, and a scalar load in flight turns its LDS waits into
+    // waits for every read
+    int Nv = pl.Nv;
+    asm volatile("" : "+s"(Nv));
     const int ntiles = KS == 1 ? qk.ntiles : (qk.ntiles - group + KS - 1) / KS;  // of this group
     const int nsteps = (qk.ntiles + KS - 1) / KS;                                // of the longest group
     // per-key side data staged through LDS two tiles ahead: the token index of each key of the
@@ -164,15 +186,15 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     for (int h = 0; h < QH; ++h)
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) oacc[h][db] = f32x16{0};
-    // m_ref: reference subtracted inside exp2 (raw score units), finite from the start; has_ref: it has
-    // been taken from real scores of this row; l_run: this lane's share of the softmax denominator
+    // m_ref: reference subtracted inside exp2, in the units of its argument (score times c); kNoReference until it has
+    // been taken from real scores of this row.  c is below 1, so any finite score outgrows that, and what was
+    // accumulated relative to it (nothing) is scaled by exp2 of it: 0.  l_run: this lane's share of the softmax denominator
+    constexpr float kNoReference = -FLT_MAX;
     float m_ref[QH], l_run[QH];
-    bool has_ref[QH];
 #pragma unroll
     for (int h = 0; h < QH; ++h) {
-        m_ref[h] = 0.f;
+        m_ref[h] = kNoReference;
         l_run[h] = 0.f;
-        has_ref[h] = false;
     }
     const float c = a.scale_log2;
 
@@ -415,13 +437,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
         const bool mine = (KS == 1 && !is_band(MODE)) || kind != 2;
         f32x16 s[QH][2];
         if (mine) {
+        if (RAISE == RAISE_SCORES || RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
         scores(t, e_cur, is_band(MODE) ? kind == 1 : (e_cur & RF_PLAN_PARTIAL) != 0, s);
-        // With eight wavefronts at head_dim 128 the softmax section (VALU only) runs at raised
-        // priority and the two MFMA sections at the default: the wavefront that shares the SIMD is
-        // then served in the gaps of this one's VALU work rather than the other way round (measured
-        // +1 % there; neutral at head_dim 96 and 1-4 % slower with four wavefronts, so not there).
-        constexpr bool kSoftmaxPriority = D == 128 && NW == 8;
-        if (kSoftmaxPriority) __builtin_amdgcn_s_setprio(1);
+        if (RAISE != RAISE_NONE) __builtin_amdgcn_s_setprio(RAISE == RAISE_SOFTMAX ? 1 : 0);
 #pragma unroll
         for (int h = 0; h < QH; ++h) {
             float mt = s[h][0][0];
@@ -431,27 +449,23 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                 for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[h][kb2][r]);
             // the two halves of the wavefront hold different keys of the same 32 queries: their maxima
             // are exchanged only when some lane asks for the reference to move
-            const bool grow = has_ref[h] ? (mt - m_ref[h]) * c > kRescaleSlack : mt > -INFINITY;
-            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+            if (__builtin_amdgcn_ballot_w64(fmaf(mt, c, -m_ref[h]) > kRescaleSlack) != 0) {
                 mt = fmaxf(mt, other_half(mt));
                 if (mt > -INFINITY) {
-                    const float m_new = has_ref[h] ? fmaxf(m_ref[h], mt) : mt;
-                    const float alpha = has_ref[h] ? fast_exp2((m_ref[h] - m_new) * c) : 0.f;  // nothing accumulated before
+                    const float m_new = fmaxf(m_ref[h], mt * c), alpha = fast_exp2(m_ref[h] - m_new);
                     l_run[h] *= alpha;
 #pragma unroll
                     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) oacc[h][db][r] *= alpha;
                     m_ref[h] = m_new;
-                    has_ref[h] = true;
                 }
             }
-            // p = exp2((s - m_ref) * c) in place
-            const float mc = m_ref[h] * c;
+            // p = exp2(s * c - m_ref) in place
 #pragma unroll
             for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[h][kb2][r] = fast_exp2(fmaf(s[h][kb2][r], c, -mc));
+                for (int r = 0; r < 16; ++r) s[h][kb2][r] = fast_exp2(fmaf(s[h][kb2][r], c, -m_ref[h]));
             // P is rounded to bf16 for the second MFMA; the denominator sums those same rounded values
             // (two per v_dot2c_f32_bf16), so numerator and denominator of Eq. 2 see identical weights
 #pragma unroll
@@ -467,7 +481,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                     pf[h][2 * kb2 + u2] = as_bf16x8(w);
                 }
         }
-        if (kSoftmaxPriority) __builtin_amdgcn_s_setprio(0);
+        if (RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
+        else if (RAISE == RAISE_SOFTMAX) __builtin_amdgcn_s_setprio(0);
+        else if (NW == 8) __builtin_amdgcn_sched_barrier(0);  // the operand reads of P V stay behind the softmax
         if constexpr (AHEAD > 0) accumulate(t);
         }
         if constexpr (AHEAD == 0) {
@@ -499,7 +515,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
         auto part = [&](int g, int chunk) {
             return (lds_f32x4*)(uintptr_t)(ST::lds_offset(smem_all) + g * SM::GROUP_BYTES + wave * (D * 128) + (chunk * 32 + m) * 16);
         };
-        const float l_own = l_run[0] + other_half(l_run[0]), m_own = has_ref[0] ? m_ref[0] : -INFINITY;
+        const float l_own = l_run[0] + other_half(l_run[0]), m_own = m_ref[0];
         if (hf == 0) {
             *stat(group, 0) = m_own;
             *stat(group, 1) = l_own;
@@ -511,10 +527,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
         float l_all = 0.f;
 #pragma unroll
         for (int g = 0; g < KS; ++g) {
-            const float m_g = *stat(g, 0);
-            if (m_g > -INFINITY) l_all += *stat(g, 1) * fast_exp2((m_g - m_all) * c);
+            l_all += *stat(g, 1) * fast_exp2(*stat(g, 0) - m_all);
         }
-        const float scale = l_all > 0.f && has_ref[0] ? fast_exp2((m_own - m_all) * c) / l_all : 0.f;
+        const float scale = l_all > 0.f ? fast_exp2(m_own - m_all) / l_all : 0.f;
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -693,7 +708,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
     auto run = [&](auto mode, const DevicePlan& plan, const QueryBlock& block) {
         constexpr int MODE = decltype(mode)::value;
         if constexpr (LOOP == LOOP_64_PIPELINED) attend_wide<D, NW, MODE>(a, plan, block, smem);
-        else attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD>(a, plan, block, smem);
+        else attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM)>(a, plan, block, smem);
     };
     int ordinal, bh;  // position in the block order, and the head
     qs.locate(item, xcd, &bh, &ordinal);
