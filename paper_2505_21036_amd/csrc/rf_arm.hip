@@ -14,10 +14,13 @@
 // samples exists anywhere.  The recalls' sums over 32 rows go to scratch and are reduced in a fixed order by
 // arm_finish_kernel, which also applies the decision rule.
 //
-// Bound by vector issue (about nine vector instructions per MFMA; each score costs a maximum, an exponent and a
-// sum, and three or four more per pass where a band's edge crosses its tile).  Measured, recall and finish, 24
-// heads of 3600 samples at head_dim 128: equal-interval 257 -> 162 us, first-frame 249 -> 218 us; 24 heads of 448
+// Bound by vector issue (about eight vector instructions per MFMA; each score costs a maximum, an exponent and a
+// sum, and three more per pass where a band's edge crosses its tile: the Temporal band does in every tile at equal
+// intervals).  Measured, recall and finish, 24 heads of 3600 samples at head_dim 128: equal-interval 257 us with the mask
+// applied to every score, 161 with the edges told apart, 149 with three instructions there instead of four and the scores
+// at raised priority; first-frame 249 -> 218 -> 215 us; 24 heads of 448
 // at head_dim 96: 39.9 -> 14.6 and 29.0 -> 16.6 us; 6 heads of 130 at head_dim 128: 21.6 -> 12.5 us.
+#include <cfloat>
 #include <mutex>
 
 #include "rf_device.h"
@@ -43,7 +46,7 @@ constexpr int arm_waves_per_simd(int D, bool both, int KS) { return KS > 1 ? 2 :
 template <int D, int R, int KS>
 struct ArmSmem {
     using ST = DirectTile<D, R>;
-    // per group: two K' tiles, then per tile and pass the 64 samples' attributes and bounds on them (lowest, highest)
+    // per group: two K' tiles, then per tile and pass the 64 samples' attributes (float) and bounds on them (lowest, highest)
     static constexpr int ATTR_SLOT = kTileK + 4;  // 16-byte aligned
     static constexpr int ATTR_OFF = 2 * ST::K_BYTES;
     static constexpr int GROUP_BYTES = (ATTR_OFF + 2 * 2 * ATTR_SLOT * 4 + 255) / 256 * 256;
@@ -63,7 +66,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
     using SM = ArmSmem<D, R, KS>;
     using ST = typename SM::ST;
     typedef __attribute__((address_space(3))) float lds_float;
-    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+    typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
     extern __shared__ __attribute__((aligned(256))) unsigned char smem_all[];  // the kernel's only LDS: starts at address 0
     const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * R));
     unsigned char* smem = smem_all + group * SM::GROUP_BYTES;
@@ -122,10 +125,11 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
         }
     }
 
-    // m_ref: reference subtracted inside exp2 (raw score units); l_all / l_kept: this lane's share of
+    // m_ref: reference subtracted inside exp2, in the units of its argument (score times c, which is below 1);
+    // kNoReference, which any finite score outgrows, until it has been taken from one; l_all / l_kept: this lane's share of
     // the denominator over all sampled keys and over the kept ones, both relative to m_ref
-    float m_ref = 0.f, l_all = 0.f, l_kept[NP][kMaxBw];
-    bool has_ref = false;
+    constexpr float kNoReference = -FLT_MAX;
+    float m_ref = kNoReference, l_all = 0.f, l_kept[NP][kMaxBw];
 #pragma unroll
     for (int i = 0; i < NP; ++i)
 #pragma unroll
@@ -163,7 +167,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
         for (int i = 0; i < NP; ++i) {
             if (is_run[i]) continue;
             int* slot = attr_slot(t, i);
-            slot[tid] = attr_reg[i];
+            slot[tid] = __float_as_int(static_cast<float>(attr_reg[i]));
             int low = __builtin_amdgcn_readlane(attr_reg[i], 0), high = __builtin_amdgcn_readlane(attr_reg[i], kTileK - 1);
             if (!ps[i].by_frame && first / ps[i].HW != last / ps[i].HW) {
                 low = 0;
@@ -191,7 +195,11 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
             const int k0 = first_of(t);
 
             f32x16 s[2];
+            // the wavefronts of a SIMD leave the barrier together: one that forms scores goes before one in its sums, so
+            // that the matrix pipe works while others use the vector unit
+            __builtin_amdgcn_s_setprio(1);
             st.template scores<kAheadK>(st.k_address(k_lds(t)), qf, s);
+            __builtin_amdgcn_s_setprio(0);
             if (k0 + kTileK > n) {  // ragged last tile: samples past the end do not exist
 #pragma unroll
                 for (int kb2 = 0; kb2 < 2; ++kb2)
@@ -206,22 +214,18 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
                 for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[kb2][r]);
             // the two halves of the wavefront hold different keys of the same 32 queries: their maxima are
             // exchanged, and the sums rescaled, only when some lane asks for the reference to move
-            const bool grow = has_ref ? (mt - m_ref) * c > kArmRescaleSlack : mt > -INFINITY;
-            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+            if (__builtin_amdgcn_ballot_w64(fmaf(mt, c, -m_ref) > kArmRescaleSlack) != 0) {
                 mt = fmaxf(mt, other_half(mt));
                 if (mt > -INFINITY) {
-                    const float m_new = has_ref ? fmaxf(m_ref, mt) : mt;
-                    const float alpha = has_ref ? fast_exp2((m_ref - m_new) * c) : 0.f;  // nothing accumulated before
+                    const float m_new = fmaxf(m_ref, mt * c), alpha = fast_exp2(m_ref - m_new);
                     l_all *= alpha;
 #pragma unroll
                     for (int i = 0; i < NP; ++i)
 #pragma unroll
                         for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] *= alpha;
                     m_ref = m_new;
-                    has_ref = true;
                 }
             }
-            const float mc = m_ref * c;
             // the tile's terms of the denominator, summed in the same order whatever the masks need: four chains,
             // so that an addition need not wait for the one before it
             float part[4] = {0.f, 0.f, 0.f, 0.f};
@@ -229,7 +233,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
             for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    s[kb2][r] = fast_exp2(fmaf(s[kb2][r], c, -mc));
+                    s[kb2][r] = fast_exp2(fmaf(s[kb2][r], c, -m_ref));
                     part[r & 3] += s[kb2][r];
                     if ((r & 7) == 7) __builtin_amdgcn_sched_barrier(0);  // keeps the temporaries few
                 }
@@ -287,10 +291,12 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
                     for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] += ((inside >> b) & 1) ? sum_all : 0.f;
                     continue;
                 }
-                // the test |difference| <= radius as one unsigned comparison
+                // The attributes are whole numbers below 2^24, exact as floats:  radius + 1 - |difference|, held between 0
+                // and 1, is 1 on kept entries and 0 on the others, and the product with it is added exactly as a kept
+                // entry would be.  Three full-rate instructions where integers take a difference, a comparison, a
+                // choice and a sum.
                 auto sum_within = [&](int radius) {
-                    const int low = q_attr[i] - radius;
-                    const uint32_t span = 2u * static_cast<uint32_t>(radius);
+                    const float own = static_cast<float>(q_attr[i]), edge = static_cast<float>(radius + 1);
                     uint32_t table = ST::lds_offset(reinterpret_cast<const unsigned char*>(al)) + 32 * hf;
                     asm volatile("" : "+v"(table));  // read anew for every candidate: not kept in 32 registers
                     float k4[4] = {0.f, 0.f, 0.f, 0.f};
@@ -298,9 +304,10 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
                     for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
                         for (int r = 0; r < 16; r += 4) {
-                            const u32x4 at = *(lds_u32x4*)(uintptr_t)(table + 4 * (32 * kb2 + key_of_reg(r, 0)));
+                            const f32x4 at = *(lds_f32x4*)(uintptr_t)(table + 4 * (32 * kb2 + key_of_reg(r, 0)));
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) k4[j] += at[j] - static_cast<uint32_t>(low) <= span ? s[kb2][r + j] : 0.f;
+                            for (int j = 0; j < 4; ++j)
+                                k4[j] = fmaf(s[kb2][r + j], __builtin_amdgcn_fmed3f(edge - fabsf(at[j] - own), 0.f, 1.f), k4[j]);
                             asm volatile("" : "+v"(k4[0]), "+v"(k4[1]), "+v"(k4[2]), "+v"(k4[3]));  // four attributes in registers at a time
                         }
                     return (k4[0] + k4[1]) + (k4[2] + k4[3]);
@@ -330,7 +337,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
             return (lds_float*)(uintptr_t)(ST::lds_offset(smem_all) + g * SM::GROUP_BYTES + ((wave * SM::PART + which) * 32 + m) * 4);
         };
         if (hf == 0) {
-            *slot(group, 0) = has_ref ? m_ref : -INFINITY;
+            *slot(group, 0) = m_ref;
             *slot(group, 1) = l_all;
 #pragma unroll
             for (int i = 0; i < NP; ++i)
@@ -340,7 +347,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
         }
         __syncthreads();
         if (group != 0) return;
-        float top = -INFINITY;
+        float top = kNoReference;
 #pragma unroll
         for (int g = 0; g < KS; ++g) top = fmaxf(top, *slot(g, 0));
         l_all = 0.f;
@@ -350,7 +357,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
             for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] = 0.f;
 #pragma unroll
         for (int g = 0; g < KS; ++g) {
-            const float m_g = *slot(g, 0), w = m_g > -INFINITY ? fast_exp2((m_g - top) * c) : 0.f;
+            const float w = fast_exp2(*slot(g, 0) - top);
             l_all += w * *slot(g, 1);
 #pragma unroll
             for (int i = 0; i < NP; ++i)
