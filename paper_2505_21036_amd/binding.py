@@ -116,13 +116,15 @@ def _check_bf16(t, name, shape=None):
     import torch
     if not (t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.dim() == 4):
         raise ValueError("%s must be a contiguous bf16 device tensor [B, nH, N, D]" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
 
 
 def _stream():
+    """Handle of torch's current stream on the current device (without the object that torch.cuda.current_stream makes
+    for it, which took a quarter of the time of a call of the smallest sizes)."""
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def rf_arm_classify(Q, K, layout, params=None, sample_mode=RF_SAMPLE_FIRST_FRAME, threshold=0.9,
@@ -138,9 +140,8 @@ def rf_arm_classify(Q, K, layout, params=None, sample_mode=RF_SAMPLE_FIRST_FRAME
         head_class = torch.empty(B, nH, dtype=torch.int32, device=Q.device)
     if recalls is None:
         recalls = torch.empty(B, nH, 2, dtype=torch.float32, device=Q.device)
-    need = rf_arm_workspace_bytes(B, nH, layout, params)
     if workspace is None:
-        workspace = torch.empty(max(need, 4), dtype=torch.uint8, device=Q.device)
+        workspace = torch.empty(max(rf_arm_workspace_bytes(B, nH, layout, params), 4), dtype=torch.uint8, device=Q.device)
     st = load_library().rf_arm_classify(Q.data_ptr(), K.data_ptr(), B, nH, D, C.byref(layout), _pp(params),
                                         sample_mode, threshold, head_class.data_ptr(), recalls.data_ptr(),
                                         workspace.data_ptr(), workspace.numel() * workspace.element_size(),
