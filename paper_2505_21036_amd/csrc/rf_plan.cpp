@@ -258,8 +258,8 @@ namespace {
 //
 // copies: up to 256 rows, rows gathered through an index table cost nothing that can be measured, so no copies are
 // made (17776 tokens, 24 heads, head_dim 128, 128 rows: 1.92 ms either way); twelve wavefronts at head_dim 96 and
-// 128 and the 64-row wavefronts at 64 have no registers for the loop that gathers Temporal heads (3.79 ms in token
-// order against 1.85 ms with copies at 384 rows).
+// 128 have no registers for the loop that gathers Temporal heads (3.79 ms in token order against 1.85 ms with copies at
+// 384 rows); the 64-row wavefronts at 64 run either way (see Kernel::packs).
 struct Kernel {
     AttnForm form;
     int per_cu;           // workgroups a CU holds
@@ -269,6 +269,11 @@ struct Kernel {
     double dense;         // times tile_us where no list is walked
     double text;          // times tile_us in a block that holds text rows, which walks every tile, most of them masked
     double text_tile_us;  // per tile of such a block where nothing else is left to run: no launch ends before it
+    bool gathers = false; // the form has copies, but runs without them too
+    // With room, copies are made where they pay: a form that gathers as well reads rows through the L2s as fast as long as the
+    // heads in work fit the memory-side cache (48 heads of 17776 tokens at head_dim 64 2095 us without and 2116 with,
+    // 24 of 86626 22.7 ms and 22.2).
+    bool packs(bool far) const { return form.copies && (far || !gathers); }
 };
 struct Chip {
     double start_us;             // of a launch
@@ -284,7 +289,7 @@ constexpr int kForms = 6;  // of one head_dim, at most
 const Kernel kKernels[3][kForms] = {{{{64, 4, false, false}, 1, 0.478, 5.0, 0, 0.750, 2.00, 0.59},  // head_dim 64
                                      {{64, 2, false, false}, 3, 1.175, 6.1, 0.72, 0.754, 1.58, 1.09},
                                      {{128, 1, false, false}, 3, 2.130, 4.7, 0.72, 0.765, 1.02, 2.15},
-                                     {{256, 1, true, true}, 2, 2.675, 3.9, 0.74, 0.779, 0.50, 3.46},
+                                     {{256, 1, true, true}, 2, 2.675, 3.9, 0.74, 0.779, 0.50, 3.46, true},
                                      {{384, 1, true, false}, 1, 2.022, 1.7, 0, 0.774, 1.10, 3.00},
                                      {{0, 0, false, false}, 0, 0, 0, 0, 0, 0, 0}},
                                     {{{64, 4, false, false}, 1, 0.630, 6.0, 0, 0.704, 2.00, 0.72},  // head_dim 96
@@ -346,7 +351,7 @@ double mean_tiles(const Geometry& g, int rows, double textural) {
 }
 
 // Time of a launch in form k, us; HUGE_VAL if the form is not to be taken at this size.  textural: textural_tiles(g).
-double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense, double textural) {
+double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense, bool room, double textural) {
     constexpr int kCUs = 256;  // MI355X
     const Chip& chip = kChips[index_of(D)];
     const int rows = k.form.rows;
@@ -377,26 +382,26 @@ double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense, 
     double us = item * length * (1 - (dense ? chip.many_dense : chip.many) * (1 - 1 / std::max(1.0, rounds)));
     if (longs > 0) us = std::max(us, k.text_tile_us * tiles * (chip.alone + (1 - chip.alone) * std::min(1.0, items / slots)) + k.item_us);
     us += chip.start_us + (k.form.queued ? chip.queue_us : 0);
-    if (k.form.copies && !dense) us += 3 + chip.copy_us * (2. / 3) * 8e-6 * BH * g.N * D;  // two patterns in three walk copies
+    if (k.packs(far) && room && !dense) us += 3 + chip.copy_us * (2. / 3) * 8e-6 * BH * g.N * D;  // two patterns in three walk copies
     return us;
 }
 
-// The form of least cost(form) among those of head_dim D, copies: with those that walk copies of K and V.
-template <typename F>
-AttnForm cheapest(int D, bool copies, F cost) {
+// The kernel of least cost(kernel) among those of head_dim D that `allowed` admits.
+template <typename A, typename F>
+const Kernel& cheapest(int D, A allowed, F cost) {
     const Kernel* of_d = kernels_of(D);
     const Kernel* best = nullptr;
     double least = 0;
     for (int i = 0; i < kForms; ++i) {
         const Kernel& k = of_d[i];
-        if (k.per_cu == 0 || (k.form.copies && !copies)) continue;
+        if (k.per_cu == 0 || !allowed(k)) continue;
         const double c = cost(k);
         if (!best || c < least) {
             best = &k;
             least = c;
         }
     }
-    return best->form;
+    return *best;
 }
 
 }  // namespace
@@ -405,24 +410,28 @@ AttnForm cheapest(int D, bool copies, F cost) {
 // may say so through the classes), so a tenth of the weight goes to the dense walk.  It decides between forms that are
 // nearly even for the patterns; head_dim 64 has the widest gap, 48 heads of 17776 tokens: 128 rows 2221 us with the
 // patterns in turn and 4252 dense, 256 from queues 2316 and 3994, 384 2318 and 4085.
-static double mixed_cost(const Kernel& k, const Geometry& g, int BH, int D, double textural) {
-    const double sparse = launch_us(k, g, BH, D, false, textural), cube = sparse * sparse * sparse;
-    return cube * cube * cube * launch_us(k, g, BH, D, true, textural);  // tenth power of the weighted geometric mean
+static double mixed_cost(const Kernel& k, const Geometry& g, int BH, int D, bool room, double textural) {
+    const double sparse = launch_us(k, g, BH, D, false, room, textural), cube = sparse * sparse * sparse;
+    return cube * cube * cube * launch_us(k, g, BH, D, true, room, textural);  // tenth power of the weighted geometric mean
 }
 
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
     const double textural = textural_tiles(g);
-    // without room a form with copies would walk Temporal heads in token order: up to twice the time
-    return cheapest(D, room || dense, [&](const Kernel& k) { return dense ? launch_us(k, g, BH, D, true, textural) : mixed_cost(k, g, BH, D, textural); });
+    // without room the other forms with copies would walk Temporal heads in token order: up to twice the time
+    auto allowed = [&](const Kernel& k) { return !k.form.copies || room || dense || k.gathers; };
+    const Kernel& k = cheapest(D, allowed, [&](const Kernel& k) { return dense ? launch_us(k, g, BH, D, true, room, textural) : mixed_cost(k, g, BH, D, room, textural); });
+    AttnForm form = k.form;
+    if (!dense && !(room && k.packs(!whole_heads_fit(g, D)))) form.copies = false;
+    return form;
 }
 
 AttnForm choose_fixed_form(const Geometry& g, int D) {
     const double textural = textural_tiles(g);
-    return cheapest(D, false, [&](const Kernel& k) {
+    return cheapest(D, [](const Kernel& k) { return !k.form.copies; }, [&](const Kernel& k) {
         double product = 1;  // of numbers below 1e10 ^ 10 each at any size that runs
-        for (int heads : {12, 24, 48}) product *= std::pow(mixed_cost(k, g, heads, D, textural), 0.1);
+        for (int heads : {12, 24, 48}) product *= std::pow(mixed_cost(k, g, heads, D, false, textural), 0.1);
         return product;
-    });
+    }).form;
 }
 
 // cls in the public numbering: a head class, or RF_LIST_TEMPORAL_POSITION_MAJOR
