@@ -16,13 +16,20 @@
 //
 // Bound by vector issue (about eight vector instructions per MFMA; each score costs a maximum, an exponent and a
 // sum, and three more per pass where a band's edge crosses its tile: the Temporal band does in every tile at equal
-// intervals).  Measured, recall and finish, 24 heads of 3600 samples at head_dim 128: equal-interval 257 us with the mask
-// applied to every score, 161.4 with the edges told apart, 150.7 with three instructions there instead of four, 149.5 with the
-// scores at raised priority too; first-frame 249, 215.5, 213.3, 213.3.  The priority is worth 1 % at head_dim 96 (143.0 -> 141.5
-// us, 24 heads of 3600) and nothing at 64 (55.8, 48 heads of 1350).  24 heads of 448
-// at head_dim 96: 39.9 -> 14.6 and 29.0 -> 16.6 us; 6 heads of 130 at head_dim 128: 21.6 -> 12.5 us.
+// intervals).  Measured, recall and finish, us:
+//   24 heads of 3600 samples at head_dim 128, equal intervals 257 with the mask applied to every score, 161 with the edges told
+//   apart, 151 with three instructions there instead of four, 149.5 with the scores at raised priority too, 133 with all reads of
+//   the table of attributes asked for before the first is used (each was waited for by itself), positions carried from tile to
+//   tile instead of divided out, and the radius of a call with one bandwidth in a register; first frame 249, 215, 213, 213 and
+//   200 (a pass of its own needs no table at all)
+//   three candidates 252 -> 197; head_dim 96, 24 heads of 3600, equal 141 -> 120, first 188 -> 169; head_dim 64, 48 of 1350, 54.9 -> 44.7
+//   and 62.1 -> 51.4; 24 of 448 at head_dim 96 39.9, 13.8 and 11.9 now, first 29.0, 16.2 and 13.5; 40 heads of 2800 at head_dim 64,
+//   four candidates, 282 -> 199
+// Also tried: the products of the next tile dealt out between the sums of this one, 1.0-1.03 at head_dim 64 and 96 and 0.96 at 128 of
+// the same time, where the second set of scores spills; the differences of the attributes from the matrix unit, 1.00.
 #include <cfloat>
 #include <mutex>
+#include <type_traits>
 
 #include "rf_device.h"
 
@@ -39,16 +46,16 @@ constexpr int kArmSplitItemsBoth = 256, kArmSplitItemsApart = 128;
 // as in the attention kernel: the reference in the exponent moves only when a row outgrows it by this
 constexpr float kArmRescaleSlack = 8.f;
 
-// Wavefronts per SIMD the register allocation is held to: what the tile loop fits without spills (head_dim 96, one pass:
-// four with eight bytes spilled outside the loop; one pass at head_dim 128 does fit four, with spills on a rare path of
-// the loop, and measured 2-7 % slower so).
-constexpr int arm_waves_per_simd(int D, bool both, int KS) { return KS > 1 ? 2 : (both ? (D == 64 ? 4 : 3) : (D == 128 ? 3 : 4)); }
+// Wavefronts per SIMD the register allocation is held to: what the tile loop fits without spills (head_dim 96, one pass,
+// several candidates: four with a few registers spilled outside the loop; head_dim 128: four for one pass with one
+// bandwidth, 198.7 -> 196.4 us for 24 heads of 3600 samples).
+constexpr int arm_waves_per_simd(int D, bool both, int KS, int NB) { return KS > 1 ? 2 : (both ? (D == 64 ? 4 : 3) : (D == 128 && NB > 1 ? 3 : 4)); }
 
 template <int D, int R, int KS>
 struct ArmSmem {
     using ST = DirectTile<D, R>;
-    // per group: two K' tiles, then per tile and pass the 64 samples' attributes (float) and bounds on them (lowest, highest)
-    static constexpr int ATTR_SLOT = kTileK + 4;  // 16-byte aligned
+    // per group: two K' tiles, then per tile and pass the 64 samples' attributes (float)
+    static constexpr int ATTR_SLOT = kTileK;
     static constexpr int ATTR_OFF = 2 * ST::K_BYTES;
     static constexpr int GROUP_BYTES = (ATTR_OFF + 2 * 2 * ATTR_SLOT * 4 + 255) / 256 * 256;
     static constexpr int BYTES = KS * GROUP_BYTES;
@@ -61,8 +68,9 @@ struct ArmSmem {
 // BOTH: the two passes use the same sample (equal-interval sampling), so one workgroup forms each
 // score tile once and keeps the kept-key sums of both masks; the arithmetic per pass, and so every
 // recall, is the same as when the passes run apart.
-template <int D, bool BOTH, int R, int KS>
-__global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_eu(arm_waves_per_simd(D, BOTH, KS), arm_waves_per_simd(D, BOTH, KS)))) arm_recall_kernel(ArmArgs a, int nQB) {
+// NB: candidate bandwidths there is room for (1 or kMaxBw).
+template <int D, bool BOTH, int R, int KS, int NB>
+__global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_eu(arm_waves_per_simd(D, BOTH, KS, NB), arm_waves_per_simd(D, BOTH, KS, NB)))) arm_recall_kernel(ArmArgs a, int nQB) {
     constexpr int BQ = 32 * R, NP = BOTH ? 2 : 1;
     using SM = ArmSmem<D, R, KS>;
     using ST = typename SM::ST;
@@ -97,16 +105,15 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
         return ps[i].by_frame ? token / ps[i].HW : token % ps[i].HW;
     };
     // With one candidate bandwidth, a query's kept samples are one run of sample indices if the attribute rises with
-    // the index (frames; positions inside the first frame): then lo .. hi, and no table is needed.  Otherwise the
-    // attributes of a tile's samples are compared with the query's.
-    const int n_bw = a.n_bw;
-    bool is_run[NP];
+    // the index: frames always, positions where the passes have samples of their own (pass 0 then the first frame's).
+    // Then lo .. hi, and no table is needed.  Otherwise the attributes of a tile's samples are compared with the query's.
+    constexpr auto is_run = [](int i) { return NB == 1 && (!BOTH || i == 1); };
+    const int n_bw = NB == 1 ? 1 : a.n_bw;
     int q_attr[NP], lo[NP], hi[NP];
     // range of the attribute over the wavefront's 32 queries (both halves hold the same queries)
     int q_min[NP], q_max[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        is_run[i] = n_bw == 1 && (ps[i].by_frame || (stride == 1 && n <= ps[i].HW));
         q_attr[i] = attr_of(i, qsc);
         int low = q_attr[i], high = q_attr[i];
 #pragma unroll
@@ -130,11 +137,11 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
     // kNoReference, which any finite score outgrows, until it has been taken from one; l_all / l_kept: this lane's share of
     // the denominator over all sampled keys and over the kept ones, both relative to m_ref
     constexpr float kNoReference = -FLT_MAX;
-    float m_ref = kNoReference, l_all = 0.f, l_kept[NP][kMaxBw];
+    float m_ref = kNoReference, l_all = 0.f, l_kept[NP][NB];
 #pragma unroll
     for (int i = 0; i < NP; ++i)
 #pragma unroll
-        for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] = 0.f;
+        for (int b = 0; b < NB; ++b) l_kept[i][b] = 0.f;
     const float c = a.scale_log2;
     const int all_tiles = (n + kTileK - 1) / kTileK;
     const int ntiles = (all_tiles - group + KS - 1) / KS, nsteps = (all_tiles + KS - 1) / KS;  // this group's; the longest's
@@ -144,41 +151,36 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
     auto first_of = [&](int t) { return (t * KS + group) * kTileK; };  // the group's t-th tile starts at this sample
     auto k_lds = [&](int t) { return smem + (t & 1) * ST::K_BYTES; };
     auto attr_slot = [&](int t, int i) { return abuf + ((t & 1) * 2 + i) * SM::ATTR_SLOT; };
-    int attr_reg[NP] = {};
     auto fetch_tile = [&](int t) {
         const int k0 = first_of(t);
         if (stride == 1 && k0 + kTileK <= n)
             st.template issue_consecutive<false>(Kh + static_cast<size_t>(k0) * (2 * D), nullptr, k_lds(t), nullptr);
         else
             st.template issue<false>(Kh, nullptr, k_lds(t), nullptr, [&](int r) { return min(k0 + r, n - 1) * stride; });
-        // the tile's attributes (first wavefront, one sample per lane)
-        if (tid < kTileK) {
-#pragma unroll
-            for (int i = 0; i < NP; ++i)
-                if (!is_run[i]) attr_reg[i] = attr_of(i, min(k0 + tid, n - 1));
+    };
+    // Where samples are told apart by a table: frame and in-frame position of sample first_of(t) + lane of the tile t last
+    // stashed, and of the tile worked on its first sample's, both moved on from tile to tile without a division.  Samples
+    // past the last one go on in the same way: their weights are 0, and bounds that take them in are only too wide.
+    // (A stride beyond the last token leaves one sample, and the products below 2^32.)
+    const unsigned HW = ps[0].HW, hop = min(stride, a.N), step = kTileK * KS * hop;
+    const int span = (kTileK - 1) * hop, span_frames = span / HW, span_rest = span % HW, step_frames = step / HW, step_rest = step % HW;
+    auto advance = [&](int& frame, int& at) {
+        at += step_rest;
+        frame += step_frames;
+        if (at >= static_cast<int>(HW)) {
+            at -= HW;
+            ++frame;
         }
     };
-    // Also bounds on the tile's attributes: samples are in token order, so frames never decrease, and
-    // positions do not either as long as the tile stays inside one frame; a tile that crosses into
-    // another frame gets the widest bounds (the caller then masks it entry by entry, which is exact).
+    int own_frame = (first_of(0) + lane) * hop / HW, own_at = (first_of(0) + lane) * hop % HW;
+    int tile_frame = first_of(0) * hop / HW, tile_at = first_of(0) * hop % HW;
     auto stash_attr = [&](int t) {
-        if (tid >= kTileK) return;
-        const int first = first_of(t) * stride, last = min(first_of(t) + kTileK - 1, n - 1) * stride;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            if (is_run[i]) continue;
-            int* slot = attr_slot(t, i);
-            slot[tid] = __float_as_int(static_cast<float>(attr_reg[i]));
-            int low = __builtin_amdgcn_readlane(attr_reg[i], 0), high = __builtin_amdgcn_readlane(attr_reg[i], kTileK - 1);
-            if (!ps[i].by_frame && first / ps[i].HW != last / ps[i].HW) {
-                low = 0;
-                high = ps[i].HW - 1;
-            }
-            if (tid == 0) {
-                slot[kTileK] = low;
-                slot[kTileK + 1] = high;
-            }
+            if (is_run(i)) continue;
+            if (tid < kTileK) attr_slot(t, i)[tid] = __float_as_int(static_cast<float>(ps[i].by_frame ? own_frame : own_at));
         }
+        advance(own_frame, own_at);
     };
     if (ntiles > 0) {
         fetch_tile(0);
@@ -202,11 +204,14 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
             st.template scores<kAheadK>(st.k_address(k_lds(t)), qf, s);
             __builtin_amdgcn_s_setprio(0);
             if (k0 + kTileK > n) {  // ragged last tile: samples past the end do not exist
+                int end = n - k0 - 8 * hf;
 #pragma unroll
                 for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (k0 + 32 * kb2 + key_of_reg(r, hf) >= n) s[kb2][r] = -INFINITY;
+                    for (int r = 0; r < 16; ++r) {
+                        if (32 * kb2 + key_of_reg(r, 0) >= end) s[kb2][r] = -INFINITY;
+                        if ((r & 3) == 3) asm volatile("" : "+v"(end));  // few comparisons' results at a time
+                    }
             }
             float mt = s[0][0];
 #pragma unroll
@@ -223,7 +228,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
                     for (int i = 0; i < NP; ++i)
 #pragma unroll
-                        for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] *= alpha;
+                        for (int b = 0; b < NB; ++b) l_kept[i][b] *= alpha;
                     m_ref = m_new;
                 }
             }
@@ -240,21 +245,25 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
                 }
             const float sum_all = (part[0] + part[1]) + (part[2] + part[3]);
             l_all += sum_all;
-            // sum of the terms that keep(entry) holds, entry = (half, register)
-            auto sum_of = [&](auto keep) {
+            // sum of the terms whose place in the tile, counted from this half's first, is from .. to, of which only the ends
+            // asked for are looked at; the ends are opaque, or all comparisons are made first and their results kept
+            auto sum_of_run = [&](auto look_from, int from, auto look_to, int to) {
+                constexpr bool FROM = decltype(look_from)::value, TO = decltype(look_to)::value;
                 float k4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        k4[r & 3] += keep(kb2, r) ? s[kb2][r] : 0.f;
-                        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                        if ((r & 3) == 0) asm volatile("" : "+v"(from), "+v"(to));
+                        const int at = 32 * kb2 + key_of_reg(r, 0);
+                        k4[r & 3] += (!FROM | (at >= from)) & (!TO | (at <= to)) ? s[kb2][r] : 0.f;
+                        if ((r & 3) == 3) asm volatile("" : "+v"(k4[0]), "+v"(k4[1]), "+v"(k4[2]), "+v"(k4[3]));
                     }
                 return (k4[0] + k4[1]) + (k4[2] + k4[3]);
             };
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
-                if (is_run[i]) {
+                if (is_run(i)) {
                     // entry (kb2, r) of this lane is sample  k0 + 8*hf + 32*kb2 + 16*(r/8) + r%8
                     const bool all = lo[i] <= k0 && hi[i] >= min(k0 + kTileK, n) - 1, none = hi[i] < k0 || lo[i] >= k0 + kTileK;
                     if (__builtin_amdgcn_ballot_w64(!all) == 0) {
@@ -262,64 +271,76 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
                     } else if (__builtin_amdgcn_ballot_w64(!none) != 0) {
                         const int from = lo[i] - k0 - 8 * hf, to = hi[i] - k0 - 8 * hf;
                         // usually one end of the run lies in the tile for the 32 queries: one comparison each
-                        if (__builtin_amdgcn_ballot_w64(hi[i] < k0 + kTileK - 1) == 0)
-                            l_kept[i][0] += sum_of([&](int kb2, int r) { return 32 * kb2 + key_of_reg(r, 0) >= from; });
-                        else if (__builtin_amdgcn_ballot_w64(lo[i] > k0) == 0)
-                            l_kept[i][0] += sum_of([&](int kb2, int r) { return 32 * kb2 + key_of_reg(r, 0) <= to; });
-                        else
-                            l_kept[i][0] += sum_of([&](int kb2, int r) {
-                                const int at = 32 * kb2 + key_of_reg(r, 0);
-                                return (at >= from) & (at <= to);
-                            });
+                        constexpr std::true_type look{};
+                        constexpr std::false_type skip{};
+                        if (__builtin_amdgcn_ballot_w64(hi[i] < k0 + kTileK - 1) == 0) l_kept[i][0] += sum_of_run(look, from, skip, to);
+                        else if (__builtin_amdgcn_ballot_w64(lo[i] > k0) == 0) l_kept[i][0] += sum_of_run(skip, from, look, to);
+                        else l_kept[i][0] += sum_of_run(look, from, look, to);
                     }
                     continue;
                 }
                 // Where does the band's edge fall for this (wavefront, tile) pair?  inside: bit b set if every
                 // pair is within radius b; mixed: some candidate has both kept and dropped pairs here.
-                const int* al = attr_slot(t, i);
-                const int k_min = __builtin_amdgcn_readfirstlane(al[kTileK]), k_max = __builtin_amdgcn_readfirstlane(al[kTileK + 1]);
+                // Frames never decrease from sample to sample, and positions do not either inside one frame; a tile that
+                // crosses into another frame gets the widest bounds (it is then masked entry by entry, which is exact).
+                const int end = tile_at + span_rest >= static_cast<int>(HW) ? 1 : 0;  // of the frame, once more than span_frames times
+                const bool crosses = span_frames + end > 0;
+                const int k_min = ps[i].by_frame ? tile_frame : crosses ? 0 : tile_at;
+                const int k_max = ps[i].by_frame ? tile_frame + span_frames + end : crosses ? static_cast<int>(HW) - 1 : tile_at + span;
                 const int reach = max(k_max - q_min[i], q_max[i] - k_min), gap = max(k_min - q_max[i], q_min[i] - k_max);
                 int inside = 0;
                 bool mixed = false;
 #pragma unroll
-                for (int b = 0; b < kMaxBw; ++b) {
+                for (int b = 0; b < NB; ++b) {
                     if (b >= n_bw) break;
                     if (reach <= ps[i].radius[b]) inside |= 1 << b;
                     else if (gap <= ps[i].radius[b]) mixed = true;
                 }
                 if (!mixed) {
 #pragma unroll
-                    for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] += ((inside >> b) & 1) ? sum_all : 0.f;
+                    for (int b = 0; b < NB; ++b) l_kept[i][b] += ((inside >> b) & 1) ? sum_all : 0.f;
                     continue;
                 }
                 // The attributes are whole numbers below 2^24, exact as floats:  radius + 1 - |difference|, held between 0
                 // and 1, is 1 on kept entries and 0 on the others, and the product with it is added exactly as a kept
-                // entry would be.  Three full-rate instructions where integers take a difference, a comparison, a
-                // choice and a sum.
+                // entry would be: three full-rate instructions, two for every further candidate.  All reads of the table are
+                // asked for before the first is used.
+                const float own = static_cast<float>(q_attr[i]);
+                f32x4 apart[8];  // of entries 4 * k to 4 * k + 3
+                const uint32_t table = ST::lds_offset(reinterpret_cast<const unsigned char*>(attr_slot(t, i))) + 32 * hf;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) apart[k] = *(lds_f32x4*)(uintptr_t)(table + 4 * (32 * (k >> 2) + key_of_reg(4 * (k & 3), 0)));
+                __builtin_amdgcn_sched_barrier(0);
+                if (NB > 1) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) apart[k][j] -= own;
+                }
                 auto sum_within = [&](int radius) {
-                    const float own = static_cast<float>(q_attr[i]), edge = static_cast<float>(radius + 1);
-                    uint32_t table = ST::lds_offset(reinterpret_cast<const unsigned char*>(al)) + 32 * hf;
-                    asm volatile("" : "+v"(table));  // read anew for every candidate: not kept in 32 registers
+                    const float edge = static_cast<float>(radius + 1);
                     float k4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int kb2 = 0; kb2 < 2; ++kb2)
+                    for (int k = 0; k < 8; ++k)
 #pragma unroll
-                        for (int r = 0; r < 16; r += 4) {
-                            const f32x4 at = *(lds_f32x4*)(uintptr_t)(table + 4 * (32 * kb2 + key_of_reg(r, 0)));
-#pragma unroll
-                            for (int j = 0; j < 4; ++j)
-                                k4[j] = fmaf(s[kb2][r + j], __builtin_amdgcn_fmed3f(edge - fabsf(at[j] - own), 0.f, 1.f), k4[j]);
-                            asm volatile("" : "+v"(k4[0]), "+v"(k4[1]), "+v"(k4[2]), "+v"(k4[3]));  // four attributes in registers at a time
+                        for (int j = 0; j < 4; ++j) {
+                            const float d = NB > 1 ? apart[k][j] : apart[k][j] - own;
+                            k4[j] = fmaf(s[k >> 2][4 * (k & 3) + j], __builtin_amdgcn_fmed3f(edge - fabsf(d), 0.f, 1.f), k4[j]);
                         }
                     return (k4[0] + k4[1]) + (k4[2] + k4[3]);
                 };
-#pragma clang loop unroll(disable)  // unrolled, the candidates' differences would be kept: 40 more registers
-                for (int b = 0; b < n_bw; ++b) {
-                    const float kept = sum_within(a.pass[pass0 + i].radius[b]);
+                if constexpr (NB == 1) {
+                    l_kept[i][0] += sum_within(ps[i].radius[0]);
+                } else {
+#pragma clang loop unroll(disable)  // unrolled, more registers
+                    for (int b = 0; b < n_bw; ++b) {
+                        const float kept = sum_within(a.pass[pass0 + i].radius[b]);
 #pragma unroll
-                    for (int k = 0; k < kMaxBw; ++k) l_kept[i][k] += k == b ? kept : 0.f;
+                        for (int k = 0; k < NB; ++k) l_kept[i][k] += k == b ? kept : 0.f;
+                    }
                 }
             }
+            advance(tile_frame, tile_at);
         }
         if (t + 1 < ntiles) stash_attr(t + 1);
         ST::template wait_landed<0>();
@@ -330,7 +351,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
     for (int i = 0; i < NP; ++i)
 #pragma unroll
-        for (int b = 0; b < kMaxBw; ++b)
+        for (int b = 0; b < NB; ++b)
             if (b < n_bw) l_kept[i][b] += other_half(l_kept[i][b]);
     if constexpr (KS > 1) {
         // the first group adds up what the groups found, at the largest of their references
@@ -343,7 +364,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
             for (int i = 0; i < NP; ++i)
 #pragma unroll
-                for (int b = 0; b < kMaxBw; ++b)
+                for (int b = 0; b < NB; ++b)
                     if (b < n_bw) *slot(group, 2 + i * kMaxBw + b) = l_kept[i][b];
         }
         __syncthreads();
@@ -355,7 +376,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int i = 0; i < NP; ++i)
 #pragma unroll
-            for (int b = 0; b < kMaxBw; ++b) l_kept[i][b] = 0.f;
+            for (int b = 0; b < NB; ++b) l_kept[i][b] = 0.f;
 #pragma unroll
         for (int g = 0; g < KS; ++g) {
             const float w = fast_exp2(*slot(g, 0) - top);
@@ -363,7 +384,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
             for (int i = 0; i < NP; ++i)
 #pragma unroll
-                for (int b = 0; b < kMaxBw; ++b)
+                for (int b = 0; b < NB; ++b)
                     if (b < n_bw) l_kept[i][b] += w * *slot(g, 2 + i * kMaxBw + b);
         }
     }
@@ -371,7 +392,7 @@ __global__ void __launch_bounds__(64 * R * KS) __attribute__((amdgpu_waves_per_e
 #pragma unroll
     for (int i = 0; i < NP; ++i)
 #pragma unroll
-        for (int b = 0; b < kMaxBw; ++b) {
+        for (int b = 0; b < NB; ++b) {
             if (b >= n_bw) break;
             float sum = qs < n ? l_kept[i][b] / l_all : 0.f;
 #pragma unroll
@@ -418,8 +439,8 @@ __global__ void __launch_bounds__(64 * 2 * kMaxBw) arm_finish_kernel(ArmArgs a) 
     }
 }
 
-template <int D, bool BOTH, int R, int KS>
-static int launch_recall(const ArmArgs& a, hipStream_t st) {
+template <int D, bool BOTH, int R, int KS, int NB>
+static int launch_recall_nb(const ArmArgs& a, hipStream_t st) {
     const int nQB = (a.max_n + 32 * R - 1) / (32 * R), total = nQB * (BOTH ? 1 : 2) * a.BH;
     constexpr int smem = ArmSmem<D, R, KS>::BYTES;
     if (smem > 64 * 1024) {  // above what a kernel may have by itself: once per device
@@ -432,13 +453,18 @@ static int launch_recall(const ArmArgs& a, hipStream_t st) {
         if (dev < 0 || dev >= kMaxDevices) return static_cast<int>(hipErrorInvalidDevice);
         std::lock_guard<std::mutex> lock(mu);
         if (!ready_on[dev]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&arm_recall_kernel<D, BOTH, R, KS>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&arm_recall_kernel<D, BOTH, R, KS, NB>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
             if (e != hipSuccess) return static_cast<int>(e);
             ready_on[dev] = true;
         }
     }
-    hipLaunchKernelGGL((arm_recall_kernel<D, BOTH, R, KS>), dim3(8 * ((total + 7) / 8)), dim3(64 * R * KS), smem, st, a, nQB);
+    hipLaunchKernelGGL((arm_recall_kernel<D, BOTH, R, KS, NB>), dim3(8 * ((total + 7) / 8)), dim3(64 * R * KS), smem, st, a, nQB);
     return static_cast<int>(hipGetLastError());
+}
+
+template <int D, bool BOTH, int R, int KS>
+static int launch_recall(const ArmArgs& a, hipStream_t st) {
+    return a.n_bw == 1 ? launch_recall_nb<D, BOTH, R, KS, 1>(a, st) : launch_recall_nb<D, BOTH, R, KS, kMaxBw>(a, st);
 }
 
 template <int D>
