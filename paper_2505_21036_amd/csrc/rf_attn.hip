@@ -402,7 +402,11 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     // because the loads of a compacted tile take their row indices from it).  e[i] = entry of tile t+i.
     // AHEAD = 0 (one buffer for K and one for V): K(t+1) is loaded while P V of tile t runs, V(t) while
     // the scores and the softmax of tile t do; each has a barrier that says its buffer is free and the other's full.
+    // With one wavefront to a group (kOwnTiles) nobody else reads its tiles, and its own waits say when a buffer is free or
+    // full: K(t+1) is asked for as soon as the scores of tile t are formed, V(t+1) after P V, and there is no barrier.
     constexpr int AHEAD = SM::AHEAD;
+    constexpr bool kOwnTiles = NW == 1;
+    static_assert(!kOwnTiles || (AHEAD == 0 && ST::EVEN), "the waits of the loop count whole tensors");
     int e[DEPTH + 1] = {};
     auto fetch_k = [&](int t, int entry) { fetch_some(std::false_type{}, std::true_type{}, t, entry); };
     auto fetch_v = [&](int t, int entry) { fetch_some(std::true_type{}, std::false_type{}, t, entry); };
@@ -452,10 +456,17 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
         const int kind = KS == 1 || t < ntiles ? tile_kind(e_cur) : 2;
         const bool mine = (KS == 1 && !is_band(MODE)) || kind != 2;
         f32x16 s[QH][2];
+        if (kOwnTiles && t < ntiles) ST::wait_all_but_one_tensor();  // K(t) is there, V(t) on its way
         if (mine) {
         if (RAISE == RAISE_SCORES || RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
         scores(t, e_cur, is_band(MODE) ? kind == 1 : (e_cur & RF_PLAN_PARTIAL) != 0, s);
         if (RAISE != RAISE_NONE) __builtin_amdgcn_s_setprio(RAISE == RAISE_SOFTMAX ? 1 : 0);
+        }
+        if (kOwnTiles && t + 1 < ntiles) {
+            stash_side(t + 1, e[1]);
+            fetch_k(t + 1, e[1]);
+        }
+        if (mine) {
 #pragma unroll
         for (int h = 0; h < QH; ++h) {
             float mt = s[h][0][0];
@@ -500,6 +511,13 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
         if (RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
         else if (RAISE == RAISE_SOFTMAX) __builtin_amdgcn_s_setprio(0);
         if constexpr (AHEAD > 0) accumulate(t);
+        }
+        if constexpr (kOwnTiles) {
+            if (t + 1 < ntiles) ST::wait_all_but_one_tensor();  // V(t) is there, K(t + 1) on its way
+            else ST::template wait_landed<0>();
+            if (mine) accumulate(t);
+            e[0] = e[1];
+            continue;
         }
         if constexpr (AHEAD == 0) {
             ST::template wait_landed<0>();
@@ -602,6 +620,8 @@ enum : int {
     LOOP_64 = 2            // wavefronts of 64 rows on the plain loop (attend with two halves): head_dim 64 only, where two fit a SIMD
 };
 constexpr int rows_per_wave(int LOOP) { return LOOP == LOOP_64_PIPELINED || LOOP == LOOP_64 ? 64 : 32; }
+// Workgroups that share a query block of an item kernel of NW-wavefront groups.
+constexpr int workgroups_per_block(int NW) { return NW == 1 ? 2 : 1; }
 // Which instances walk banded lists by key index (MODE_BAND, MODE_BAND_GATHER) instead of by attribute table
 // (MODE_LISTED): two halves, and twelve wavefronts but at head_dim 64, have no registers left for the other masks.
 // (Those that do are the ones that need no copies of K and V: AttnForm::copies.)
@@ -653,7 +673,7 @@ __device__ __forceinline__ int take_item(int* ctr, int home, const Queues<false>
 }
 
 template <int D, int NW, int LOOP, int KS = 1, int AHEAD = RF_TILES_AHEAD>
-__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem);
+__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem, int part = 0);
 
 // Eight queue counters, then the sweep words (-1: nothing published yet).  One workgroup, one thread per word.
 constexpr int kResetThreads = 128;
@@ -707,24 +727,30 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(at
 // against 3.72 ms; 24 of 48000: 12.7 against 14.3); dense walks stay even or better from the grid (32 of 16384: 3.73
 // against 3.84 ms; 24 of 119056: 147 against 149).
 // KS groups of NW wavefronts split the walk of 32 * NW rows.  AHEAD = 0 keeps one buffer for K and one for V, so
-// that twice the workgroups fit a CU's LDS.
+// that twice the workgroups fit a CU's LDS.  NW = 1: a block of 64 rows is two workgroups' work, taken while each of them
+// has a CU to itself (see launch_items_d).
 template <int D, int NW, int KS, int AHEAD, int WAVES>
 __global__ void __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) attn_item_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(256))) unsigned char smem[];  // the kernel's only LDS: starts at address 0
     const Queues<true> qs = queues_of<true>(a);
-    const int xcd = blockIdx.x & 7, item = blockIdx.x >> 3;
+    constexpr int PARTS = workgroups_per_block(NW);
+    const int xcd = blockIdx.x & 7, item = (blockIdx.x >> 3) / PARTS, part = (blockIdx.x >> 3) % PARTS;
     if (item >= qs.items(xcd)) return;
-    process_item<D, NW, LOOP_ITEM, KS, AHEAD>(a, item, xcd, -1, qs, smem);
+    process_item<D, NW, LOOP_ITEM, KS, AHEAD>(a, item, xcd, -1, qs, smem, part);
 }
 
 // One (head, query block) item: item-th of queue xcd.  seen: the sweep word of this workgroup's XCD
 // (it serves its own L2, whichever queue the item came from), or -1.
 template <int D, int NW, int LOOP, int KS, int AHEAD>
-__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem) {
+__device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem, int part) {
     auto run = [&](auto mode, const DevicePlan& plan, const QueryBlock& block) {
         constexpr int MODE = decltype(mode)::value;
         if constexpr (LOOP == LOOP_64_PIPELINED) attend_wide<D, NW, MODE>(a, plan, block, smem);
-        else attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE)>(a, plan, block, smem);
+        else {
+            QueryBlock rows = block;  // the lists are the block's, the rows this workgroup's part of it
+            if constexpr (LOOP == LOOP_ITEM && workgroups_per_block(NW) > 1) rows.qb = block.qb * workgroups_per_block(NW) + part;
+            attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE)>(a, plan, rows, smem);
+        }
     };
     int ordinal, bh;  // position in the block order, and the head
     qs.locate(item, xcd, &bh, &ordinal);
@@ -759,6 +785,8 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
     const int list = temporal_pm ? kListTemporalPM : cls;
     // dense heads: text-holding blocks first, then token order
     if constexpr (!kOneItem) qk.qb = cls == RF_DENSE ? (ordinal < qs.nTB ? qs.nVB + ordinal : ordinal - qs.nTB) : pl.qorder[list][ordinal];
+    constexpr int PARTS = kOneItem ? workgroups_per_block(NW) : 1;
+    if (PARTS > 1 && (qk.qb * PARTS + part) * (32 * NW) >= pl.N) return;  // the last block ends in its first part
     qk.first = 0;
     qk.cols = nullptr;
     qk.sweep = a.join_sweep ? sweep_word(a.queue, blockIdx.x & 7, bh) : nullptr;
@@ -915,7 +943,7 @@ static int launch_items(const AttnArgs& a, hipStream_t st) {
             ready_on[dev] = true;
         }
     }
-    const int most = queues_of<true>(a).items(0);
+    const int most = queues_of<true>(a).items(0) * workgroups_per_block(NW);
     AttnArgs s = a;
     s.join_sweep = 0;  // its words are not there: nothing resets them
     hipLaunchKernelGGL((attn_item_kernel<D, NW, KS, AHEAD, WAVES>), dim3(8 * most), dim3(NT), smem, st, s);
@@ -926,7 +954,17 @@ static int launch_items(const AttnArgs& a, hipStream_t st) {
 // head_dim 64, where 128 rows measured 6 % faster).  Wavefronts per SIMD: three where the registers allow it.
 template <int D>
 static int launch_items_d(const AttnArgs& a, hipStream_t st) {
-    if (a.plan[0].block == 64 && a.key_groups == 4) return launch_items<D, 2, 4, 0, 2>(a, st);
+    if (a.plan[0].block == 64 && a.key_groups == 4) {
+        // A launch this small is bound by latency: two loads of memory, a barrier and a tile's worth of dependent work one
+        // after the other in every step.  As two workgroups of 32 rows a block's steps are half as long and have no barrier, as
+        // long as each has a CU to itself; the sums, and so the bits, are the same.  us, 64 rows / 32: 6 heads of 960 tokens,
+        // head_dim 128, 20.5 / 17.3 with and 16.6 / 14.4 without text, 64 11.7 / 10.2; 1 of 7936, 128, 60.3 / 46.7; 2 of
+        // 4032, 96, dense 33.5 / 26.6; 2 of 256, 64, 7.4 / 6.7.  With a CU short (17 blocks on an XCD): 4 of 2030, 128, dense
+        // 24.2 / 37.3, 21 of 380, 96, 11.8 / 14.2; two to a CU, which fit at 64: 2 of 8192 33.2 / 36.2, 10 of 1600 12.6 / 14.4.
+        constexpr int kCUsPerXCD = 32;  // MI355X
+        if (2 * queues_of<true>(a).items(0) <= kCUsPerXCD) return launch_items<D, 1, 4, 0, 2>(a, st);
+        return launch_items<D, 2, 4, 0, 2>(a, st);
+    }
     if (a.plan[0].block == 64 && a.key_groups == 2) return launch_items<D, 2, 2, 0, D == 64 ? 3 : 2>(a, st);
     if (a.plan[0].block == 128) return launch_items<D, 4, 1, 0, D == 128 ? 2 : 3>(a, st);
     if constexpr (D != 64)

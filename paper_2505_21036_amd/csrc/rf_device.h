@@ -143,15 +143,16 @@ struct DirectTile {
     int k_base;          // byte offset of this lane's K operand for kb2 = 0 (chunk 0 of its row when !POW2)
     int k_rot;           // !POW2: hf + rotation of this lane's K row
     int v_base;          // byte offset of this lane's V operand for u = 0, first half, channel block 0
-    // Loads of a tile of consecutive tokens: load j of a lane reads  base + j*STEP + lane_off[j].
-    // With power-of-two rows a lane keeps its slot position and moves down ROWS_PER_LOAD rows per
-    // load, and the permutations have period 16 (K) and 4 (V) rows, so one offset serves every j
-    // (K: only if a load covers a multiple of 16 rows); 12-chunk rows need an offset per load.
-    static constexpr int ROWS_PER_LOAD = 64 * NW / CH;
-    static constexpr int STEP = POW2 ? ROWS_PER_LOAD * ROW : 0;
-    static constexpr int K_VARIANTS = (POW2 && ROWS_PER_LOAD % 16 == 0) ? 1 : PER_WAVE;
-    static constexpr int V_VARIANTS = POW2 ? 1 : PER_WAVE;
-    static_assert(!POW2 || ROWS_PER_LOAD % 4 == 0, "V row permutation must not change between loads");
+    // Loads of a tile of consecutive tokens: load j of a lane reads  base + (j / VARIANTS) * VARIANTS * STEP +
+    // lane_off[j % VARIANTS].  The K permutation has a period of 16 rows and the V permutation of 4, so a lane's offsets
+    // repeat, further down, as soon as some loads cover a multiple of that many rows (with 12-chunk rows: of whole rows too).
+    static constexpr int first_repeat(int slots) {
+        int p = 1;
+        while (p < PER_WAVE && p * NT % slots != 0) ++p;
+        return p;
+    }
+    static constexpr int STEP = NT * 16;  // bytes of a load of all wavefronts
+    static constexpr int K_VARIANTS = first_repeat(16 * CH), V_VARIANTS = first_repeat(POW2 ? 4 * CH : CH);
     uint32_t k_lane_off[K_VARIANTS], v_lane_off[V_VARIANTS];
 
     __device__ __forceinline__ void init(int tid) {
@@ -164,8 +165,8 @@ struct DirectTile {
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int slot = min((j * NW + wave) * 64 + lane, kTileK * CH - 1), row = slot / CH, pos = slot % CH;
-            if (j < K_VARIANTS) k_lane_off[j] = row * ROW + 16 * k_chunk(row, pos) - j * STEP;
-            if (j < V_VARIANTS) v_lane_off[j] = row * ROW + 16 * v_slot(row, pos) - j * STEP;
+            if (j < K_VARIANTS) k_lane_off[j] = row * ROW + 16 * k_chunk(row, pos);
+            if (j < V_VARIANTS) v_lane_off[j] = row * ROW + 16 * v_slot(row, pos);
         }
         // V operand of channel block db: chunk 4*db + r of row vrow (+ 16*u + 4*half: multiples of 4,
         // invisible to the V permutation).  With the XOR permutation the chunk lands in slot
@@ -207,8 +208,8 @@ struct DirectTile {
         for (int j = 0; j < PER_WAVE; ++j) {
             const int seg = j * NW + wave;
             if (!EVEN && seg >= SEGS) break;
-            if (WITH_K) dma16(kh + j * STEP, off(k_lane_off[j % K_VARIANTS]), lds_offset(kl) + seg * 1024);
-            if (WITH_V) dma16(vh + j * STEP, off(v_lane_off[j % V_VARIANTS]), lds_offset(vl) + seg * 1024);
+            if (WITH_K) dma16(kh + j / K_VARIANTS * K_VARIANTS * STEP, off(k_lane_off[j % K_VARIANTS]), lds_offset(kl) + seg * 1024);
+            if (WITH_V) dma16(vh + j / V_VARIANTS * V_VARIANTS * STEP, off(v_lane_off[j % V_VARIANTS]), lds_offset(vl) + seg * 1024);
         }
     }
     // load instructions per tensor and tile this wavefront issues (the first SEGS % NW wavefronts take the odd round)
@@ -221,6 +222,12 @@ struct DirectTile {
     static __device__ __forceinline__ void wait_landed() {
         static_assert(LATER * MIN_LOADS_PER_TILE < 64, "vmcnt is a 6-bit counter");
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER * MIN_LOADS_PER_TILE) : "memory");
+    }
+
+    // All but the newest loads of one tensor's tile have landed.
+    static __device__ __forceinline__ void wait_all_but_one_tensor() {
+        static_assert(PER_WAVE < 64, "vmcnt is a 6-bit counter");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_WAVE) : "memory");
     }
 
     // The same wait with a wavefront-uniform run-time count: all but the newest n loads have landed.
