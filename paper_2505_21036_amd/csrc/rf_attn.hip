@@ -147,9 +147,10 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     unsigned char* smem = smem_all + group * SM::GROUP_BYTES;
     // how many slabs ahead of their MFMAs the LDS operand reads run: with two halves every slab feeds two
     // MFMAs and the registers are all in use, and two measured best (dense CogVideoX-shaped layer 4.25 ->
-    // 3.99 ms against the depths of the one-half loop); twelve wavefronts at head_dim 128 have 168
-    // registers each, which the loops fit without spills at depth two
-    constexpr int AK = (QH == 2 || (NW == 12 && D == 128)) ? 2 : kAheadK, AV = (QH == 2 || (NW == 12 && D == 128)) ? 2 : kAheadV;
+    // 3.99 ms against the depths of the one-half loop); twelve wavefronts at head_dim 128 and keys split two ways at 96
+    // have 168 registers each, which the loops fit (but for a spill or two off the common path) at depth two
+    constexpr bool kTight = (NW == 12 && D == 128) || (KS == 2 && D == 96);
+    constexpr int AK = (QH == 2 || kTight) ? 2 : kAheadK, AV = (QH == 2 || kTight) ? 2 : kAheadV;
     const int tid = threadIdx.x - group * (64 * NW), lane = tid & 63, wave = tid >> 6, hf = lane >> 5, m = lane & 31;
     const int N = pl.N, keyN = qk.keyN;
     // opaque, or the loop may load it anew from the arguments, and a scalar load in flight turns its LDS waits into
@@ -218,11 +219,20 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     st.init(tid);
     int side_reg = 0;
 
+    // Keys split two ways at head_dim 96: three wavefronts on a SIMD, and two lane numbers too many for their registers, which
+    // are formed again from the thread's where they are wanted: its place in the wavefront, and 8 * hf.
+    auto thread_again = [&]() {
+        int thread = tid;
+        asm volatile("" : "+v"(thread));
+        return thread;
+    };
+    auto lane_of_list = [&]() { return KS == 2 && D == 96 ? thread_again() & 63 : lane; };
+    auto half_of_mask = [&]() { return KS == 2 && D == 96 ? (thread_again() & 32) >> 2 : 8 * hf; };
     // Tile entries of a listed query block are read 64 at a time, one per lane, and handed out with
     // v_readlane: no scalar-load latency in the loop.  ent_cur covers [ent_base, ent_base + 64).
     int ent_cur = 0, ent_nxt = 0, ent_base = 0;
     auto load_entries = [&](int from) {
-        const int j = min((from + lane) * KS + group, qk.ntiles - 1) + qk.first;  // the walk starts at entry qk.first and wraps
+        const int j = min((from + lane_of_list()) * KS + group, qk.ntiles - 1) + qk.first;  // the walk starts at entry qk.first and wraps
         return qk.cols[j < qk.ntiles ? j : j - qk.ntiles];
     };
     if (has_list(MODE) && ntiles > 0) {
@@ -256,14 +266,14 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     };
     auto k_lds = [&](int t) { return smem + SM::K_OFF + (t % DEPTH) * ST::K_BYTES; };
     auto v_lds = [&](int t) { return smem + SM::V_OFF + (t % DEPTH) * ST::V_BYTES; };
-    // three workgroups of four wavefronts per CU at head_dim 96 have 168 registers each, and the banded loop one pair too few
-    constexpr bool kNarrow = D == 96 && NW == 4 && KS == 1 && MODE == MODE_BAND;
+    // three workgroups of four wavefronts per CU at head_dim 96 have 168 registers each, too few for lane offsets of 64 bits
+    constexpr bool kNarrow = D == 96 && ((NW == 4 && KS == 1 && MODE == MODE_BAND) || KS == 2);
     auto fetch_some = [&](auto with_v, auto with_k, int t, int entry) {
         constexpr bool WV = decltype(with_v)::value, WK = decltype(with_k)::value;
         const int k0 = (entry & kTileIndexMask) * kTileK;
         if (gathers(MODE)) {
             const int* idx = side + (t % SM::SIDE_SLOTS) * kTileK;
-            st.template issue<WV, WK>(Kh, Vh, k_lds(t), v_lds(t), [&](int row) { return idx[row]; });
+            st.template issue<WV, WK, false, kNarrow && KS == 2>(Kh, Vh, k_lds(t), v_lds(t), [&](int row) { return idx[row]; });
         } else if (k0 + kTileK <= keyN && !(qk.text_shift != 0 && k0 < Nv && k0 + kTileK > Nv)) {
             // full tile of consecutive tensor rows: everything but the tile origin is loop invariant
             const int r0 = k0 + (k0 < Nv ? qk.video_shift : qk.text_shift);
@@ -324,11 +334,12 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                 if (is_band(MODE)) {
                     // keys lo .. hi of the tile (counted from this half's first) are kept.  Where only one end of the
                     // run lies in the tile for every row of the wavefront, one comparison with a constant decides.
-                    const int lo = -static_cast<int>(q_lo[h]) - k0 - 8 * hf, hi = lo + static_cast<int>(q_span[h]);
+                    const int first = half_of_mask();
+                    const int lo = -static_cast<int>(q_lo[h]) - k0 - first, hi = lo + static_cast<int>(q_span[h]);
                     if (band_only && __builtin_amdgcn_ballot_w64(hi < kTileK - 1) == 0) drop([&](int c) { return c >= lo; });
                     else if (band_only && __builtin_amdgcn_ballot_w64(lo > 0) == 0) drop([&](int c) { return c <= hi; });
                     else {
-                        const int text = band_only ? kTileK : Nv - k0 - 8 * hf, end = keyN - k0 - 8 * hf;
+                        const int text = band_only ? kTileK : Nv - k0 - first, end = keyN - k0 - first;
                         drop([&](int c) { return (((c >= lo) & (c <= hi)) | (c >= text)) & (c < end); });
                     }
                 } else if (MODE != MODE_LISTED) {
@@ -574,7 +585,12 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                 *part(group, 8 * db + 2 * rq + hf) = w;
             }
         __syncthreads();
-        uint16_t* orow = a.O + static_cast<size_t>(qk.bh) * N * D + static_cast<size_t>(qtok[0]) * D;
+        // row and token formed again, as they would cost registers throughout the tile loop (gathered rows keep theirs: a load)
+        int thread = tid;
+        asm volatile("" : "+v"(thread));
+        const int row = qk.qb * BQ + (thread >> 6) * 32 + (thread & 31), row_c = min(row, N - 1);
+        const int token = gathers(MODE) ? qtok[0] : has_list(MODE) && qk.row_token ? qk.row_token[row_c] : row_c + (row_c < Nv ? pl.video_shift : pl.text_shift);
+        uint16_t* orow = a.O + static_cast<size_t>(qk.bh) * N * D + static_cast<size_t>(token) * D;
 #pragma unroll
         for (int i = 0; i < D / 4 / KS / 2; ++i) {
             const int chunk = group * (D / 4 / KS) + 2 * i + hf;
@@ -584,7 +600,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
             u32x2 w;
             w.x = pack_bf16(sum[0], sum[1]);
             w.y = pack_bf16(sum[2], sum[3]);
-            if (qrow[0] < N) *reinterpret_cast<u32x2*>(orow + 4 * chunk) = w;
+            if (row < N) *reinterpret_cast<u32x2*>(orow + 4 * chunk) = w;
         }
         return;
     }
@@ -951,7 +967,9 @@ static int launch_items(const AttnArgs& a, hipStream_t st) {
 }
 
 // The item kernels of one head_dim: 64 rows with the keys split four or two ways, 128 rows, 256 rows (not at
-// head_dim 64, where 128 rows measured 6 % faster).  Wavefronts per SIMD: three where the registers allow it.
+// head_dim 64, where 128 rows measured 6 % faster).  Wavefronts per SIMD: three where the registers allow it.  (Keys split two
+// ways at head_dim 96, two wavefronts a SIMD / three: 24 heads of 4109 tokens 122.5 / 117.5 us, dense 213.7 / 202.5, 34 of 5540
+// 286.6 / 255.7; with the spills that three had before their loops kept fewer lane offsets, 0.86-0.94 of the speed of two.)
 template <int D>
 static int launch_items_d(const AttnArgs& a, hipStream_t st) {
     if (a.plan[0].block == 64 && a.key_groups == 4) {
@@ -965,7 +983,7 @@ static int launch_items_d(const AttnArgs& a, hipStream_t st) {
         if (2 * queues_of<true>(a).items(0) <= kCUsPerXCD) return launch_items<D, 1, 4, 0, 2>(a, st);
         return launch_items<D, 2, 4, 0, 2>(a, st);
     }
-    if (a.plan[0].block == 64 && a.key_groups == 2) return launch_items<D, 2, 2, 0, D == 64 ? 3 : 2>(a, st);
+    if (a.plan[0].block == 64 && a.key_groups == 2) return launch_items<D, 2, 2, 0, D == 128 ? 2 : 3>(a, st);
     if (a.plan[0].block == 128) return launch_items<D, 4, 1, 0, D == 128 ? 2 : 3>(a, st);
     if constexpr (D != 64)
         if (a.plan[0].block == 256) return launch_items<D, 8, 1, 1, 2>(a, st);

@@ -179,8 +179,10 @@ struct DirectTile {
     // tok(row): token whose K/V row goes to tile row `row`; kh/vh: byte pointers the tokens index.
     // WITH_V = false: K only (the ARM needs no V); WITH_K = false: V only (the attention loop for 64-row
     // wavefronts loads the K and V of different tiles).  RARE: the lane's rows and chunks are worked out on the spot
-    // instead of being kept in registers across the caller's loop.
-    template <bool WITH_V = true, bool WITH_K = true, bool RARE = false, typename F>
+    // instead of being kept in registers across the caller's loop.  NARROW: kept, but only as many as there are before
+    // they repeat further down, and as 32-bit numbers (left to itself the compiler keeps all, K's and V's chunks widened
+    // to 64 bits: up to 30 registers).
+    template <bool WITH_V = true, bool WITH_K = true, bool RARE = false, bool NARROW = false, typename F>
     __device__ __forceinline__ void issue(const unsigned char* kh, const unsigned char* vh, unsigned char* kl,
                                           unsigned char* vl, F tok) {
         int lane = this->lane;
@@ -189,10 +191,13 @@ struct DirectTile {
         for (int j = 0; j < PER_WAVE; ++j) {
             const int seg = j * NW + wave;
             if (!EVEN && seg >= SEGS) break;
-            const int slot = seg * 64 + lane, row = slot / CH, pos = slot % CH;
-            const uint32_t row_off = static_cast<uint32_t>(tok(row)) * ROW;
-            if (WITH_K) dma16(kh, row_off + 16u * k_chunk(row, pos), lds_offset(kl) + seg * 1024);
-            if (WITH_V) dma16(vh, row_off + 16u * v_slot(row, pos), lds_offset(vl) + seg * 1024);
+            const int like = NARROW ? j % K_VARIANTS : j;  // load `like` is j's, (j - like) loads further up
+            const int slot = (like * NW + wave) * 64 + lane, row = slot / CH, pos = slot % CH;
+            const uint32_t row_off = static_cast<uint32_t>(tok(row + (j - like) * NT / CH)) * ROW;
+            uint32_t k_off = row_off + 16u * k_chunk(row, pos), v_off = row_off + 16u * v_slot(row, pos);
+            if (NARROW) asm volatile("" : "+v"(k_off), "+v"(v_off));
+            if (WITH_K) dma16(kh, k_off, lds_offset(kl) + seg * 1024);
+            if (WITH_V) dma16(vh, v_off, lds_offset(vl) + seg * 1024);
         }
     }
     // same for a tile of 64 consecutive tokens starting at kh / vh.  NARROW: the lane offsets stay 32 bits wide between
