@@ -219,15 +219,16 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     st.init(tid);
     int side_reg = 0;
 
-    // Keys split two ways at head_dim 96: three wavefronts on a SIMD, and two lane numbers too many for their registers, which
-    // are formed again from the thread's where they are wanted: its place in the wavefront, and 8 * hf.
+    // Keys split two ways at head_dim 96: three wavefronts on a SIMD, and some numbers too many for their registers, which
+    // are formed again from the thread's where they are wanted: its place in the wavefront, 8 * hf, its row.
+    constexpr bool kFewLanes = KS == 2 && D == 96;
     auto thread_again = [&]() {
         int thread = tid;
         asm volatile("" : "+v"(thread));
         return thread;
     };
-    auto lane_of_list = [&]() { return KS == 2 && D == 96 ? thread_again() & 63 : lane; };
-    auto half_of_mask = [&]() { return KS == 2 && D == 96 ? (thread_again() & 32) >> 2 : 8 * hf; };
+    auto lane_of_list = [&]() { return kFewLanes ? thread_again() & 63 : lane; };
+    auto half_of_mask = [&]() { return kFewLanes ? (thread_again() & 32) >> 2 : 8 * hf; };
     // Tile entries of a listed query block are read 64 at a time, one per lane, and handed out with
     // v_readlane: no scalar-load latency in the loop.  ent_cur covers [ent_base, ent_base + 64).
     int ent_cur = 0, ent_nxt = 0, ent_base = 0;
@@ -585,11 +586,13 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
                 *part(group, 8 * db + 2 * rq + hf) = w;
             }
         __syncthreads();
-        // row and token formed again, as they would cost registers throughout the tile loop (gathered rows keep theirs: a load)
-        int thread = tid;
-        asm volatile("" : "+v"(thread));
-        const int row = qk.qb * BQ + (thread >> 6) * 32 + (thread & 31), row_c = min(row, N - 1);
-        const int token = gathers(MODE) ? qtok[0] : has_list(MODE) && qk.row_token ? qk.row_token[row_c] : row_c + (row_c < Nv ? pl.video_shift : pl.text_shift);
+        int row = qrow[0], token = qtok[0];
+        if (kFewLanes) {  // (gathered rows keep theirs: a load)
+            const int thread = thread_again();
+            row = qk.qb * BQ + (thread >> 6) * 32 + (thread & 31);
+            const int row_c = min(row, N - 1);
+            if (!gathers(MODE)) token = has_list(MODE) && qk.row_token ? qk.row_token[row_c] : row_c + (row_c < Nv ? pl.video_shift : pl.text_shift);
+        }
         uint16_t* orow = a.O + static_cast<size_t>(qk.bh) * N * D + static_cast<size_t>(token) * D;
 #pragma unroll
         for (int i = 0; i < D / 4 / KS / 2; ++i) {
