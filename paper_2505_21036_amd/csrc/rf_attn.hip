@@ -12,6 +12,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "rf_band.h"
 #include "rf_device.h"
 #include "rf_queues.h"
 
@@ -109,6 +110,7 @@ struct QueryBlock {
     int* sweep;           // null, or: where this workgroup publishes how far its walk has come (see join_sweep)
     int sweep_tag;        // which key sequence the published tile index refers to
     int keyN;             // length of the key sequence walked (N, or Nc when compacted)
+    BandTiles band;       // item kernels, banded modes: what cols would say
 };
 
 // Workgroups of one XCD share that XCD's L2, so they should walk the same key tiles at the same time.
@@ -137,7 +139,7 @@ namespace rf {
 // QH: 32-query halves a wavefront owns (1, or 2: every K and V slab read from LDS then feeds two MFMAs).
 // KS: groups of NW wavefronts that split the walk (group g takes its tiles g, g + KS, ... into LDS of its own
 // and keeps a softmax of its own); the groups' results are added up at the end.
-template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD, int RAISE = RAISE_NONE>
+template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD, int RAISE = RAISE_NONE, bool ITEM = false>
 __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, const QueryBlock& qk, unsigned char* smem_all) {
     constexpr int BQ = 32 * NW * QH;
     using ST = DirectTile<D, NW>;
@@ -168,6 +170,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     const unsigned char* Vh = qk.vbase;
     const uint16_t* Qh = a.Q + static_cast<size_t>(qk.bh) * N * D;
 
+    auto row_of_position_major = [&](int n) {
+        return position_major_row(n, pl.group_rows[kListTemporalPM], pl.group_rows[RF_SPATIAL], Nv, pl.video_shift, pl.text_shift);
+    };
     // this lane's queries, one per half
     int qrow[QH], qtok[QH];
     bf16x8 qf[QH][D / 16];
@@ -176,7 +181,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     for (int h = 0; h < QH; ++h) {
         qrow[h] = qk.qb * BQ + wave * (32 * QH) + 32 * h + m;  // row of the walked order
         const int qrow_c = min(qrow[h], N - 1);
-        qtok[h] = (has_list(MODE) && qk.row_token) ? qk.row_token[qrow_c]
+        qtok[h] = ITEM && MODE == MODE_BAND_GATHER ? row_of_position_major(qrow_c) : (has_list(MODE) && qk.row_token) ? qk.row_token[qrow_c]
                                                         : qrow_c + (qrow_c < Nv ? pl.video_shift : pl.text_shift);
         load_q_frags<D>(Qh, qtok[h], hf, qf[h]);
         // a key of attribute x is kept iff x + q_lo <= q_span (unsigned); text queries keep everything
@@ -232,9 +237,10 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     // Tile entries of a listed query block are read 64 at a time, one per lane, and handed out with
     // v_readlane: no scalar-load latency in the loop.  ent_cur covers [ent_base, ent_base + 64).
     int ent_cur = 0, ent_nxt = 0, ent_base = 0;
+    constexpr bool kComputed = ITEM && is_band(MODE);  // one workgroup per block: no load of the list between its start and its first tile
     auto load_entries = [&](int from) {
         const int j = min((from + lane_of_list()) * KS + group, qk.ntiles - 1) + qk.first;  // the walk starts at entry qk.first and wraps
-        return qk.cols[j < qk.ntiles ? j : j - qk.ntiles];
+        return kComputed ? qk.band.entry(j, keyN, Nv) : qk.cols[j < qk.ntiles ? j : j - qk.ntiles];
     };
     if (has_list(MODE) && ntiles > 0) {
         ent_cur = load_entries(0);
@@ -256,9 +262,13 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     };
     // side data is needed for every gathered tile, and for partial tiles masked by the table
     auto wants_side = [&](int entry) { return gathers(MODE) || (MODE == MODE_LISTED && (entry & RF_PLAN_PARTIAL)); };
-    auto load_side = [&](int entry) {
+    auto load_side = [&](int entry, bool first = false) {
         if (!wants_side(entry)) return;
         const int k0 = (entry & kTileIndexMask) * kTileK;
+        if (ITEM && first && MODE == MODE_BAND_GATHER) {  // nor of the table (cheaper than the arithmetic, but for its latency)
+            if (tid < kTileK) side_reg = row_of_position_major(min(k0 + tid, keyN - 1));
+            return;
+        }
         if (tid < kTileK) side_reg = side_src[min(k0 + tid, keyN - 1)];
     };
     auto stash_side = [&](int t, int entry) {
@@ -426,7 +436,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     for (int i = 0; i < DEPTH; ++i)
         if (i < ntiles) {
             e[i] = entry_of(i);
-            load_side(e[i]);
+            load_side(e[i], true);
             if (AHEAD == 0 && !gathers(MODE)) fetch_k(i, e[i]);
             stash_side(i, e[i]);
         }
@@ -768,7 +778,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
         else {
             QueryBlock rows = block;  // the lists are the block's, the rows this workgroup's part of it
             if constexpr (LOOP == LOOP_ITEM && workgroups_per_block(NW) > 1) rows.qb = block.qb * workgroups_per_block(NW) + part;
-            attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE)>(a, plan, rows, smem);
+            attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE), LOOP == LOOP_ITEM>(a, plan, rows, smem);
         }
     };
     int ordinal, bh;  // position in the block order, and the head
@@ -783,16 +793,14 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
     }
     const DevicePlan& pl = a.plan[which];
     // One item per workgroup: what stands between its start and its first tile are these loads, one after the
-    // other, so the list bounds of every pattern are asked for along with the class, and the blocks keep their order.
+    // other, so the list bounds of the one pattern whose list is read are asked for along with the class, and the blocks keep
+    // their order.
     constexpr bool kOneItem = LOOP == LOOP_ITEM;
-    int lo[kLists] = {}, hi[kLists] = {};
+    int lo = 0, hi = 0;
     if constexpr (kOneItem) {
         qk.qb = ordinal < qs.nTB ? qs.nVB + ordinal : ordinal - qs.nTB;
-#pragma unroll
-        for (int l = 0; l < kLists; ++l) {
-            lo[l] = pl.row_ptr[l][qk.qb];
-            hi[l] = pl.row_ptr[l][qk.qb + 1];
-        }
+        lo = pl.row_ptr[RF_TEXTURAL][qk.qb];
+        hi = pl.row_ptr[RF_TEXTURAL][qk.qb + 1];
     }
     int cls = a.head_class ? a.head_class[qk.bh] : RF_DENSE;
     if (static_cast<unsigned>(cls) > 3u) cls = RF_DENSE;
@@ -853,11 +861,20 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
             }
             qk.video_shift = qk.text_shift = 0;
         }
-        auto of_list = [&](const int (&v)[kLists]) { return list == 0 ? v[0] : list == 1 ? v[1] : list == 2 ? v[2] : v[3]; };
-        const int e0 = kOneItem ? of_list(lo) : pl.row_ptr[list][qk.qb];
-        qk.ntiles = (kOneItem ? of_list(hi) : pl.row_ptr[list][qk.qb + 1]) - e0;
-        qk.cols = pl.cols[list] + e0;
-        if constexpr (!kOneItem) qk.first = pl.first_entry[list][qk.qb];
+        if constexpr (kOneItem) {
+            if (cls == RF_TEXTURAL) {
+                qk.ntiles = hi - lo;
+                qk.cols = pl.cols[RF_TEXTURAL] + lo;
+            } else {
+                qk.band = BandTiles(qk.qb * pl.block, pl.block, pl.group_rows[list], pl.radius[list], pl.N, pl.Nv);
+                qk.ntiles = qk.band.tiles;
+            }
+        } else {
+            const int e0 = pl.row_ptr[list][qk.qb];
+            qk.ntiles = pl.row_ptr[list][qk.qb + 1] - e0;
+            qk.cols = pl.cols[list] + e0;
+            qk.first = pl.first_entry[list][qk.qb];
+        }
         qk.keyN = pl.N;
         qk.sweep_tag = tag_of(temporal_pm ? 2 : 0);
         if (same_sequence() && qk.ntiles > 0) {
