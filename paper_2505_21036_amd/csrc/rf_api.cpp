@@ -367,6 +367,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     if (named && named->rows < 256 && g.N > kSmallBlockTokens) return RF_ERR_PARAM;  // no such lists
     a.queued = form.queued ? 1 : 0;
     a.key_groups = form.key_groups;
+    a.three_to_a_cu = form.key_groups == 2 && D == 96 && three_to_a_cu(g, B * nH, force_dense) ? 1 : 0;
     a.n_plans = bandwidths ? n_bw : 1;
     for (int k = 0; k < a.n_plans; ++k) {
         Geometry gk = g;

@@ -139,7 +139,7 @@ namespace rf {
 // QH: 32-query halves a wavefront owns (1, or 2: every K and V slab read from LDS then feeds two MFMAs).
 // KS: groups of NW wavefronts that split the walk (group g takes its tiles g, g + KS, ... into LDS of its own
 // and keeps a softmax of its own); the groups' results are added up at the end.
-template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD, int RAISE = RAISE_NONE, bool ITEM = false>
+template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD, int RAISE = RAISE_NONE, bool ITEM = false, bool FEW = false>
 __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, const QueryBlock& qk, unsigned char* smem_all) {
     constexpr int BQ = 32 * NW * QH;
     using ST = DirectTile<D, NW>;
@@ -149,9 +149,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     unsigned char* smem = smem_all + group * SM::GROUP_BYTES;
     // how many slabs ahead of their MFMAs the LDS operand reads run: with two halves every slab feeds two
     // MFMAs and the registers are all in use, and two measured best (dense CogVideoX-shaped layer 4.25 ->
-    // 3.99 ms against the depths of the one-half loop); twelve wavefronts at head_dim 128 and keys split two ways at 96
+    // 3.99 ms against the depths of the one-half loop); twelve wavefronts at head_dim 128 and keys split two ways at 96 (FEW)
     // have 168 registers each, which the loops fit (but for a spill or two off the common path) at depth two
-    constexpr bool kTight = (NW == 12 && D == 128) || (KS == 2 && D == 96);
+    constexpr bool kTight = (NW == 12 && D == 128) || FEW;
     constexpr int AK = (QH == 2 || kTight) ? 2 : kAheadK, AV = (QH == 2 || kTight) ? 2 : kAheadV;
     const int tid = threadIdx.x - group * (64 * NW), lane = tid & 63, wave = tid >> 6, hf = lane >> 5, m = lane & 31;
     const int N = pl.N, keyN = qk.keyN;
@@ -224,16 +224,15 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     st.init(tid);
     int side_reg = 0;
 
-    // Keys split two ways at head_dim 96: three wavefronts on a SIMD, and some numbers too many for their registers, which
-    // are formed again from the thread's where they are wanted: its place in the wavefront, 8 * hf, its row.
-    constexpr bool kFewLanes = KS == 2 && D == 96;
+    // FEW: some numbers too many for the registers, which are formed again from the thread's where they are wanted: its place
+    // in the wavefront, 8 * hf, its row.
     auto thread_again = [&]() {
         int thread = tid;
         asm volatile("" : "+v"(thread));
         return thread;
     };
-    auto lane_of_list = [&]() { return kFewLanes ? thread_again() & 63 : lane; };
-    auto half_of_mask = [&]() { return kFewLanes ? (thread_again() & 32) >> 2 : 8 * hf; };
+    auto lane_of_list = [&]() { return FEW ? thread_again() & 63 : lane; };
+    auto half_of_mask = [&]() { return FEW ? (thread_again() & 32) >> 2 : 8 * hf; };
     // Tile entries of a listed query block are read 64 at a time, one per lane, and handed out with
     // v_readlane: no scalar-load latency in the loop.  ent_cur covers [ent_base, ent_base + 64).
     int ent_cur = 0, ent_nxt = 0, ent_base = 0;
@@ -278,13 +277,13 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     auto k_lds = [&](int t) { return smem + SM::K_OFF + (t % DEPTH) * ST::K_BYTES; };
     auto v_lds = [&](int t) { return smem + SM::V_OFF + (t % DEPTH) * ST::V_BYTES; };
     // three workgroups of four wavefronts per CU at head_dim 96 have 168 registers each, too few for lane offsets of 64 bits
-    constexpr bool kNarrow = D == 96 && ((NW == 4 && KS == 1 && MODE == MODE_BAND) || KS == 2);
+    constexpr bool kNarrow = FEW || (D == 96 && NW == 4 && KS == 1 && MODE == MODE_BAND);
     auto fetch_some = [&](auto with_v, auto with_k, int t, int entry) {
         constexpr bool WV = decltype(with_v)::value, WK = decltype(with_k)::value;
         const int k0 = (entry & kTileIndexMask) * kTileK;
         if (gathers(MODE)) {
             const int* idx = side + (t % SM::SIDE_SLOTS) * kTileK;
-            st.template issue<WV, WK, false, kNarrow && KS == 2>(Kh, Vh, k_lds(t), v_lds(t), [&](int row) { return idx[row]; });
+            st.template issue<WV, WK, false, FEW>(Kh, Vh, k_lds(t), v_lds(t), [&](int row) { return idx[row]; });
         } else if (k0 + kTileK <= keyN && !(qk.text_shift != 0 && k0 < Nv && k0 + kTileK > Nv)) {
             // full tile of consecutive tensor rows: everything but the tile origin is loop invariant
             const int r0 = k0 + (k0 < Nv ? qk.video_shift : qk.text_shift);
@@ -597,7 +596,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
             }
         __syncthreads();
         int row = qrow[0], token = qtok[0];
-        if (kFewLanes) {  // (gathered rows keep theirs: a load)
+        if (FEW) {  // (gathered rows keep theirs: a load)
             const int thread = thread_again();
             row = qk.qb * BQ + (thread >> 6) * 32 + (thread & 31);
             const int row_c = min(row, N - 1);
@@ -701,7 +700,7 @@ __device__ __forceinline__ int take_item(int* ctr, int home, const Queues<false>
     }
 }
 
-template <int D, int NW, int LOOP, int KS = 1, int AHEAD = RF_TILES_AHEAD>
+template <int D, int NW, int LOOP, int KS = 1, int AHEAD = RF_TILES_AHEAD, bool FEW = false>
 __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem, int part = 0);
 
 // Eight queue counters, then the sweep words (-1: nothing published yet).  One workgroup, one thread per word.
@@ -765,12 +764,12 @@ __global__ void __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_
     constexpr int PARTS = workgroups_per_block(NW);
     const int xcd = blockIdx.x & 7, item = (blockIdx.x >> 3) / PARTS, part = (blockIdx.x >> 3) % PARTS;
     if (item >= qs.items(xcd)) return;
-    process_item<D, NW, LOOP_ITEM, KS, AHEAD>(a, item, xcd, -1, qs, smem, part);
+    process_item<D, NW, LOOP_ITEM, KS, AHEAD, D == 96 && KS == 2 && WAVES == 3>(a, item, xcd, -1, qs, smem, part);
 }
 
 // One (head, query block) item: item-th of queue xcd.  seen: the sweep word of this workgroup's XCD
 // (it serves its own L2, whichever queue the item came from), or -1.
-template <int D, int NW, int LOOP, int KS, int AHEAD>
+template <int D, int NW, int LOOP, int KS, int AHEAD, bool FEW>
 __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem, int part) {
     auto run = [&](auto mode, const DevicePlan& plan, const QueryBlock& block) {
         constexpr int MODE = decltype(mode)::value;
@@ -778,7 +777,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
         else {
             QueryBlock rows = block;  // the lists are the block's, the rows this workgroup's part of it
             if constexpr (LOOP == LOOP_ITEM && workgroups_per_block(NW) > 1) rows.qb = block.qb * workgroups_per_block(NW) + part;
-            attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE), LOOP == LOOP_ITEM>(a, plan, rows, smem);
+            attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE), LOOP == LOOP_ITEM, FEW>(a, plan, rows, smem);
         }
     };
     int ordinal, bh;  // position in the block order, and the head
@@ -987,9 +986,7 @@ static int launch_items(const AttnArgs& a, hipStream_t st) {
 }
 
 // The item kernels of one head_dim: 64 rows with the keys split four or two ways, 128 rows, 256 rows (not at
-// head_dim 64, where 128 rows measured 6 % faster).  Wavefronts per SIMD: three where the registers allow it.  (Keys split two
-// ways at head_dim 96, two wavefronts a SIMD / three: 24 heads of 4109 tokens 122.5 / 117.5 us, dense 213.7 / 202.5, 34 of 5540
-// 286.6 / 255.7; with the spills that three had before their loops kept fewer lane offsets, 0.86-0.94 of the speed of two.)
+// head_dim 64, where 128 rows measured 6 % faster).  Wavefronts per SIMD: three where the registers allow it.
 template <int D>
 static int launch_items_d(const AttnArgs& a, hipStream_t st) {
     if (a.plan[0].block == 64 && a.key_groups == 4) {
@@ -1003,7 +1000,13 @@ static int launch_items_d(const AttnArgs& a, hipStream_t st) {
         if (2 * queues_of<true>(a).items(0) <= kCUsPerXCD) return launch_items<D, 1, 4, 0, 2>(a, st);
         return launch_items<D, 2, 4, 0, 2>(a, st);
     }
-    if (a.plan[0].block == 64 && a.key_groups == 2) return launch_items<D, 2, 2, 0, D == 128 ? 2 : 3>(a, st);
+    if (a.plan[0].block == 64 && a.key_groups == 2) {
+        // at head_dim 96 three leave the loops few registers (FEW in attend): see three_to_a_cu
+        if constexpr (D == 96) {
+            if (!a.three_to_a_cu) return launch_items<D, 2, 2, 0, 2>(a, st);
+        }
+        return launch_items<D, 2, 2, 0, D == 128 ? 2 : 3>(a, st);
+    }
     if (a.plan[0].block == 128) return launch_items<D, 4, 1, 0, D == 128 ? 2 : 3>(a, st);
     if constexpr (D != 64)
         if (a.plan[0].block == 256) return launch_items<D, 8, 1, 1, 2>(a, st);

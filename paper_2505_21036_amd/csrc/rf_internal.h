@@ -96,6 +96,8 @@ AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room);
 // are summed up, so a head's bits are the same in any batch, on any share of the heads and with any workspace only if
 // none of these decides the form.  Without copies, and best on the (geometric) mean of 12, 24 and 48 heads.
 AttnForm choose_fixed_form(const Geometry& g, int D);
+// Keys split two ways at head_dim 96: whether three workgroups to a CU (three wavefronts a SIMD) are faster than two.
+bool three_to_a_cu(const Geometry& g, int BH, bool dense);
 // The form with these numbers, if head_dim D has one.
 bool find_form(int D, int rows, int key_groups, bool queued, AttnForm* form);
 
@@ -136,6 +138,7 @@ struct AttnArgs {
     int item_order;          // ORDER_*: which items an XCD takes, and when (rf_queues.h)
     int queued;              // see AttnForm
     int key_groups;          // see AttnForm
+    int three_to_a_cu;       // keys split two ways at head_dim 96: see the function of that name
     int wide_rows;           // 1: wavefronts of 64 query rows (256-row blocks only)
     int join_sweep;          // 1: a starting item joins the tile walk of the workgroups already running on its XCD; 0: fixed start
     int n_plans;

@@ -415,6 +415,21 @@ static double mixed_cost(const Kernel& k, const Geometry& g, int BH, int D, doub
     return cube * cube * cube * launch_us(k, g, BH, D, true, textural);  // tenth power of the weighted geometric mean
 }
 
+// The two kernels of that form by the same model, the third workgroup's numbers fitted to 25 sizes of 3813 to 9040 tokens, 8 to 34
+// heads, 28 to 512 text tokens, bandwidths 1/4 and 0.13.  Three are 1.03-1.12 times as fast where the launch is many rounds (14
+// heads of 6006 164.3 -> 149.6 us, 24 of 4109 123.3 -> 117.1), but each is slower by itself: where the launch waits for the long
+// walks of its text blocks (those 6006 at 0.13, 125.3 -> 135.5) or three leave the last round nearly empty (12 of 5140 113.1 ->
+// 122.8) two stay.  The line, 5 %, leaves none of the 25 slower and gives away 1 % on the mean.
+bool three_to_a_cu(const Geometry& g, int BH, bool dense) {
+    const Kernel& two = kKernels[1][1];
+    Kernel three = two;
+    three.per_cu = 3;
+    three.tile_us = 1.58;
+    three.text_tile_us = 1.30;
+    const double textural = textural_tiles(g);
+    return launch_us(three, g, BH, 96, dense, textural) < 0.95 * launch_us(two, g, BH, 96, dense, textural);
+}
+
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
     const double textural = textural_tiles(g);
     // without room a form with copies would walk Temporal heads in token order: up to twice the time

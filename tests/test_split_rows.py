@@ -2,6 +2,10 @@
 wavefronts have tiles of their own; otherwise one's.  On both sides of that line a head's output is the same bits, and the
 oracle's within the suite's bounds, where the last block has rows in its second half and where it has none, with and
 without text, with the masks of all patterns, with more groups than tiles and with a tile left over."""
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -11,9 +15,8 @@ import paper_2505_21036_amd as rf
 import rf_inputs as inp
 from attn_forms import attention_as
 
-pytestmark = pytest.mark.gpu
 
-
+@pytest.mark.gpu
 @pytest.mark.parametrize("D", [64, 96, 128])
 @pytest.mark.parametrize("lay,text_first", [((2, 3, 5, 0), False), ((3, 7, 9, 5), False), ((2, 8, 10, 0), False), ((4, 9, 13, 45), False),
                                             ((4, 9, 13, 45), True), ((5, 11, 8, 0), False), ((7, 10, 13, 50), False)])
@@ -42,3 +45,48 @@ def test_both_ways_of_a_block(D, lay, text_first):
         err = torch.roll(O[0, h], -shift, dims=0).double().cpu().numpy() - ref
         rel = np.linalg.norm(err) / np.linalg.norm(ref)
         assert np.abs(err).max() <= 2e-2 and np.abs(err).mean() <= 2e-3 and rel <= 5.2e-3, (h, rel)
+
+
+# Keys split two ways at head_dim 96: layouts and how often four heads are repeated for three workgroups to a CU
+THREE = [((4, 9, 13, 45), False, 60), ((4, 9, 13, 45), True, 60), ((5, 11, 8, 0), False, 70), ((7, 10, 13, 50), False, 40)]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_two_and_three_workgroups_to_a_cu_are_both_reached(tmp_path):
+    src, exe, root = tmp_path / "three.cpp", str(tmp_path / "three"), os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src.write_text("""#include <cstdio>
+#include "rf_internal.h"
+int main() {
+    int T, H, W, text, BH;
+    while (std::scanf("%d %d %d %d %d", &T, &H, &W, &text, &BH) == 5) {
+        const rf_layout layout = {T, H, W, text};
+        rf::Geometry g;
+        if (rf::resolve_geometry(&layout, nullptr, &g) != RF_OK) return 1;
+        std::printf("%d\\n", rf::three_to_a_cu(g, BH, false) ? 1 : 0);
+    }
+    return 0;
+}
+""")
+    csrc = os.path.join(root, "paper_2505_21036_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(root, "include"), "-I", csrc, str(src), os.path.join(csrc, "rf_plan.cpp"), "-o", exe])
+    lines = ["%d %d %d %d %d" % (*lay, nH) for lay, _, times in THREE for nH in (4, 4 * times)]
+    said = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.split()
+    assert said == ["0", "1"] * len(THREE)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lay,text_first,times", THREE)
+def test_two_and_three_workgroups_to_a_cu_give_the_same_bits(lay, text_first, times):
+    T, H, W, tl = lay
+    print("case", lay, text_first, times, flush=True)
+    rl, N = rf.rf_layout(T, H, W, tl), T * H * W + tl
+    rp = rf.rf_params(0.25, 0.25, 2, 0, rf.RF_FLAG_TEXT_FIRST if text_first else 0)
+    g = torch.Generator(device="cuda").manual_seed(9400 + N)
+    Q, K, V = ((3.0 * torch.randn(1, 4, N, 96, generator=g, device="cuda")).bfloat16() for _ in range(3))
+    classes = torch.arange(4, dtype=torch.int32, device="cuda").reshape(1, 4)
+    O = attention_as((64, 2, 0), Q, K, V, classes, rl, rp)  # the oracle's within bounds: the suite's other tests of this form
+    many = attention_as((64, 2, 0), *(t.repeat(1, times, 1, 1) for t in (Q, K, V)), classes.repeat(1, times), rl, rp,
+                        out=torch.full((1, 4 * times, N, 96), float("nan"), dtype=torch.bfloat16, device="cuda"))
+    torch.cuda.synchronize()
+    for i in range(times):
+        assert torch.equal(many[:, 4 * i:4 * i + 4], O), i
