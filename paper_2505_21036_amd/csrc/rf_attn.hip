@@ -110,7 +110,7 @@ struct QueryBlock {
     int* sweep;           // null, or: where this workgroup publishes how far its walk has come (see join_sweep)
     int sweep_tag;        // which key sequence the published tile index refers to
     int keyN;             // length of the key sequence walked (N, or Nc when compacted)
-    BandTiles band;       // item kernels, banded modes: what cols would say
+    BandTiles band;       // COMPUTED, banded modes: what cols would say
 };
 
 // Workgroups of one XCD share that XCD's L2, so they should walk the same key tiles at the same time.
@@ -139,7 +139,7 @@ namespace rf {
 // QH: 32-query halves a wavefront owns (1, or 2: every K and V slab read from LDS then feeds two MFMAs).
 // KS: groups of NW wavefronts that split the walk (group g takes its tiles g, g + KS, ... into LDS of its own
 // and keeps a softmax of its own); the groups' results are added up at the end.
-template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD, int RAISE = RAISE_NONE, bool ITEM = false, bool FEW = false>
+template <int D, int NW, int MODE, int QH = 1, int KS = 1, int TILES_AHEAD = RF_TILES_AHEAD, int RAISE = RAISE_NONE, bool COMPUTED = false, bool FEW = false>
 __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, const QueryBlock& qk, unsigned char* smem_all) {
     constexpr int BQ = 32 * NW * QH;
     using ST = DirectTile<D, NW>;
@@ -181,7 +181,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     for (int h = 0; h < QH; ++h) {
         qrow[h] = qk.qb * BQ + wave * (32 * QH) + 32 * h + m;  // row of the walked order
         const int qrow_c = min(qrow[h], N - 1);
-        qtok[h] = ITEM && MODE == MODE_BAND_GATHER ? row_of_position_major(qrow_c) : (has_list(MODE) && qk.row_token) ? qk.row_token[qrow_c]
+        qtok[h] = COMPUTED && MODE == MODE_BAND_GATHER ? row_of_position_major(qrow_c) : (has_list(MODE) && qk.row_token) ? qk.row_token[qrow_c]
                                                         : qrow_c + (qrow_c < Nv ? pl.video_shift : pl.text_shift);
         load_q_frags<D>(Qh, qtok[h], hf, qf[h]);
         // a key of attribute x is kept iff x + q_lo <= q_span (unsigned); text queries keep everything
@@ -236,10 +236,10 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     // Tile entries of a listed query block are read 64 at a time, one per lane, and handed out with
     // v_readlane: no scalar-load latency in the loop.  ent_cur covers [ent_base, ent_base + 64).
     int ent_cur = 0, ent_nxt = 0, ent_base = 0;
-    constexpr bool kComputed = ITEM && is_band(MODE);  // one workgroup per block: no load of the list between its start and its first tile
+    // COMPUTED: no load of a list or a table between the workgroup's start and its first tile
     auto load_entries = [&](int from) {
         const int j = min((from + lane_of_list()) * KS + group, qk.ntiles - 1) + qk.first;  // the walk starts at entry qk.first and wraps
-        return kComputed ? qk.band.entry(j, keyN, Nv) : qk.cols[j < qk.ntiles ? j : j - qk.ntiles];
+        return COMPUTED && is_band(MODE) ? qk.band.entry(j, keyN, Nv) : qk.cols[j < qk.ntiles ? j : j - qk.ntiles];
     };
     if (has_list(MODE) && ntiles > 0) {
         ent_cur = load_entries(0);
@@ -264,7 +264,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
     auto load_side = [&](int entry, bool first = false) {
         if (!wants_side(entry)) return;
         const int k0 = (entry & kTileIndexMask) * kTileK;
-        if (ITEM && first && MODE == MODE_BAND_GATHER) {  // nor of the table (cheaper than the arithmetic, but for its latency)
+        if (COMPUTED && first && MODE == MODE_BAND_GATHER) {  // (a load is cheaper than the arithmetic, but for its latency)
             if (tid < kTileK) side_reg = row_of_position_major(min(k0 + tid, keyN - 1));
             return;
         }
@@ -771,13 +771,16 @@ __global__ void __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_
 // (it serves its own L2, whichever queue the item came from), or -1.
 template <int D, int NW, int LOOP, int KS, int AHEAD, bool FEW>
 __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xcd, int seen, const Queues<LOOP == LOOP_ITEM>& qs, unsigned char* smem, int part) {
+    // Where few rows leave a launch bound by latency, the tiles of a band are worked out; the others' items are long enough for
+    // the loads of the list not to show (15 heads of 4340 tokens, head_dim 128, 256 rows 103.3 / 104.2 us worked out).
+    constexpr bool kComputed = LOOP == LOOP_ITEM && KS > 1;
     auto run = [&](auto mode, const DevicePlan& plan, const QueryBlock& block) {
         constexpr int MODE = decltype(mode)::value;
         if constexpr (LOOP == LOOP_64_PIPELINED) attend_wide<D, NW, MODE>(a, plan, block, smem);
         else {
             QueryBlock rows = block;  // the lists are the block's, the rows this workgroup's part of it
             if constexpr (LOOP == LOOP_ITEM && workgroups_per_block(NW) > 1) rows.qb = block.qb * workgroups_per_block(NW) + part;
-            attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE), LOOP == LOOP_ITEM, FEW>(a, plan, rows, smem);
+            attend<D, NW, MODE, rows_per_wave(LOOP) / 32, KS, AHEAD, raise_of(D, NW, KS, LOOP != LOOP_ITEM, MODE), kComputed, FEW>(a, plan, rows, smem);
         }
     };
     int ordinal, bh;  // position in the block order, and the head
@@ -792,14 +795,18 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
     }
     const DevicePlan& pl = a.plan[which];
     // One item per workgroup: what stands between its start and its first tile are these loads, one after the
-    // other, so the list bounds of the one pattern whose list is read are asked for along with the class, and the blocks keep
-    // their order.
+    // other, so the list bounds (where they are read: of every pattern) are asked for along with the class, and the blocks
+    // keep their order.
     constexpr bool kOneItem = LOOP == LOOP_ITEM;
-    int lo = 0, hi = 0;
+    int lo[kLists] = {}, hi[kLists] = {};
     if constexpr (kOneItem) {
         qk.qb = ordinal < qs.nTB ? qs.nVB + ordinal : ordinal - qs.nTB;
-        lo = pl.row_ptr[RF_TEXTURAL][qk.qb];
-        hi = pl.row_ptr[RF_TEXTURAL][qk.qb + 1];
+#pragma unroll
+        for (int l = 0; l < kLists; ++l) {
+            if (kComputed && l != RF_TEXTURAL) continue;
+            lo[l] = pl.row_ptr[l][qk.qb];
+            hi[l] = pl.row_ptr[l][qk.qb + 1];
+        }
     }
     int cls = a.head_class ? a.head_class[qk.bh] : RF_DENSE;
     if (static_cast<unsigned>(cls) > 3u) cls = RF_DENSE;
@@ -860,19 +867,15 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, int item, int xc
             }
             qk.video_shift = qk.text_shift = 0;
         }
-        if constexpr (kOneItem) {
-            if (cls == RF_TEXTURAL) {
-                qk.ntiles = hi - lo;
-                qk.cols = pl.cols[RF_TEXTURAL] + lo;
-            } else {
-                qk.band = BandTiles(qk.qb * pl.block, pl.block, pl.group_rows[list], pl.radius[list], pl.N, pl.Nv);
-                qk.ntiles = qk.band.tiles;
-            }
+        if (kComputed && cls != RF_TEXTURAL) {
+            qk.band = BandTiles(qk.qb * pl.block, pl.block, pl.group_rows[list], pl.radius[list], pl.N, pl.Nv);
+            qk.ntiles = qk.band.tiles;
         } else {
-            const int e0 = pl.row_ptr[list][qk.qb];
-            qk.ntiles = pl.row_ptr[list][qk.qb + 1] - e0;
+            auto of_list = [&](const int (&v)[kLists]) { return list == 0 ? v[0] : list == 1 ? v[1] : list == 2 ? v[2] : v[3]; };
+            const int e0 = kOneItem ? of_list(lo) : pl.row_ptr[list][qk.qb];
+            qk.ntiles = (kOneItem ? of_list(hi) : pl.row_ptr[list][qk.qb + 1]) - e0;
             qk.cols = pl.cols[list] + e0;
-            qk.first = pl.first_entry[list][qk.qb];
+            if constexpr (!kOneItem) qk.first = pl.first_entry[list][qk.qb];
         }
         qk.keyN = pl.N;
         qk.sweep_tag = tag_of(temporal_pm ? 2 : 0);
