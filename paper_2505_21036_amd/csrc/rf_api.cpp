@@ -367,7 +367,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
     if (named && named->rows < 256 && g.N > kSmallBlockTokens) return RF_ERR_PARAM;  // no such lists
     a.queued = form.queued ? 1 : 0;
     a.key_groups = form.key_groups;
-    a.three_to_a_cu = form.key_groups == 2 && D == 96 && three_to_a_cu(g, B * nH, force_dense) ? 1 : 0;
+    a.three_to_a_cu = form.key_groups == 2 && D == 96 ? 1 : 0;
     a.n_plans = bandwidths ? n_bw : 1;
     for (int k = 0; k < a.n_plans; ++k) {
         Geometry gk = g;
@@ -375,6 +375,7 @@ static int sparse_attention_impl(const void* Q, const void* K, const void* V, co
             st = geometry_with_bandwidth(layout, params, bandwidths[k], &gk);
             if (st != RF_OK) return st;
         }
+        if (a.three_to_a_cu && !three_to_a_cu(gk, B * nH, force_dense)) a.three_to_a_cu = 0;  // by the narrowest bandwidth
         st = get_attention_plan(gk, form.rows, a.wide_rows != 0, &a.plan[k]);
         if (st != RF_OK) return st;
     }

@@ -336,8 +336,9 @@ double textural_tiles(const Geometry& g) {
     return (static_cast<double>(kept) * g.T + g.text_len) / kTileK;
 }
 
-// Tiles of 64 keys that a block of `rows` rows visits on the average over the three patterns.
-double mean_tiles(const Geometry& g, int rows, double textural) {
+// Tiles of 64 keys that a block of `rows` rows visits under each pattern.
+struct PatternTiles { double spatial, temporal, textural; };
+PatternTiles pattern_tiles(const Geometry& g, int rows, double textural) {
     const double tiles = (g.N + kTileK - 1) / kTileK;
     // a band of radius r over n groups of `group` rows: its share of the pairs, and what blocks and tiles that are not
     // aligned with the groups take in beside it
@@ -347,7 +348,12 @@ double mean_tiles(const Geometry& g, int rows, double textural) {
         const double beside = rows - std::gcd(rows, group) + kTileK - std::gcd(kTileK, group);
         return std::min(tiles, (share * g.Nv + beside + g.text_len) / kTileK);
     };
-    return (band(g.T, g.r_spatial, g.HW) + band(g.HW, g.r_temporal, g.T) + textural) / 3;
+    return {band(g.T, g.r_spatial, g.HW), band(g.HW, g.r_temporal, g.T), textural};
+}
+// The same on the average over the three.
+double mean_tiles(const Geometry& g, int rows, double textural) {
+    const PatternTiles p = pattern_tiles(g, rows, textural);
+    return (p.spatial + p.temporal + p.textural) / 3;
 }
 
 // Time of a launch in form k, us; HUGE_VAL if the form is not to be taken at this size.  textural: textural_tiles(g).
@@ -415,19 +421,22 @@ static double mixed_cost(const Kernel& k, const Geometry& g, int BH, int D, doub
     return cube * cube * cube * launch_us(k, g, BH, D, true, textural);  // tenth power of the weighted geometric mean
 }
 
-// The two kernels of that form by the same model, the third workgroup's numbers fitted to 25 sizes of 3813 to 9040 tokens, 8 to 34
-// heads, 28 to 512 text tokens, bandwidths 1/4 and 0.13.  Three are 1.03-1.12 times as fast where the launch is many rounds (14
-// heads of 6006 164.3 -> 149.6 us, 24 of 4109 123.3 -> 117.1), but each is slower by itself: where the launch waits for the long
-// walks of its text blocks (those 6006 at 0.13, 125.3 -> 135.5) or three leave the last round nearly empty (12 of 5140 113.1 ->
-// 122.8) two stay.  The line, 5 %, leaves none of the 25 slower and gives away 1 % on the mean.
+// A third workgroup on a CU hides more, but each is slower by itself.  Measured both ways at 2883 drawn sizes (1500 to 100000 tokens, 1
+// to 40 heads, bandwidths 0.13 to 1/2, classes in turn or all the same; a third of them in profiles/two_or_three_to_a_cu.txt), the rule
+// from 1191 of them: three pay where they make one round of what two would start a second for (512 to 768 blocks, no text: 1.16-1.24 of
+// the speed of two; with fewer than 8 heads down to 0.94), and from three rounds on (1.05-1.11), unless the launch waits for the walks of its
+// text blocks, which visit every tile and are 1.1 times as long with three: then down to 0.87 (4 heads of 22697, 0.13, Temporal 348 us -> 391).  So
+// a text block's tiles may be 0.9 of what a slot has to visit if all heads are of the shortest pattern.  Of the 2883 it takes three at 501,
+// 1.11 on the mean, none below 0.98 (the two runs of one kernel differ by as much), and leaves 3 % or more to be had at 1070 others,
+// whose classes, unknown here, decide.  Dense calls: 0.99 below one round, too few of them in this form beyond.
 bool three_to_a_cu(const Geometry& g, int BH, bool dense) {
-    const Kernel& two = kKernels[1][1];
-    Kernel three = two;
-    three.per_cu = 3;
-    three.tile_us = 1.58;
-    three.text_tile_us = 1.30;
-    const double textural = textural_tiles(g);
-    return launch_us(three, g, BH, 96, dense, textural) < 0.95 * launch_us(two, g, BH, 96, dense, textural);
+    constexpr int kCUs = 256;  // MI355X
+    const double tiles = (g.N + kTileK - 1) / kTileK, items = tiles * BH;  // a block has as many rows as a tile has keys
+    if (dense) return false;
+    if (items < 3 * 2 * kCUs) return g.text_len == 0 && BH >= 8 && items > 2 * kCUs && items <= 3 * kCUs;
+    if (g.text_len == 0) return true;
+    const PatternTiles p = pattern_tiles(g, kTileK, textural_tiles(g));
+    return tiles <= 0.9 * items / (2 * kCUs) * std::min({p.spatial, p.temporal, p.textural});
 }
 
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {

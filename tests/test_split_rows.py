@@ -90,3 +90,36 @@ def test_two_and_three_workgroups_to_a_cu_give_the_same_bits(lay, text_first, ti
     torch.cuda.synchronize()
     for i in range(times):
         assert torch.equal(many[:, 4 * i:4 * i + 4], O), i
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_a_third_workgroup_to_a_cu_is_not_taken_where_it_is_slower(tmp_path):
+    """Replays the times of both kernels (profiles/two_or_three_to_a_cu.txt) through the rule.  Runs of one kernel differ by 1-3 %."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    with open(os.path.join(root, "profiles", "two_or_three_to_a_cu.txt")) as f:
+        rows = [l.split() for l in f if not l.startswith("#")][1:]
+    src, exe, csrc = tmp_path / "rule.cpp", str(tmp_path / "rule"), os.path.join(root, "paper_2505_21036_amd", "csrc")
+    src.write_text("""#include <cstdio>
+#include "rf_internal.h"
+int main() {
+    int T, H, W, text, BH;
+    float bw;
+    while (std::scanf("%d %d %d %d %d %f", &T, &H, &W, &text, &BH, &bw) == 6) {
+        const rf_layout layout = {T, H, W, text};
+        const rf_params params = {bw, bw, 2, 0, 0};
+        rf::Geometry g;
+        if (rf::resolve_geometry(&layout, &params, &g) != RF_OK || rf::three_to_a_cu(g, BH, true)) return 1;  // dense calls never
+        std::printf("%d\\n", rf::three_to_a_cu(g, BH, false) ? 1 : 0);
+    }
+    return 0;
+}
+""")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(root, "include"), "-I", csrc, str(src), os.path.join(csrc, "rf_plan.cpp"), "-o", exe])
+    said = subprocess.run([exe], input="\n".join(" ".join(r[:6]) for r in rows), capture_output=True, text=True, check=True).stdout.split()
+    assert len(said) == len(rows) > 500
+    for draw in ("fit", "held"):
+        gain = {r: float(r[7]) / float(r[8]) for r, s in zip(map(tuple, rows), said) if s == "1" and r[9] == draw}
+        worst = min(gain, key=gain.get)
+        mean = np.exp(np.mean(np.log(list(gain.values()))))
+        print(draw, len(gain), "mean %.3f worst %.3f at %s" % (mean, gain[worst], worst))
+        assert len(gain) >= 50 and gain[worst] >= 0.97 and mean >= 1.05
