@@ -478,67 +478,73 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const DevicePlan& pl, 
         const bool mine = (KS == 1 && !is_band(MODE)) || kind != 2;
         f32x16 s[QH][2];
         if (kOwnTiles && t < ntiles) ST::wait_all_but_one_tensor();  // K(t) is there, V(t) on its way
-        if (mine) {
-        if (RAISE == RAISE_SCORES || RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
-        scores(t, e_cur, is_band(MODE) ? kind == 1 : (e_cur & RF_PLAN_PARTIAL) != 0, s);
-        if (RAISE != RAISE_NONE) __builtin_amdgcn_s_setprio(RAISE == RAISE_SOFTMAX ? 1 : 0);
-        }
-        if (kOwnTiles && t + 1 < ntiles) {
-            stash_side(t + 1, e[1]);
-            fetch_k(t + 1, e[1]);
-        }
-        if (mine) {
+        auto form_scores = [&]() {
+            if (RAISE == RAISE_SCORES || RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
+            scores(t, e_cur, is_band(MODE) ? kind == 1 : (e_cur & RF_PLAN_PARTIAL) != 0, s);
+            if (RAISE != RAISE_NONE) __builtin_amdgcn_s_setprio(RAISE == RAISE_SOFTMAX ? 1 : 0);
+        };
+        auto weigh = [&]() {
 #pragma unroll
-        for (int h = 0; h < QH; ++h) {
-            float mt = s[h][0][0];
+            for (int h = 0; h < QH; ++h) {
+                float mt = s[h][0][0];
 #pragma unroll
-            for (int kb2 = 0; kb2 < 2; ++kb2)
+                for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[h][kb2][r]);
-            // the two halves of the wavefront hold different keys of the same 32 queries: their maxima
-            // are exchanged only when some lane asks for the reference to move
-            if (__builtin_amdgcn_ballot_w64(fmaf(mt, c, -m_ref[h]) > kRescaleSlack) != 0) {
-                mt = fmaxf(mt, other_half(mt));
-                if (mt > -INFINITY) {
-                    const float m_new = fmaxf(m_ref[h], mt * c), alpha = fast_exp2(m_ref[h] - m_new);
-                    l_run[h] *= alpha;
+                    for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[h][kb2][r]);
+                // the two halves of the wavefront hold different keys of the same 32 queries: their maxima
+                // are exchanged only when some lane asks for the reference to move
+                if (__builtin_amdgcn_ballot_w64(fmaf(mt, c, -m_ref[h]) > kRescaleSlack) != 0) {
+                    mt = fmaxf(mt, other_half(mt));
+                    if (mt > -INFINITY) {
+                        const float m_new = fmaxf(m_ref[h], mt * c), alpha = fast_exp2(m_ref[h] - m_new);
+                        l_run[h] *= alpha;
 #pragma unroll
-                    for (int db = 0; db < D / 32; ++db)
+                        for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) oacc[h][db][r] *= alpha;
-                    m_ref[h] = m_new;
+                            for (int r = 0; r < 16; ++r) oacc[h][db][r] *= alpha;
+                        m_ref[h] = m_new;
+                    }
                 }
+                // p = exp2(s * c - m_ref) in place
+#pragma unroll
+                for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[h][kb2][r] = fast_exp2(fmaf(s[h][kb2][r], c, -m_ref[h]));
+                // P is rounded to bf16 for the second MFMA; the denominator sums those same rounded values
+                // (two per v_dot2c_f32_bf16), so numerator and denominator of Eq. 2 see identical weights
+#pragma unroll
+                for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+                    for (int u2 = 0; u2 < 2; ++u2) {
+                        u32x4 w;
+                        w.x = pack_bf16(s[h][kb2][8 * u2 + 0], s[h][kb2][8 * u2 + 1]);
+                        w.y = pack_bf16(s[h][kb2][8 * u2 + 2], s[h][kb2][8 * u2 + 3]);
+                        w.z = pack_bf16(s[h][kb2][8 * u2 + 4], s[h][kb2][8 * u2 + 5]);
+                        w.w = pack_bf16(s[h][kb2][8 * u2 + 6], s[h][kb2][8 * u2 + 7]);
+                        l_run[h] = add_bf16_pair(add_bf16_pair(add_bf16_pair(add_bf16_pair(l_run[h], w.x), w.y), w.z), w.w);
+                        pf[h][2 * kb2 + u2] = as_bf16x8(w);
+                    }
             }
-            // p = exp2(s * c - m_ref) in place
-#pragma unroll
-            for (int kb2 = 0; kb2 < 2; ++kb2)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[h][kb2][r] = fast_exp2(fmaf(s[h][kb2][r], c, -m_ref[h]));
-            // P is rounded to bf16 for the second MFMA; the denominator sums those same rounded values
-            // (two per v_dot2c_f32_bf16), so numerator and denominator of Eq. 2 see identical weights
-#pragma unroll
-            for (int kb2 = 0; kb2 < 2; ++kb2)
-#pragma unroll
-                for (int u2 = 0; u2 < 2; ++u2) {
-                    u32x4 w;
-                    w.x = pack_bf16(s[h][kb2][8 * u2 + 0], s[h][kb2][8 * u2 + 1]);
-                    w.y = pack_bf16(s[h][kb2][8 * u2 + 2], s[h][kb2][8 * u2 + 3]);
-                    w.z = pack_bf16(s[h][kb2][8 * u2 + 4], s[h][kb2][8 * u2 + 5]);
-                    w.w = pack_bf16(s[h][kb2][8 * u2 + 6], s[h][kb2][8 * u2 + 7]);
-                    l_run[h] = add_bf16_pair(add_bf16_pair(add_bf16_pair(add_bf16_pair(l_run[h], w.x), w.y), w.z), w.w);
-                    pf[h][2 * kb2 + u2] = as_bf16x8(w);
-                }
-        }
-        if (RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
-        else if (RAISE == RAISE_SOFTMAX) __builtin_amdgcn_s_setprio(0);
-        if constexpr (AHEAD > 0) accumulate(t);
-        }
+            if (RAISE == RAISE_PRODUCTS) __builtin_amdgcn_s_setprio(1);
+            else if (RAISE == RAISE_SOFTMAX) __builtin_amdgcn_s_setprio(0);
+            if constexpr (AHEAD > 0) accumulate(t);
+        };
         if constexpr (kOwnTiles) {
+            if (mine) form_scores();
+            if (t + 1 < ntiles) {
+                stash_side(t + 1, e[1]);
+                fetch_k(t + 1, e[1]);
+            }
+            if (mine) weigh();
             if (t + 1 < ntiles) ST::wait_all_but_one_tensor();  // V(t) is there, K(t + 1) on its way
             else ST::template wait_landed<0>();
             if (mine) accumulate(t);
             e[0] = e[1];
             continue;
+        }
+        if (mine) {  // one block: asked twice, 24 heads of 17776 tokens at head_dim 128 (128 rows) took 2016 us, not 1959
+            form_scores();
+            weigh();
         }
         if constexpr (AHEAD == 0) {
             ST::template wait_landed<0>();

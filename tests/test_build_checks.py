@@ -80,6 +80,17 @@ def test_twelve_wavefront_kernel_fits_its_registers():
     assert m and int(m.group(1)) <= 168
 
 
+@pytest.mark.parametrize("D,waves", [(64, 3), (96, 2), (128, 2)])
+def test_whether_a_tile_is_its_rows_is_asked_once(D, waves):
+    """Performance guard: a tile's scores and its softmax are one block.  As two, each behind the same question, every step of
+    every kernel took two more branches and the scores' registers were copied (1 % with the keys split two ways, 2 % with 128 rows
+    and from queues).  Looked at in the walk of a compacted sequence, the plainest that asks."""
+    loops = _tile_loops(device_assembly("rf_attn.hip"), "_ZN2rf16attn_item_kernelILi%dELi2ELi2ELi0ELi%dEEEvNS_8AttnArgsE" % (D, waves), D // 4)
+    gathered = [b for b in loops if any(x.startswith("ds_read") and "tr" not in x and "b128" not in x for x in b)]
+    plainest = min(gathered, key=len)
+    assert sum("s_cbranch" in x for x in plainest) <= 16  # 18 as two blocks
+
+
 def test_no_tile_loop_reloads_from_scratch():
     """The same for every kernel instance of both files: the tile loops of the attention (D / 4 MFMAs per tile and 32
     query rows) and of the ARM (D / 8) hold no access to scratch.  The pipelined loop for 64-row wavefronts, which runs
