@@ -200,6 +200,25 @@ struct DirectTile {
             if (WITH_V) dma16(vh, v_off, lds_offset(vl) + seg * 1024);
         }
     }
+    // The same in two steps, for a wavefront that loads the K and later the V of a tile: where the rows of this lane's loads
+    // start, and the loads.
+    template <typename F>
+    __device__ __forceinline__ void find_rows(uint32_t (&row_off)[PER_WAVE], F tok) const {
+#pragma unroll
+        for (int j = 0; j < PER_WAVE; ++j) row_off[j] = static_cast<uint32_t>(tok(((j * NW + wave) * 64 + lane) / CH)) * ROW;
+    }
+    template <bool V>
+    __device__ __forceinline__ void issue_rows(const unsigned char* base, unsigned char* to, const uint32_t (&row_off)[PER_WAVE]) const {
+        static_assert(EVEN, "every wavefront issues every round");
+#pragma unroll
+        for (int j = 0; j < PER_WAVE; ++j) {
+            // load `like` takes the same chunks of its rows, and there are few of those to keep
+            const int like = j % (V ? V_VARIANTS : K_VARIANTS), slot = (like * NW + wave) * 64 + lane, row = slot / CH, pos = slot % CH;
+            uint32_t off = row_off[j] + 16u * (V ? v_slot(row, pos) : k_chunk(row, pos));
+            asm volatile("" : "+v"(off));  // 32 bits wide: see issue
+            dma16(base, off, lds_offset(to) + (j * NW + wave) * 1024);
+        }
+    }
     // same for a tile of 64 consecutive tokens starting at kh / vh.  NARROW: the lane offsets stay 32 bits wide between
     // calls; left to itself the compiler keeps each beside a register that holds its upper half, zero
     template <bool WITH_V = true, bool WITH_K = true, bool NARROW = false>

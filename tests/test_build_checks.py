@@ -91,6 +91,22 @@ def test_whether_a_tile_is_its_rows_is_asked_once(D, waves):
     assert sum("s_cbranch" in x for x in plainest) <= 16  # 18 as two blocks
 
 
+@pytest.mark.parametrize("D", [64, 96, 128])
+def test_gathered_rows_are_asked_for_without_waiting_for_the_tile_before(D):
+    """Performance guard: wavefronts with tiles of their own ask for the next K as soon as the scores are formed.  A row number
+    put in LDS between the scores' MFMAs and those loads would wait for every load, of which V is on its way; and the row
+    numbers are read for K alone, once per load."""
+    loops = _tile_loops(device_assembly("rf_attn.hip"), "_ZN2rf16attn_item_kernelILi%dELi1ELi4ELi0ELi2EEEvNS_8AttnArgsE" % D, D // 4)
+    reads = [[x for x in b if re.match(r"ds_read\w*_b(32|64) ", x) and "tr" not in x] for b in loops]
+    assert any(reads)
+    for body, rows in zip(loops, reads):
+        if not rows:
+            continue
+        events = "".join("M" if x.startswith("v_mfma") else "L" if "global_load_lds" in x else "w" if x.startswith("ds_write_b32") else "" for x in body)
+        assert "Mw" not in events, events
+        assert sum(2 if "read2" in x else 1 for x in rows) == D // 8, rows  # loads per tensor
+
+
 def test_no_tile_loop_reloads_from_scratch():
     """The same for every kernel instance of both files: the tile loops of the attention (D / 4 MFMAs per tile and 32
     query rows) and of the ARM (D / 8) hold no access to scratch.  The pipelined loop for 64-row wavefronts, which runs
