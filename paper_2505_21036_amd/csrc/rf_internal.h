@@ -70,9 +70,10 @@ struct HostPlan {
 int resolve_geometry(const rf_layout* layout, const rf_params* params, Geometry* g);
 
 // Builds the token tables and the block lists. Pure host code.  token_order_temporal: also the Temporal list in token
-// order, the longest to build, which only RF_FLAG_WIDE_ROWS walks; without it that list is empty.
+// order, the longest to build, which only RF_FLAG_WIDE_ROWS walks; banded: the Spatial list and the Temporal one in
+// position-major order.  Without them those lists are empty.
 void build_tables(const Geometry& g, TokenTables* tables);
-void build_plan(const Geometry& g, const TokenTables& tables, int block, bool token_order_temporal, HostPlan* plan);
+void build_plan(const Geometry& g, const TokenTables& tables, int block, bool token_order_temporal, HostPlan* plan, bool banded = true);
 void build_plan(const Geometry& g, int block, HostPlan* plan);  // tables of its own, every list
 
 // How an attention call runs: query rows a workgroup takes at a time (64, 128, 256 or 384), groups of its

@@ -150,7 +150,7 @@ void build_plan(const Geometry& g, int block, HostPlan* plan) {
     build_plan(g, tables, block, true, plan);
 }
 
-void build_plan(const Geometry& g, const TokenTables& tables, int block, bool token_order_temporal, HostPlan* plan) {
+void build_plan(const Geometry& g, const TokenTables& tables, int block, bool token_order_temporal, HostPlan* plan, bool with_banded) {
     HostPlan& P = *plan;
     P.g = g;
     P.block = block;
@@ -173,7 +173,7 @@ void build_plan(const Geometry& g, const TokenTables& tables, int block, bool to
         auto& co = P.cols[cls];
         rp.assign(P.nQB + 1, 0);
         co.clear();
-        if (cls == RF_TEMPORAL && !token_order_temporal) continue;
+        if ((cls == RF_TEMPORAL && !token_order_temporal) || (banded && !with_banded)) continue;
         // of the video keys of every tile: the groups they lie in, or which of them the Textural pattern keeps
         for (int kb = 0; kb < P.nKT; ++kb) {
             const int k0 = kb * kTileK, kv1 = std::min(k0 + kTileK, Nv);
