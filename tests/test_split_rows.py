@@ -47,8 +47,68 @@ def test_both_ways_of_a_block(D, lay, text_first):
         assert np.abs(err).max() <= 2e-2 and np.abs(err).mean() <= 2e-3 and rel <= 5.2e-3, (h, rel)
 
 
+def sampled_rows(N, Nv, seed):
+    """The first rows, the last ones, those around the end of the video tokens, and some between."""
+    rows = set(range(8)) | set(range(N - 8, N)) | {n for n in range(Nv - 4, Nv + 4) if n < N}
+    return np.array(sorted(rows | set(np.random.default_rng(seed).integers(0, N, 40).tolist())))
+
+
+def check_rows(O, w, h, cls, ol, op, shift, scale, rows):
+    """Rows of O [N, D], in the tensor's order, against the oracle; rows: numbers with the text behind; the suite's bounds."""
+    q, k, v = (t.float().numpy() for t in inp.head_qkv(w, 0, h, scale))
+    ref = orc.attention_rows(q, k, v, cls, ol, op, rows)
+    err = torch.roll(O, -shift, dims=0)[torch.as_tensor(rows, device=O.device)].double().cpu().numpy() - ref
+    rel = np.linalg.norm(err) / np.linalg.norm(ref)
+    assert np.abs(err).max() <= 2e-2 and np.abs(err).mean() <= 2e-3 and rel <= 5.2e-3, (h, cls, rel)
+
+
+# Wavefronts with tiles of their own near the end of their range: 60 and 120 tiles, 15 and 30 to a wavefront.
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("lay,text_first", [((7, 20, 27, 61), False), ((7, 20, 27, 61), True), ((11, 18, 38, 0), False), ((5, 31, 47, 226), False)])
+def test_long_walks_without_barriers(D, lay, text_first):
+    T, H, W, tl = lay
+    rl, ol = rf.rf_layout(T, H, W, tl), orc.Layout(T, H, W, tl)
+    rp, op = rf.rf_params(0.4, 0.4, 2, 0, rf.RF_FLAG_TEXT_FIRST if text_first else 0), orc.Params(0.4, 0.4)
+    w = inp.Workload("long_rows", 1, 1, D, T, H, W, tl, 64, 9500 + D + T)
+    shift, scale = (tl if text_first else 0), 5.0
+    assert (w.N + 63) // 64 <= 8 * 15  # one head: a CU for each half
+    Q, K, V = (torch.roll(t, shift, dims=2).contiguous() for t in inp.full_qkv(w, "cuda:0", scale))
+    for cls in range(4):
+        print("case", D, lay, text_first, cls, flush=True)
+        classes = torch.full((1, 1), cls, dtype=torch.int32, device="cuda")
+        O = attention_as((64, 4, 0), Q, K, V, classes, rl, rp, out=torch.full_like(Q, float("nan")))
+        many = attention_as((64, 4, 0), *(t.repeat(1, 3, 1, 1) for t in (Q, K, V)), classes.repeat(1, 3), rl, rp)  # two wavefronts to a tile
+        torch.cuda.synchronize()
+        assert all(torch.equal(many[:, i], O[:, 0]) for i in range(3)), cls
+        check_rows(O[0, 0], w, 0, cls, ol, op, shift, scale, sampled_rows(w.N, w.Nv, D))
+
+
+# More than 64 tiles to a group: its entries are worked out, or read, 64 at a time.  192 tiles, of which a band of half of all
+# frames and positions visits some 145; at head_dim 96 both kernels.
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,times", [(64, 1), (96, 3), (128, 1)])
+@pytest.mark.parametrize("text_first", [False, True])
+def test_walks_of_more_than_64_tiles_to_a_group(D, times, text_first):
+    T, H, W, tl = 5, 43, 55, 426
+    print("case", D, text_first, flush=True)
+    rl, ol = rf.rf_layout(T, H, W, tl), orc.Layout(T, H, W, tl)
+    rp, op = rf.rf_params(0.5, 0.5, 2, 0, rf.RF_FLAG_TEXT_FIRST if text_first else 0), orc.Params(0.5, 0.5)
+    w = inp.Workload("long_lists", 1, 4, D, T, H, W, tl, 64, 9600 + D)
+    shift, scale = (tl if text_first else 0), 5.0
+    Q, K, V = (torch.roll(t, shift, dims=2).contiguous() for t in inp.full_qkv(w, "cuda:0", scale))
+    classes = torch.arange(4, dtype=torch.int32, device="cuda").reshape(1, 4)
+    O = attention_as((64, 2, 0), Q, K, V, classes, rl, rp, out=torch.full_like(Q, float("nan")))
+    many = attention_as((64, 2, 0), *(t.repeat(1, times, 1, 1) for t in (Q, K, V)), classes.repeat(1, times), rl, rp)
+    torch.cuda.synchronize()
+    for i in range(times):
+        assert torch.equal(many[:, 4 * i:4 * i + 4], O), i
+    for h in range(4):
+        check_rows(O[0, h], w, h, h, ol, op, shift, scale, sampled_rows(w.N, w.Nv, D))
+
+
 # Keys split two ways at head_dim 96: layouts and how often four heads are repeated for three workgroups to a CU
-THREE = [((4, 9, 13, 45), False, 60), ((4, 9, 13, 45), True, 60), ((5, 11, 8, 0), False, 70), ((7, 10, 13, 50), False, 40)]
+THREE = [((4, 9, 13, 45), False, 60), ((4, 9, 13, 45), True, 60), ((5, 11, 8, 0), False, 70), ((7, 10, 13, 50), False, 40), ((5, 43, 55, 426), False, 3)]
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
