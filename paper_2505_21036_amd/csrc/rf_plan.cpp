@@ -421,20 +421,23 @@ static double mixed_cost(const Kernel& k, const Geometry& g, int BH, int D, doub
     return cube * cube * cube * launch_us(k, g, BH, D, true, textural);  // tenth power of the weighted geometric mean
 }
 
-// A third workgroup on a CU hides more, but each is slower by itself.  Measured both ways at 2883 drawn sizes (1500 to 100000 tokens, 1
-// to 40 heads, bandwidths 0.13 to 1/2, classes in turn or all the same; a third of them in profiles/two_or_three_to_a_cu.txt), the rule
-// from 1191 of them: three pay where they make one round of what two would start a second for (512 to 768 blocks, no text: 1.16-1.24 of
-// the speed of two; with fewer than 8 heads down to 0.94), and from three rounds on (1.05-1.11), unless the launch waits for the walks of its
-// text blocks, which visit every tile and are 1.1 times as long with three: then down to 0.87 (4 heads of 22697, 0.13, Temporal 348 us -> 391).  So
-// a text block's tiles may be 0.9 of what a slot has to visit if all heads are of the shortest pattern.  Of the 2883 it takes three at 501,
-// 1.11 on the mean, none below 0.98 (the two runs of one kernel differ by as much), and leaves 3 % or more to be had at 1070 others,
-// whose classes, unknown here, decide.  Dense calls: 0.99 below one round, too few of them in this form beyond.
+// A third workgroup on a CU hides more, but each is slower by itself.  Measured both ways at 5962 drawn sizes (150 to 60000 tokens, 1 to 120
+// heads, bandwidths 0.13 to 1/2), each with the classes in turn and with all heads of one (one in ten: profiles/two_or_three_to_a_cu.txt);
+// the lines were drawn from 3662 of them, and the other 2300 agree.  Three pay
+//   - where they make one round of what two would start a second for, 512 to 768 blocks: without text 1.20 of the speed of two, from 8
+//     heads on (below, down to 0.89); with text from 32 heads on, 1.17, with all heads Textural 1.01 (0.90 to 1.2).  With fewer the launch
+//     waits for the walks of its text blocks, which visit every tile and take 1.1 times as long with three (Textural 0.94, down to 0.89);
+//   - in many rounds: from three on if a text block's tiles are at most 0.9 of what a slot has to visit if all heads are of the shortest
+//     pattern (1.08; beyond, down to 0.87), and where 24 heads or more give the text blocks company, from 2.25 on (1.10).
+// Between those, 1.5 to 2 rounds: 0.97 to 1.02.  With the classes in turn 1.13 on the mean of the 1830 sizes that take three, the worst
+// 0.93, 14 of them below 0.97.  Dense calls: 0.99 below one round, too few of them in this form beyond.
 bool three_to_a_cu(const Geometry& g, int BH, bool dense) {
     constexpr int kCUs = 256;  // MI355X
     const double tiles = (g.N + kTileK - 1) / kTileK, items = tiles * BH;  // a block has as many rows as a tile has keys
-    if (dense) return false;
-    if (items < 3 * 2 * kCUs) return g.text_len == 0 && BH >= 8 && items > 2 * kCUs && items <= 3 * kCUs;
-    if (g.text_len == 0) return true;
+    if (dense || items <= 2 * kCUs) return false;
+    if (items <= 3 * kCUs) return BH >= (g.text_len > 0 ? 32 : 8);
+    if (items < 6 * kCUs) return BH >= 24 && items >= 4.5 * kCUs;
+    if (BH >= 24 || g.text_len == 0) return true;
     const PatternTiles p = pattern_tiles(g, kTileK, textural_tiles(g));
     return tiles <= 0.9 * items / (2 * kCUs) * std::min({p.spatial, p.temporal, p.textural});
 }

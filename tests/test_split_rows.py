@@ -154,7 +154,8 @@ def test_two_and_three_workgroups_to_a_cu_give_the_same_bits(lay, text_first, ti
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_a_third_workgroup_to_a_cu_is_not_taken_where_it_is_slower(tmp_path):
-    """Replays the times of both kernels (profiles/two_or_three_to_a_cu.txt) through the rule.  Runs of one kernel differ by 1-3 %."""
+    """Replays the times of both kernels (profiles/two_or_three_to_a_cu.txt) through the rule: classes in turn, and all of one.
+    Runs of one kernel differ by 1-3 %, a few by 5."""
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     with open(os.path.join(root, "profiles", "two_or_three_to_a_cu.txt")) as f:
         rows = [l.split() for l in f if not l.startswith("#")][1:]
@@ -177,9 +178,10 @@ int main() {
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(root, "include"), "-I", csrc, str(src), os.path.join(csrc, "rf_plan.cpp"), "-o", exe])
     said = subprocess.run([exe], input="\n".join(" ".join(r[:6]) for r in rows), capture_output=True, text=True, check=True).stdout.split()
     assert len(said) == len(rows) > 500
-    for draw in ("fit", "held"):
-        gain = {r: float(r[7]) / float(r[8]) for r, s in zip(map(tuple, rows), said) if s == "1" and r[9] == draw}
-        worst = min(gain, key=gain.get)
-        mean = np.exp(np.mean(np.log(list(gain.values()))))
-        print(draw, len(gain), "mean %.3f worst %.3f at %s" % (mean, gain[worst], worst))
-        assert len(gain) >= 50 and gain[worst] >= 0.97 and mean >= 1.05
+    for draw in ("lines", "held"):
+        taken = np.array([[float(x) for x in r[6:16]] for r, one in zip(rows, said) if one == "1" and r[16] == draw])
+        gain = taken[:, 0::2] / taken[:, 1::2]  # classes in turn, Spatial, Temporal, Textural, dense
+        means, worst = np.exp(np.log(gain).mean(0)), gain.min(0)
+        print(draw, len(gain), "means", means.round(3), "worst", worst.round(3))
+        assert len(gain) >= 50 and means[0] >= 1.1 and means.min() >= 1.05
+        assert worst[[0, 1, 2, 4]].min() >= 0.92 and worst[3] >= 0.88
