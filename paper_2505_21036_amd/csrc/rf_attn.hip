@@ -1029,8 +1029,7 @@ static int launch_items_d(const AttnArgs& a, hipStream_t st) {
         // head_dim 128, 20.5 / 17.3 with and 16.6 / 14.4 without text, 64 11.7 / 10.2; 1 of 7936, 128, 60.3 / 46.7; 2 of
         // 4032, 96, dense 33.5 / 26.6; 2 of 256, 64, 7.4 / 6.7.  With a CU short (17 blocks on an XCD): 4 of 2030, 128, dense
         // 24.2 / 37.3, 21 of 380, 96, 11.8 / 14.2; two to a CU, which fit at 64: 2 of 8192 33.2 / 36.2, 10 of 1600 12.6 / 14.4.
-        constexpr int kCUsPerXCD = 32;  // MI355X
-        if (2 * queues_of<true>(a).items(0) <= kCUsPerXCD) return launch_items<D, 1, 4, 0, 2>(a, st);
+        if (halves_have_cus(queues_of<true>(a).items(0))) return launch_items<D, 1, 4, 0, 2>(a, st);
         return launch_items<D, 2, 4, 0, 2>(a, st);
     }
     if (a.plan[0].block == 64 && a.key_groups == 2) {

@@ -248,17 +248,17 @@ namespace {
 // What a launch takes in each form, us: the model by which the form is chosen.  The numbers are fitted to the times
 // that the kernels without wave priorities had at 107 sizes (256 to 119056 tokens, 1 to 160 heads), dense and with the
 // three patterns in turn at bandwidth 1/4 and stride 2, and at 58 of them at bandwidths 1/8 to 1/2 and strides 1 to 4.
-// They were not fitted again; over the times that the same sizes have taken since (profiles/forms_sweep.txt) the form
-// they pick is, on the geometric mean, 0.3 % from the best where all heads are dense (1.2 % at head_dim
-// 64) and 1.1 to 2.2 % with the patterns; the worst are 17 to 34 %, mostly a few heads of short layouts with text.  Few
-// rows: keys split four ways, then two ways (16 heads of 960 tokens, head_dim 128: 22 us, 26 and with 128 rows 39; 24
-// heads of 4109: 186, 151 and 170).  Many: the forms with the most rows do the least per row and tile (48 heads of
-// 17776: 5.0, 4.6 and 4.0 ms for these, 3.84 and 3.68 with 256 rows from the grid and from queues, 3.57 with 384; 24 of 48000, dense:
-// 26.5 ms with 128 rows, 24.6 with 256, 23.4 with 384).  Between them what counts is how full the last round of
+// They were not fitted again, but for the two kernels that changed most (kThreeToACu, and choose_form for few blocks); over the
+// present kernels' times at the same sizes (profiles/forms_sweep.txt) the form they pick is, on the geometric mean, 0.2 % from the best
+// where all heads are dense (1.2 % at head_dim 64) and 1.2 to 2.4 % with the patterns; the worst are 7 to 33 %, mostly a few heads of short
+// layouts with text.  Few rows: keys split four ways, then two ways (16 heads of 960 tokens, head_dim 128: 21 us, 25 and with 128 rows 39;
+// 24 heads of 4109: 175, 147 and 168).  Many: the forms with the most rows do the least per row and tile (48 heads of
+// 17776: 4.7, 4.4 and 3.8 ms for these, 3.62 and 3.60 with 256 rows from the grid and from queues, 3.58 with 384; 24 of 48000, dense:
+// 26.4 ms with 128 rows, 24.5 with 256, 23.4 with 384).  Between them what counts is how full the last round of
 // workgroups is, on the fullest XCD where the XCDs cannot help each other.
 //
 // At head_dim 64 the model has 256 rows from queues slower than they are with the priorities (48 heads of 17776 tokens, patterns
-// in turn: 2316 us when it was fitted, 2086 since, against 2163 with 128 rows), so some sizes with room for copies stay with 128
+// in turn: 2316 us when it was fitted, 2062 since, against 2102 with 128 rows), so some sizes with room for copies stay with 128
 // rows, in whose launches every block starts at a fixed tile: their O is the same bits in every call.
 //
 // copies: up to 256 rows, rows gathered through an index table cost nothing that can be measured, so no copies are
@@ -304,6 +304,11 @@ const Kernel kKernels[3][kForms] = {{{{64, 4, false, false}, 1, 0.478, 5.0, 0, 0
                                      {{256, 1, false, false}, 1, 2.250, 7.1, 0, 0.707, 1.23, 2.70},
                                      {{256, 1, true, false}, 1, 2.196, 6.8, 0, 0.762, 1.07, 2.85},
                                      {{384, 1, true, true}, 1, 3.043, 6.3, 0, 0.775, 1.22, 3.70}}};
+// 64 rows, keys split two ways, at head_dim 96 where three workgroups to a CU make one round (three_to_a_cu).  Fitted to the sizes of the
+// sweep at which three are taken.  With the numbers of two the model is 1.31 too long there: 160 heads of 256 tokens took 256 rows, 18.9
+// us, not 13.4, 24 of 1536 33.5, not 24.9.  From three rounds on the numbers of two stay: there 128 rows are even (us, keys split / 128
+// rows: 120 heads of 960 50.4 / 51.9, 160 63.5 / 62.0, 72 of 2000 100 / 95).
+const Kernel kThreeToACu = {{64, 2, false, false}, 3, 1.525, 6.0, 0.81, 0.70, 1.20, 1.34};
 const Chip kChips[3] = {{4.4, 0.51, 0.05, 0.15, 6.1, 0.46, 1.11, 1.02, 0.40, 0.112, -0.048},
                         {3.2, 0.50, 0.13, 0.08, 4.9, 0.30, 1.08, 1.03, 0.52, 0.103, -0.090},
                         {2.6, 0.53, 0.10, 0.08, 6.6, 0.24, 1.07, 1.03, 0.51, 0.087, -0.112}};
@@ -356,9 +361,17 @@ double mean_tiles(const Geometry& g, int rows, double textural) {
     return (p.spatial + p.temporal + p.textural) / 3;
 }
 
+// Items of the fullest XCD of a launch from the grid whose heads are nVB + nTB blocks each.
+int most_items(const Geometry& g, int BH, int D, bool dense, int nVB, int nTB) {
+    return Queues<true>(BH, nVB, nTB, item_order(!whole_heads_fit(g, D), false, dense, BH, static_cast<long long>(nVB + nTB) * BH)).items(0);
+}
+
 // Time of a launch in form k, us; HUGE_VAL if the form is not to be taken at this size.  textural: textural_tiles(g).
-double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense, double textural) {
+double launch_us(const Kernel& of_form, const Geometry& g, int BH, int D, bool dense, double textural) {
     constexpr int kCUs = 256;  // MI355X
+    const bool one_round_of_three = D == 96 && of_form.form.key_groups == 2 && three_to_a_cu(g, BH, dense) &&
+                                    static_cast<long long>((g.N + 63) / 64) * BH <= 3 * kCUs;
+    const Kernel& k = one_round_of_three ? kThreeToACu : of_form;
     const Chip& chip = kChips[index_of(D)];
     const int rows = k.form.rows;
     if (rows < 256 && g.N > kSmallBlockTokens) return HUGE_VAL;
@@ -373,8 +386,7 @@ double launch_us(const Kernel& k, const Geometry& g, int BH, int D, bool dense, 
     double rounds = items / slots;
     if (!k.form.queued) {  // what the fullest XCD has to do; beyond some thousand heads all are equally full
         const int heads = std::min(BH, 4096);
-        const int most = Queues<true>(heads, nVB, nTB, item_order(far, false, dense, BH, static_cast<long long>(nQB) * BH)).items(0);
-        rounds = 8.0 * most * (static_cast<double>(BH) / heads) / slots;
+        rounds = 8.0 * most_items(g, heads, D, dense, nVB, nTB) * (static_cast<double>(BH) / heads) / slots;
     }
     rounds *= 1 + longs / items * (text_item / item - 1);
     // how long an item takes where n workgroups share the chip, relative to a full one
@@ -443,6 +455,13 @@ bool three_to_a_cu(const Geometry& g, int BH, bool dense) {
 }
 
 AttnForm choose_form(const Geometry& g, int BH, int D, bool dense, bool room) {
+    // Few blocks: two workgroups to each, whose wavefronts have tiles of their own (launch_items_d).  The model does not know
+    // them, and need not: on this side of the line they are the fastest at all 111 sizes of the sweep, by up to 1.5 (2 heads of 1536
+    // tokens at head_dim 64, 9.7 us against 14.4 with the keys split two ways), and 1.00-1.33 times as fast as what the model takes at
+    // 180 drawn ones; with one or two tiles, which leave groups idle, 0.92 at worst.
+    const int nQB = (g.N + kTileK - 1) / kTileK, nTB = g.text_len > 0 ? nQB - g.Nv / kTileK : 0;
+    AttnForm few;
+    if (nQB >= 3 && static_cast<long long>(nQB) * BH <= 8 * 16 && halves_have_cus(most_items(g, BH, D, dense, nQB - nTB, nTB)) && find_form(D, 64, 4, false, &few)) return few;
     const double textural = textural_tiles(g);
     // without room a form with copies would walk Temporal heads in token order: up to twice the time
     return cheapest(D, room || dense, [&](const Kernel& k) { return dense ? launch_us(k, g, BH, D, true, textural) : mixed_cost(k, g, BH, D, textural); });

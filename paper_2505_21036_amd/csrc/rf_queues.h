@@ -104,4 +104,10 @@ struct Queues {
     }
 };
 
+// Keys split four ways: whether each half of a 64-row block can be a workgroup with a CU to itself.  items: of the fullest XCD.
+RF_BOTH bool halves_have_cus(int items) {
+    constexpr int kCUsPerXCD = 32;  // MI355X
+    return 2 * items <= kCUsPerXCD;
+}
+
 }  // namespace rf
