@@ -1025,10 +1025,11 @@ static int launch_items_d(const AttnArgs& a, hipStream_t st) {
     if (a.plan[0].block == 64 && a.key_groups == 4) {
         // A launch this small is bound by latency: two loads of memory, a barrier and a tile's worth of dependent work one
         // after the other in every step.  As two workgroups of 32 rows a block's steps are half as long and have no barrier, as
-        // long as each has a CU to itself; the sums, and so the bits, are the same.  us, 64 rows / 32: 6 heads of 960 tokens,
-        // head_dim 128, 20.5 / 17.3 with and 16.6 / 14.4 without text, 64 11.7 / 10.2; 1 of 7936, 128, 60.3 / 46.7; 2 of
-        // 4032, 96, dense 33.5 / 26.6; 2 of 256, 64, 7.4 / 6.7.  With a CU short (17 blocks on an XCD): 4 of 2030, 128, dense
-        // 24.2 / 37.3, 21 of 380, 96, 11.8 / 14.2; two to a CU, which fit at 64: 2 of 8192 33.2 / 36.2, 10 of 1600 12.6 / 14.4.
+        // long as each has a CU to itself; the sums, and so the bits, are the same.  us, 64 rows / 32: 6 heads of 960 tokens, head_dim
+        // 128, 20.2 / 17.2 with and 16.6 / 12.5 without text, 64 15.5 / 13.3; 1 of 7936, 128, Spatial 61.9 / 49.2, Temporal 46.5 / 35.0;
+        // 2 of 4032, 96, dense 32.9 / 24.8, classes in turn 24.4 / 19.4; 2 of 256, 64, 7.7 / 6.7.  With a CU short (17 or 18 blocks on an
+        // XCD): 4 of 2112, 128, dense 24.2 / 37.2, Temporal 19.4 / 26.6, 23 of 380, 96, dense 8.6 / 14.3; at 64, where two fit a CU, 2 of
+        // 8192 34.2 / 38.9, 10 of 1600 dense 14.7 / 15.6, classes in turn 15.4 / 13.5.
         if (halves_have_cus(queues_of<true>(a).items(0))) return launch_items<D, 1, 4, 0, 2>(a, st);
         return launch_items<D, 2, 4, 0, 2>(a, st);
     }

@@ -1,5 +1,5 @@
 // What the lists of the banded patterns and the table of the position-major order say, by arithmetic, for workgroups that
-// work one block and would wait for both before their first tile: the same on the host and on the device.
+// split a block's keys and would wait for both before their first tile: the same on the host and on the device.
 #pragma once
 #include "rf_internal.h"
 #if defined(__HIPCC__)

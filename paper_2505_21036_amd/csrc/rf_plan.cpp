@@ -250,7 +250,7 @@ namespace {
 // three patterns in turn at bandwidth 1/4 and stride 2, and at 58 of them at bandwidths 1/8 to 1/2 and strides 1 to 4.
 // They were not fitted again, but for the two kernels that changed most (kThreeToACu, and choose_form for few blocks); over the
 // present kernels' times at the same sizes (profiles/forms_sweep.txt) the form they pick is, on the geometric mean, 0.2 % from the best
-// where all heads are dense (1.2 % at head_dim 64) and 1.2 to 2.4 % with the patterns; the worst are 7 to 33 %, mostly a few heads of short
+// where all heads are dense (1.2 % at head_dim 64) and 1.3 to 2.2 % with the patterns; the worst are 7 to 33 %, mostly a few heads of short
 // layouts with text.  Few rows: keys split four ways, then two ways (16 heads of 960 tokens, head_dim 128: 21 us, 25 and with 128 rows 39;
 // 24 heads of 4109: 175, 147 and 168).  Many: the forms with the most rows do the least per row and tile (48 heads of
 // 17776: 4.7, 4.4 and 3.8 ms for these, 3.62 and 3.60 with 256 rows from the grid and from queues, 3.58 with 384; 24 of 48000, dense:

@@ -1,6 +1,6 @@
-"""The banded lists and the position-major table by arithmetic (rf_band.h), as the kernels with one workgroup per block have
-them, against the lists and the table that build_plan makes: every entry of every block of 64, 128 and 256 rows and every
-row, over layouts with and without text, in front and behind, frames and positions that tiles divide and that they do
+"""The banded lists and the position-major table by arithmetic (rf_band.h), as the kernels that split the keys of 64-row blocks
+have them, against the lists and the table that build_plan makes: every entry of every block of 64 rows (and of 128 and 256, at
+which no kernel works them out: the arithmetic does not depend on it) and every row, over layouts with and without text, in front and behind, frames and positions that tiles divide and that they do
 not, one frame, one position, and bands from nothing to everything."""
 import os
 import shutil
